@@ -198,3 +198,120 @@ def tolerance(case):
     if case["kind"] in ("forward", "run"):
         return {"rel": 1.5e-2, "max": 7e-2}
     return {"rel": 1e-2, "max": 5e-2}
+
+
+# ---- the same results in 64 bits, in plain torch
+
+def _exact_ddim(steps):
+    abar = torch.cumprod(1.0 - torch.linspace(1e-4, 2e-2, 1000, dtype=torch.float64), 0)
+    ts = [(steps - 1 - i) * (1000 // steps) for i in range(steps)]
+    prev = [abar[t].item() for t in ts[1:]] + [1.0]
+    a = [math.sqrt(p / abar[t].item()) for t, p in zip(ts, prev)]
+    b = [math.sqrt(1.0 - p) - f * math.sqrt(1.0 - abar[t].item()) for t, p, f in zip(ts, prev, a)]
+    return ts, a, b
+
+
+def _exact_attention(q, k, v, scale):
+    """[N, H, d] each; a head at a time, in blocks of query rows."""
+    out = torch.empty_like(q)
+    for h in range(q.shape[1]):
+        kt, vh = k[:, h].t().contiguous(), v[:, h].contiguous()
+        for r in range(0, q.shape[0], 4096):
+            out[r:r + 4096, h] = torch.softmax(q[r:r + 4096, h].contiguous() @ kt * scale, -1) @ vh
+    return out
+
+
+def _exact_forward(cfg, weights, x, ctx, t):
+    """One sample: x [C, F, H, W], ctx [L, D] or None, t an integer."""
+    wide = lambda w: w.to(torch.float64)
+    silu = lambda u: u * torch.sigmoid(u)
+    ln = lambda u: torch.nn.functional.layer_norm(u, (u.shape[-1],), eps=cfg.ln_eps)
+    D, L, ps = cfg.hidden, cfg.text_tokens, cfg.patch
+    C, F, H, W = cfg.latent_shape
+    Hp, Wp, d = H // ps, W // ps, cfg.head_dim
+    it = iter(weights)
+    lin = lambda u: u @ wide(next(it)).t() + wide(next(it))
+    patches = x.reshape(C, F, Hp, ps, Wp, ps).permute(1, 2, 4, 0, 3, 5).reshape(F * Hp * Wp, -1)
+    X = lin(patches)
+    if L:
+        X = torch.cat([wide(ctx), X])
+    w = torch.exp(-torch.arange(D // 2, dtype=torch.float64, device=x.device) / (D // 2) * math.log(10000.0))
+    c = silu(lin(silu(lin(torch.cat([torch.cos(t * w), torch.sin(t * w)])))))
+    grid = torch.meshgrid(*(torch.arange(n, dtype=torch.float64, device=x.device) for n in (F, Hp, Wp)), indexing="ij")
+    ang = [p.reshape(-1, 1) * cfg.rope_theta ** (-2.0 * torch.arange(n // 2, dtype=torch.float64, device=x.device) / n)
+           for p, n in zip(grid, (d // 4, 3 * d // 8, 3 * d // 8))]
+    rot = torch.polar(torch.ones((), dtype=torch.float64, device=x.device), torch.cat(ang, 1))[:, None, :]
+
+    def turned(u):
+        v = torch.view_as_complex(u[L:].reshape(-1, cfg.heads, d // 2, 2).contiguous()) * rot
+        return torch.cat([u[:L], torch.view_as_real(v).reshape(-1, cfg.heads, d)])
+
+    for _ in range(cfg.layers):
+        mod = lin(c).view(2, 6, D)                      # video, text
+        m = [torch.cat([mod[1, i].expand(L, D), mod[0, i].expand(X.shape[0] - L, D)]) for i in range(6)]
+        q, k, v = (u.reshape(-1, cfg.heads, d) for u in lin(ln(X) * (1 + m[1]) + m[0]).split(D, 1))
+        X = X + m[2] * lin(_exact_attention(turned(q), turned(k), v, d ** -0.5).reshape(-1, D))
+        u = torch.nn.functional.gelu(lin(ln(X) * (1 + m[4]) + m[3]), approximate="tanh")
+        X = X + m[5] * lin(u)
+    shift, scale = lin(c).split(D)
+    out = lin(ln(X[L:]) * (1 + scale) + shift)
+    return out.reshape(F, Hp, Wp, C, ps, ps).permute(3, 0, 1, 4, 2, 5).reshape(C, F, H, W)
+
+
+def _exact_run(case, cfg, weights, x, ctx):
+    ts, a, b = _exact_ddim(case["steps"])
+    predict = lambda y, i: _exact_forward(cfg, weights, y, ctx, ts[i])
+    step = lambda y, e, i: y + ((a[i] - 1.0) * y + b[i] * e)
+    sums, last, i, calls = [], None, 0, 0
+    cache = [None] * case["window"]
+
+    def take(y, e, i):
+        new = step(y, e, i)
+        zero = torch.zeros((), dtype=torch.float64, device=y.device)
+        sums.append(torch.stack([(new - y).abs().sum(), new.abs().sum(), (e - last).abs().sum() if last is not None else zero,
+                                 e.abs().sum()]))
+        return new
+
+    while i < min(case["warmup"], case["steps"]):
+        e = predict(x, i)
+        x, last, cache, calls, i = take(x, e, i), e, [e] * case["window"], calls + 1, i + 1
+    while i < case["steps"]:
+        n = min(case["window"], case["steps"] - i)
+        eps = []
+        for r in range(n):                              # rank r's sample: advanced r times with what it predicted last
+            y = x
+            for j in range(r):
+                y = step(y, cache[r], i + j)
+            eps.append(predict(y, i + r))
+        for r in range(n):
+            x, last, cache[r] = take(x, eps[r], i + r), eps[r], eps[r]
+        i, calls = i + n, calls + (1 if case["batched"] else n)
+    return x, torch.stack(sums), calls
+
+
+def exact(case, seed):
+    """What `run` returns, in 64 bits; None where that would take too long."""
+    kind = case["kind"]
+    if work(case)["flops"] > 5e13:
+        return None
+    s = prepare(case, seed)
+    wide = lambda u: u.to(torch.float64)
+    if kind in ("forward", "run"):
+        cfg, weights, ctx = _config(case), s["dit"].weights, s["ctx"]
+        if kind == "forward":
+            return torch.stack([_exact_forward(cfg, weights, wide(s["x"][i]), None if ctx is None else ctx[i], s["t"][i])
+                                for i in range(case["batch"])])
+        x, sums, calls = _exact_run(case, cfg, weights, wide(s["x"][0]), None if ctx is None else ctx[0])
+        return x[None], sums, calls
+    if kind == "attn":
+        return torch.stack([_exact_attention(wide(s["q"][i]), wide(s["k"][i]), wide(s["v"][i]), s["scale"])
+                            for i in range(case["batch"])])
+    if kind == "linear":
+        out = wide(s["a"]) @ wide(s["w"]).t() + wide(s["bias"])
+        return torch.nn.functional.gelu(out, approximate="tanh") if case["act"] else out
+    x, eps = wide(s["x"]), wide(s["eps"])
+    delta = (s["a"] - 1.0) * x + s["b"] * eps
+    new, other = x + delta, wide(s["other"])
+    sums = torch.stack([delta.abs().sum(), new.abs().sum(), (eps - wide(s["eps_prev"])).abs().sum(), eps.abs().sum()])
+    mae = torch.stack([(other - new).abs().sum(), other.abs().sum()])
+    return new, sums, torch.cat([mae, mae[:1] / mae[1:]])
