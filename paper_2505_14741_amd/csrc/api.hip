@@ -189,6 +189,10 @@ int forward_impl(dit* d, const float* x, const void* ctx, const int32_t* t_host,
     // the MFMA attention kernel takes queries that already carry scale*log2(e); the QKV
     // projection applies the factor in fp32, before its single rounding to bf16
     const bool prescale = attention_uses_mfma(dt, c.head_dim, path);
+    const int P = c.in_channels * c.patch * c.patch;
+    const bool final_gemm = gemm_uses_mfma(dt, N, P, D, path);
+    // a gated projection of few tokens leaves its K pieces to the LayerNorm that follows
+    PendingResidual pend{};
 
     for (int l = 0; l < L; ++l) {
         const LayerW& lw = d->layers[l];
@@ -198,7 +202,8 @@ int forward_impl(dit* d, const float* x, const void* ctx, const int32_t* t_host,
         int nflags = 0;
         float* flags = attention_head_flags(dt, batch, c.heads, c.head_dim, attn_ws, path, st, false, &nflags);
         // h = LN(X)(1+scale_a)+shift_a
-        PS_TIMED(KC_LN, launch_ln_modulate(dt, X, Hb, M, D, c.ln_eps, mod_l, mod_bs, 0, 1, geom, st, flags, nflags));
+        PS_TIMED(KC_LN, launch_ln_modulate(dt, X, Hb, M, D, c.ln_eps, mod_l, mod_bs, 0, 1, geom, st, flags, nflags,
+                                           &pend, c.text_tokens, mod_bs));
         // [q|k|v] = W_qkv h + b, rotary on video q,k
         Epilogue eq{};
         eq.kind = EPI_QKV_ROPE; eq.bias = lw.b_qkv; eq.D = D; eq.geom = geom;
@@ -216,22 +221,26 @@ int forward_impl(dit* d, const float* x, const void* ctx, const int32_t* t_host,
         eo.kind = EPI_GATE_RESIDUAL; eo.bias = lw.b_o; eo.resid = X; eo.mod_layer = mod_l;
         eo.mod_batch_stride = mod_bs; eo.gate_chunk = 2; eo.D = D; eo.geom = geom;
         eo.split_ws = gemm_ws; eo.split_ws_bytes = w.gemm_bytes;
-        PS_TIMED(KC_OPROJ, launch_gemm(dt, Hb, lw.W_o, nullptr, batch, N, D, D, eo, path, st));
+        pend = PendingResidual{0, gemm_ws, lw.b_o, mod_l, 2};
+        PS_TIMED(KC_OPROJ, launch_gemm(dt, Hb, lw.W_o, nullptr, batch, N, D, D, eo, path, st, &pend.pieces));
         // h2 = LN(X)(1+scale_m)+shift_m ; u = GELU(W_1 h2 + b_1) ; X += gate_m * (W_2 u + b_2)
-        PS_TIMED(KC_LN, launch_ln_modulate(dt, X, Hb, M, D, c.ln_eps, mod_l, mod_bs, 3, 4, geom, st));
+        PS_TIMED(KC_LN, launch_ln_modulate(dt, X, Hb, M, D, c.ln_eps, mod_l, mod_bs, 3, 4, geom, st, nullptr, 0,
+                                           &pend, c.text_tokens, mod_bs));
         Epilogue e1{};
         e1.kind = EPI_BIAS_GELU; e1.bias = lw.b_1;
         e1.split_ws = gemm_ws; e1.split_ws_bytes = w.gemm_bytes;
         PS_TIMED(KC_FC1, launch_gemm(dt, Hb, lw.W_1, QKV, batch, N, c.mlp_ratio * D, D, e1, path, st));
         Epilogue e2 = eo;
         e2.bias = lw.b_2; e2.gate_chunk = 5;
-        PS_TIMED(KC_FC2, launch_gemm(dt, QKV, lw.W_2, nullptr, batch, N, D, c.mlp_ratio * D, e2, path, st));
+        pend = PendingResidual{0, gemm_ws, lw.b_2, mod_l, 5};
+        PS_TIMED(KC_FC2, launch_gemm(dt, QKV, lw.W_2, nullptr, batch, N, D, c.mlp_ratio * D, e2, path, st,
+                                     l + 1 < L || final_gemm ? &pend.pieces : nullptr));
     }
     // eps = unpatchify(W_out (LN(X)(1+scale_f)+shift_f) + b_out) over the video tokens
-    const int P = c.in_channels * c.patch * c.patch;
-    if (gemm_uses_mfma(dt, N, P, D, path)) {
-        // as every other projection: normalised rows in bf16 (text rows included, dropped by the epilogue)
-        PS_TIMED(KC_LN, launch_ln_modulate(dt, X, Hb, M, D, c.ln_eps, modf, 2L * D, 0, 1, TokenGeom{N, 0}, st));
+    if (final_gemm) {
+        // as every other projection: normalised rows in the network's type (text rows included, dropped by the epilogue)
+        PS_TIMED(KC_LN, launch_ln_modulate(dt, X, Hb, M, D, c.ln_eps, modf, 2L * D, 0, 1, TokenGeom{N, 0}, st, nullptr, 0,
+                                           &pend, c.text_tokens, mod_bs));
         Epilogue ef{};
         ef.kind = EPI_UNPATCHIFY; ef.bias = d->b_out; ef.resid = eps_out; ef.geom = geom;
         ef.pg = PatchGeom{c.in_channels, c.frames, c.height, c.width, c.patch};

@@ -80,14 +80,18 @@ inline bool kernel_path_valid(int path) {
 // sample's result is bit-identical whatever batch it is computed in.
 // scratch that lets launch_gemm split its last partial round along K (0: the shape does not profit)
 size_t gemm_split_workspace_bytes(int dtype, int batch, int tokens, int Nn, int K, int path);
-// whether launch_gemm sends a bf16 shape to the MFMA kernel (EPI_UNPATCHIFY exists only there)
+// whether launch_gemm sends a shape to one of the matrix kernels (EPI_UNPATCHIFY exists only there)
 bool gemm_uses_mfma(int dtype, int tokens, int Nn, int K, int path);
 
 // ---- launchers (each validates nothing; callers have checked shapes) -----------------
 // C[batch * tokens, Nn] = A[batch * tokens, K] * W[Nn, K]^T with epilogue.  A, W, C in `dtype` (C ignored for
 // EPI_GATE_RESIDUAL).
 hipError_t launch_gemm(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K,
-                       const Epilogue& epi, int path, hipStream_t st);
+                       const Epilogue& epi, int path, hipStream_t st, int* deferred = nullptr);
+// deferred (EPI_GATE_RESIDUAL only): if the call splits K, it leaves the update undone and stores the number of pieces
+// there (0: the update is done); the pieces lie in epi.split_ws as [piece][batch * tokens][Nn] and
+// launch_ln_modulate() adds them.
+struct PendingResidual { int pieces; const float* part; const float* bias; const float* mod_layer; int gate_chunk; };
 
 // Full attention with explicit strides (in elements) for token, head and batch.
 struct AttnStrides { long q_tok, q_head, q_batch, k_tok, k_head, k_batch, v_tok, v_head, v_batch,
@@ -138,9 +142,12 @@ hipError_t launch_patch_embed(int dtype, const float* x, const void* ctx, const 
                               int patch, int text_tokens, int D, long ctx_batch_stride,
                               hipStream_t st);
 // out[m, :] = LN(X[m, :]) * (1 + scale) + shift with per-token stream selection.
-hipError_t launch_ln_modulate(int dtype, const float* X, void* out, int M, int D, float eps,
+// pending: first X[m, :] += gate * (sum of the pieces + bias), with the gates of layer pending->mod_layer (its batch
+// stride is pending_bs) and text_tokens text rows per sample.
+hipError_t launch_ln_modulate(int dtype, float* X, void* out, int M, int D, float eps,
                               const float* mod_layer, long mod_batch_stride, int shift_chunk,
-                              int scale_chunk, TokenGeom geom, hipStream_t st, float* zero_buf = nullptr, int zero_n = 0);
+                              int scale_chunk, TokenGeom geom, hipStream_t st, float* zero_buf = nullptr, int zero_n = 0,
+                              const PendingResidual* pending = nullptr, int text_tokens = 0, long pending_bs = 0);
 hipError_t launch_final_proj(int dtype, const float* X, const float* modf, const void* W_out,
                              const float* b_out, float* eps_out, int batch, int C, int F, int H,
                              int Wd, int patch, int text_tokens, int D, float eps, hipStream_t st);

@@ -335,12 +335,107 @@ __global__ void ln_modulate_kernel(const float* __restrict__ X, T* __restrict__ 
     }
 }
 
-hipError_t launch_ln_modulate(int dtype, const float* X, void* out, int M, int D, float eps,
+// Sum over the 256 threads of a workgroup, the same value in every thread.  `sm`: 4 floats, one set per call.
+__device__ __forceinline__ float block_sum(float v, float* sm) {
+    v = wave_sum(v);
+    if (threadIdx.x % WAVE == 0) sm[threadIdx.x / WAVE] = v;
+    __syncthreads();
+    return (sm[0] + sm[1]) + (sm[2] + sm[3]);
+}
+
+// The same for samples of few tokens: one workgroup per row, so that 112 rows occupy 112 compute units and a thread
+// has two 16-byte loads per operand instead of eight.  It also finishes a projection whose K pieces are still apart
+// (PendingResidual): the pieces are added in order, X is updated in place and its new row is normalised from registers,
+// which saves the launch and the pass over X that a reduction of its own would take.
+template <typename T>
+__global__ void __launch_bounds__(256)
+ln_modulate_row_kernel(float* __restrict__ X, T* __restrict__ out, int M, int D, float eps,
+                       const float* __restrict__ mod_layer, long mod_bs, int shift_chunk, int scale_chunk, TokenGeom g,
+                       float* __restrict__ zero_buf, int zero_n, PendingResidual pd, int pd_text, long pd_bs) {
+    constexpr int MAXV = 2;
+    __shared__ float sm[2][4];
+    const int row = blockIdx.x, b = row / g.tokens, n = row - b * g.tokens, nvec = D / 4;
+    if (row == 0)
+        for (int i = threadIdx.x; i < zero_n; i += 256) zero_buf[i] = 0.f;
+    const int off = n < g.text_tokens ? 6 : 0;
+    const float4* sh = reinterpret_cast<const float4*>(mod_layer + b * mod_bs + (long)(shift_chunk + off) * D);
+    const float4* sc = reinterpret_cast<const float4*>(mod_layer + b * mod_bs + (long)(scale_chunk + off) * D);
+    float4* xr = reinterpret_cast<float4*>(X + (long)row * D);
+    float4 v[MAXV], h[MAXV], k[MAXV];
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < MAXV; ++i) {
+        const int c = threadIdx.x + i * 256;
+        v[i] = h[i] = k[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (c >= nvec) continue;
+        v[i] = xr[c]; h[i] = sh[c]; k[i] = sc[c];
+        if (pd.pieces > 0) {
+            const float4 bi = reinterpret_cast<const float4*>(pd.bias)[c];
+            const float4 ga = reinterpret_cast<const float4*>(
+                pd.mod_layer + b * pd_bs + (long)(pd.gate_chunk + (n < pd_text ? 6 : 0)) * D)[c];
+            float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+            for (int p = 0; p < pd.pieces; ++p) {
+                const float4 u = reinterpret_cast<const float4*>(pd.part + ((long)p * M + row) * D)[c];
+                t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+            }
+            v[i].x += ga.x * (t.x + bi.x); v[i].y += ga.y * (t.y + bi.y);
+            v[i].z += ga.z * (t.z + bi.z); v[i].w += ga.w * (t.w + bi.w);
+            xr[c] = v[i];
+        }
+        s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+    }
+    const float mean = block_sum(s, sm[0]) / (float)D;
+    float q = 0.f;
+#pragma unroll
+    for (int i = 0; i < MAXV; ++i) {
+        if ((int)threadIdx.x + i * 256 >= nvec) continue;
+        const float a = v[i].x - mean, bb = v[i].y - mean, cc = v[i].z - mean, d = v[i].w - mean;
+        q += (a * a + bb * bb) + (cc * cc + d * d);
+    }
+    const float rstd = 1.0f / sqrtf(block_sum(q, sm[1]) / (float)D + eps);
+    T* orow = out + (long)row * D;
+#pragma unroll
+    for (int i = 0; i < MAXV; ++i) {
+        const int c = threadIdx.x + i * 256;
+        if (c >= nvec) continue;
+        const float y0 = (v[i].x - mean) * rstd * (1.f + k[i].x) + h[i].x;
+        const float y1 = (v[i].y - mean) * rstd * (1.f + k[i].y) + h[i].y;
+        const float y2 = (v[i].z - mean) * rstd * (1.f + k[i].z) + h[i].z;
+        const float y3 = (v[i].w - mean) * rstd * (1.f + k[i].w) + h[i].w;
+        if constexpr (sizeof(T) == 2) {
+            union { bf16_t h4[4]; uint2 u; } pk;
+            pk.h4[0] = __float2bfloat16(y0); pk.h4[1] = __float2bfloat16(y1);
+            pk.h4[2] = __float2bfloat16(y2); pk.h4[3] = __float2bfloat16(y3);
+            *reinterpret_cast<uint2*>(orow + 4 * c) = pk.u;
+        } else {
+            *reinterpret_cast<float4*>(orow + 4 * c) = make_float4(y0, y1, y2, y3);
+        }
+    }
+}
+
+// up to this many tokens per sample a row gets a workgroup (the choice changes the order of a row's sums, so it must
+// not depend on the batch)
+static constexpr int LN_ROW_TOKENS = 2048;
+
+hipError_t launch_ln_modulate(int dtype, float* X, void* out, int M, int D, float eps,
                               const float* mod_layer, long mod_bs, int shift_chunk, int scale_chunk,
-                              TokenGeom geom, hipStream_t st, float* zero_buf, int zero_n) {
+                              TokenGeom geom, hipStream_t st, float* zero_buf, int zero_n,
+                              const PendingResidual* pending, int text_tokens, long pending_bs) {
+    if (D % 4 != 0 || D > 64 * 4 * 8) return hipErrorInvalidValue;
+    const bool pend = pending && pending->pieces > 0;
+    if (pend || geom.tokens <= LN_ROW_TOKENS) {
+        const PendingResidual pd = pend ? *pending : PendingResidual{};
+        if (dtype == PS_BF16)
+            ln_modulate_row_kernel<bf16_t><<<M, 256, 0, st>>>(X, (bf16_t*)out, M, D, eps, mod_layer, mod_bs, shift_chunk,
+                                                              scale_chunk, geom, zero_buf, zero_n, pd, text_tokens, pending_bs);
+        else
+            ln_modulate_row_kernel<float><<<M, 256, 0, st>>>(X, (float*)out, M, D, eps, mod_layer, mod_bs, shift_chunk,
+                                                             scale_chunk, geom, zero_buf, zero_n, pd, text_tokens, pending_bs);
+        return hipGetLastError();
+    }
     int threads = 256;
     int blocks = (M + 3) / 4;
-    if (D % 4 != 0 || D > 64 * 4 * 8) return hipErrorInvalidValue;
     if (dtype == PS_BF16)
         ln_modulate_kernel<bf16_t, 8><<<blocks, threads, 0, st>>>(X, (bf16_t*)out, M, D, eps, mod_layer, mod_bs,
                                                                  shift_chunk, scale_chunk, geom, zero_buf, zero_n);

@@ -1,6 +1,6 @@
 // C[M, Nn] = A[M, K] * W[Nn, K]^T with fused epilogue.
 // This file holds the dispatcher and the generic LDS-tiled fp32-FMA kernel used for the
-// fp32 configuration and for bf16 shapes the MFMA kernel does not cover.
+// shapes that neither matrix kernel covers and for kernel path 1.
 #include "common.h"
 #include "epilogue.h"
 
@@ -78,14 +78,33 @@ bool gemm_mfma_supported(int tokens, int Nn, int K);
 hipError_t launch_gemm_mfma(const bf16_t* A, const bf16_t* W, bf16_t* C, int batch, int tokens, int Nn, int K,
                             const Epilogue& ep, int path, hipStream_t st);
 
-bool gemm_uses_mfma(int dtype, int tokens, int Nn, int K, int path) {
+bool gemm_small_supported(int dtype, int tokens, int Nn, int K, int path);
+size_t gemm_small_workspace_bytes(int dtype, int batch, int tokens, int Nn, int K, int path);
+hipError_t launch_gemm_small(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K,
+                             const Epilogue& ep, int path, int* deferred, hipStream_t st);
+size_t gemm_tiles_workspace_bytes(int batch, int tokens, int Nn, int K, int path);
+
+static bool uses_tiles(int dtype, int tokens, int Nn, int K, int path) {
     return dtype == PS_BF16 && (path & 0xff) != 1 && gemm_mfma_supported(tokens, Nn, K);
 }
 
+bool gemm_uses_mfma(int dtype, int tokens, int Nn, int K, int path) {
+    return gemm_small_supported(dtype, tokens, Nn, K, path) || uses_tiles(dtype, tokens, Nn, K, path);
+}
+
+size_t gemm_split_workspace_bytes(int dtype, int batch, int tokens, int Nn, int K, int path) {
+    if (gemm_small_supported(dtype, tokens, Nn, K, path))
+        return gemm_small_workspace_bytes(dtype, batch, tokens, Nn, K, path);
+    return uses_tiles(dtype, tokens, Nn, K, path) ? gemm_tiles_workspace_bytes(batch, tokens, Nn, K, path) : 0;
+}
+
 hipError_t launch_gemm(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K,
-                       const Epilogue& epi, int path, hipStream_t st) {
+                       const Epilogue& epi, int path, hipStream_t st, int* deferred) {
+    if (deferred) *deferred = 0;
     if (batch <= 0 || tokens <= 0 || Nn <= 0 || K <= 0 || (Nn & 1)) return hipErrorInvalidValue;
-    const bool mfma = gemm_uses_mfma(dtype, tokens, Nn, K, path);
+    if (gemm_small_supported(dtype, tokens, Nn, K, path))
+        return launch_gemm_small(dtype, A, W, C, batch, tokens, Nn, K, epi, path, deferred, st);
+    const bool mfma = uses_tiles(dtype, tokens, Nn, K, path);
     if (epi.kind == EPI_UNPATCHIFY && !mfma) return hipErrorInvalidValue;
     if (mfma)
         return launch_gemm_mfma((const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C, batch, tokens, Nn, K, epi, path, st);
