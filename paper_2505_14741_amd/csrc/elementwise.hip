@@ -187,67 +187,87 @@ hipError_t launch_rope_table(float* table, int F, int Hp, int Wp, int head_dim,
 
 // ------------------------------------------------------------------------ patch embedding
 // X[b, L_txt + (f,i,j), :] = W_pe . patch(c,dy,dx) + b_pe ; X[b, n < L_txt, :] = ctx[b, n, :].
-// One workgroup per TOK tokens; patch vectors staged in LDS, threads stride over D.
-template <typename T, int TOK>
-__global__ void patch_embed_kernel(const float* __restrict__ x, const T* __restrict__ ctx,
-                                   const T* __restrict__ W_pe, const float* __restrict__ b_pe,
-                                   float* __restrict__ X, int C, int F, int H, int Wd, int patch,
-                                   int text_tokens, int D, long ctx_bs) {
-    extern __shared__ float pv[];        // [P][TOK]: the TOK values one weight multiplies are contiguous
-    int Hp = H / patch, Wp = Wd / patch;
-    int Nv = F * Hp * Wp;
-    int N = text_tokens + Nv;
-    int P = C * patch * patch;
-    int b = blockIdx.y;
-    int tok0 = blockIdx.x * TOK;         // token index within the sample (text first)
-    for (int e = threadIdx.x; e < TOK * P; e += blockDim.x) {
-        int tl = e / P, pi = e % P;
-        int n = tok0 + tl;
-        float val = 0.f;
-        if (n < N && n >= text_tokens) {
-            int nv = n - text_tokens;
-            int j = nv % Wp, i = (nv / Wp) % Hp, f = nv / (Wp * Hp);
-            int dx = pi % patch, dy = (pi / patch) % patch, c = pi / (patch * patch);
-            val = x[((((long)b * C + c) * F + f) * H + (i * patch + dy)) * Wd + (j * patch + dx)];
-        }
-        pv[pi * TOK + tl] = val;
-    }
-    __syncthreads();
-    for (int col = threadIdx.x; col < D; col += blockDim.x) {
-        float acc[TOK];
+// A matrix product in fp32 (v_mfma_f32_16x16x4_f32 on the fp32 latent and the widened weights): one workgroup per 64
+// tokens x 64 columns, both operands staged in LDS 64 patch values at a time.  The weights are the first operand, so a
+// lane ends with 4 adjacent columns of one token: X is written in 16-byte stores, and writing it is the bound for many
+// tokens.  (One workgroup per 16 tokens whose threads each walked a whole weight row took 98 us at 112 tokens -- seven
+// workgroups, uncoalesced -- and 116 us at 4516; this takes 15 and 38, 17776 tokens 159 -> 120.)
+template <typename T>
+__global__ void __launch_bounds__(256)
+patch_embed_kernel(const float* __restrict__ x, const T* __restrict__ ctx, const T* __restrict__ W_pe,
+                   const float* __restrict__ b_pe, float* __restrict__ X, int C, int F, int H, int Wd, int patch,
+                   int text_tokens, int D, long ctx_bs) {
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    constexpr int TILE = 64, KC = 64, LD = KC + 4;       // (rows 16-byte aligned, 4 banks apart)
+    __shared__ __attribute__((aligned(16))) float pt[TILE * LD], wt[TILE * LD];
+    const int Hp = H / patch, Wp = Wd / patch, N = text_tokens + F * Hp * Wp, P = C * patch * patch;
+    const int tiles_d = (D + TILE - 1) / TILE;           // the column tiles of a token tile are neighbours
+    const int n0 = blockIdx.x / tiles_d * TILE, d0 = blockIdx.x % tiles_d * TILE, b = blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, kgrp = lane >> 4;
+    f4 acc[2][2];                                        // [16 columns][16 tokens]
 #pragma unroll
-        for (int tl = 0; tl < TOK; ++tl) acc[tl] = b_pe[col];
-        const T* w = W_pe + (long)col * P;
-        int pi = 0;
-        if ((P & 7) == 0 && (reinterpret_cast<size_t>(W_pe) & 15) == 0) {   // rows of W_pe start 16-byte aligned: 8 weights per load
-            for (; pi < P; pi += 8) {
-                float wv[8];
-                if constexpr (sizeof(T) == 2) {
-                    union { uint4 u; bf16_t h[8]; } pk;
-                    pk.u = *reinterpret_cast<const uint4*>(w + pi);
+    for (int y = 0; y < 2; ++y)
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) wv[k] = to_f32(pk.h[k]);
-                } else {
+        for (int t = 0; t < 2; ++t) acc[y][t] = f4{0.f, 0.f, 0.f, 0.f};
+    if (n0 + TILE > text_tokens) {                       // (a tile of text rows only has nothing to multiply)
+        const int n = n0 + lane, nv = n - text_tokens;   // lane = token while staging: neighbours read adjacent pixels
+        const bool video = n < N && nv >= 0;
+        const int j = nv % Wp, i = (nv / Wp) % Hp, f = nv / (Wp * Hp);
+        const float* xp = x + (((long)b * C * F + f) * H + (long)i * patch) * Wd + (long)j * patch;
+        for (int k0 = 0; k0 < P; k0 += KC) {
+            float pv[KC / 4], wv[TILE / 4];              // all 32 loads of a thread in flight together
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) wv[k] = to_f32(w[pi + k]);
+            for (int u = 0; u < KC / 4; ++u) {           // patch value wave + 4u of every token (uniform per wave)
+                const int pi = k0 + wave + 4 * u, dx = pi % patch, dy = (pi / patch) % patch, c = pi / (patch * patch);
+                pv[u] = video && pi < P ? xp[((long)c * F * H + dy) * Wd + dx] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < TILE / 4; ++u) {         // weight k0 + lane of row wave + 4u
+                const int r = d0 + wave + 4 * u;
+                wv[u] = k0 + lane < P && r < D ? to_f32(W_pe[(long)r * P + k0 + lane]) : 0.f;
+            }
+            if (k0) __syncthreads();
+#pragma unroll
+            for (int u = 0; u < KC / 4; ++u) pt[lane * LD + wave + 4 * u] = pv[u];
+#pragma unroll
+            for (int u = 0; u < TILE / 4; ++u) wt[(wave + 4 * u) * LD + lane] = wv[u];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < KC; k += 16) {           // instruction e multiplies the k = 4 * kgrp + e of the 16
+                f4 p[2], w[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    p[t] = *reinterpret_cast<const f4*>(pt + (wm * 32 + t * 16 + l16) * LD + k + kgrp * 4);
+                    w[t] = *reinterpret_cast<const f4*>(wt + (wn * 32 + t * 16 + l16) * LD + k + kgrp * 4);
                 }
 #pragma unroll
-                for (int k = 0; k < 8; ++k)              // same order of additions as the one-by-one loop
+                for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int tl = 0; tl < TOK; ++tl) acc[tl] += wv[k] * pv[(pi + k) * TOK + tl];
+                    for (int y = 0; y < 2; ++y)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+                            acc[y][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[y][e], p[t][e], acc[y][t], 0, 0, 0);
             }
         }
-        for (; pi < P; ++pi) {
-            float wv = to_f32(w[pi]);
+    }
 #pragma unroll
-            for (int tl = 0; tl < TOK; ++tl) acc[tl] += wv * pv[pi * TOK + tl];
-        }
+    for (int t = 0; t < 2; ++t) {
+        const int n = n0 + wm * 32 + t * 16 + l16;
+        if (n >= N) continue;
 #pragma unroll
-        for (int tl = 0; tl < TOK; ++tl) {
-            int n = tok0 + tl;
-            if (n >= N) continue;
-            float v = n < text_tokens ? to_f32(ctx[b * ctx_bs + (long)n * D + col]) : acc[tl];
-            X[((long)b * N + n) * D + col] = v;
+        for (int y = 0; y < 2; ++y) {
+            const int col = d0 + wn * 32 + y * 16 + kgrp * 4;    // D % 4 == 0: inside or outside together
+            if (col >= D) continue;
+            f4 v;
+            if (n < text_tokens) {
+                const T* cp = ctx + b * ctx_bs + (long)n * D + col;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = to_f32(cp[e]);
+            } else {
+                v = acc[y][t] + *reinterpret_cast<const f4*>(b_pe + col);
+            }
+            *reinterpret_cast<f4*>(X + ((long)b * N + n) * D + col) = v;
         }
     }
 }
@@ -255,17 +275,14 @@ __global__ void patch_embed_kernel(const float* __restrict__ x, const T* __restr
 hipError_t launch_patch_embed(int dtype, const float* x, const void* ctx, const void* W_pe,
                               const float* b_pe, float* X, int batch, int C, int F, int H, int Wd,
                               int patch, int text_tokens, int D, long ctx_bs, hipStream_t st) {
-    constexpr int TOK = 16;
-    int N = text_tokens + F * (H / patch) * (Wd / patch);
-    int P = C * patch * patch;
-    dim3 grid((N + TOK - 1) / TOK, batch);
-    size_t sh = (size_t)TOK * P * sizeof(float);
+    const long N = text_tokens + (long)F * (H / patch) * (Wd / patch);
+    dim3 grid((unsigned)((N + 63) / 64 * ((D + 63) / 64)), batch);   // at most 2^18 x 2^5
     if (dtype == PS_BF16)
-        patch_embed_kernel<bf16_t, TOK><<<grid, 256, sh, st>>>(x, (const bf16_t*)ctx, (const bf16_t*)W_pe,
-                                                               b_pe, X, C, F, H, Wd, patch, text_tokens, D, ctx_bs);
+        patch_embed_kernel<bf16_t><<<grid, 256, 0, st>>>(x, (const bf16_t*)ctx, (const bf16_t*)W_pe,
+                                                         b_pe, X, C, F, H, Wd, patch, text_tokens, D, ctx_bs);
     else
-        patch_embed_kernel<float, TOK><<<grid, 256, sh, st>>>(x, (const float*)ctx, (const float*)W_pe, b_pe,
-                                                              X, C, F, H, Wd, patch, text_tokens, D, ctx_bs);
+        patch_embed_kernel<float><<<grid, 256, 0, st>>>(x, (const float*)ctx, (const float*)W_pe, b_pe,
+                                                        X, C, F, H, Wd, patch, text_tokens, D, ctx_bs);
     return hipGetLastError();
 }
 
