@@ -1,7 +1,8 @@
 // Full (unmasked) softmax attention over the flattened text + (frame,row,col) token axis.
 //
-//  * attn_generic_kernel: one thread per query row, fp32 math, any supported head_dim;
-//    serves the fp32 configuration and shapes the MFMA kernel does not cover.
+//  * attn_generic_kernel: one thread per query row, fp32 math, any supported head_dim; kernel path 1.
+//  * attn_f32_kernel: fp32 math on v_mfma_f32_16x16x4_f32, any supported head_dim; serves the fp32
+//    configuration and the bf16 head dims the bf16 kernels do not cover.
 //  * attn_mfma_kernel: flash-style kernel for bf16, head_dim 64, on
 //    v_mfma_f32_32x32x16_bf16.  It works on transposed tiles so that a lane owns a QUERY
 //    column: S^T = K Q^T puts the keys of one query into one lane's accumulator
@@ -89,6 +90,133 @@ static hipError_t launch_generic_attn(const T* q, const T* k, const T* v, T* o, 
         case 16: attn_generic_kernel<T, 16><<<grid, 128, 0, st>>>(q, k, v, o, seq, heads, scale, s); break;
         case 32: attn_generic_kernel<T, 32><<<grid, 128, 0, st>>>(q, k, v, o, seq, heads, scale, s); break;
         case 64: attn_generic_kernel<T, 64><<<grid, 128, 0, st>>>(q, k, v, o, seq, heads, scale, s); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// --------------------------------------------------------------------------------- fp32 on matrix instructions
+// A workgroup takes 64 queries of a head (16 per wave) and walks the keys 64 at a time, K and V widened to fp32 in LDS,
+// the next tile's global loads in flight meanwhile.  S^T = K Q^T leaves a query in lane % 16 with keys 4 * (lane / 16) + i
+// of every 16-key block, which is the layout the second operand of O^T = V^T P^T wants: the probabilities stay in their
+// registers, in fp32.  Full fp32 products, sums and expf throughout.  The matrix instructions bind (128 of them, 32
+// cycles each, per wave and tile; LDS reads take a quarter of that).  One thread per query took 130 us at 112 tokens x 30
+// heads, 1104 at 1024 tokens and 9.7 us at 32 tokens x 4 heads of 16; this takes 10.2, 107 (75 TFLOP/s) and 3.5.
+typedef __attribute__((ext_vector_type(4))) float attn_f4_t;
+__device__ __forceinline__ attn_f4_t load_quad(const float* p) { return *reinterpret_cast<const attn_f4_t*>(p); }
+__device__ __forceinline__ attn_f4_t load_quad(const bf16_t* p) {
+    typedef __attribute__((ext_vector_type(4))) __bf16 b4;
+    return __builtin_convertvector(*reinterpret_cast<const b4*>(p), attn_f4_t);
+}
+__device__ __forceinline__ void store_quad(float* p, attn_f4_t v) { *reinterpret_cast<attn_f4_t*>(p) = v; }
+__device__ __forceinline__ void store_quad(bf16_t* p, attn_f4_t v) {
+    typedef __attribute__((ext_vector_type(4))) __bf16 b4;
+    *reinterpret_cast<b4*>(p) = __builtin_convertvector(v, b4);
+}
+
+template <typename T, int HD>
+__global__ void __launch_bounds__(256)
+attn_f32_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, T* __restrict__ o, int seq,
+                float scale, AttnStrides s) {
+    constexpr int KT = 64, LD = HD + 4, NB = HD / 16;    // LD: rows 16-byte aligned, four rows 16 banks apart
+    __shared__ __attribute__((aligned(16))) float Ks[KT * LD], Vs[KT * LD];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kgrp = lane >> 4;
+    const int h = blockIdx.y, b = blockIdx.z;
+    const int qi = blockIdx.x * 64 + wave * 16 + l16, qr = min(qi, seq - 1);
+    const T* kb = k + b * s.k_batch + h * s.k_head;
+    const T* vb = v + b * s.v_batch + h * s.v_head;
+    attn_f4_t qf[NB];
+#pragma unroll
+    for (int d = 0; d < NB; ++d)
+        qf[d] = load_quad(q + b * s.q_batch + (long)qr * s.q_tok + h * s.q_head + d * 16 + kgrp * 4) * scale;
+
+    attn_f4_t kn[NB], vn[NB];                            // the next tile; rows past the end are zero
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int e = threadIdx.x + 256 * u, r = k0 + e / (HD / 4), c = e % (HD / 4) * 4;
+            kn[u] = vn[u] = attn_f4_t{0.f, 0.f, 0.f, 0.f};
+            if (r < seq) {
+                kn[u] = load_quad(kb + (long)r * s.k_tok + c);
+                vn[u] = load_quad(vb + (long)r * s.v_tok + c);
+            }
+        }
+    };
+    attn_f4_t acc[NB];                                   // O^T: lane's query, d = 16 * block + 4 * kgrp + i
+#pragma unroll
+    for (int d = 0; d < NB; ++d) acc[d] = attn_f4_t{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;                        // l: over this lane's keys only
+    fetch(0);
+    for (int k0 = 0; k0 < seq; k0 += KT) {
+        __syncthreads();                                 // nobody reads the last tile any more
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int e = threadIdx.x + 256 * u, off = e / (HD / 4) * LD + e % (HD / 4) * 4;
+            *reinterpret_cast<attn_f4_t*>(Ks + off) = kn[u];
+            *reinterpret_cast<attn_f4_t*>(Vs + off) = vn[u];
+        }
+        __syncthreads();
+        if (k0 + KT < seq) fetch(k0 + KT);
+        const int blocks = min(4, (seq - k0 + 15) / 16); // 16-key blocks with a key in them
+        attn_f4_t sc[4];
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            sc[g] = attn_f4_t{0.f, 0.f, 0.f, 0.f};
+            if (g < blocks) {
+#pragma unroll
+                for (int d = 0; d < NB; ++d) {
+                    const attn_f4_t kf = *reinterpret_cast<const attn_f4_t*>(Ks + (g * 16 + l16) * LD + d * 16 + kgrp * 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qf[d][e], sc[g], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (k0 + g * 16 + kgrp * 4 + i >= seq) sc[g][i] = -INFINITY;
+                tmax = fmaxf(tmax, sc[g][i]);
+            }
+        }
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+        const float mn = fmaxf(m, tmax), alpha = expf(m - mn);   // exp(-inf) = 0 on the first tile
+        m = mn;
+        l *= alpha;
+#pragma unroll
+        for (int d = 0; d < NB; ++d) acc[d] *= alpha;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            if (g >= blocks) continue;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                sc[g][i] = expf(sc[g][i] - mn);          // masked keys: exp(-inf) = 0
+                l += sc[g][i];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int d = 0; d < NB; ++d)
+                    acc[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(Vs[(g * 16 + kgrp * 4 + e) * LD + d * 16 + l16], sc[g][e],
+                                                                  acc[d], 0, 0, 0);
+        }
+    }
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    if (qi >= seq) return;
+    const float inv = 1.0f / l;
+    T* op = o + b * s.o_batch + (long)qi * s.o_tok + h * s.o_head + kgrp * 4;
+#pragma unroll
+    for (int d = 0; d < NB; ++d) store_quad(op + d * 16, acc[d] * inv);
+}
+
+template <typename T>
+static hipError_t launch_f32_attn(const T* q, const T* k, const T* v, T* o, int batch, int seq, int heads, int head_dim,
+                                  float scale, const AttnStrides& s, hipStream_t st) {
+    dim3 grid((seq + 63) / 64, heads, batch);
+    switch (head_dim) {
+        case 16: attn_f32_kernel<T, 16><<<grid, 256, 0, st>>>(q, k, v, o, seq, scale, s); break;
+        case 32: attn_f32_kernel<T, 32><<<grid, 256, 0, st>>>(q, k, v, o, seq, scale, s); break;
+        case 64: attn_f32_kernel<T, 64><<<grid, 256, 0, st>>>(q, k, v, o, seq, scale, s); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1062,6 +1190,14 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
         return hipGetLastError();
     }
     if (q_prescaled) return hipErrorInvalidValue;     // only the MFMA kernel takes pre-scaled queries
+    // (the sources are read 4 elements at a time: every entry point passes 16-byte aligned rows)
+    if ((path & 0xff) != 1) {
+        if (dtype == PS_BF16)
+            return launch_f32_attn<bf16_t>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, batch, seq,
+                                           heads, head_dim, scale, s, st);
+        return launch_f32_attn<float>((const float*)q, (const float*)k, (const float*)v, (float*)o, batch, seq, heads,
+                                      head_dim, scale, s, st);
+    }
     if (dtype == PS_BF16)
         return launch_generic_attn<bf16_t>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, batch,
                                            seq, heads, head_dim, scale, s, st);
