@@ -64,7 +64,7 @@ WsLayout ws_layout(const dit* d, int batch) {
     w.cvec = take((size_t)batch * c.time_embed_dim * 4);
     w.rope = take(rope_table_floats(c.frames, d->Hp, d->Wp, c.head_dim) * 4);   // (cos, sin) per axis position and pair
     w.attn = take(attention_workspace_bytes(c.dtype, batch, d->N, c.heads, c.head_dim));
-    {   // K-split scratch of the projections: the largest need of the four shapes of a layer, under any tile
+    {   // K-split scratch of the projections: the largest need of the four shapes of a layer and of the final one, under any tile
         // variant a kernel path can force (so the size does not change when the handle's path does)
         const int Di = (int)D, Fi = (int)(c.mlp_ratio * D);
         size_t g = 0;
@@ -74,6 +74,7 @@ WsLayout ws_layout(const dit* d, int batch) {
             g = std::max(g, gemm_split_workspace_bytes(c.dtype, batch, d->N, Di, Di, path));
             g = std::max(g, gemm_split_workspace_bytes(c.dtype, batch, d->N, Fi, Di, path));
             g = std::max(g, gemm_split_workspace_bytes(c.dtype, batch, d->N, Di, Fi, path));
+            g = std::max(g, gemm_split_workspace_bytes(c.dtype, batch, d->N, d->P, Di, path));
         }
         w.gemm_bytes = g;
         w.gemm = take(g);
@@ -243,6 +244,7 @@ int forward_impl(dit* d, const float* x, const void* ctx, const int32_t* t_host,
                                            &pend, c.text_tokens, mod_bs));
         Epilogue ef{};
         ef.kind = EPI_UNPATCHIFY; ef.bias = d->b_out; ef.resid = eps_out; ef.geom = geom;
+        ef.split_ws = gemm_ws; ef.split_ws_bytes = w.gemm_bytes;
         ef.pg = PatchGeom{c.in_channels, c.frames, c.height, c.width, c.patch};
         PS_TIMED(KC_OTHER, launch_gemm(dt, Hb, d->W_out, nullptr, batch, N, P, D, ef, path, st));
     } else {

@@ -52,22 +52,34 @@ __device__ __forceinline__ void store_quad(bf16_t* p, f32x4_t v) {
     *reinterpret_cast<bf16x4_t*>(p) = __builtin_convertvector(v, bf16x4_t);
 }
 
-// Epilogue of 4 adjacent output columns of row n of a sample; x is the finished sum.
+// What the epilogue of 4 adjacent output columns of row n of a sample reads besides the sum.
+struct EpiOperands { f32x4_t bias, gate, resid; };
+template <int KIND>
+__device__ __forceinline__ EpiOperands epilogue_operands(const Epilogue& ep, int Nn, int sample, int n, int col) {
+    EpiOperands o;
+    o.bias = *reinterpret_cast<const f32x4_t*>(ep.bias + col);
+    o.gate = o.resid = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if constexpr (KIND == EPI_GATE_RESIDUAL) {
+        o.gate = *reinterpret_cast<const f32x4_t*>(ep.mod_layer + sample * ep.mod_batch_stride +
+                                                   (long)(ep.gate_chunk + (n < ep.geom.text_tokens ? 6 : 0)) * ep.D + col);
+        o.resid = *reinterpret_cast<const f32x4_t*>(ep.resid + ((long)sample * ep.geom.tokens + n) * Nn + col);
+    }
+    return o;
+}
+
+// x is the finished sum.
 template <int KIND, typename T>
 __device__ __forceinline__ void epilogue_quad(const Epilogue& ep, T* __restrict__ C, int Nn, int sample, int n, int col,
-                                              f32x4_t x) {
+                                              f32x4_t x, const EpiOperands& o) {
     const long row = (long)sample * ep.geom.tokens + n;
     const int text = ep.geom.text_tokens;
-    x += *reinterpret_cast<const f32x4_t*>(ep.bias + col);
+    x += o.bias;
     if constexpr (KIND == EPI_BIAS_GELU) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) x[c] = gelu_of(x[c], T{});
     }
     if constexpr (KIND == EPI_GATE_RESIDUAL) {
-        const f32x4_t gate = *reinterpret_cast<const f32x4_t*>(
-            ep.mod_layer + sample * ep.mod_batch_stride + (long)(ep.gate_chunk + (n < text ? 6 : 0)) * ep.D + col);
-        f32x4_t* xp = reinterpret_cast<f32x4_t*>(ep.resid + row * Nn + col);
-        *xp = *xp + gate * x;
+        *reinterpret_cast<f32x4_t*>(ep.resid + row * Nn + col) = o.resid + o.gate * x;
         return;
     }
     if constexpr (KIND == EPI_UNPATCHIFY) {
@@ -160,13 +172,29 @@ gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restric
 
     // W fragments are the first operand, A fragments the second: lane l of a 16 x 16 result then holds 4 adjacent
     // output columns (4 * (l / 16) ..) of row l % 16, and the epilogue works on 16-byte quads without a transpose
-    f32x4_t acc[2][2];                                   // [16 columns][16 rows]
+    // (fp32: the two k steps of a stage have sums of their own, a shorter chain of roundings: error of the fp32 step on
+    // 112 tokens against 64 bits 5.3e-7 with them, 5.5e-7 without, 1.36e-6 on the fp32-FMA kernel)
+    constexpr int SETS = sizeof(T) == 4 ? 2 : 1;
+    f32x4_t acc[SETS][2][2];                             // [set][16 columns][16 rows]
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
+    for (int z = 0; z < SETS; ++z)
 #pragma unroll
-        for (int x = 0; x < 2; ++x) acc[y][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) acc[z][y][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int aoff = (wm * 32 + l16) * ROWB, woff = (TILE + wn * 32 + l16) * ROWB, sw = (l16 >> 1) & 7;
 
+    // the epilogue's operands are requested now, with the first stages, and not when the sums are done
+    // (rows and columns past the edge: clamped, not stored)
+    EpiOperands eo[2][2];
+    if (g.nsplit == 1) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+                eo[x][y] = epilogue_operands<KIND>(ep, Nn, sample, min(m0 + wm * 32 + x * 16 + l16, tokens - 1),
+                                                   min(n0 + wn * 32 + y * 16 + kgrp * 4, Nn - 4));
+    }
     for (int p = 0; p < NST - 1 && p < nkt; ++p) issue(p);
     for (int kt = 0; kt < nkt; ++kt) {
         wait_stages(min(NST - 2, nkt - 1 - kt));         // own share of stage kt has landed
@@ -187,7 +215,7 @@ gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restric
                 for (int y = 0; y < 2; ++y)
 #pragma unroll
                     for (int x = 0; x < 2; ++x)
-                        acc[y][x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[y], a[x], acc[y][x], 0, 0, 0);
+                        acc[0][y][x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[y], a[x], acc[0][y][x], 0, 0, 0);
             } else {
                 // one 16-byte read gives a lane 4 adjacent k: instruction e multiplies the k = 4 * group + e
                 f32x4_t a[2], w[2];
@@ -202,7 +230,7 @@ gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restric
                     for (int y = 0; y < 2; ++y)
 #pragma unroll
                         for (int x = 0; x < 2; ++x)
-                            acc[y][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[y][e], a[x][e], acc[y][x], 0, 0, 0);
+                            acc[ks][y][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[y][e], a[x][e], acc[ks][y][x], 0, 0, 0);
             }
         }
     }
@@ -214,10 +242,12 @@ gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restric
         for (int y = 0; y < 2; ++y) {
             const int col = n0 + wn * 32 + y * 16 + kgrp * 4;
             if (col >= Nn) continue;
+            f32x4_t sum = acc[0][y][x];
+            if constexpr (SETS == 2) sum += acc[1][y][x];
             if (g.nsplit > 1)                            // [piece][row][column]
-                *reinterpret_cast<f32x4_t*>(ep.split_ws + (((long)piece * g.batch + sample) * tokens + n) * Nn + col) = acc[y][x];
+                *reinterpret_cast<f32x4_t*>(ep.split_ws + (((long)piece * g.batch + sample) * tokens + n) * Nn + col) = sum;
             else
-                epilogue_quad<KIND, T>(ep, C, Nn, sample, n, col, acc[y][x]);
+                epilogue_quad<KIND, T>(ep, C, Nn, sample, n, col, sum, eo[x][y]);
         }
     }
 }
@@ -234,7 +264,8 @@ gemm_small_reduce_kernel(T* __restrict__ C, int Nn, SmallGrid g, Epilogue ep) {
     f32x4_t s = {0.f, 0.f, 0.f, 0.f};
     for (int p = 0; p < g.nsplit; ++p) s += *reinterpret_cast<const f32x4_t*>(ep.split_ws + (p * rows + row) * Nn + col);
     const int sample = (int)(row / ep.geom.tokens);
-    epilogue_quad<KIND, T>(ep, C, Nn, sample, (int)(row - (long)sample * ep.geom.tokens), col, s);
+    const int n = (int)(row - (long)sample * ep.geom.tokens);
+    epilogue_quad<KIND, T>(ep, C, Nn, sample, n, col, s, epilogue_operands<KIND>(ep, Nn, sample, n, col));
 }
 
 // A sample's plan: a function of the sample's shape alone, so that its result does not depend on the batch.
@@ -244,7 +275,7 @@ gemm_small_reduce_kernel(T* __restrict__ C, int Nn, SmallGrid g, Epilogue ep) {
 //     31.3; 1920 x 1920 at 1000 (480) 17.1 against 24.7, at 1500 (720) 26.4 against 24.3.
 //   fp32: every size (the matrix instructions bind, 32 cycles per 2048 operations, not the LDS reads).
 // K pieces: as many as bring the workgroups to 256 (one per compute unit) where K is short, 512 where it is long (60
-// stages and more), 8 at most and each at least 5 stages.  1920 x 1920 bf16 at 112 tokens (60 tiles): 1 piece 14.2 us,
+// stages and more), 8 at most (fp32 16) and each at least 5 stages.  1920 x 1920 bf16 at 112 tokens (60 tiles): 1 piece 14.2 us,
 // 4 pieces 11.5, 6 pieces 12.2 with the reduction launch; 1920 x 7680: 42.8, 19.0 (4 pieces), 18.5 (8).
 static constexpr int BF16_MAX_TILES = 640;
 struct SmallPlan { bool use; int tiles_m, tiles_n, nsplit; };
@@ -258,8 +289,9 @@ static SmallPlan small_plan(int dtype, int tokens, int Nn, int K, int path) {
     if (dtype == PS_BF16 && (Nn < 64 || tiles > BF16_MAX_TILES)) return p;
     p.use = true;
     if ((path & 0xff) == 4) return p;
+    const long most = dtype == PS_BF16 ? 8 : 16;
     long ns = (nk >= 60 ? 512 : 256) / tiles;
-    ns = ns < 8 ? ns : 8;
+    ns = ns < most ? ns : most;
     ns = ns < nk / 5 ? ns : nk / 5;
     p.nsplit = ns > 1 ? (int)ns : 1;
     return p;
