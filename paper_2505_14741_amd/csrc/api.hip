@@ -201,7 +201,7 @@ int forward_impl(dit* d, const float* x, const void* ctx, const int32_t* t_host,
         // the attention kernels mark heads in a small flag array; the LayerNorm kernel in front of the QKV projection
         // clears it instead of a launch of its own
         int nflags = 0;
-        float* flags = attention_head_flags(dt, batch, c.heads, c.head_dim, attn_ws, path, st, false, &nflags);
+        float* flags = attention_head_flags(dt, batch, N, c.heads, c.head_dim, attn_ws, path, st, false, &nflags);
         // h = LN(X)(1+scale_a)+shift_a
         PS_TIMED(KC_LN, launch_ln_modulate(dt, X, Hb, M, D, c.ln_eps, mod_l, mod_bs, 0, 1, geom, st, flags, nflags,
                                            &pend, c.text_tokens, mod_bs));

@@ -1084,9 +1084,13 @@ static int compute_units() {
     }
     return cached[dev];
 }
+// Up to this many keys the launches cost more than the faster loop gains, and the reference-tracking kernel does every
+// head alone: one launch instead of two (three outside a network).  30 heads: 112 keys 7.6 us against 10.5, 512 keys 16.0
+// against 18.2; at 1500 keys 36.5 against 36.1.
+static constexpr int TRACKED_ONLY_KEYS = 512;
 // kernel path 3 sends every head to the reference-tracking kernel; otherwise every head first takes the
 // software-pipelined kernel without a reference, which marks the heads it could not do
-static bool attention_checked_path(int path) { return (path & 0xff) != 3; }
+static bool attention_checked_path(int path, int seq) { return (path & 0xff) != 3 && seq > TRACKED_ONLY_KEYS; }
 static AttnPlan attention_plan(int seq, int heads) {
     constexpr int KV = 64;
     AttnPlan p;
@@ -1096,10 +1100,17 @@ static AttnPlan attention_plan(int seq, int heads) {
     const int slots = compute_units() * 2;               // two resident workgroups per CU
     const int tail = p.items_ps % slots;
     const int ntiles = (seq + KV - 1) / KV;
-    int ns = tail > 0 ? slots / tail : 1;
+    // Fewer items than slots: splitting pays only while most compute units would stay empty, for two workgroups on a unit
+    // share its matrix cores and every piece costs 70 KB of partial sums written and read.  Items are split to about half
+    // of the compute units, so that a batch of two still gains.  4 heads, 4096 keys (64 items): 75 us whole, 51 in
+    // two pieces, a batch of two 76 and 58 (a batch of four 81 and 96: the plan must not depend on the batch).  30 heads,
+    // 1000 keys (120 items) in 4 pieces: 38.7 us against 27.2 whole, so such shapes stay whole.
+    const int room = p.items_ps < slots ? slots / 4 : slots;
+    int ns = tail > 0 ? room / tail : 1;
     if (ns > 8) ns = 8;
-    if (ns > ntiles / 2) ns = ntiles / 2;
-    if (tail == 0 || p.items_ps < slots || ns < 2) { p.full_ps = p.items_ps; p.tail_ps = 0; p.nsplit = 1; }
+    const int least = p.items_ps < slots ? 8 : 2;        // key tiles per piece
+    if (ns > ntiles / least) ns = ntiles / least;
+    if (tail == 0 || ns < 2) { p.full_ps = p.items_ps; p.tail_ps = 0; p.nsplit = 1; }
     else { p.full_ps = p.items_ps - tail; p.tail_ps = tail; p.nsplit = ns; }
     return p;
 }
@@ -1118,10 +1129,10 @@ bool attention_uses_mfma(int dtype, int head_dim, int path) {
     return dtype == PS_BF16 && head_dim == 64 && (path & 0xff) != 1;
 }
 
-float* attention_head_flags(int dtype, int batch, int heads, int head_dim, void* ws, int path, hipStream_t st,
+float* attention_head_flags(int dtype, int batch, int seq, int heads, int head_dim, void* ws, int path, hipStream_t st,
                             bool clear, int* count) {
     if (count) *count = 0;
-    if (!ws || !attention_uses_mfma(dtype, head_dim, path) || !attention_checked_path(path)) return nullptr;
+    if (!ws || !attention_uses_mfma(dtype, head_dim, path) || !attention_checked_path(path, seq)) return nullptr;
     const int nb = batch * heads;
     if (count) *count = nb;
     if (!clear) return (float*)ws;
@@ -1136,9 +1147,11 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
     if (attention_uses_mfma(dtype, head_dim, path)) {
         if (ws == nullptr) return hipErrorInvalidValue;
         if (s.k_tok >= (1 << 24) || s.v_tok >= (1 << 24)) return hipErrorInvalidValue;   // 32-bit in-tile offsets
-        const bool checked = attention_checked_path(path);
+        const bool checked = attention_checked_path(path, seq);
         AttnPlan p = attention_plan(seq, heads);
-        if ((path & 0xff) == 2) { p.full_ps = p.items_ps; p.tail_ps = 0; p.nsplit = 1; }
+        // the reference-tracking kernel on its own splits nothing where the items do not fill the chip: its items are
+        // then the same as when it repeats a marked head
+        if ((path & 0xff) == 2 || (!checked && p.full_ps == 0)) { p.full_ps = p.items_ps; p.tail_ps = 0; p.nsplit = 1; }
         const float c = scale * 1.4426950408889634f;
         const float cexp = q_prescaled ? 1.0f : c;
         const bf16_t *qq = (const bf16_t*)q, *kk = (const bf16_t*)k, *vv = (const bf16_t*)v;

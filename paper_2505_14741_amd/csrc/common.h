@@ -109,7 +109,7 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
 // The per-(batch, head) flag array of the bf16 head-dim-64 attention inside ws (nullptr if this shape or path has
 // none); *count = its length in 4-byte words; clear: zero it with a launch of its own (else the caller zeroes it
 // before the attention call, e.g. from a kernel that runs anyway).
-float* attention_head_flags(int dtype, int batch, int heads, int head_dim, void* ws, int path, hipStream_t st,
+float* attention_head_flags(int dtype, int batch, int seq, int heads, int head_dim, void* ws, int path, hipStream_t st,
                             bool clear = true, int* count = nullptr);
 
 hipError_t launch_sinusoid(const int32_t* t_host, float* out, int batch, int D, hipStream_t st);
