@@ -137,12 +137,42 @@ int validate_forward(const dit* d, const float* x, const void* ctx, const int32_
     return PS_OK;
 }
 
-// ctx_shared: every sample reads the same [text_tokens, hidden] context (the ranks of a
-// reuse-then-predict cycle share one prompt).
-int forward_impl(dit* d, const float* x, const void* ctx, const int32_t* t_host, float* eps_out,
-                 int batch, void* workspace, hipStream_t st, bool ctx_shared = false) {
+// What the layers read besides the tokens: the modulation vectors of `batch` timesteps and the rotary table.
+struct Conditioning { float *sinus, *hid, *cvec, *mod, *modf, *rope; };
+
+// time conditioning: c = SiLU(W_t2 SiLU(W_t1 s(t) + b_t1) + b_t2); all modulation vectors, and the rotary table if asked
+int condition(dit* d, const int32_t* t_host, int batch, const Conditioning& k, bool rope, hipStream_t st) {
     const dit_config& c = d->cfg;
-    const int D = c.hidden, Dt = c.time_embed_dim, L = c.layers, N = d->N, M = batch * N;
+    const int D = c.hidden, Dt = c.time_embed_dim, L = c.layers, dt = c.dtype;
+    Prof prof{d, st};
+    PS_TIMED(KC_OTHER, launch_tables(t_host, k.sinus, batch, D, rope ? k.rope : nullptr, c.frames, d->Hp, d->Wp, c.head_dim,
+                                     c.rope_theta, st));
+    PS_TIMED(KC_OTHER, launch_gemv(dt, d->W_t1, d->b_t1, k.sinus, k.hid, Dt, D, batch, D, Dt, 1, st));
+    PS_TIMED(KC_OTHER, launch_gemv(dt, d->W_t2, d->b_t2, k.hid, k.cvec, Dt, Dt, batch, Dt, Dt, 1, st));
+    for (int l0 = 0; l0 <= L; l0 += GEMV_SET) {          // the layers' matrices and, as number L, the final one
+        ModSet set{};
+        const int cnt = L + 1 - l0 < GEMV_SET ? L + 1 - l0 : GEMV_SET;
+        for (int i = 0; i < cnt; ++i) {
+            const int l = l0 + i;
+            set.g.W[i] = l < L ? d->layers[l].W_mod : d->W_fm;
+            set.g.bias[i] = l < L ? d->layers[l].b_mod : d->b_fm;
+            set.g.out[i] = l < L ? k.mod + (long)l * 12 * D : k.modf;
+            set.rows[i] = l < L ? 12 * D : 2 * D;
+            set.out_bs[i] = l < L ? (long)L * 12 * D : 2L * D;
+        }
+        PS_TIMED(KC_OTHER, launch_modulation(dt, set, cnt, k.cvec, Dt, batch, Dt, st));
+    }
+    return PS_OK;
+}
+
+// ctx_shared: every sample reads the same [text_tokens, hidden] context (the ranks of a
+// reuse-then-predict cycle share one prompt).  cond: conditioning of these timesteps computed before (else it is computed
+// here, from t_host, in the workspace).
+int forward_impl(dit* d, const float* x, const void* ctx, const int32_t* t_host, float* eps_out,
+                 int batch, void* workspace, hipStream_t st, bool ctx_shared = false,
+                 const Conditioning* cond = nullptr) {
+    const dit_config& c = d->cfg;
+    const int D = c.hidden, L = c.layers, N = d->N, M = batch * N;
     const int dt = c.dtype, path = d->kernel_path;
     WsLayout w = ws_layout(d, batch);
     char* base = (char*)workspace;
@@ -161,21 +191,12 @@ int forward_impl(dit* d, const float* x, const void* ctx, const int32_t* t_host,
     TokenGeom geom{N, c.text_tokens};
     const long mod_bs = (long)L * 12 * D;
 
-    // time conditioning: c = SiLU(W_t2 SiLU(W_t1 s(t) + b_t1) + b_t2); all modulation vectors
-    PS_TIMED(KC_OTHER, launch_sinusoid(t_host, sinus, batch, D, st));
-    PS_TIMED(KC_OTHER, launch_gemv(dt, d->W_t1, d->b_t1, sinus, hid, Dt, D, batch, D, Dt, 1, st));
-    PS_TIMED(KC_OTHER, launch_gemv(dt, d->W_t2, d->b_t2, hid, cvec, Dt, Dt, batch, Dt, Dt, 1, st));
-    for (int l0 = 0; l0 < L; l0 += GEMV_SET) {           // the layers' modulation matrices, 32 per launch
-        GemvSet set{};
-        const int cnt = L - l0 < GEMV_SET ? L - l0 : GEMV_SET;
-        for (int i = 0; i < cnt; ++i) {
-            set.W[i] = d->layers[l0 + i].W_mod; set.bias[i] = d->layers[l0 + i].b_mod;
-            set.out[i] = mod + (long)(l0 + i) * 12 * D;
-        }
-        PS_TIMED(KC_OTHER, launch_gemv_set(dt, set, cnt, cvec, 12 * D, Dt, batch, Dt, mod_bs, 0, st));
+    if (!cond) {
+        const int rc = condition(d, t_host, batch, Conditioning{sinus, hid, cvec, mod, modf, rope}, true, st);
+        if (rc != PS_OK) return rc;
+    } else {
+        mod = cond->mod; modf = cond->modf; rope = cond->rope;
     }
-    PS_TIMED(KC_OTHER, launch_gemv(dt, d->W_fm, d->b_fm, cvec, modf, 2 * D, Dt, batch, Dt, 2 * D, 0, st));
-    PS_TIMED(KC_OTHER, launch_rope_table(rope, c.frames, d->Hp, d->Wp, c.head_dim, c.rope_theta, st));
     PS_TIMED(KC_OTHER, launch_patch_embed(dt, x, ctx, d->W_pe, d->b_pe, X, batch, c.in_channels, c.frames,
                                           c.height, c.width, c.patch, c.text_tokens, D,
                                           ctx_shared ? 0L : (long)c.text_tokens * D, st));
@@ -584,7 +605,7 @@ int plan_schedule(const sampler_schedule* s, RunPlan* plan) {
 // [per-rank samples | per-rank eps_cache | two eps buffers] is the state a run carries from step to step
 // (Algorithm 1: x and eps_cache of every rank, plus the eps of the last step for the adjacent-step sums);
 // everything after `state_end` is scratch.
-struct RunWs { size_t xbuf, cache, pp, state_end, xb, eb, red, dit, total; };
+struct RunWs { size_t xbuf, cache, pp, state_end, xb, eb, red, sinus, hid, cvec, mod, modf, rope, dit, total; int cond_steps; };
 
 RunWs run_layout(const dit* d, const sampler_schedule* s, const RunPlan& plan) {
     size_t n = (size_t)d->cfg.in_channels * d->cfg.frames * d->cfg.height * d->cfg.width;
@@ -600,6 +621,17 @@ RunWs run_layout(const dit* d, const sampler_schedule* s, const RunPlan& plan) {
     w.xb = take(s->batched ? nb * p : 0);
     w.eb = take(s->batched ? nb * p : 0);
     w.red = take(reduce_workspace_bytes(n));
+    // conditioning of up to MAX_BATCH predictor steps at a time: the weights behind it are read once for all of them
+    // (a fifth of a layer's weights; every modulation matrix was read once per step)
+    const dit_config& c = d->cfg;
+    const size_t D = c.hidden, T = s->steps < MAX_BATCH ? s->steps : MAX_BATCH;
+    w.cond_steps = (int)T;
+    w.sinus = take(T * D * 4);
+    w.hid = take(T * c.time_embed_dim * 4);
+    w.cvec = take(T * c.time_embed_dim * 4);
+    w.mod = take(T * c.layers * 12 * D * 4);
+    w.modf = take(T * 2 * D * 4);
+    w.rope = take(rope_table_floats(c.frames, d->Hp, d->Wp, c.head_dim) * 4);
     w.dit = take(dit_workspace_bytes(d, s->batched ? p : 1));
     w.total = off;
     return w;
@@ -694,6 +726,40 @@ int sampler_run_steps(dit* d, const sampler_schedule* s, sampler_state* state, i
     };
 #define PS_RC(expr) do { int rc__ = (expr); if (rc__ != PS_OK) return rc__; } while (0)
 
+    // Conditioning of the steps from `i` on that call the predictor, as many as the workspace holds; it is
+    // computed again when they are used up.  `need` steps from `step` on are asked for together.
+    Conditioning cd{(float*)(base + w.sinus), (float*)(base + w.hid), (float*)(base + w.cvec), (float*)(base + w.mod),
+                    (float*)(base + w.modf), (float*)(base + w.rope)};
+    std::vector<int> cond_steps;
+    bool rope_done = false;
+    auto conditioned = [&](int step, int need, Conditioning* out) -> int {
+        size_t at = 0;
+        while (at < cond_steps.size() && cond_steps[at] != step) ++at;
+        if (at + need > cond_steps.size()) {
+            int32_t ts[MAX_BATCH];
+            cond_steps.clear();
+            for (int j = step; j < stop_step && (int)cond_steps.size() < w.cond_steps; ++j) {
+                int c2, r2;
+                if (s->mode == 1 && position_of(plan, j, &c2, &r2) && r2 != 0) continue;   // direct reuse: no call there
+                ts[cond_steps.size()] = s->timesteps[j];
+                cond_steps.push_back(j);
+            }
+            const int rc2 = condition(d, ts, (int)cond_steps.size(), cd, !rope_done, st);
+            if (rc2 != PS_OK) return rc2;
+            rope_done = true;
+            at = 0;
+        }
+        *out = cd;
+        out->mod += at * (size_t)d->cfg.layers * 12 * d->cfg.hidden;
+        out->modf += at * 2 * (size_t)d->cfg.hidden;
+        return PS_OK;
+    };
+    auto predict = [&](const float* x, float* e, int step, int count, bool shared) -> int {
+        Conditioning k;
+        const int rc2 = conditioned(step, count, &k);
+        return rc2 != PS_OK ? rc2 : forward_impl(d, x, ctx, nullptr, e, count, dws, st, shared, &k);
+    };
+
     // the eps of the last step: nowhere yet (-1), eps buffer 0 / 1, or rank r's cache (2 + r)
     auto eps_at = [&](int code) -> float* { return code < 0 ? nullptr : code < 2 ? pp(code) : cache(code - 2); };
     int calls = fresh ? 0 : state->calls;
@@ -708,12 +774,11 @@ int sampler_run_steps(dit* d, const sampler_schedule* s, sampler_state* state, i
         // rank r's current sample lives in xbuf[src[r]] (after a broadcast every rank reads
         // rank 0's buffer until its next own update)
         for (; i < stop_step; ++i) {
-            int32_t t = s->timesteps[i];
             const float* eprev = eps_at(eprev_code);
             if (i < plan.warm) {
                 const int ecode = toggle;
                 float* e = pp(toggle); toggle ^= 1;
-                PS_RC(forward_impl(d, xbuf(0), ctx, &t, e, 1, dws, st)); ++calls;
+                PS_RC(predict(xbuf(0), e, i, 1, false)); ++calls;
                 PS_RC(step(xbuf(0), e, eprev, xbuf(0), i, true));
                 eprev_code = ecode;
                 if (i == plan.warm - 1) {                                   // eps_cache of every rank
@@ -728,7 +793,7 @@ int sampler_run_steps(dit* d, const sampler_schedule* s, sampler_state* state, i
                 if (rnd == 0) {
                     const int ecode = toggle;
                     float* en = pp(toggle); toggle ^= 1;
-                    PS_RC(forward_impl(d, xbuf(0), ctx, &t, en, 1, dws, st)); ++calls;
+                    PS_RC(predict(xbuf(0), en, i, 1, false)); ++calls;
                     e = en;
                     eprev_code = ecode;
                 }
@@ -739,7 +804,7 @@ int sampler_run_steps(dit* d, const sampler_schedule* s, sampler_state* state, i
                 int ecode;
                 if (master == 0 || latest) { ecode = toggle; e = pp(toggle); toggle ^= 1; }
                 else { ecode = 2 + master; e = cache(master); }
-                PS_RC(forward_impl(d, xbuf(src[master]), ctx, &t, e, 1, dws, st)); ++calls;
+                PS_RC(predict(xbuf(src[master]), e, i, 1, false)); ++calls;
                 // ranks that still have to predict in this cycle advance with their own cache;
                 // they may read rank 0's buffer, so they go before rank 0's in-place update
                 for (int r = master + 1; r < p; ++r) {
@@ -760,10 +825,8 @@ int sampler_run_steps(dit* d, const sampler_schedule* s, sampler_state* state, i
     } else {
         // batched: rank 0's sample lives in xbuf(0); inputs of a cycle in xb(r); the eps of the last step in pp(0)
         float* eprev_buf = pp(0);
-        int32_t tb[MAX_BATCH];
         for (; i < plan.warm && i < stop_step; ++i) {
-            tb[0] = s->timesteps[i];
-            PS_RC(forward_impl(d, xbuf(0), ctx, tb, eb(0), 1, dws, st)); ++calls;
+            PS_RC(predict(xbuf(0), eb(0), i, 1, false)); ++calls;
             PS_RC(step(xbuf(0), eb(0), eprev_code >= 0 ? eprev_buf : nullptr, xbuf(0), i, true));
             PS_RC(copy(eprev_buf, eb(0)));
             eprev_code = 0;
@@ -779,9 +842,8 @@ int sampler_run_steps(dit* d, const sampler_schedule* s, sampler_state* state, i
                 PS_RC(step(xbuf(0), cache(r), nullptr, xb(r), i, false));
                 for (int jj = 1; jj < r; ++jj) PS_RC(step(xb(r), cache(r), nullptr, xb(r), i + jj, false));
             }
-            for (int r = 0; r < nn; ++r) tb[r] = s->timesteps[i + r];
             // the text context is shared by all ranks of the cycle
-            PS_RC(forward_impl(d, xb(0), ctx, tb, eb(0), nn, dws, st, true)); ++calls;
+            PS_RC(predict(xb(0), eb(0), i, nn, true)); ++calls;
             for (int r = 0; r < nn; ++r) {
                 const float* prev = r == 0 ? (eprev_code >= 0 ? eprev_buf : nullptr) : eb(r - 1);
                 PS_RC(step(xbuf(0), eb(r), prev, xbuf(0), i + r, true));

@@ -112,11 +112,19 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
 float* attention_head_flags(int dtype, int batch, int seq, int heads, int head_dim, void* ws, int path, hipStream_t st,
                             bool clear = true, int* count = nullptr);
 
-hipError_t launch_sinusoid(const int32_t* t_host, float* out, int batch, int D, hipStream_t st);
+// sinusoid vectors of `batch` timesteps and, if rope is given, the rotary table, in one launch
+hipError_t launch_tables(const int32_t* t_host, float* sinus, int batch, int D, float* rope, int F, int Hp, int Wp,
+                         int head_dim, float theta, hipStream_t st);
 // out[b, r] = act(W[r,:] . in[b,:] + bias[r]);  act: 0 none, 1 SiLU.  W in dtype, in/out fp32.
 // up to GEMV_SET matrices of one shape applied to one input in a single launch
 constexpr int GEMV_SET = 32;
 struct GemvSet { const void* W[GEMV_SET]; const float* bias[GEMV_SET]; float* out[GEMV_SET]; };
+// The modulation matrices of a network (12 * D rows each) and the final one (2 * D rows), all applied to the same vectors:
+// a matrix product in fp32 on matrix instructions where cols % 64 == 0, cols <= 1000 and rows % 4 == 0, one launch_gemv per matrix otherwise.
+// out_bs[i]: batch stride of matrix i's output; rows[i]: its rows.
+struct ModSet { GemvSet g; int rows[GEMV_SET]; long out_bs[GEMV_SET]; };
+hipError_t launch_modulation(int dtype, const ModSet& set, int count, const float* in, int cols, int batch, long in_bs,
+                             hipStream_t st);
 hipError_t launch_gemv_set(int dtype, const GemvSet& set, int count, const float* in, int rows, int cols, int batch,
                            long in_bs, long out_bs, int act, hipStream_t st);
 // Rotary (cos, sin) of pair `pair` (0 .. d/2-1) for video token nv: which axis the pair belongs to, its index on
@@ -135,8 +143,6 @@ hipError_t launch_gemv(int dtype, const void* W, const float* bias, const float*
                        int rows, int cols, int batch, long in_bstride, long out_bstride, int act,
                        hipStream_t st);
 size_t rope_table_floats(int F, int Hp, int Wp, int head_dim);
-hipError_t launch_rope_table(float* table, int F, int Hp, int Wp, int head_dim,
-                             float theta, hipStream_t st);
 hipError_t launch_patch_embed(int dtype, const float* x, const void* ctx, const void* W_pe,
                               const float* b_pe, float* X, int batch, int C, int F, int H, int Wd,
                               int patch, int text_tokens, int D, long ctx_batch_stride,

@@ -25,23 +25,13 @@ struct TList { int t[16]; };
 
 // s(t) = [cos(t w_j) | sin(t w_j)], w_j = 10000^(-j/(D/2)); double precision because
 // t*w reaches ~1e3 rad and the result feeds an fp32 MLP compared at 1e-4.
-__global__ void sinusoid_kernel(TList tl, float* __restrict__ out, int D) {
-    int b = blockIdx.y;
+__device__ __forceinline__ void sinusoid_entry(const TList& tl, float* __restrict__ out, int D, int b, int j) {
     int half = D / 2;
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= half) return;
     double w = exp(-(double)j / (double)half * 9.210340371976184);   // ln(10000)
     double ang = (double)tl.t[b] * w;
     out[(long)b * D + j] = (float)cos(ang);
     out[(long)b * D + half + j] = (float)sin(ang);
-}
-
-hipError_t launch_sinusoid(const int32_t* t_host, float* out, int batch, int D, hipStream_t st) {
-    TList tl;
-    for (int i = 0; i < 16; ++i) tl.t[i] = i < batch ? t_host[i] : 0;
-    dim3 grid((D / 2 + 127) / 128, batch);
-    sinusoid_kernel<<<grid, 128, 0, st>>>(tl, out, D);
-    return hipGetLastError();
 }
 
 // One wave per GEMV_ROWS consecutive output rows (8 for a single input vector, 4 for batches); weights stream once from HBM (16 bytes per lane and load when
@@ -155,15 +145,128 @@ hipError_t launch_gemv(int dtype, const void* W, const float* bias, const float*
     return launch_gemv_set(dtype, set, 1, in, rows, cols, batch, in_bs, out_bs, act, st);
 }
 
+// The modulation matrices as one matrix product in fp32, out[b][row] = W[row] . in[b] + bias[row], on
+// v_mfma_f32_16x16x4_f32: 16 rows x up to 16 vectors per instruction, weights widened to fp32, so that one pass over the
+// weights (708 MB for 30 layers of 1920) serves every timestep of a run's next steps.  Reading them is the bound.  A wave
+// takes 16 or 32 rows at a time; lane l reads 16 adjacent weights of row l % 16, whole 128-byte lines (bf16) per row and 64 columns.  Four
+// sums per output.  The same kernel serves one vector, so a vector's result does not depend on the batch.
+// (The kernel above pays six shuffles per row and vector: 148 us for one vector and 30 layers, 295 for four; this takes 163
+// for one and 181 for nine.)
+static constexpr int MOD_MAX_COLS = 1000;                // 16 vectors of cols + 4 floats within 64 KB of LDS
+template <typename T, int R>                             // R: groups of 16 rows per wave and pass
+__global__ void __launch_bounds__(256)
+modulation_kernel(ModSet set, const float* __restrict__ in, int cols, int batch, long in_bs, int wg_rows) {
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    extern __shared__ __attribute__((aligned(16))) float xs[];   // [batch][cols + 4]: 4 banks from vector to vector
+    const int rows = set.rows[blockIdx.y], ld = cols + 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kgrp = lane >> 4;
+    if ((int)blockIdx.x * wg_rows >= rows) return;       // (whole workgroup)
+    for (int e = threadIdx.x * 4; e < batch * cols; e += 1024) {
+        const int b = e / cols, c = e - b * cols;
+        *reinterpret_cast<f4*>(xs + b * ld + c) = *reinterpret_cast<const f4*>(in + b * in_bs + c);
+    }
+    __syncthreads();
+    const T* W = static_cast<const T*>(set.g.W[blockIdx.y]);
+    const float* x = xs + (l16 < batch ? l16 : 0) * ld + kgrp * 16;   // columns past the batch repeat vector 0, unused
+    for (int row0 = blockIdx.x * wg_rows + wave * 16 * R; row0 < min(rows, (int)(blockIdx.x + 1) * wg_rows); row0 += 64 * R) {
+        const T* w[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) w[r] = W + (long)min(row0 + r * 16 + l16, rows - 1) * cols + kgrp * 16;
+        f4 acc[R][4];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) acc[r][a] = f4{0.f, 0.f, 0.f, 0.f};
+        // 16 loads of 16 bytes per lane requested together, then multiplied (512 columns in bf16 with R = 1)
+        constexpr int NQ = sizeof(T);                    // 16-byte loads per 16 weights: 2 (bf16) or 4
+        constexpr int CH = 16 / (NQ * R);                      // steps of 64 columns in flight
+        for (int c0 = 0; c0 < cols; c0 += 64 * CH) {
+            uint4 raw[CH][R][NQ];
+#pragma unroll
+            for (int h = 0; h < CH; ++h)
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int i = 0; i < NQ; ++i) {
+                        const int c = min(c0 + 64 * h, cols - 64);   // (past the end: read again, not multiplied)
+                        raw[h][r][i] = *reinterpret_cast<const uint4*>(w[r] + c + i * (16 / NQ));
+                    }
+#pragma unroll
+            for (int h = 0; h < CH; ++h) {
+                if (c0 + 64 * h >= cols) break;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const f4 xv = *reinterpret_cast<const f4*>(x + c0 + 64 * h + i * 4);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        f4 wv;
+                        if constexpr (sizeof(T) == 2) {
+                            const unsigned* u = reinterpret_cast<const unsigned*>(&raw[h][r][i / 2]) + (i & 1) * 2;
+#pragma unroll
+                            for (int e = 0; e < 2; ++e) {            // bf16 -> fp32: the upper half of the word
+                                wv[2 * e] = __uint_as_float(u[e] << 16);
+                                wv[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
+                            }
+                        } else {
+                            wv = __builtin_bit_cast(f4, raw[h][r][i]);
+                        }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            acc[r][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], xv[e], acc[r][e], 0, 0, 0);
+                    }
+                }
+            }
+        }
+        if (l16 >= batch) continue;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int row = row0 + r * 16 + kgrp * 4;    // rows % 4 == 0: inside or outside together
+            if (row >= rows) continue;
+            const f4 s = (acc[r][0] + acc[r][1]) + (acc[r][2] + acc[r][3]);
+            *reinterpret_cast<f4*>(set.g.out[blockIdx.y] + l16 * set.out_bs[blockIdx.y] + row) =
+                s + *reinterpret_cast<const f4*>(set.g.bias[blockIdx.y] + row);
+        }
+    }
+}
+
+hipError_t launch_modulation(int dtype, const ModSet& set, int count, const float* in, int cols, int batch, long in_bs,
+                             hipStream_t st) {
+    if (count < 1 || count > GEMV_SET || batch < 1 || batch > 16) return hipErrorInvalidValue;
+    int most = 0;
+    bool ok = cols % 64 == 0 && cols <= MOD_MAX_COLS && in_bs % 4 == 0;   // (never a matter of the batch)
+    for (int i = 0; i < count; ++i) {
+        if (set.rows[i] > most) most = set.rows[i];
+        ok = ok && set.rows[i] % 4 == 0 && set.out_bs[i] % 4 == 0;
+    }
+    if (!ok) {
+        for (int i = 0; i < count; ++i) {
+            const hipError_t e = launch_gemv(dtype, set.g.W[i], set.g.bias[i], in, set.g.out[i], set.rows[i], cols, batch, in_bs,
+                                             set.out_bs[i], 0, st);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    // Few matrices have to fill the chip: 64 rows per workgroup, 16 per wave.  Many: 256, 32 at a time, so that the vectors
+    // are read from LDS half as often and staged less.  (The values are the same.)  23040 x 512 bf16, one layer and the
+    // final matrix: 13.7 us against 26; 30 layers: 188 us against 163.
+    const bool few = (long)most * count <= 200000;
+    const int wg_rows = few ? 64 : 256;
+    dim3 grid((most + wg_rows - 1) / wg_rows, count);
+    const size_t sh = (size_t)batch * (cols + 4) * sizeof(float);
+    auto go = [&](auto kernel) { kernel<<<grid, 256, sh, st>>>(set, in, cols, batch, in_bs, wg_rows); };
+    if (dtype == PS_BF16) { if (few) go(modulation_kernel<bf16_t, 1>); else go(modulation_kernel<bf16_t, 2>); }
+    else { if (few) go(modulation_kernel<float, 1>); else go(modulation_kernel<float, 2>); }
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------------------- 3D RoPE table
 // (cos, sin) of pos * theta^(-2m/d_A), axis widths d/4, 3d/8, 3d/8 over (frame, row, col), double precision
 // angles.  The angle of a pair depends on the token only through its position on the pair's axis, so the table is
 // stored per axis -- [F][d/8], [Hp][3d/16], [Wp][3d/16] entries of (cos, sin) -- about 1 KB instead of 256 bytes
 // per token: the projection epilogue that rotates q and k finds it in the nearest cache.
-__global__ void rope_table_kernel(float2* __restrict__ table, int F, int Hp, int Wp, int head_dim, float theta) {
+__device__ __forceinline__ void rope_entry(float2* __restrict__ table, int F, int Hp, int Wp, int head_dim, float theta, int idx) {
     const int p0 = head_dim / 8, p1 = 3 * head_dim / 16;
     const int total = F * p0 + (Hp + Wp) * p1;
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= total) return;
     int pos, m, dA;
     if (idx < F * p0) { pos = idx / p0; m = idx % p0; dA = 2 * p0; }
@@ -177,11 +280,31 @@ size_t rope_table_floats(int F, int Hp, int Wp, int head_dim) {
     return 2 * ((size_t)F * (head_dim / 8) + (size_t)(Hp + Wp) * (3 * head_dim / 16));
 }
 
-hipError_t launch_rope_table(float* table, int F, int Hp, int Wp, int head_dim,
-                             float theta, hipStream_t st) {
-    const int total = (int)(rope_table_floats(F, Hp, Wp, head_dim) / 2);
-    if (total == 0) return hipSuccess;
-    rope_table_kernel<<<(total + 255) / 256, 256, 0, st>>>(reinterpret_cast<float2*>(table), F, Hp, Wp, head_dim, theta);
+// Both tables in one launch (each was a few microseconds of its own): rows 0 .. batch - 1 of the grid are the timesteps,
+// the last row the rotary table.
+__global__ void __launch_bounds__(128)
+tables_kernel(TList tl, float* __restrict__ sinus, int D, int batch, float2* __restrict__ rope, int F, int Hp, int Wp,
+              int head_dim, float theta) {
+    const int stride = gridDim.x * 128;
+    if ((int)blockIdx.y < batch) {
+        for (int j = blockIdx.x * 128 + threadIdx.x; j < D / 2; j += stride) sinusoid_entry(tl, sinus, D, blockIdx.y, j);
+    } else {
+        const int total = F * (head_dim / 8) + (Hp + Wp) * (3 * head_dim / 16);
+        for (int i = blockIdx.x * 128 + threadIdx.x; i < total; i += stride) rope_entry(rope, F, Hp, Wp, head_dim, theta, i);
+    }
+}
+
+hipError_t launch_tables(const int32_t* t_host, float* sinus, int batch, int D, float* rope, int F, int Hp, int Wp,
+                         int head_dim, float theta, hipStream_t st) {
+    TList tl;
+    for (int i = 0; i < 16; ++i) tl.t[i] = i < batch ? t_host[i] : 0;
+    const size_t entries = rope ? rope_table_floats(F, Hp, Wp, head_dim) / 2 : 0;
+    size_t most = (size_t)(D / 2) > entries ? (size_t)(D / 2) : entries;
+    size_t blocks = (most + 127) / 128;
+    if (blocks < 1) return hipSuccess;
+    if (blocks > 65536) blocks = 65536;                  // (a longer table is walked)
+    tables_kernel<<<dim3((unsigned)blocks, batch + (entries ? 1 : 0)), 128, 0, st>>>(
+        tl, sinus, D, batch, reinterpret_cast<float2*>(rope), F, Hp, Wp, head_dim, theta);
     return hipGetLastError();
 }
 
