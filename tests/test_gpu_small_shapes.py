@@ -1,0 +1,137 @@
+"""Kernels for few tokens and for fp32 operands at the sizes where they can go wrong: edges of 64 x 64 tiles, K pieces of
+unequal length, pieces added by the following LayerNorm, ragged keys, more predictor steps than one conditioning chunk."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import parastep_oracle as O
+from paper_2505_14741_amd import binding as B
+from paper_2505_14741_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def rel(ref, out):
+    return float(np.linalg.norm(out.astype(np.float64) - ref) / np.linalg.norm(ref))
+
+
+# bounds: fp32 sums of K products, error at most about sqrt(K) * 2^-24 of the result's norm (K = 7680: 5e-6); bf16 results
+# are rounded once, 2^-9 at most
+@pytest.mark.parametrize("M", [1, 63, 64, 65, 130])
+@pytest.mark.parametrize("Nn,K", [(64, 64), (68, 320), (196, 1984), (1920, 7680), (4, 96)])
+@pytest.mark.parametrize("act", [0, 1])
+def test_linear_few_rows_split_and_whole(M, Nn, K, act):
+    print(f"dit_linear M={M} N={Nn} K={K} act={act}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M * 7 + Nn)
+    for td, bound in ((torch.float32, 5e-6), (torch.bfloat16, 2.0 ** -9)):
+        a = torch.randn(M, K, generator=g, device=DEV).to(td)
+        w = (torch.randn(Nn, K, generator=g, device=DEV) / math.sqrt(K)).to(td)
+        bias = torch.randn(Nn, generator=g, device=DEV)
+        ref = a.double() @ w.double().t() + bias.double()
+        if act:
+            ref = torch.nn.functional.gelu(ref, approximate="tanh")
+        ref = ref.cpu().numpy()
+        for kw in ({}, {"use_workspace": False}, {"kernel_path": 4}):     # in K pieces, and whole both ways
+            assert rel(ref, B.dit_linear(a, w, bias, act, **kw).double().cpu().numpy()) <= bound, (td, kw)
+
+
+@pytest.mark.parametrize("N", [640 * 64 // 30, 640 * 64 // 30 + 64])
+def test_linear_on_both_sides_of_the_tile_limit(N):
+    """1920 columns are 30 column tiles: 21 row tiles are 630 of them, 22 are 660, beyond the limit of 640."""
+    N = N // 64 * 64
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N)
+    for K in (1920, 7680):                           # 7680: K pieces on either kernel
+        a = torch.randn(N, K, generator=g, device=DEV).bfloat16()
+        w = (torch.randn(1920, K, generator=g, device=DEV) / math.sqrt(K)).bfloat16()
+        bias = torch.randn(1920, generator=g, device=DEV)
+        ref = (a.double() @ w.double().t() + bias.double()).cpu().numpy()
+        assert rel(ref, B.dit_linear(a, w, bias, 0).double().cpu().numpy()) <= 2.0 ** -9
+
+
+@pytest.mark.parametrize("N", [1, 15, 16, 17, 63, 64, 65, 200])
+@pytest.mark.parametrize("d", [16, 32, 64])
+def test_attention_fp32_math_ragged(N, d):
+    """fp32, and bf16 at the head dims that run with fp32 math (one rounding of the result); logits of order 10 in one head."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N + d)
+    for td, bound in ((torch.float32, 2e-6), (torch.bfloat16, 2.0 ** -9)):
+        if td == torch.bfloat16 and d == 64:
+            continue
+        q, k, v = (torch.randn(2, N, 3, d, generator=g, device=DEV).to(td) for _ in range(3))
+        q[:, :, 1] *= 4.0
+        out = B.attn3d(q, k, v, d ** -0.5)
+        s = torch.einsum("bqhd,bkhd->bhqk", q.double().cpu(), k.double().cpu()) * d ** -0.5
+        ref = torch.einsum("bhqk,bkhd->bqhd", torch.softmax(s, -1), v.double().cpu()).numpy()
+        assert rel(ref, out.double().cpu().numpy()) <= bound
+
+
+@pytest.mark.parametrize("N", [512, 513, 1024, 4096])
+def test_attention_bf16_around_the_one_launch_limit_and_with_few_items(N):
+    """4 heads: whole items through one kernel, then two kernels, then items in key pieces; the batch changes no bit."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N)
+    q, k, v = (torch.randn(2, N, 4, 64, generator=g, device=DEV).bfloat16() for _ in range(3))
+    out = B.attn3d(q, k, v, 0.125)
+    assert torch.equal(B.attn3d(q[1:], k[1:], v[1:], 0.125)[0], out[1])
+    rows = torch.tensor([0, 1, N // 2, N - 1])
+    for h in range(4):
+        kd, vd = k[0, :, h].double().cpu(), v[0, :, h].double().cpu()
+        ref = (torch.softmax(q[0, rows, h].double().cpu() @ kd.t() * 0.125, -1) @ vd).numpy()
+        # probabilities and result in bf16: two roundings of 2^-9
+        assert rel(ref, out[0, rows, h].double().cpu().numpy()) <= 2 * 2.0 ** -8
+
+
+@pytest.mark.parametrize("text", [0, 6, 70])
+@pytest.mark.parametrize("frames,rows,cols", [(1, 3, 3), (2, 8, 8), (3, 5, 7)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_forward_few_tokens(dtype, frames, rows, cols, text):
+    """Text rows and video rows in one tile, tiles of text only, token counts off the tile; both types against the oracle."""
+    base = I.CONFIGS["tiny_text"] if dtype == "f32" else I.CONFIGS["reduced"].with_(layers=2)
+    cfg = base.with_(frames=frames, height=2 * rows, width=2 * cols, text_tokens=text)
+    print(f"forward {dtype} tokens {cfg.tokens} text {text}", flush=True)
+    W = I.make_weights(cfg, 1001, "unit")
+    d = B.dit_create(cfg, B.weights_to_device(cfg, W, DEV))
+    x, ctx = I.make_latent(cfg, 2), I.make_context(cfg, 2) if text else None
+    ctxd = torch.from_numpy(ctx).to(DEV).to(B.torch_dtype(dtype)) if text else None
+    xd = torch.from_numpy(x).to(DEV)
+    eps = B.dit_forward(d, xd, ctxd, [900, 20])
+    ref = O.dit_forward(cfg, dict(W), x, ctx, [900, 20])
+    for b in range(2):
+        assert O.rel_mae(ref[b], eps[b].cpu().numpy())[2] <= (1e-4 if dtype == "f32" else 2e-2)
+        one = B.dit_forward(d, xd[b:b + 1].contiguous(), None if ctxd is None else ctxd[b:b + 1].contiguous(), [[900, 20][b]])
+        assert torch.equal(one[0], eps[b])
+
+
+@pytest.mark.parametrize("mode,batched,S,m,cyc", [(0, False, 37, 3, [4] * 9), (1, False, 37, 1, [3] * 12), (0, True, 37, 2, [7] * 5)])
+def test_run_longer_than_one_conditioning_chunk(mode, batched, S, m, cyc):
+    """More predictor calls than the 16 whose modulation is computed together: step by step (one at a time) equals the whole
+    run bit for bit."""
+    cfg = I.CONFIGS["tiny_text"]
+    d = B.dit_create(cfg, B.weights_to_device(cfg, I.make_weights(cfg, 1001, "unit"), DEV))
+    x_T = torch.from_numpy(I.make_latent(cfg, 1)).to(DEV)
+    ctx = torch.from_numpy(I.make_context(cfg, 1)).to(DEV)
+    ts, a, b = B.ddim_coefficients(S)
+    sched = B.Schedule(ts, a, b, m, cyc, batched=batched, mode=mode)
+    x0, sums, _ = B.sampler_run(d, sched, x_T, ctx)
+    ws, state, out, sums2 = B.sampler_workspace(d, sched, DEV), B.SamplerState(), torch.empty_like(x_T), torch.zeros_like(sums)
+    stops = list(range(1, S + 1)) if not batched else list(range(1, m + 1)) + [min(S, m + 7 * (i + 1)) for i in range(5)]
+    for stop in stops:
+        B.sampler_run_steps(d, sched, state, stop, x_T, ctx, ws, out, sums2)
+    assert torch.equal(out, x0) and torch.equal(sums2, sums)
+
+
+@pytest.mark.parametrize("Dt", [64, 72, 1024])
+def test_modulation_widths_on_and_off_the_matrix_path(Dt):
+    """time_embed_dim a multiple of 64 up to 1000 takes the matrix kernel, others one vector product per matrix."""
+    cfg = I.CONFIGS["tiny_text"].with_(time_embed_dim=Dt)
+    W = I.make_weights(cfg, 1001, "unit")
+    d = B.dit_create(cfg, B.weights_to_device(cfg, W, DEV))
+    x, ctx = I.make_latent(cfg, 3), I.make_context(cfg, 3)
+    eps = B.dit_forward(d, torch.from_numpy(x).to(DEV), torch.from_numpy(ctx).to(DEV), [900, 500, 20])
+    ref = O.dit_forward(cfg, dict(W), x, ctx, [900, 500, 20])
+    assert O.rel_mae(ref, eps.cpu().numpy())[2] <= 1e-4
