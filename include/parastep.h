@@ -31,9 +31,10 @@
  * Shape limits (anything beyond them is PS_ERR_SHAPE at dit_create, never a slow or wrong
  * path): layers <= 64, hidden <= 2048 and a multiple of 8, head_dim in {16, 32, 64},
  * mlp_ratio <= 8, batch <= 16, in_channels*patch^2 <= 1024, at most 2^24 tokens per sample
- * and, for bf16, tokens * hidden * max(mlp_ratio, 3) < 2^31.  The MFMA kernels serve bf16
- * with K % 64 == 0 and at least 64 outputs (projections) and head_dim 64 (attention);
- * every other accepted shape runs on generic fp32-FMA kernels.
+ * and, for bf16, tokens * hidden * max(mlp_ratio, 3) < 2^31.  Matrix kernels serve bf16
+ * with K % 64 == 0 and at least 64 outputs and fp32 with K % 32 == 0 (projections, outputs
+ * a multiple of 4) and every attention shape (bf16 products at head_dim 64, fp32 otherwise);
+ * every other accepted projection runs on a generic fp32-FMA kernel.
  */
 #ifndef PARASTEP_H
 #define PARASTEP_H
@@ -102,8 +103,8 @@ PS_API int dit_destroy(dit* d);
  * 0 the fastest kernel for each shape, 1 the generic fp32-FMA kernels, 2 bf16 attention without
  * the key split of its last partial round of workgroups, 3 bf16 head-dim-64 attention always
  * through the kernel that tracks a softmax reference (the one without is not tried first),
- * 4 projections whose last partial round of workgroups is not divided along k.  Bits 8-11: tile variant of the bf16
- * MFMA projections (0 automatic, 1: 256x256, 2: 128x128, 3: 192x256, 4: 192x128); the variant
+ * 4 projections not divided along k.  Bits 8-11: tile variant of the bf16
+ * MFMA projections beyond the size that one kernel of 64x64 tiles serves whatever the variant (0 automatic, 1: 256x256, 2: 128x128, 3: 192x256, 4: 192x128); the variant
  * decides which workgroup computes an output and, for k >= 4096, which outputs of the last partial
  * round are summed in k pieces (a different rounding of those); nothing else.  Other values:
  * PS_ERR_SHAPE.
@@ -148,7 +149,7 @@ PS_API int ps_mfma_probe(int iters, float* sink, double* flops_out, void* hip_st
  * read, but V must be finite (masked keys multiply V by an exact 0).
  * workspace: DEVICE, 256-byte aligned, >= attn3d_workspace_bytes(...) (may be NULL when
  * that is 0); scratch only.  It is non-zero for bf16 with head_dim 64: the kernel that needs no
- * running maximum checks its own sums and marks, per (batch, head), what it could not do there
+ * running maximum (sequences beyond 512) checks its own sums and marks, per (batch, head), what it could not do there
  * (a second kernel that tracks a softmax reference recomputes those heads), and the workgroups
  * that split their keys in the last, partial round leave their partial sums there (merged by
  * that second launch).
@@ -164,8 +165,8 @@ PS_API int attn3d(const void* q, const void* k, const void* v, void* o,
  * 16-byte aligned.  n_out even, k % 8 == 0; bf16 shapes of the MFMA kernel (k % 64 == 0,
  * n_out % 4 == 0, n_out >= 64) need m * n_out < 2^31.
  * workspace: DEVICE scratch, 256-byte aligned, or NULL.  With at least
- * dit_linear_workspace_bytes(...) of it, shapes whose output tiles do not fill the last round
- * of workgroups split those tiles along k (fp32 partial sums pass through the workspace and
+ * dit_linear_workspace_bytes(...) of it, shapes whose output tiles do not fill the chip, or the
+ * last round of workgroups on it, split those tiles along k (fp32 partial sums pass through the workspace and
  * are added in a fixed order); with NULL or less the call computes the same product unsplit.
  * The two differ only in summation order.
  * kernel_path: as for dit_set_kernel_path (0 = default); it enters the workspace size. */
