@@ -314,7 +314,7 @@ hipError_t launch_tables(const int32_t* t_host, float* sinus, int batch, int D, 
 // tokens x 64 columns, both operands staged in LDS 64 patch values at a time.  The weights are the first operand, so a
 // lane ends with 4 adjacent columns of one token: X is written in 16-byte stores, and writing it is the bound for many
 // tokens.  (One workgroup per 16 tokens whose threads each walked a whole weight row took 98 us at 112 tokens -- seven
-// workgroups, uncoalesced -- and 116 us at 4516; this takes 15 and 38, 17776 tokens 159 -> 120.)
+// workgroups, uncoalesced -- and 116 us at 4516; this takes 13 and 33, 17776 tokens 159 -> 100.)
 template <typename T>
 __global__ void __launch_bounds__(256)
 patch_embed_kernel(const float* __restrict__ x, const T* __restrict__ ctx, const T* __restrict__ W_pe,
@@ -340,10 +340,15 @@ patch_embed_kernel(const float* __restrict__ x, const T* __restrict__ ctx, const
         const float* xp = x + (((long)b * C * F + f) * H + (long)i * patch) * Wd + (long)j * patch;
         for (int k0 = 0; k0 < P; k0 += KC) {
             float pv[KC / 4], wv[TILE / 4];              // all 32 loads of a thread in flight together
+            // where patch value k0 + lane lies, one division per lane; read from that lane below (a division per value and
+            // wave cost 38 against 33 us at 4516 tokens, 120 against 100 at 17776)
+            const int lp = k0 + lane, lc = lp / (patch * patch), lr = lp - lc * patch * patch, ly = lr / patch;
+            const int in_plane = ly * Wd + (lr - ly * patch);
 #pragma unroll
             for (int u = 0; u < KC / 4; ++u) {           // patch value wave + 4u of every token (uniform per wave)
-                const int pi = k0 + wave + 4 * u, dx = pi % patch, dy = (pi / patch) % patch, c = pi / (patch * patch);
-                pv[u] = video && pi < P ? xp[((long)c * F * H + dy) * Wd + dx] : 0.f;
+                const int c = __builtin_amdgcn_readlane(lc, wave + 4 * u);
+                const int at = __builtin_amdgcn_readlane(in_plane, wave + 4 * u);
+                pv[u] = video && k0 + wave + 4 * u < P ? xp[(long)c * F * H * Wd + at] : 0.f;
             }
 #pragma unroll
             for (int u = 0; u < TILE / 4; ++u) {         // weight k0 + lane of row wave + 4u
