@@ -135,3 +135,20 @@ def test_modulation_widths_on_and_off_the_matrix_path(Dt):
     eps = B.dit_forward(d, torch.from_numpy(x).to(DEV), torch.from_numpy(ctx).to(DEV), [900, 500, 20])
     ref = O.dit_forward(cfg, dict(W), x, ctx, [900, 500, 20])
     assert O.rel_mae(ref, eps.cpu().numpy())[2] <= 1e-4
+
+
+@pytest.mark.parametrize("n", [1, 5, 4095, 4096, 4097])
+def test_update_and_rel_mae_on_one_and_two_workgroups(n):
+    """Up to 4096 elements one workgroup writes the sums itself; a thread adds at most 16 values in fp32, the rest is double."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    x, e, ep = (torch.randn(n, generator=g, device=DEV) for _ in range(3))
+    out, sums = B.sampler_step(x, e, ep, 1.01, -0.05)
+    xd, ed = x.double(), e.double()
+    dl = 0.01 * xd - 0.05 * ed
+    ref = torch.stack([dl.abs().sum(), (xd + dl).abs().sum(), (ed - ep.double()).abs().sum(), ed.abs().sum()])
+    assert torch.allclose(sums.double(), ref, rtol=16 * 2.0 ** -23, atol=0)
+    r = B.rel_mae(x, e).double()
+    num, den = (xd - ed).abs().sum(), xd.abs().sum()
+    assert torch.allclose(r, torch.stack([num, den, num / den]), rtol=16 * 2.0 ** -23, atol=0)
+    assert torch.isnan(B.rel_mae(torch.zeros(n, device=DEV), torch.zeros(n, device=DEV))[2])
