@@ -37,8 +37,7 @@ __device__ __forceinline__ void sinusoid_entry(const TList& tl, float* __restric
 // One wave per GEMV_ROWS consecutive output rows (8 for a single input vector, 4 for batches); weights stream once from HBM (16 bytes per lane and load when
 // the row length allows, the loads of the wave's rows in flight together), inputs stay in cache and are read once
 // for the wave's rows.  Each row's sum is formed as if the wave had that row alone (same lanes, same order).
-// blockIdx.y picks one of up to GEMV_SET matrices of the same shape applied to the same input (the modulation
-// matrices of all layers in one launch).
+// blockIdx.y picks one of up to GEMV_SET matrices of the same shape applied to the same input.
 template <typename T, int MAXB, int GEMV_ROWS>
 __global__ void gemv_kernel(GemvSet set, const float* __restrict__ in, int rows,
                             int cols, int batch, long in_bs, long out_bs, int act) {
@@ -559,9 +558,10 @@ ln_modulate_row_kernel(float* __restrict__ X, T* __restrict__ out, int M, int D,
     }
 }
 
-// up to this many tokens per sample a row gets a workgroup (the choice changes the order of a row's sums, so it must
+// up to this many tokens per sample a row gets a workgroup: 112 rows 8.4 -> 5.5 us, 2060 rows 9.6 -> 7.3, 4400 rows 13.9 ->
+// 11.4, 6200 rows 19.7 -> 14.1; 17776 rows take the wave kernel 40 us, 5.1 TB/s (the choice changes the order of a row's sums, so it must
 // not depend on the batch)
-static constexpr int LN_ROW_TOKENS = 2048;
+static constexpr int LN_ROW_TOKENS = 6144;
 
 hipError_t launch_ln_modulate(int dtype, float* X, void* out, int M, int D, float eps,
                               const float* mod_layer, long mod_bs, int shift_chunk, int scale_chunk,
