@@ -13,6 +13,7 @@
 //    workgroup, each wave owning 64 queries; V stays in its natural [key][d] layout and
 //    its transposed fragments come from ds_read_b64_tr_b16.
 #include "common.h"
+#include "plan.h"
 #include <type_traits>
 
 namespace ps {
@@ -367,9 +368,8 @@ __device__ __forceinline__ void attn_item(const AttnGrid& g, int id, int nt, int
 __device__ __forceinline__ void
 attn_merge_rows(int block, const float* __restrict__ part, bf16_t* __restrict__ o, int seq, const AttnGrid& g,
                 int nitems, float cexp, int bq, const AttnStrides& s, const unsigned* __restrict__ fail) {
-    const int gid = block * 256 + threadIdx.x;
-    const int d4 = gid & 15, rowid = gid >> 4;          // 16 threads per row
-    const int item = rowid / bq, row = rowid % bq;      // item: over all samples
+    const MergeRow mr = merge_row(block, threadIdx.x, bq);
+    const int item = mr.item, row = mr.row, d4 = mr.d4;
     if (item >= nitems) return;
     const int sample = item / g.tail_ps;
     const int local = g.full_ps + item % g.tail_ps;
