@@ -1100,17 +1100,13 @@ static AttnPlan attention_plan(int seq, int heads) {
     const int slots = compute_units() * 2;               // two resident workgroups per CU
     const int tail = p.items_ps % slots;
     const int ntiles = (seq + KV - 1) / KV;
-    // Fewer items than slots: splitting pays only while most compute units would stay empty, for two workgroups on a unit
-    // share its matrix cores and every piece costs 70 KB of partial sums written and read.  Items are split to about half
-    // of the compute units, so that a batch of two still gains.  4 heads, 4096 keys (64 items): 75 us whole, 51 in
-    // two pieces, a batch of two 76 and 58 (a batch of four 81 and 96: the plan must not depend on the batch).  30 heads,
-    // 1000 keys (120 items) in 4 pieces: 38.7 us against 27.2 whole, so such shapes stay whole.
-    const int room = p.items_ps < slots ? slots / 4 : slots;
-    int ns = tail > 0 ? room / tail : 1;
+    // Fewer items than slots are never split: the plan must not depend on the batch, and a batch that fills the chip by
+    // itself pays 70 KB of partial sums per piece for nothing.  (4 heads x 4096 keys in two pieces: 74 -> 49 us alone, but
+    // 80 -> 94 for four samples and 256 -> 330 for sixteen; 16 heads x 1000 keys, four samples: 30 -> 50.)
+    int ns = tail > 0 ? slots / tail : 1;
     if (ns > 8) ns = 8;
-    const int least = p.items_ps < slots ? 8 : 2;        // key tiles per piece
-    if (ns > ntiles / least) ns = ntiles / least;
-    if (tail == 0 || ns < 2) { p.full_ps = p.items_ps; p.tail_ps = 0; p.nsplit = 1; }
+    if (ns > ntiles / 2) ns = ntiles / 2;
+    if (tail == 0 || p.items_ps < slots || ns < 2) { p.full_ps = p.items_ps; p.tail_ps = 0; p.nsplit = 1; }
     else { p.full_ps = p.items_ps - tail; p.tail_ps = tail; p.nsplit = ns; }
     return p;
 }
@@ -1149,9 +1145,7 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
         if (s.k_tok >= (1 << 24) || s.v_tok >= (1 << 24)) return hipErrorInvalidValue;   // 32-bit in-tile offsets
         const bool checked = attention_checked_path(path, seq);
         AttnPlan p = attention_plan(seq, heads);
-        // the reference-tracking kernel on its own splits nothing where the items do not fill the chip: its items are
-        // then the same as when it repeats a marked head
-        if ((path & 0xff) == 2 || (!checked && p.full_ps == 0)) { p.full_ps = p.items_ps; p.tail_ps = 0; p.nsplit = 1; }
+        if ((path & 0xff) == 2) { p.full_ps = p.items_ps; p.tail_ps = 0; p.nsplit = 1; }
         const float c = scale * 1.4426950408889634f;
         const float cexp = q_prescaled ? 1.0f : c;
         const bf16_t *qq = (const bf16_t*)q, *kk = (const bf16_t*)k, *vv = (const bf16_t*)v;

@@ -184,6 +184,9 @@ def test_attn3d_validation():
     # block here); a short sequence has no key-split pieces.  The other kernels need no scratch.
     assert L.attn3d_workspace_bytes(1, 100, 2, 64, 1) == 256
     assert f(dt=1, d=64, ws=None, wsb=0) == -4
+    # nor has a sample whose query blocks do not fill the chip, whatever the batch: flags only
+    assert L.attn3d_workspace_bytes(1, 4096, 4, 64, 1) == 256
+    assert L.attn3d_workspace_bytes(1024, 1024, 16, 64, 1) == 1024 * 16 * 4
     assert L.attn3d_workspace_bytes(1, 100, 2, 16, 0) == 0
     assert L.attn3d_workspace_bytes(0, 100, 2, 16, 0) == 0
 
