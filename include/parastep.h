@@ -103,11 +103,10 @@ PS_API int dit_destroy(dit* d);
  * 0 the fastest kernel for each shape, 1 the generic fp32-FMA kernels, 2 bf16 attention without
  * the key split of its last partial round of workgroups, 3 bf16 head-dim-64 attention always
  * through the kernel that tracks a softmax reference (the one without is not tried first),
- * 4 projections not divided along k.  Bits 8-11: tile variant of the bf16
- * MFMA projections beyond the size that one kernel of 64x64 tiles serves whatever the variant (0 automatic, 1: 256x256, 2: 128x128, 3: 192x256, 4: 192x128); the variant
- * decides which workgroup computes an output and, for k >= 4096, which outputs of the last partial
- * round are summed in k pieces (a different rounding of those); nothing else.  Other values:
- * PS_ERR_SHAPE.
+ * 4 projections not divided along k.  Bits 8-11: tile variant of the bf16 MFMA projections (0
+ * automatic, 1: 256x256, 2: 128x128, 3: 192x256, 4: 192x128); the variant decides which workgroup
+ * computes an output and, for k >= 4096 beyond few tokens, which outputs of the last partial round are
+ * summed in k pieces (a different rounding of those); nothing else.  Other values: PS_ERR_SHAPE.
  * dit_workspace_bytes does not depend on the path. */
 PS_API int dit_set_kernel_path(dit* d, int path);
 PS_API int dit_get_kernel_path(const dit* d);    /* the handle's path, PS_ERR_NULL for NULL */

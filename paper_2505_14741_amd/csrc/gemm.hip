@@ -3,6 +3,7 @@
 // shapes that neither matrix kernel covers and for kernel path 1.
 #include "common.h"
 #include "epilogue.h"
+#include "plan.h"
 
 namespace ps {
 
@@ -76,38 +77,42 @@ static hipError_t launch_generic(const T* A, const T* W, T* C, int M, int Nn, in
 
 bool gemm_mfma_supported(int tokens, int Nn, int K);
 hipError_t launch_gemm_mfma(const bf16_t* A, const bf16_t* W, bf16_t* C, int batch, int tokens, int Nn, int K,
-                            const Epilogue& ep, int path, hipStream_t st);
-
-bool gemm_small_supported(int dtype, int tokens, int Nn, int K, int path);
-size_t gemm_small_workspace_bytes(int dtype, int batch, int tokens, int Nn, int K, int path);
+                            const Epilogue& ep, int path, int pieces, hipStream_t st);
+size_t gemm_tiles_workspace_bytes(int batch, int tokens, int Nn, int K, int path, int pieces);
 hipError_t launch_gemm_small(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K,
-                             const Epilogue& ep, int path, int* deferred, hipStream_t st);
-size_t gemm_tiles_workspace_bytes(int batch, int tokens, int Nn, int K, int path);
+                             const Epilogue& ep, const FewPlan& plan, int* deferred, hipStream_t st);
 
 static bool uses_tiles(int dtype, int tokens, int Nn, int K, int path) {
     return dtype == PS_BF16 && (path & 0xff) != 1 && gemm_mfma_supported(tokens, Nn, K);
 }
 
+// A forced tile variant takes a bf16 shape of few tokens to the tile kernel, with the K pieces of the shape: it decides
+// which workgroup computes an output, not its value.
+static bool forced_tiles(int dtype, int path) { return dtype == PS_BF16 && (path >> 8) != 0; }
+
 bool gemm_uses_mfma(int dtype, int tokens, int Nn, int K, int path) {
-    return gemm_small_supported(dtype, tokens, Nn, K, path) || uses_tiles(dtype, tokens, Nn, K, path);
+    return few_plan(dtype == PS_BF16, tokens, Nn, K, path).use || uses_tiles(dtype, tokens, Nn, K, path);
 }
 
 size_t gemm_split_workspace_bytes(int dtype, int batch, int tokens, int Nn, int K, int path) {
-    if (gemm_small_supported(dtype, tokens, Nn, K, path))
-        return gemm_small_workspace_bytes(dtype, batch, tokens, Nn, K, path);
-    return uses_tiles(dtype, tokens, Nn, K, path) ? gemm_tiles_workspace_bytes(batch, tokens, Nn, K, path) : 0;
+    const FewPlan few = few_plan(dtype == PS_BF16, tokens, Nn, K, path);
+    if (few.use && !forced_tiles(dtype, path)) return few_workspace_bytes(few, batch, tokens, Nn);
+    return uses_tiles(dtype, tokens, Nn, K, path)
+               ? gemm_tiles_workspace_bytes(batch, tokens, Nn, K, path, few.use ? few.nsplit : 0) : 0;
 }
 
 hipError_t launch_gemm(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K,
                        const Epilogue& epi, int path, hipStream_t st, int* deferred) {
     if (deferred) *deferred = 0;
     if (batch <= 0 || tokens <= 0 || Nn <= 0 || K <= 0 || (Nn & 1)) return hipErrorInvalidValue;
-    if (gemm_small_supported(dtype, tokens, Nn, K, path))
-        return launch_gemm_small(dtype, A, W, C, batch, tokens, Nn, K, epi, path, deferred, st);
+    const FewPlan few = few_plan(dtype == PS_BF16, tokens, Nn, K, path);
+    if (few.use && !forced_tiles(dtype, path))
+        return launch_gemm_small(dtype, A, W, C, batch, tokens, Nn, K, epi, few, deferred, st);
     const bool mfma = uses_tiles(dtype, tokens, Nn, K, path);
     if (epi.kind == EPI_UNPATCHIFY && !mfma) return hipErrorInvalidValue;
     if (mfma)
-        return launch_gemm_mfma((const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C, batch, tokens, Nn, K, epi, path, st);
+        return launch_gemm_mfma((const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C, batch, tokens, Nn, K, epi, path,
+                                few.use ? few.nsplit : 0, st);
     const int M = batch * tokens;                    // (the generic kernel forms 64-bit offsets)
     if (dtype == PS_BF16)
         return launch_generic<bf16_t>((const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C, M, Nn, K, epi, st);

@@ -630,7 +630,8 @@ static int tail_split(int tiles, int slots, int K, bool allow_split) {
     return ns >= 2 ? ns : 1;
 }
 
-static GemmPlan gemm_plan(int batch, int tokens, int Nn, int K, bool allow_split, int forced_variant) {
+// pieces > 0: every tile is summed in that many K pieces (1: whole), which the caller has fixed for the sample's shape.
+static GemmPlan gemm_plan(int batch, int tokens, int Nn, int K, bool allow_split, int forced_variant, int pieces) {
     GemmPlan p{};
     const int cus = gemm_compute_units();
     int v = forced_variant;
@@ -641,7 +642,7 @@ static GemmPlan gemm_plan(int batch, int tokens, int Nn, int K, bool allow_split
         // Which tiles are summed in K pieces depends on the variant, and must not depend on the batch: where a split
         // is possible (long K) the choice looks at one sample; elsewhere the variant never changes a value and the
         // choice may count the tiles of the whole batch.
-        const bool may_split = allow_split && K >= 4096;
+        const bool may_split = pieces == 0 && allow_split && K >= 4096;
         const int nb = may_split ? 1 : batch;
         float best = 0.f;
         v = 2;
@@ -667,9 +668,9 @@ static GemmPlan gemm_plan(int batch, int tokens, int Nn, int K, bool allow_split
     // the second launch cost less than the round they save -- measured at 17776 tokens: true with a long K
     // (fc2 on 128x128 tiles: 0.62 -> 0.57 ms), not for K = 1920 (0.188 -> 0.196 ms)
     const int slots = cus * p.per_cu;
-    const int ns = tail_split(tiles, slots, K, allow_split);
+    const int ns = pieces > 0 ? pieces : tail_split(tiles, slots, K, allow_split);
     if (ns > 1) {
-        const int tail = tiles % slots;
+        const int tail = pieces > 0 ? tiles : tiles % slots;
         p.full = tiles - tail; p.tail = tail; p.nsplit = ns;
         p.ws_bytes_per_sample = (size_t)tail * ns * p.bm * p.bn * sizeof(float);
     }
@@ -679,9 +680,9 @@ static GemmPlan gemm_plan(int batch, int tokens, int Nn, int K, bool allow_split
 // kernel path: low byte = mode (4: never split a tail along K), bits 8-11 = forced tile variant (0: automatic)
 static int forced_variant_of(int path) { return (path >> 8) & 0xf; }
 
-size_t gemm_tiles_workspace_bytes(int batch, int tokens, int Nn, int K, int path) {
+size_t gemm_tiles_workspace_bytes(int batch, int tokens, int Nn, int K, int path, int pieces) {
     if ((path & 0xff) == 4) return 0;
-    return gemm_plan(batch, tokens, Nn, K, true, forced_variant_of(path)).ws_bytes_per_sample * (size_t)batch;
+    return gemm_plan(batch, tokens, Nn, K, true, forced_variant_of(path), pieces).ws_bytes_per_sample * (size_t)batch;
 }
 
 template <int BM, int BN, int WR, int WC, int BK, int NST, int KIND>
@@ -711,11 +712,12 @@ static hipError_t launch_tile(const bf16_t* A, const bf16_t* W, bf16_t* C, int b
 }
 
 hipError_t launch_gemm_mfma(const bf16_t* A, const bf16_t* W, bf16_t* C, int batch, int tokens, int Nn, int K,
-                            const Epilogue& ep, int path, hipStream_t st) {
+                            const Epilogue& ep, int path, int pieces, hipStream_t st) {
     const bool tails = (path & 0xff) != 4;
     const int fv = forced_variant_of(path);
-    GemmPlan p = gemm_plan(batch, tokens, Nn, K, ep.split_ws != nullptr && tails, fv);
-    if (p.ws_bytes_per_sample * (size_t)batch > ep.split_ws_bytes) p = gemm_plan(batch, tokens, Nn, K, false, fv);
+    GemmPlan p = gemm_plan(batch, tokens, Nn, K, ep.split_ws != nullptr && tails, fv, pieces);
+    if (p.ws_bytes_per_sample * (size_t)batch > (ep.split_ws ? ep.split_ws_bytes : 0))
+        p = gemm_plan(batch, tokens, Nn, K, false, fv, pieces > 0 ? 1 : 0);
     switch (p.variant) {
         case 1: return launch_tile<256, 256, 2, 4, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 8 waves, 128x64 each
         case 2: return launch_tile<128, 128, 2, 2, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 4 waves, 64x64 each, 2 per CU

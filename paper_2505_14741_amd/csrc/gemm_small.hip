@@ -9,6 +9,7 @@
 // fp32 (v_mfma_f32_16x16x4_f32: full fp32 products and sums) at 112 tokens against the 64 x 64 fp32-FMA kernel:
 // 5760 x 1920 229 -> 43 us, 1920 x 7680 ~900 -> 45 us; at 512 tokens 101 TFLOP/s.
 #include "common.h"
+#include "plan.h"
 
 namespace ps {
 
@@ -16,8 +17,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
 
-static constexpr int TILE = 64;                          // output rows and columns of a workgroup
-static constexpr int ROWB = 128;                         // bytes of an operand row per stage: 64 bf16 or 32 fp32
+static constexpr int TILE = FEW_TILE;                    // output rows and columns of a workgroup
+static constexpr int ROWB = FEW_ROW_BYTES;               // bytes of an operand row per stage: 64 bf16 or 32 fp32
 static constexpr int STAGE = 2 * TILE * ROWB;            // A rows, then W rows
 
 // global->LDS load of 16 bytes per lane; lane j's bytes land at lds_addr + 16*j (lds_addr wave-uniform)
@@ -143,7 +144,7 @@ gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restric
         m0 = (band * 8 + in_band % rows_here) * TILE;
         n0 = in_band / rows_here * TILE;
     }
-    const int nk = K * (int)sizeof(T) / ROWB;
+    const int nk = K / (ROWB / (int)sizeof(T));
     const int k0 = nk * piece / g.nsplit, nkt = nk * (piece + 1) / g.nsplit - k0;
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -268,44 +269,8 @@ gemm_small_reduce_kernel(T* __restrict__ C, int Nn, SmallGrid g, Epilogue ep) {
     epilogue_quad<KIND, T>(ep, C, Nn, sample, n, col, s, epilogue_operands<KIND>(ep, Nn, sample, n, col));
 }
 
-// A sample's plan: a function of the sample's shape alone, so that its result does not depend on the batch.
-//   bf16: up to 640 tiles of 64 x 64; beyond that the 128-wide tiles of the other kernel win by reading less per output.
-//     Both measured, weights cold, against 128 x 128 tiles: 5760 x 1920 weights at 448 tokens (630 tiles) 25.4 against
-//     30.4 us, at 700 (990 tiles) 35.5 against 30.7; 7680 x 1920 at 256 (480) 21.8 against 29.6, at 448 (840) 36.1 against
-//     31.3; 1920 x 1920 at 1000 (480) 17.1 against 24.7, at 1500 (720) 26.4 against 24.3.
-//   fp32: every size (the matrix instructions bind, 32 cycles per 2048 operations, not the LDS reads).
-// K pieces: as many as bring the workgroups to 256 (one per compute unit) where K is short, 512 where it is long (60
-// stages and more), 8 at most (fp32 16) and each at least 5 stages.  1920 x 1920 bf16 at 112 tokens (60 tiles): 1 piece 14.2 us,
-// 4 pieces 11.5, 6 pieces 12.2 with the reduction launch; 1920 x 7680: 42.8, 19.0 (4 pieces), 18.5 (8).
-static constexpr int BF16_MAX_TILES = 640;
-struct SmallPlan { bool use; int tiles_m, tiles_n, nsplit; };
-static SmallPlan small_plan(int dtype, int tokens, int Nn, int K, int path) {
-    SmallPlan p{false, 0, 0, 1};
-    const long row_bytes = (long)K * (dtype == PS_BF16 ? 2 : 4);
-    if ((path & 0xff) == 1 || row_bytes % ROWB != 0 || Nn % 4 != 0 || tokens < 1) return p;
-    p.tiles_m = (tokens + TILE - 1) / TILE;
-    p.tiles_n = (Nn + TILE - 1) / TILE;
-    const long tiles = (long)p.tiles_m * p.tiles_n, nk = row_bytes / ROWB;
-    if (dtype == PS_BF16 && (Nn < 64 || tiles > BF16_MAX_TILES)) return p;
-    p.use = true;
-    if ((path & 0xff) == 4) return p;
-    const long most = dtype == PS_BF16 ? 8 : 16;
-    long ns = (nk >= 60 ? 512 : 256) / tiles;
-    ns = ns < most ? ns : most;
-    ns = ns < nk / 5 ? ns : nk / 5;
-    p.nsplit = ns > 1 ? (int)ns : 1;
-    return p;
-}
-
-bool gemm_small_supported(int dtype, int tokens, int Nn, int K, int path) { return small_plan(dtype, tokens, Nn, K, path).use; }
-
-size_t gemm_small_workspace_bytes(int dtype, int batch, int tokens, int Nn, int K, int path) {
-    const SmallPlan p = small_plan(dtype, tokens, Nn, K, path);
-    return p.use && p.nsplit > 1 ? (size_t)p.nsplit * batch * tokens * Nn * sizeof(float) : 0;
-}
-
 template <typename T, int KIND>
-static hipError_t launch_small_kind(const T* A, const T* W, T* C, int batch, int tokens, int Nn, int K, const SmallPlan& p,
+static hipError_t launch_small_kind(const T* A, const T* W, T* C, int batch, int tokens, int Nn, int K, const FewPlan& p,
                                     const Epilogue& ep, int* deferred, hipStream_t st) {
     const SmallGrid g{batch, p.tiles_m, p.tiles_n, p.nsplit};
     const long blocks = (long)batch * p.tiles_m * p.tiles_n * p.nsplit;
@@ -321,7 +286,7 @@ static hipError_t launch_small_kind(const T* A, const T* W, T* C, int batch, int
 }
 
 template <typename T>
-static hipError_t launch_small(const T* A, const T* W, T* C, int batch, int tokens, int Nn, int K, const SmallPlan& p,
+static hipError_t launch_small(const T* A, const T* W, T* C, int batch, int tokens, int Nn, int K, const FewPlan& p,
                                const Epilogue& ep, int* deferred, hipStream_t st) {
     switch (ep.kind) {
         case EPI_BIAS: return launch_small_kind<T, EPI_BIAS>(A, W, C, batch, tokens, Nn, K, p, ep, nullptr, st);
@@ -334,13 +299,12 @@ static hipError_t launch_small(const T* A, const T* W, T* C, int batch, int toke
 }
 
 hipError_t launch_gemm_small(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K,
-                             const Epilogue& epi, int path, int* deferred, hipStream_t st) {
+                             const Epilogue& epi, const FewPlan& plan, int* deferred, hipStream_t st) {
     Epilogue ep = epi;
     ep.geom.tokens = tokens;                             // (the plain kinds leave it unset)
-    SmallPlan p = small_plan(dtype, tokens, Nn, K, path);
+    FewPlan p = plan;
     if (!p.use) return hipErrorInvalidValue;
-    const size_t need = (size_t)p.nsplit * batch * tokens * Nn * sizeof(float);
-    if ( ep.split_ws == nullptr || ep.split_ws_bytes < need) p.nsplit = 1;
+    if (ep.split_ws == nullptr || ep.split_ws_bytes < few_workspace_bytes(p, batch, tokens, Nn)) p.nsplit = 1;
     if (dtype == PS_BF16)
         return launch_small<bf16_t>((const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C, batch, tokens, Nn, K, p, ep, deferred, st);
     return launch_small<float>((const float*)A, (const float*)W, (float*)C, batch, tokens, Nn, K, p, ep, deferred, st);

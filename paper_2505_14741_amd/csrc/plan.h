@@ -2,6 +2,8 @@
 // program can evaluate them at sizes no test can run.  (constexpr functions are callable from kernels as they are.)
 #pragma once
 
+#include <stddef.h>
+
 namespace ps {
 
 // ---- merge of attention's key pieces: 16 threads per query row, 16 rows per workgroup of 256
@@ -11,6 +13,45 @@ struct MergeRow { int item, row, d4; };              // split item (over all sam
 constexpr MergeRow merge_row(int block, int thread, int bq) {
     const int rowid = block * 16 + (thread >> 4);
     return MergeRow{rowid / bq, rowid % bq, thread & 15};
+}
+
+// ---- projections of few tokens and of fp32 operands (gemm_small.hip): C[tokens, Nn] = A[tokens, K] * W[Nn, K]^T per sample
+constexpr int FEW_TILE = 64;                             // output rows and columns of a workgroup
+constexpr int FEW_ROW_BYTES = 128;                       // bytes of an operand row per stage: 64 bf16 or 32 fp32
+constexpr int FEW_MAX_TILES = 640;
+
+// A sample's plan: a function of the sample's shape alone, so that its result does not depend on the batch.
+//   bf16: up to 640 tiles of 64 x 64; beyond that the 128-wide tiles of the other kernel win by reading less per output.
+//     Both measured, weights cold, against 128 x 128 tiles: 5760 x 1920 weights at 448 tokens (630 tiles) 25.4 against
+//     30.4 us, at 700 (990 tiles) 35.5 against 30.7; 7680 x 1920 at 256 (480) 21.8 against 29.6, at 448 (840) 36.1 against
+//     31.3; 1920 x 1920 at 1000 (480) 17.1 against 24.7, at 1500 (720) 26.4 against 24.3.
+//   fp32: every size (the matrix instructions bind, 32 cycles per 2048 operations, not the LDS reads).
+// K pieces: as many as bring the workgroups to 256 (one per compute unit) where K is short, 512 where it is long (60
+// stages and more), 8 at most (fp32 16) and each at least 5 stages.  1920 x 1920 bf16 at 112 tokens (60 tiles): 1 piece 14.2 us,
+// 4 pieces 11.5, 6 pieces 12.2 with the reduction launch; 1920 x 7680: 42.8, 19.0 (4 pieces), 18.5 (8).
+// path: kernel path (low byte 1: generic kernels, 4: no K pieces).
+struct FewPlan { bool use; int tiles_m, tiles_n, nsplit; };
+constexpr FewPlan few_plan(bool bf16, int tokens, int Nn, int K, int path) {
+    FewPlan p{false, 0, 0, 1};
+    const long row_bytes = (long)K * (bf16 ? 2 : 4);
+    if ((path & 0xff) == 1 || row_bytes % FEW_ROW_BYTES != 0 || Nn % 4 != 0 || tokens < 1) return p;
+    p.tiles_m = (tokens + FEW_TILE - 1) / FEW_TILE;
+    p.tiles_n = (Nn + FEW_TILE - 1) / FEW_TILE;
+    const long tiles = (long)p.tiles_m * p.tiles_n, nk = row_bytes / FEW_ROW_BYTES;
+    if (bf16 && (Nn < 64 || tiles > FEW_MAX_TILES)) return p;
+    p.use = true;
+    if ((path & 0xff) == 4) return p;
+    const long most = bf16 ? 8 : 16;
+    long ns = (nk >= 60 ? 512 : 256) / tiles;
+    ns = ns < most ? ns : most;
+    ns = ns < nk / 5 ? ns : nk / 5;
+    p.nsplit = ns > 1 ? (int)ns : 1;
+    return p;
+}
+
+// scratch for the K pieces, [piece][row][column] in fp32
+constexpr size_t few_workspace_bytes(const FewPlan& p, int batch, int tokens, int Nn) {
+    return p.nsplit > 1 ? (size_t)p.nsplit * batch * tokens * Nn * sizeof(float) : 0;
 }
 
 }  // namespace ps

@@ -420,10 +420,13 @@ def test_attention_full_shape_sampled_rows(name, batch):
 
 
 # ------------------------------------------------------------------------------ dit_linear
-@pytest.mark.parametrize("M,Nn,K", [(777, 320, 256), (4516, 1920, 1920), (200, 64, 128)])
+@pytest.mark.parametrize("M,Nn,K", [(777, 320, 256), (4516, 1920, 1920), (200, 64, 128), (2500, 1092, 192),
+                                    (112, 1920, 1920), (130, 196, 1984)])
 def test_linear_tile_variants_give_identical_results(M, Nn, K):
     """The tile variant decides which workgroup computes an output, never its value: every variant sums the k
-    products of an output in the same order."""
+    products of an output in the same order.  Up to 640 tiles of 64 x 64 variant 0 is the kernel of few tokens (the last
+    two shapes in 4 and 6 K pieces), at 4516 and 2500 rows a tile variant; 777, 200, 2500 and 130 rows have tiles
+    that end inside a variant's tile in rows and columns."""
     print(f"dit_linear tile variants M={M} N={Nn} K={K}", flush=True)
     rng = np.random.default_rng(M)
     a = dev(I.make_tokens(M, K, 5, "bf16"), torch.bfloat16)

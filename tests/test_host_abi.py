@@ -210,6 +210,11 @@ def test_dit_linear_validation_and_workspace_size():
     assert L.dit_linear_workspace_bytes(17776, 1920, 7680, 1, 0x204) == 0   # mode 4: no K-split
     assert L.dit_linear_workspace_bytes(17776, 1920, 1920, 1, 0x200) == 0   # short K
     assert L.dit_linear_workspace_bytes(17776, 7680, 1920, 1, 0x100) == 0   # 256 x 256 tiles
+    # few tokens: 60 tiles of 64 x 64 in 4 K pieces, [piece][row][column]; a forced tile variant (192 x 256: 8 tiles) keeps
+    # the pieces, in its own layout
+    assert L.dit_linear_workspace_bytes(112, 1920, 1920, 1, 0) == 4 * 112 * 1920 * 4
+    assert L.dit_linear_workspace_bytes(112, 1920, 1920, 1, 0x300) == 4 * 8 * 192 * 256 * 4
+    assert L.dit_linear_workspace_bytes(112, 1920, 1920, 1, 0x304) == 0
     assert L.dit_linear_workspace_bytes(17776, 1920, 7680, 0, 0) == 0       # fp32 runs on the generic kernel
     assert L.dit_linear_workspace_bytes(100, 64, 64, 1, 0) == 0
     assert L.dit_linear_workspace_bytes(100, 64, 64, 1, 0x700) == 0         # unknown tile variant
