@@ -3,8 +3,8 @@
 // With few tokens a projection is a stream of weights (22 MB for 5760 x 1920 in bf16, 4 us at the 5.1 TB/s a large copy
 // reaches) and is bound by latency: a 128 x 128 tile leaves 15 of 256 compute units busy at 112 tokens x 1920 columns, each
 // walking all of K with one stage in flight.  Here a workgroup takes 64 x 64 outputs, K is cut into pieces where the tiles
-// do not fill the chip, and an LDS ring of 8 stages of 16 KB (one workgroup per CU; 4 stages and two workgroups where there
-// are more than 256) keeps up to 112 KB of loads in flight.  112 tokens, weights cold, before and after:
+// do not fill the chip, and an LDS ring of 8 stages of 16 KB (one workgroup per CU; 4 stages and two workgroups, 3 and three
+// where there are more of them) keeps up to 112 KB of loads in flight.  112 tokens, weights cold, before and after:
 // 5760 x 1920 24.1 -> 15.0 us, 7680 x 1920 31.0 -> 16.0, 1920 x 1920 24.4 -> 11.5, 1920 x 7680 106.6 -> 18.5.
 // fp32 (v_mfma_f32_16x16x4_f32: full fp32 products and sums) at 112 tokens against the 64 x 64 fp32-FMA kernel:
 // 5760 x 1920 229 -> 43 us, 1920 x 7680 ~900 -> 45 us; at 512 tokens 101 TFLOP/s.
@@ -121,7 +121,7 @@ __device__ __forceinline__ void epilogue_quad(const Epilogue& ep, T* __restrict_
 struct SmallGrid { int batch, tiles_m, tiles_n, nsplit; };
 
 template <typename T, int KIND, int NST>
-__global__ void __launch_bounds__(256, NST <= 4 ? 2 : 1)
+__global__ void __launch_bounds__(256, NST == 3 ? 3 : NST == 4 ? 2 : 1)
 gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict__ C, int Nn, int K, SmallGrid g,
                   Epilogue ep) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
@@ -275,8 +275,13 @@ static hipError_t launch_small_kind(const T* A, const T* W, T* C, int batch, int
     const SmallGrid g{batch, p.tiles_m, p.tiles_n, p.nsplit};
     const long blocks = (long)batch * p.tiles_m * p.tiles_n * p.nsplit;
     if (blocks >= (1L << 31)) return hipErrorInvalidValue;
-    if (blocks <= 256) gemm_small_kernel<T, KIND, 8><<<(int)blocks, 256, 0, st>>>(A, W, C, Nn, K, g, ep);
-    else gemm_small_kernel<T, KIND, 4><<<(int)blocks, 256, 0, st>>>(A, W, C, Nn, K, g, ep);
+    auto go = [&](auto kernel) { kernel<<<(int)blocks, 256, 0, st>>>(A, W, C, Nn, K, g, ep); };
+    // as deep a ring as lets every workgroup start at once (with two per CU, 513 to 768 are a second, nearly empty round:
+    // 1920 x 1920 at 1100 rows, 540 tiles, 23.8 -> 20.8 us with three; 5760 x 1920 at 440, 630 tiles, 23.2 -> 20.7, both
+    // with the weights in cache)
+    if (blocks <= 256) go(gemm_small_kernel<T, KIND, 8>);
+    else if (blocks <= 512) go(gemm_small_kernel<T, KIND, 4>);
+    else go(gemm_small_kernel<T, KIND, 3>);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.nsplit == 1) return e;
     if (deferred) { *deferred = p.nsplit; return e; }

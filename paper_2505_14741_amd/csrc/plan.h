@@ -18,13 +18,14 @@ constexpr MergeRow merge_row(int block, int thread, int bq) {
 // ---- projections of few tokens and of fp32 operands (gemm_small.hip): C[tokens, Nn] = A[tokens, K] * W[Nn, K]^T per sample
 constexpr int FEW_TILE = 64;                             // output rows and columns of a workgroup
 constexpr int FEW_ROW_BYTES = 128;                       // bytes of an operand row per stage: 64 bf16 or 32 fp32
-constexpr int FEW_MAX_TILES = 640;
 
 // A sample's plan: a function of the sample's shape alone, so that its result does not depend on the batch.
 //   bf16: up to 640 tiles of 64 x 64; beyond that the 128-wide tiles of the other kernel win by reading less per output.
-//     Both measured, weights cold, against 128 x 128 tiles: 5760 x 1920 weights at 448 tokens (630 tiles) 25.4 against
-//     30.4 us, at 700 (990 tiles) 35.5 against 30.7; 7680 x 1920 at 256 (480) 21.8 against 29.6, at 448 (840) 36.1 against
-//     31.3; 1920 x 1920 at 1000 (480) 17.1 against 24.7, at 1500 (720) 26.4 against 24.3.
+//     Weights cold / in cache, against 128 x 128 tiles: 5760 x 1920 weights at 440 tokens (630 tiles) 27.4 / 20.7 against
+//     29.9 / 22.7 us; 7680 x 1920 at 300 (600) 27.5 / 20.5 against 29.5 / 22.1; 1920 x 1920 at 1340 (630) 21.2 / 21.1
+//     against 23.0 / 23.0, at 1500 (720) 26.4 against 24.3 cold.
+//     K >= 4096: up to 512.  Beyond, no tile has a second K piece here, while 128 x 128 tiles are cut: 1920 x 7680 at 1100
+//     tokens (540 tiles) 78.9 / 76.8 whole here, 58.5 / 54.6 in 3 pieces there; at 1000 (480) 61.1 / 49.0 here.
 //   fp32: every size (the matrix instructions bind, 32 cycles per 2048 operations, not the LDS reads).
 // K pieces: as many as bring the workgroups to 256 (one per compute unit) where K is short, 512 where it is long (60
 // stages and more), 8 at most (fp32 16) and each at least 5 stages.  1920 x 1920 bf16 at 112 tokens (60 tiles): 1 piece 14.2 us,
@@ -38,7 +39,7 @@ constexpr FewPlan few_plan(bool bf16, int tokens, int Nn, int K, int path) {
     p.tiles_m = (tokens + FEW_TILE - 1) / FEW_TILE;
     p.tiles_n = (Nn + FEW_TILE - 1) / FEW_TILE;
     const long tiles = (long)p.tiles_m * p.tiles_n, nk = row_bytes / FEW_ROW_BYTES;
-    if (bf16 && (Nn < 64 || tiles > FEW_MAX_TILES)) return p;
+    if (bf16 && (Nn < 64 || tiles > (K >= 4096 ? 512 : 640))) return p;
     p.use = true;
     if ((path & 0xff) == 4) return p;
     const long most = bf16 ? 8 : 16;

@@ -39,13 +39,13 @@ def test_linear_few_rows_split_and_whole(M, Nn, K, act):
             assert rel(ref, B.dit_linear(a, w, bias, act, **kw).double().cpu().numpy()) <= bound, (td, kw)
 
 
-@pytest.mark.parametrize("N", [640 * 64 // 30, 640 * 64 // 30 + 64])
+@pytest.mark.parametrize("N", [1088, 1152, 1344, 1408])
 def test_linear_on_both_sides_of_the_tile_limit(N):
-    """1920 columns are 30 column tiles: 21 row tiles are 630 of them, 22 are 660, beyond the limit of 640."""
-    N = N // 64 * 64
+    """1920 columns are 30 column tiles: 17 and 18 row tiles are 510 and 540 of them, around the limit of 512 for K = 7680
+    (whole below, 128-wide tiles in K pieces above), 21 and 22 are 630 and 660, around the limit of 640 for K = 1920."""
     g = torch.Generator(device=DEV)
     g.manual_seed(N)
-    for K in (1920, 7680):                           # 7680: K pieces on either kernel
+    for K in (1920, 7680):
         a = torch.randn(N, K, generator=g, device=DEV).bfloat16()
         w = (torch.randn(1920, K, generator=g, device=DEV) / math.sqrt(K)).bfloat16()
         bias = torch.randn(1920, generator=g, device=DEV)

@@ -13,6 +13,10 @@ extern "C" void merge(int block, int thread, int bq, int* out) {
     const ps::MergeRow r = ps::merge_row(block, thread, bq);
     out[0] = r.item; out[1] = r.row; out[2] = r.d4;
 }
+extern "C" int few(int bf16, int tokens, int n, int k, int path) {   // 0: another kernel, else the number of K pieces
+    const ps::FewPlan p = ps::few_plan(bf16 != 0, tokens, n, k, path);
+    return p.use ? p.nsplit : 0;
+}
 """
 
 
@@ -36,3 +40,15 @@ def test_merge_rows_of_many_items(rules, nitems):
             rules.merge(block, thread, 256, out)
             gid = block * 256 + thread
             assert list(out) == [gid // 16 // 256, gid // 16 % 256, gid % 16] and 0 <= out[0] < nitems
+
+
+def test_few_token_projections_end_where_wider_tiles_are_faster(rules):
+    few = lambda *a: rules.few(1, *a, 0)
+    # K = 1920: 640 tiles of 64 x 64; long K: 512, beyond which only 128-wide tiles are cut along K
+    assert few(1344, 1920, 1920) == 1 and few(1345, 1920, 1920) == 0
+    assert few(1088, 1920, 7680) == 1 and few(1089, 1920, 7680) == 0
+    assert few(112, 1920, 7680) == 8 and few(112, 1920, 1920) == 4 and few(112, 5760, 1920) == 1
+    assert few(1344, 1920, 4032) == 1 and few(1344, 1920, 4096) == 0     # where 128-wide tiles start to be cut
+    assert rules.few(0, 4096, 1920, 7680, 0) == 1                        # fp32: every size
+    assert rules.few(1, 112, 1920, 1920, 4) == 1 and rules.few(1, 112, 1920, 1920, 1) == 0
+    assert few(112, 1922, 1920) == 0 and few(112, 1920, 1928) == 0 and few(112, 62, 1920) == 0
