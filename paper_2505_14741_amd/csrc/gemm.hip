@@ -80,7 +80,7 @@ hipError_t launch_gemm_mfma(const bf16_t* A, const bf16_t* W, bf16_t* C, int bat
                             const Epilogue& ep, int path, int pieces, hipStream_t st);
 size_t gemm_tiles_workspace_bytes(int batch, int tokens, int Nn, int K, int path, int pieces);
 hipError_t launch_gemm_small(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K,
-                             const Epilogue& ep, const FewPlan& plan, int* deferred, hipStream_t st);
+                             const Epilogue& ep, const FewPlan& plan, bool inreg, int* deferred, hipStream_t st);
 
 static bool uses_tiles(int dtype, int tokens, int Nn, int K, int path) {
     return dtype == PS_BF16 && (path & 0xff) != 1 && gemm_mfma_supported(tokens, Nn, K);
@@ -96,7 +96,7 @@ bool gemm_uses_mfma(int dtype, int tokens, int Nn, int K, int path) {
 
 size_t gemm_split_workspace_bytes(int dtype, int batch, int tokens, int Nn, int K, int path) {
     const FewPlan few = few_plan(dtype == PS_BF16, tokens, Nn, K, path);
-    if (few.use && !forced_tiles(dtype, path)) return few_workspace_bytes(few, batch, tokens, Nn);
+    if (few.use && !forced_tiles(dtype, path)) return few_workspace_bytes(dtype == PS_BF16, few, batch, tokens, Nn, K);
     return uses_tiles(dtype, tokens, Nn, K, path)
                ? gemm_tiles_workspace_bytes(batch, tokens, Nn, K, path, few.use ? few.nsplit : 0) : 0;
 }
@@ -105,9 +105,15 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, void* C, int bat
                        const Epilogue& epi, int path, hipStream_t st, int* deferred) {
     if (deferred) *deferred = 0;
     if (batch <= 0 || tokens <= 0 || Nn <= 0 || K <= 0 || (Nn & 1)) return hipErrorInvalidValue;
-    const FewPlan few = few_plan(dtype == PS_BF16, tokens, Nn, K, path);
-    if (few.use && !forced_tiles(dtype, path))
-        return launch_gemm_small(dtype, A, W, C, batch, tokens, Nn, K, epi, few, deferred, st);
+    const bool bf16 = dtype == PS_BF16;
+    FewPlan few = few_plan(bf16, tokens, Nn, K, path);
+    if (few.use && !forced_tiles(dtype, path)) {
+        if (epi.split_ws == nullptr || epi.split_ws_bytes < few_workspace_bytes(bf16, few, batch, tokens, Nn, K)) few.nsplit = 1;
+        const FewHow how = few_how(bf16, few, batch, K);
+        if (how != FEW_TILES)
+            return launch_gemm_small(dtype, A, W, C, batch, tokens, Nn, K, epi, few, how == FEW_INREG, deferred, st);
+        return launch_gemm_mfma((const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C, batch, tokens, Nn, K, epi, path, few.nsplit, st);
+    }
     const bool mfma = uses_tiles(dtype, tokens, Nn, K, path);
     if (epi.kind == EPI_UNPATCHIFY && !mfma) return hipErrorInvalidValue;
     if (mfma)

@@ -268,9 +268,11 @@ __device__ __forceinline__ void wait_vmcnt() {
 // One BM x BN output tile (rows m0.., columns n0..), k-tiles k0..k1-1 of 64, by the WR x WC waves of a workgroup,
 // each owning (BM/WR) x (BN/WC) outputs.  piece >= 0: a K-split piece, accumulators go to ep.split_ws.
 // BK: K depth of an LDS stage; NST: ring depth; lds: NST * (BM + BN) * 2 * BK bytes, 1024-aligned.
-template <int BM, int BN, int WR, int WC, int BK, int NST, int KIND>
+// INREG: k0..k1-1 are summed in `nsplit` pieces that are added up in registers, in the order and with the roundings of
+// gemm_tail_kernel.
+template <int BM, int BN, int WR, int WC, int BK, int NST, int KIND, bool INREG>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, bf16_t* __restrict__ C,
-                                          int M, int Nn, int K, int m0, int n0, int k0, int k1, int piece,
+                                          int M, int Nn, int K, int m0, int n0, int k0, int k1, int piece, int nsplit,
                                           const Epilogue& ep, unsigned char* lds) {
     static_assert(BK == 64 || BK == 32, "stage depth");
     constexpr int NW = WR * WC;
@@ -340,6 +342,16 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) acc[i][j][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    f32x4_t total[INREG ? TM : 1][INREG ? TN : 1][4];    // the pieces before the current one
+    int piece_end = INREG ? (k1 - k0) / nsplit : 0, piece_no = 1;
+    if constexpr (INREG) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) total[i][j][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
 
     constexpr int FA = 2 * TM, FB = 2 * TN;              // 16-row fragments of A and of W per k-step
     static_assert(BK == 64, "two 32-deep k-steps per stage");
@@ -372,7 +384,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
     // of strip 0 still allowed in flight; no wait follows until the epilogue.  (Recovers 8 and 15 us.  One request
     // per stage over 16 stages, each allowed to stay out for one hand-over, was 20 us SLOWER: under load a request
     // needs more than a stage to return and then every one of those hand-overs stalls.)
-    constexpr bool PRE = KIND == EPI_GATE_RESIDUAL && TN == 2 && TM == 2 && NW == 4;
+    constexpr bool PRE = KIND == EPI_GATE_RESIDUAL && TN == 2 && TM == 2 && NW == 4 && !INREG;
     f32x4_t pre[PRE ? TM : 1][8];
     const int nkt = k1 - k0;
     const bool have_pre = PRE && piece < 0 && nkt >= 3;
@@ -457,6 +469,29 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+        if constexpr (INREG) {
+            if (kt + 1 == piece_end) {                   // (the last piece ends with the last stage)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            total[i][j][q] += acc[i][j][q];
+                            acc[i][j][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                        }
+                ++piece_no;
+                piece_end = nkt * piece_no / nsplit;
+            }
+        }
+    }
+    if constexpr (INREG) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[i][j][q] = total[i][j][q];
     }
     wait_vmcnt<0>();                                     // the look-ahead loads past the end have landed
     __syncthreads();                                     // ... in every wave: the stage memory is free
@@ -514,7 +549,7 @@ __device__ __forceinline__ void shift_to_sample(Epilogue& ep, int sample, int to
     }
 }
 
-template <int BM, int BN, int WR, int WC, int BK, int NST, int KIND>
+template <int BM, int BN, int WR, int WC, int BK, int NST, int KIND, bool INREG = false>
 __global__ void __launch_bounds__(WR * WC * 64, (WR * WC == 4 && BM * BN <= 192 * 128) ? 2 : 1)
 gemm_mfma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, bf16_t* __restrict__ C,
                  int Nn, int K, GemmGrid g, Epilogue ep) {
@@ -542,7 +577,7 @@ gemm_mfma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, bf1
     shift_to_sample<KIND>(ep, sample, g.tokens, Nn);
     int m0, n0;
     tile_origin(tile, g.tiles_m, g.tiles_n, BM, BN, m0, n0);
-    gemm_tile<BM, BN, WR, WC, BK, NST, KIND>(A, W, C, g.tokens, Nn, K, m0, n0, k0, k1, piece, ep, lds);
+    gemm_tile<BM, BN, WR, WC, BK, NST, KIND, INREG>(A, W, C, g.tokens, Nn, K, m0, n0, k0, k1, piece, g.nsplit, ep, lds);
 }
 
 // Sums the K-split pieces of the tail tiles (fixed order: deterministic) and applies the epilogue; one single-wave
@@ -591,7 +626,7 @@ bool gemm_mfma_supported(int tokens, int Nn, int K) {
 
 // How a sample's [tokens, Nn] output is spread over the chip: which tile variant, how many tiles run whole and
 // how the rest is split.  A function of the sample's shape only (never of the batch): see gemm_mfma_kernel.
-struct GemmPlan { int variant, bm, bn, per_cu, tiles_m, tiles_n, full, tail, nsplit; size_t ws_bytes_per_sample; };
+struct GemmPlan { int variant, bm, bn, per_cu, tiles_m, tiles_n, full, tail, nsplit; size_t ws_bytes_per_sample; bool inreg; };
 static int gemm_compute_units() {
     // per device, asked once (a constant of the device, not a setting)
     static int cached[64];
@@ -635,7 +670,10 @@ static GemmPlan gemm_plan(int batch, int tokens, int Nn, int K, bool allow_split
     GemmPlan p{};
     const int cus = gemm_compute_units();
     int v = forced_variant;
-    if (v < 1 || v > 4) {
+    const bool automatic = v < 1 || v > 4;
+    if (automatic && pieces > 1) {
+        v = 2;                                           // the variant that has room for a second set of sums
+    } else if (automatic) {
         // the variant with the least estimated time: rounds of workgroup slots (a K-split tail counts as 1/pieces of
         // a round plus a fifth of a round for its partial sums and second launch) x tile area x the tile's cost
         // per output.  Outputs with fewer tiles than slots take the smallest tile.
@@ -673,6 +711,7 @@ static GemmPlan gemm_plan(int batch, int tokens, int Nn, int K, bool allow_split
         const int tail = pieces > 0 ? tiles : tiles % slots;
         p.full = tiles - tail; p.tail = tail; p.nsplit = ns;
         p.ws_bytes_per_sample = (size_t)tail * ns * p.bm * p.bn * sizeof(float);
+        p.inreg = automatic && pieces > 1;
     }
     return p;
 }
@@ -689,6 +728,13 @@ template <int BM, int BN, int WR, int WC, int BK, int NST, int KIND>
 static hipError_t launch_kind(const bf16_t* A, const bf16_t* W, bf16_t* C, int batch, int tokens, int Nn, int K,
                               const GemmPlan& p, const Epilogue& ep, hipStream_t st) {
     dim3 block(WR * WC * 64);
+    if constexpr (BM == 128 && BN == 128) {
+        if (p.inreg) {
+            const GemmGrid g{tokens, batch, p.tiles_m, p.tiles_n, p.tiles_m * p.tiles_n, 0, p.nsplit};
+            gemm_mfma_kernel<BM, BN, WR, WC, BK, NST, KIND, true><<<batch * g.full_tiles, block, 0, st>>>(A, W, C, Nn, K, g, ep);
+            return hipGetLastError();
+        }
+    }
     const GemmGrid g{tokens, batch, p.tiles_m, p.tiles_n, p.full, p.tail, p.nsplit};
     const int grid = batch * (p.full + p.tail * p.nsplit);
     gemm_mfma_kernel<BM, BN, WR, WC, BK, NST, KIND><<<grid, block, 0, st>>>(A, W, C, Nn, K, g, ep);
@@ -716,7 +762,7 @@ hipError_t launch_gemm_mfma(const bf16_t* A, const bf16_t* W, bf16_t* C, int bat
     const bool tails = (path & 0xff) != 4;
     const int fv = forced_variant_of(path);
     GemmPlan p = gemm_plan(batch, tokens, Nn, K, ep.split_ws != nullptr && tails, fv, pieces);
-    if (p.ws_bytes_per_sample * (size_t)batch > (ep.split_ws ? ep.split_ws_bytes : 0))
+    if (!p.inreg && p.ws_bytes_per_sample * (size_t)batch > (ep.split_ws ? ep.split_ws_bytes : 0))
         p = gemm_plan(batch, tokens, Nn, K, false, fv, pieces > 0 ? 1 : 0);
     switch (p.variant) {
         case 1: return launch_tile<256, 256, 2, 4, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 8 waves, 128x64 each

@@ -10,6 +10,8 @@
 // 5760 x 1920 229 -> 43 us, 1920 x 7680 ~900 -> 45 us; at 512 tokens 101 TFLOP/s.
 #include "common.h"
 #include "plan.h"
+#include <type_traits>
+
 
 namespace ps {
 
@@ -118,9 +120,12 @@ __device__ __forceinline__ void epilogue_quad(const Epilogue& ep, T* __restrict_
 // Workgroup -> (sample, tile, K piece).  Ids that share an XCD are contiguous (see the remap in the kernel); the row
 // tiles of all samples that read one W panel come first, so the panel is fetched into that XCD's L2 once.  With more
 // than 8 row tiles the tiles go in bands of 8 rows instead.
-struct SmallGrid { int batch, tiles_m, tiles_n, nsplit; };
+// pieces: workgroups along K per tile, nsplit or 1.
+struct SmallGrid { int batch, tiles_m, tiles_n, nsplit, pieces; };
 
-template <typename T, int KIND, int NST>
+// INREG: one workgroup per tile walks all of K and adds the nsplit pieces up in registers, in the order and with the
+// roundings of the reduction.
+template <typename T, int KIND, int NST, bool INREG>
 __global__ void __launch_bounds__(256, NST == 3 ? 3 : NST == 4 ? 2 : 1)
 gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict__ C, int Nn, int K, SmallGrid g,
                   Epilogue ep) {
@@ -134,18 +139,18 @@ gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restric
     if (g.tiles_m <= 8) {
         m0 = id % g.tiles_m * TILE; id /= g.tiles_m;
         sample = id % g.batch;      id /= g.batch;
-        piece = id % g.nsplit;      n0 = id / g.nsplit * TILE;
+        piece = id % g.pieces;      n0 = id / g.pieces * TILE;
     } else {
         const int tiles = g.tiles_m * g.tiles_n, tile = id % tiles;
         id /= tiles;
-        piece = id % g.nsplit; sample = id / g.nsplit;
+        piece = id % g.pieces; sample = id / g.pieces;
         const int band = tile / (8 * g.tiles_n), in_band = tile % (8 * g.tiles_n);
         const int rows_here = min(8, g.tiles_m - band * 8);
         m0 = (band * 8 + in_band % rows_here) * TILE;
         n0 = in_band / rows_here * TILE;
     }
     const int nk = K / (ROWB / (int)sizeof(T));
-    const int k0 = nk * piece / g.nsplit, nkt = nk * (piece + 1) / g.nsplit - k0;
+    const int k0 = nk * piece / g.pieces, nkt = nk * (piece + 1) / g.pieces - k0;
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, kgrp = lane >> 4;
@@ -183,12 +188,25 @@ gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restric
         for (int y = 0; y < 2; ++y)
 #pragma unroll
             for (int x = 0; x < 2; ++x) acc[z][y][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto piece_sum = [&](int y, int x) {
+        f32x4_t v = acc[0][y][x];
+        if constexpr (SETS == 2) v += acc[1][y][x];
+        return v;
+    };
+    f32x4_t total[2][2];                                 // INREG: the pieces before the current one
+    int piece_end = INREG ? nk / g.nsplit : 0, piece_no = 1;
+    if constexpr (INREG) {
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) total[y][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
     const int aoff = (wm * 32 + l16) * ROWB, woff = (TILE + wn * 32 + l16) * ROWB, sw = (l16 >> 1) & 7;
 
     // the epilogue's operands are requested now, with the first stages, and not when the sums are done
     // (rows and columns past the edge: clamped, not stored)
     EpiOperands eo[2][2];
-    if (g.nsplit == 1) {
+    if (g.pieces == 1) {
 #pragma unroll
         for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -234,6 +252,20 @@ gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restric
                             acc[ks][y][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[y][e], a[x][e], acc[ks][y][x], 0, 0, 0);
             }
         }
+        if constexpr (INREG) {
+            if (kt + 1 == piece_end) {                   // (the last piece ends with the last stage)
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) {
+                        total[y][x] += piece_sum(y, x);
+#pragma unroll
+                        for (int z = 0; z < SETS; ++z) acc[z][y][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                    }
+                ++piece_no;
+                piece_end = nk * piece_no / g.nsplit;
+            }
+        }
     }
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
@@ -243,9 +275,8 @@ gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restric
         for (int y = 0; y < 2; ++y) {
             const int col = n0 + wn * 32 + y * 16 + kgrp * 4;
             if (col >= Nn) continue;
-            f32x4_t sum = acc[0][y][x];
-            if constexpr (SETS == 2) sum += acc[1][y][x];
-            if (g.nsplit > 1)                            // [piece][row][column]
+            const f32x4_t sum = INREG ? total[y][x] : piece_sum(y, x);
+            if (g.pieces > 1)                            // [piece][row][column]
                 *reinterpret_cast<f32x4_t*>(ep.split_ws + (((long)piece * g.batch + sample) * tokens + n) * Nn + col) = sum;
             else
                 epilogue_quad<KIND, T>(ep, C, Nn, sample, n, col, sum, eo[x][y]);
@@ -271,19 +302,23 @@ gemm_small_reduce_kernel(T* __restrict__ C, int Nn, SmallGrid g, Epilogue ep) {
 
 template <typename T, int KIND>
 static hipError_t launch_small_kind(const T* A, const T* W, T* C, int batch, int tokens, int Nn, int K, const FewPlan& p,
-                                    const Epilogue& ep, int* deferred, hipStream_t st) {
-    const SmallGrid g{batch, p.tiles_m, p.tiles_n, p.nsplit};
-    const long blocks = (long)batch * p.tiles_m * p.tiles_n * p.nsplit;
+                                    bool inreg, const Epilogue& ep, int* deferred, hipStream_t st) {
+    const SmallGrid g{batch, p.tiles_m, p.tiles_n, p.nsplit, inreg ? 1 : p.nsplit};
+    const long blocks = (long)batch * p.tiles_m * p.tiles_n * g.pieces;
     if (blocks >= (1L << 31)) return hipErrorInvalidValue;
     auto go = [&](auto kernel) { kernel<<<(int)blocks, 256, 0, st>>>(A, W, C, Nn, K, g, ep); };
     // as deep a ring as lets every workgroup start at once (with two per CU, 513 to 768 are a second, nearly empty round:
     // 1920 x 1920 at 1100 rows, 540 tiles, 23.8 -> 20.8 us with three; 5760 x 1920 at 440, 630 tiles, 23.2 -> 20.7, both
     // with the weights in cache)
-    if (blocks <= 256) go(gemm_small_kernel<T, KIND, 8>);
-    else if (blocks <= 512) go(gemm_small_kernel<T, KIND, 4>);
-    else go(gemm_small_kernel<T, KIND, 3>);
+    const auto ring = [&](auto in_registers) {
+        constexpr bool R = decltype(in_registers)::value;
+        if (blocks <= 256) go(gemm_small_kernel<T, KIND, 8, R>);
+        else if (blocks <= 512) go(gemm_small_kernel<T, KIND, 4, R>);
+        else go(gemm_small_kernel<T, KIND, 3, R>);
+    };
+    if (inreg && p.nsplit > 1) ring(std::true_type{}); else ring(std::false_type{});
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.nsplit == 1) return e;
+    if (e != hipSuccess || g.pieces == 1) return e;
     if (deferred) { *deferred = p.nsplit; return e; }
     const long quads = (long)batch * tokens * (Nn / 4);
     gemm_small_reduce_kernel<T, KIND><<<(int)((quads + 255) / 256), 256, 0, st>>>(C, Nn, g, ep);
@@ -291,28 +326,27 @@ static hipError_t launch_small_kind(const T* A, const T* W, T* C, int batch, int
 }
 
 template <typename T>
-static hipError_t launch_small(const T* A, const T* W, T* C, int batch, int tokens, int Nn, int K, const FewPlan& p,
+static hipError_t launch_small(const T* A, const T* W, T* C, int batch, int tokens, int Nn, int K, const FewPlan& p, bool inreg,
                                const Epilogue& ep, int* deferred, hipStream_t st) {
     switch (ep.kind) {
-        case EPI_BIAS: return launch_small_kind<T, EPI_BIAS>(A, W, C, batch, tokens, Nn, K, p, ep, nullptr, st);
-        case EPI_BIAS_GELU: return launch_small_kind<T, EPI_BIAS_GELU>(A, W, C, batch, tokens, Nn, K, p, ep, nullptr, st);
-        case EPI_GATE_RESIDUAL: return launch_small_kind<T, EPI_GATE_RESIDUAL>(A, W, C, batch, tokens, Nn, K, p, ep, deferred, st);
-        case EPI_QKV_ROPE: return launch_small_kind<T, EPI_QKV_ROPE>(A, W, C, batch, tokens, Nn, K, p, ep, nullptr, st);
-        case EPI_UNPATCHIFY: return launch_small_kind<T, EPI_UNPATCHIFY>(A, W, C, batch, tokens, Nn, K, p, ep, nullptr, st);
+        case EPI_BIAS: return launch_small_kind<T, EPI_BIAS>(A, W, C, batch, tokens, Nn, K, p, inreg, ep, nullptr, st);
+        case EPI_BIAS_GELU: return launch_small_kind<T, EPI_BIAS_GELU>(A, W, C, batch, tokens, Nn, K, p, inreg, ep, nullptr, st);
+        case EPI_GATE_RESIDUAL: return launch_small_kind<T, EPI_GATE_RESIDUAL>(A, W, C, batch, tokens, Nn, K, p, inreg, ep, deferred, st);
+        case EPI_QKV_ROPE: return launch_small_kind<T, EPI_QKV_ROPE>(A, W, C, batch, tokens, Nn, K, p, inreg, ep, nullptr, st);
+        case EPI_UNPATCHIFY: return launch_small_kind<T, EPI_UNPATCHIFY>(A, W, C, batch, tokens, Nn, K, p, inreg, ep, nullptr, st);
         default: return hipErrorInvalidValue;
     }
 }
 
+// inreg: one workgroup per tile, the plan's pieces added in registers; else one per piece, through epi.split_ws.
 hipError_t launch_gemm_small(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K,
-                             const Epilogue& epi, const FewPlan& plan, int* deferred, hipStream_t st) {
+                             const Epilogue& epi, const FewPlan& p, bool inreg, int* deferred, hipStream_t st) {
     Epilogue ep = epi;
     ep.geom.tokens = tokens;                             // (the plain kinds leave it unset)
-    FewPlan p = plan;
     if (!p.use) return hipErrorInvalidValue;
-    if (ep.split_ws == nullptr || ep.split_ws_bytes < few_workspace_bytes(p, batch, tokens, Nn)) p.nsplit = 1;
     if (dtype == PS_BF16)
-        return launch_small<bf16_t>((const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C, batch, tokens, Nn, K, p, ep, deferred, st);
-    return launch_small<float>((const float*)A, (const float*)W, (float*)C, batch, tokens, Nn, K, p, ep, deferred, st);
+        return launch_small<bf16_t>((const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C, batch, tokens, Nn, K, p, inreg, ep, deferred, st);
+    return launch_small<float>((const float*)A, (const float*)W, (float*)C, batch, tokens, Nn, K, p, inreg, ep, deferred, st);
 }
 
 }  // namespace ps

@@ -50,9 +50,32 @@ constexpr FewPlan few_plan(bool bf16, int tokens, int Nn, int K, int path) {
     return p;
 }
 
-// scratch for the K pieces, [piece][row][column] in fp32
-constexpr size_t few_workspace_bytes(const FewPlan& p, int batch, int tokens, int Nn) {
-    return p.nsplit > 1 ? (size_t)p.nsplit * batch * tokens * Nn * sizeof(float) : 0;
+// What runs a batch of samples of one plan.  It counts the tiles of the whole batch; the values are the same either way (same
+// instruction, same order of k, pieces added in the same order, same epilogue).
+//   FEW_PIECES  a workgroup per 64 x 64 tile and K piece; the pieces pass through memory
+//   FEW_INREG   a workgroup per 64 x 64 tile, which adds its pieces in registers
+//   FEW_TILES   128-wide tiles of the other kernel, pieces in registers (bf16)
+// Pieces of their own pay until the tiles alone occupy the chip.  Layer with cold weights, us, pieces apart / in registers:
+// 1920 x 1920 and the LayerNorm that adds the pieces, 112 tokens: 3 samples (180 tiles) 19.3 / 21.5, 4 (240) 23.1 / 22.0,
+// 8 (480) 37.1 / 26.3; 1920 x 7680, 4 samples (240) 42.1 / 50.2, 6 (360) 57.5 / 62.4, 8 (480) 74.1 / 62.2.  fp32 is bound by
+// the matrix instructions and takes finer pieces longer: 1920 x 7680 at 320 tokens, 4 samples (600 tiles) 358 / 393, 8 (1200)
+// 674 / 654.
+// 128-wide tiles need 512 of themselves for a round and take about as long for fewer; 64-wide ones, 0.036 us each: 5760 x
+// 1920, 112 tokens, 4 samples (720 tiles) 28.2 against 32.9, 6 (1080) 39.1 / 34.3, 16 (2880) 96.3 / 68.9.  In samples of up
+// to 64 tokens a 128-row tile is at least half empty: 16 of 32 tokens (1440) 42.4 / 56.7.
+enum FewHow { FEW_PIECES, FEW_INREG, FEW_TILES };
+constexpr long few_spread_tiles(bool bf16, int K) { return !bf16 ? 640 : K >= 60 * 64 ? 384 : 256; }
+constexpr FewHow few_how(bool bf16, const FewPlan& p, int batch, int K) {
+    const long tiles = (long)batch * p.tiles_m * p.tiles_n;
+    if (p.nsplit > 1 && tiles < few_spread_tiles(bf16, K)) return FEW_PIECES;
+    return bf16 && tiles > 768 && p.tiles_m > 1 ? FEW_TILES : FEW_INREG;
+}
+
+// scratch for the K pieces, [piece][row][column] in fp32; does not shrink with the batch
+constexpr size_t few_workspace_bytes(bool bf16, const FewPlan& p, int batch, int tokens, int Nn, int K) {
+    if (p.nsplit == 1) return 0;
+    const long most = (few_spread_tiles(bf16, K) - 1) / ((long)p.tiles_m * p.tiles_n);   // the largest batch of FEW_PIECES
+    return (size_t)p.nsplit * (batch < most ? batch : most) * tokens * Nn * sizeof(float);
 }
 
 }  // namespace ps

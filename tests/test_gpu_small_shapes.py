@@ -152,3 +152,32 @@ def test_update_and_rel_mae_on_one_and_two_workgroups(n):
     num, den = (xd - ed).abs().sum(), xd.abs().sum()
     assert torch.allclose(r, torch.stack([num, den, num / den]), rtol=16 * 2.0 ** -23, atol=0)
     assert torch.isnan(B.rel_mae(torch.zeros(n, device=DEV), torch.zeros(n, device=DEV))[2])
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 3), (6, 8), (12, 20), (18, 28), (24, 32), (30, 43), (36, 43), (40, 51)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_forward_of_a_batch_equals_single_calls_whatever_kernels_the_batch_takes(dtype, rows, cols):
+    """One block of width 1920.  What runs a projection or a LayerNorm depends on the rows of the whole batch (K pieces in
+    workgroups of their own or in registers, 64- or 128-wide tiles, a row per workgroup or per wave), its values do not:
+    samples of 11 to 2048 tokens, batches of 1, 2, 5 and 16, bit for bit."""
+    if dtype == "f32" and rows > 18:
+        pytest.skip("one kernel for every fp32 size")
+    cfg = I.CONFIGS["reduced"].with_(layers=1, frames=1, height=2 * rows, width=2 * cols, text_tokens=8, dtype=dtype)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows * cols)
+    td = B.torch_dtype(dtype)
+    w = []
+    for name, shape in I.weight_shapes(cfg):
+        t = torch.randn(shape, generator=g, device=DEV)
+        w.append((t * shape[1] ** -0.5).to(td) if len(shape) == 2 else t)
+    d = B.dit_create(cfg, w)
+    x = torch.randn(16, *cfg.latent_shape, generator=g, device=DEV)
+    ctx = torch.randn(16, cfg.text_tokens, cfg.hidden, generator=g, device=DEV).to(td)
+    t = [60 * b + 7 for b in range(16)]
+    one = [B.dit_forward(d, x[b:b + 1].contiguous(), ctx[b:b + 1].contiguous(), [t[b]])[0].clone() for b in range(16)]
+    assert torch.isfinite(one[0]).all()
+    for n in (2, 5, 16):
+        print(f"forward {dtype} {cfg.tokens} tokens, batch {n}", flush=True)
+        out = B.dit_forward(d, x[:n].contiguous(), ctx[:n].contiguous(), t[:n])
+        for b in range(n):
+            assert torch.equal(out[b], one[b]), (n, b)

@@ -17,6 +17,12 @@ extern "C" int few(int bf16, int tokens, int n, int k, int path) {   // 0: anoth
     const ps::FewPlan p = ps::few_plan(bf16 != 0, tokens, n, k, path);
     return p.use ? p.nsplit : 0;
 }
+extern "C" int how(int bf16, int tokens, int n, int k, int batch) {
+    return ps::few_how(bf16 != 0, ps::few_plan(bf16 != 0, tokens, n, k, 0), batch, k);
+}
+extern "C" long scratch(int bf16, int tokens, int n, int k, int batch) {
+    return (long)ps::few_workspace_bytes(bf16 != 0, ps::few_plan(bf16 != 0, tokens, n, k, 0), batch, tokens, n, k);
+}
 """
 
 
@@ -27,7 +33,9 @@ def rules(tmp_path_factory):
     with open(src, "w") as f:
         f.write(WRAPPERS)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", build.CSRC, src, "-o", lib], check=True)
-    return C.CDLL(lib)
+    lib = C.CDLL(lib)
+    lib.scratch.restype = C.c_long
+    return lib
 
 
 @pytest.mark.parametrize("nitems", [1, 28, 524800, 1 << 20])
@@ -52,3 +60,32 @@ def test_few_token_projections_end_where_wider_tiles_are_faster(rules):
     assert rules.few(0, 4096, 1920, 7680, 0) == 1                        # fp32: every size
     assert rules.few(1, 112, 1920, 1920, 4) == 1 and rules.few(1, 112, 1920, 1920, 1) == 0
     assert few(112, 1922, 1920) == 0 and few(112, 1920, 1928) == 0 and few(112, 62, 1920) == 0
+
+
+PIECES, INREG, TILES = 0, 1, 2
+
+
+def test_a_batch_that_fills_the_chip_takes_wide_tiles_and_no_pieces_of_its_own(rules):
+    how = lambda *a: rules.how(1, *a)
+    assert how(112, 1920, 1920, 1) == PIECES and how(112, 1920, 1920, 4) == PIECES      # 60 tiles, 240
+    assert how(112, 1920, 1920, 8) == INREG and how(112, 1920, 1920, 16) == TILES       # 480, 960
+    assert how(112, 1920, 7680, 6) == PIECES and how(112, 1920, 7680, 8) == INREG       # 360, 480
+    assert how(256, 7680, 1920, 1) == INREG and how(256, 7680, 1920, 8) == TILES
+    assert how(1300, 1920, 1920, 1) == INREG and how(1300, 1920, 1920, 2) == TILES      # 630, 1260
+    assert how(64, 7680, 1920, 16) == INREG                                             # a 128-row tile would be half empty
+    assert rules.how(0, 112, 1920, 7680, 8) == PIECES and rules.how(0, 320, 1920, 7680, 16) == INREG   # fp32: one kernel
+
+
+@pytest.mark.parametrize("bf16", [0, 1])
+def test_scratch_of_few_token_projections_serves_every_smaller_batch(rules, bf16):
+    """A workspace sized for a batch is used for smaller ones (the last cycle of a step-batched run), and a batch whose pieces
+    stay in registers needs no more than the largest one whose pieces do not."""
+    for tokens in (1, 32, 64, 65, 112, 256, 520, 1040, 1300):
+        for n, k in ((64, 1920), (1920, 1920), (5760, 1920), (7680, 1920), (1920, 7680), (196, 1984)):
+            pieces = rules.few(bf16, tokens, n, k, 0)
+            size = [rules.scratch(bf16, tokens, n, k, b) for b in range(1, 17)]
+            assert size == sorted(size)
+            for b in range(1, 17):
+                if pieces > 1 and rules.how(bf16, tokens, n, k, b) == PIECES:
+                    assert size[b - 1] >= 4 * pieces * b * tokens * n
+                assert size[b - 1] <= 4 * max(pieces, 1) * tokens * n * b
