@@ -268,8 +268,9 @@ __device__ __forceinline__ void wait_vmcnt() {
 // One BM x BN output tile (rows m0.., columns n0..), k-tiles k0..k1-1 of 64, by the WR x WC waves of a workgroup,
 // each owning (BM/WR) x (BN/WC) outputs.  piece >= 0: a K-split piece, accumulators go to ep.split_ws.
 // BK: K depth of an LDS stage; NST: ring depth; lds: NST * (BM + BN) * 2 * BK bytes, 1024-aligned.
-// INREG: k0..k1-1 are summed in `nsplit` pieces that are added up in registers, in the order and with the roundings of
-// gemm_tail_kernel.
+// INREG: k0..k1-1 are summed in `nsplit` pieces that the workgroup adds up itself, in the order and with the roundings of
+// gemm_tail_kernel: in a second set of registers on the 128 x 128 tile; the wide tile has none to spare, its sums wait in
+// ep.split_ws for the end of the next piece.
 template <int BM, int BN, int WR, int WC, int BK, int NST, int KIND, bool INREG>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, bf16_t* __restrict__ C,
                                           int M, int Nn, int K, int m0, int n0, int k0, int k1, int piece, int nsplit,
@@ -342,9 +343,10 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) acc[i][j][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    f32x4_t total[INREG ? TM : 1][INREG ? TN : 1][4];    // the pieces before the current one
+    constexpr bool KEEP = INREG && BM * BN <= 128 * 128; // registers for the pieces before the current one
+    f32x4_t total[KEEP ? TM : 1][KEEP ? TN : 1][4];
     int piece_end = INREG ? (k1 - k0) / nsplit : 0, piece_no = 1;
-    if constexpr (INREG) {
+    if constexpr (KEEP) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -352,6 +354,11 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
 #pragma unroll
                 for (int q = 0; q < 4; ++q) total[i][j][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
+    // [workgroup][wave][i][j][lane][16 accumulator registers], as the pieces of workgroups of their own
+    auto parked = [&](int i, int j) {
+        return reinterpret_cast<f32x4_t*>(ep.split_ws +
+                                          ((((long)blockIdx.x * NW + wave) * (TM * TN) + i * TN + j) * 64 + lane) * 16);
+    };
 
     constexpr int FA = 2 * TM, FB = 2 * TN;              // 16-row fragments of A and of W per k-step
     static_assert(BK == 64, "two 32-deep k-steps per stage");
@@ -477,15 +484,23 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
                     for (int j = 0; j < TN; ++j)
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
-                            total[i][j][q] += acc[i][j][q];
-                            acc[i][j][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                            if constexpr (KEEP) {
+                                total[i][j][q] += acc[i][j][q];
+                                acc[i][j][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                            } else {
+                                f32x4_t t = {0.f, 0.f, 0.f, 0.f};
+                                if (piece_no > 1) t = parked(i, j)[q];
+                                t += acc[i][j][q];
+                                if (more) { parked(i, j)[q] = t; t = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+                                acc[i][j][q] = t;
+                            }
                         }
                 ++piece_no;
                 piece_end = nkt * piece_no / nsplit;
             }
         }
     }
-    if constexpr (INREG) {
+    if constexpr (KEEP) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -645,7 +660,7 @@ struct TileVariant { int bm, bn, per_cu; float cost; };
 // 30-layer network at 17776 and 33976 tokens.  The loop is bound by LDS traffic (fragment reads plus the direct
 // loads' writes, 128 bytes per clock and CU): a wave tile of 128x64 reads 12 fragments per 32 MFMAs, 96x64 10 per
 // 24, 64x64 8 per 16; two co-resident workgroups win some of it back by hiding each other's epilogue.
-static const TileVariant kVariants[5] = {
+static constexpr TileVariant kVariants[5] = {
     {0, 0, 0, 0.f},
     {256, 256, 1, 1.00f},     // 1: 8 waves of 128x64
     {128, 128, 2, 1.17f},     // 2: 4 waves of 64x64, two workgroups per CU
@@ -655,7 +670,7 @@ static const TileVariant kVariants[5] = {
 
 // the K split of the last partial round: pieces per tail tile (1: none).  Where the tiles do not fill half of the slots
 // the only round is the last one and every tile is split (1920 x 7680 weights at 1500 tokens, 180 tiles of 128 x 128,
-// 2 pieces each: 104 -> 74 us; at 2000 tokens, 240 tiles, 106 -> 81).
+// 2 pieces each: 104 -> 74 us; at 2000 tokens, 240 tiles, 106 -> 81; batches: see gemm_plan).
 static int tail_split(int tiles, int slots, int K, bool allow_split) {
     const int tail = tiles % slots, nk = K / 64;
     if (!allow_split || K < 4096 || tail == 0) return 1;
@@ -665,53 +680,78 @@ static int tail_split(int tiles, int slots, int K, bool allow_split) {
     return ns >= 2 ? ns : 1;
 }
 
+// The variant with the least estimated time for `samples` samples: rounds of workgroup slots (a K-split tail counts as
+// 1/pieces of a round plus a fifth of a round for its partial sums and second launch) x tile area x the tile's cost per
+// output.  Outputs with fewer tiles than slots take the smallest tile.
+static int best_variant(int samples, int tokens, int Nn, int K, bool may_split) {
+    const int cus = gemm_compute_units();
+    float best = 0.f;
+    int v = 2;
+    for (int c = 1; c <= 4; ++c) {
+        const TileVariant& t = kVariants[c];
+        const int tiles = samples * ((tokens + t.bm - 1) / t.bm) * ((Nn + t.bn - 1) / t.bn);
+        const int slots = cus * t.per_cu;
+        if (tiles < slots) continue;
+        const int ns = tail_split(tiles, slots, K, may_split);
+        float rounds = (float)(tiles / slots);
+        if (tiles % slots) rounds += ns > 1 ? 1.0f / ns + 0.2f : 1.0f;
+        const float est = rounds * slots * t.bm * t.bn * t.cost;
+        if (best == 0.f || est < best) { best = est; v = c; }
+    }
+    return v;
+}
+
+// The variant for tiles that add up their own `pieces`: 128 x 128 in registers, or 192 x 256, whose sums wait in memory (a
+// fifth of a round per piece), where that saves a round.  4 samples of 1442 tokens, 1920 x 7680 in 2 pieces: 720 tiles, two
+// rounds, 204 us; 256, one round, 160.  16 of 256 tokens in 4 pieces: 480 and 256 tiles, one round each, 117 and 229.
+static int inreg_variant(int samples, int tokens, int Nn, int pieces) {
+    const int cus = gemm_compute_units();
+    auto estimate = [&](const TileVariant& t) {
+        const int tiles = samples * ((tokens + t.bm - 1) / t.bm) * ((Nn + t.bn - 1) / t.bn), slots = cus * t.per_cu;
+        return (float)((tiles + slots - 1) / slots) * slots * t.bm * t.bn * t.cost;
+    };
+    return estimate(kVariants[3]) * (1.0f + 0.2f * (pieces - 1)) < estimate(kVariants[2]) ? 3 : 2;
+}
+
 // pieces > 0: every tile is summed in that many K pieces (1: whole), which the caller has fixed for the sample's shape.
-static GemmPlan gemm_plan(int batch, int tokens, int Nn, int K, bool allow_split, int forced_variant, int pieces) {
+// scratch: bytes the wide tile's waiting sums may take (values do not depend on it).
+static GemmPlan gemm_plan(int batch, int tokens, int Nn, int K, bool allow_split, int forced_variant, int pieces, size_t scratch) {
     GemmPlan p{};
     const int cus = gemm_compute_units();
+    const bool automatic = forced_variant < 1 || forced_variant > 4;
+    auto lay_out = [&](int v) {
+        const TileVariant& t = kVariants[v];
+        p.variant = v; p.bm = t.bm; p.bn = t.bn; p.per_cu = t.per_cu;
+        p.tiles_m = (tokens + p.bm - 1) / p.bm;
+        p.tiles_n = (Nn + p.bn - 1) / p.bn;
+        p.full = p.tiles_m * p.tiles_n; p.tail = 0; p.nsplit = 1; p.ws_bytes_per_sample = 0; p.inreg = false;
+        return p.full;
+    };
+    // Which tiles are summed in K pieces depends on the variant, and must not depend on the batch: it is decided for one
+    // sample.  Where that sample runs whole the variant never changes a value and the choice counts the tiles of the whole
+    // batch (4 samples of 2608 tokens, 1920 x 7680: 357 us on the sample's 128 x 128 tiles, 319 on the batch's 192 x 256).
     int v = forced_variant;
-    const bool automatic = v < 1 || v > 4;
-    if (automatic && pieces > 1) {
-        v = 2;                                           // the variant that has room for a second set of sums
-    } else if (automatic) {
-        // the variant with the least estimated time: rounds of workgroup slots (a K-split tail counts as 1/pieces of
-        // a round plus a fifth of a round for its partial sums and second launch) x tile area x the tile's cost
-        // per output.  Outputs with fewer tiles than slots take the smallest tile.
-        // Which tiles are summed in K pieces depends on the variant, and must not depend on the batch: where a split
-        // is possible (long K) the choice looks at one sample; elsewhere the variant never changes a value and the
-        // choice may count the tiles of the whole batch.
-        const bool may_split = pieces == 0 && allow_split && K >= 4096;
-        const int nb = may_split ? 1 : batch;
-        float best = 0.f;
-        v = 2;
-        for (int c = 1; c <= 4; ++c) {
-            const TileVariant& t = kVariants[c];
-            const int tiles = nb * ((tokens + t.bm - 1) / t.bm) * ((Nn + t.bn - 1) / t.bn);
-            const int slots = cus * t.per_cu;
-            if (tiles < slots) continue;
-            const int ns = tail_split(tiles, slots, K, may_split);
-            float rounds = (float)(tiles / slots);
-            if (tiles % slots) rounds += ns > 1 ? 1.0f / ns + 0.2f : 1.0f;
-            const float est = rounds * slots * t.bm * t.bn * t.cost;
-            if (best == 0.f || est < best) { best = est; v = c; }
-        }
-    }
-    const TileVariant& t = kVariants[v];
-    p.variant = v; p.bm = t.bm; p.bn = t.bn; p.per_cu = t.per_cu;
-    p.tiles_m = (tokens + p.bm - 1) / p.bm;
-    p.tiles_n = (Nn + p.bn - 1) / p.bn;
-    const int tiles = p.tiles_m * p.tiles_n;
-    p.full = tiles; p.tail = 0; p.nsplit = 1; p.ws_bytes_per_sample = 0;
+    if (automatic) v = best_variant(1, tokens, Nn, K, pieces == 0 && allow_split);
+    const int tiles = lay_out(v);
     // the last partial round: split along K if the partial sums (two passes over tile-size fp32 per piece) and
     // the second launch cost less than the round they save -- measured at 17776 tokens: true with a long K
     // (fc2 on 128x128 tiles: 0.62 -> 0.57 ms), not for K = 1920 (0.188 -> 0.196 ms)
     const int slots = cus * p.per_cu;
     const int ns = pieces > 0 ? pieces : tail_split(tiles, slots, K, allow_split);
-    if (ns > 1) {
-        const int tail = pieces > 0 ? tiles : tiles % slots;
-        p.full = tiles - tail; p.tail = tail; p.nsplit = ns;
-        p.ws_bytes_per_sample = (size_t)tail * ns * p.bm * p.bn * sizeof(float);
-        p.inreg = automatic && pieces > 1;
+    if (ns == 1) {
+        if (automatic) lay_out(best_variant(batch, tokens, Nn, K, false));
+        return p;
+    }
+    p.tail = pieces > 0 ? tiles : tiles % slots;
+    p.full = tiles - p.tail; p.nsplit = ns;
+    p.ws_bytes_per_sample = (size_t)p.tail * ns * p.bm * p.bn * sizeof(float);
+    // Every tile in pieces: workgroups of their own while the batch has at most one tile per compute unit, else added up by
+    // the tile's own (1920 x 7680 at 2048 tokens, 255 tiles: 78 against 104 us; two samples 148 / 115).
+    if (automatic && p.full == 0 && (pieces > 1 || (long)batch * tiles > cus)) {
+        const int full = lay_out(inreg_variant(batch, tokens, Nn, ns));
+        if (p.variant != 2 && (size_t)batch * full * p.bm * p.bn * sizeof(float) > scratch) lay_out(2);
+        p.nsplit = ns;
+        p.inreg = true;
     }
     return p;
 }
@@ -720,17 +760,17 @@ static GemmPlan gemm_plan(int batch, int tokens, int Nn, int K, bool allow_split
 static int forced_variant_of(int path) { return (path >> 8) & 0xf; }
 
 size_t gemm_tiles_workspace_bytes(int batch, int tokens, int Nn, int K, int path, int pieces) {
-    if ((path & 0xff) == 4) return 0;
-    return gemm_plan(batch, tokens, Nn, K, true, forced_variant_of(path), pieces).ws_bytes_per_sample * (size_t)batch;
+    if ((path & 0xff) == 4 || (pieces == 0 && K < 4096)) return 0;
+    return gemm_plan(1, tokens, Nn, K, true, forced_variant_of(path), pieces, 0).ws_bytes_per_sample * (size_t)batch;
 }
 
 template <int BM, int BN, int WR, int WC, int BK, int NST, int KIND>
 static hipError_t launch_kind(const bf16_t* A, const bf16_t* W, bf16_t* C, int batch, int tokens, int Nn, int K,
                               const GemmPlan& p, const Epilogue& ep, hipStream_t st) {
     dim3 block(WR * WC * 64);
-    if constexpr (BM == 128 && BN == 128) {
+    if constexpr ((BM == kVariants[2].bm && BN == kVariants[2].bn) || (BM == kVariants[3].bm && BN == kVariants[3].bn)) {
         if (p.inreg) {
-            const GemmGrid g{tokens, batch, p.tiles_m, p.tiles_n, p.tiles_m * p.tiles_n, 0, p.nsplit};
+            const GemmGrid g{tokens, batch, p.tiles_m, p.tiles_n, p.full, 0, p.nsplit};
             gemm_mfma_kernel<BM, BN, WR, WC, BK, NST, KIND, true><<<batch * g.full_tiles, block, 0, st>>>(A, W, C, Nn, K, g, ep);
             return hipGetLastError();
         }
@@ -761,9 +801,10 @@ hipError_t launch_gemm_mfma(const bf16_t* A, const bf16_t* W, bf16_t* C, int bat
                             const Epilogue& ep, int path, int pieces, hipStream_t st) {
     const bool tails = (path & 0xff) != 4;
     const int fv = forced_variant_of(path);
-    GemmPlan p = gemm_plan(batch, tokens, Nn, K, ep.split_ws != nullptr && tails, fv, pieces);
-    if (!p.inreg && p.ws_bytes_per_sample * (size_t)batch > (ep.split_ws ? ep.split_ws_bytes : 0))
-        p = gemm_plan(batch, tokens, Nn, K, false, fv, pieces > 0 ? 1 : 0);
+    const size_t scratch = ep.split_ws ? ep.split_ws_bytes : 0;
+    GemmPlan p = gemm_plan(batch, tokens, Nn, K, ep.split_ws != nullptr && tails, fv, pieces, scratch);
+    if (p.ws_bytes_per_sample * (size_t)batch > scratch)
+        p = gemm_plan(batch, tokens, Nn, K, false, fv, pieces > 0 ? 1 : 0, 0);
     switch (p.variant) {
         case 1: return launch_tile<256, 256, 2, 4, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 8 waves, 128x64 each
         case 2: return launch_tile<128, 128, 2, 2, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 4 waves, 64x64 each, 2 per CU

@@ -154,12 +154,12 @@ def test_update_and_rel_mae_on_one_and_two_workgroups(n):
     assert torch.isnan(B.rel_mae(torch.zeros(n, device=DEV), torch.zeros(n, device=DEV))[2])
 
 
-@pytest.mark.parametrize("rows,cols", [(1, 3), (6, 8), (12, 20), (18, 28), (24, 32), (30, 43), (36, 43), (40, 51)])
+@pytest.mark.parametrize("rows,cols", [(1, 3), (6, 8), (12, 20), (18, 28), (24, 32), (30, 43), (36, 43), (40, 51), (48, 54)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_forward_of_a_batch_equals_single_calls_whatever_kernels_the_batch_takes(dtype, rows, cols):
     """One block of width 1920.  What runs a projection or a LayerNorm depends on the rows of the whole batch (K pieces in
     workgroups of their own or in registers, 64- or 128-wide tiles, a row per workgroup or per wave), its values do not:
-    samples of 11 to 2048 tokens, batches of 1, 2, 5 and 16, bit for bit."""
+    samples of 11 to 2600 tokens, batches of 1, 2, 5 and 16, bit for bit."""
     if dtype == "f32" and rows > 18:
         pytest.skip("one kernel for every fp32 size")
     cfg = I.CONFIGS["reduced"].with_(layers=1, frames=1, height=2 * rows, width=2 * cols, text_tokens=8, dtype=dtype)
