@@ -120,7 +120,8 @@ hipError_t launch_tables(const int32_t* t_host, float* sinus, int batch, int D, 
 constexpr int GEMV_SET = 32;
 struct GemvSet { const void* W[GEMV_SET]; const float* bias[GEMV_SET]; float* out[GEMV_SET]; };
 // The modulation matrices of a network (12 * D rows each) and the final one (2 * D rows), all applied to the same vectors:
-// a matrix product in fp32 on matrix instructions where cols % 64 == 0, cols <= 1000 and rows % 4 == 0, one launch_gemv per matrix otherwise.
+// a matrix product in fp32 on matrix instructions where cols % 64 == 0, cols <= 1000 and rows % 4 == 0, else launch_gemv_set
+// for the matrices of one shape.
 // out_bs[i]: batch stride of matrix i's output; rows[i]: its rows.
 struct ModSet { GemvSet g; int rows[GEMV_SET]; long out_bs[GEMV_SET]; };
 hipError_t launch_modulation(int dtype, const ModSet& set, int count, const float* in, int cols, int batch, long in_bs,

@@ -237,10 +237,13 @@ hipError_t launch_modulation(int dtype, const ModSet& set, int count, const floa
         if (set.rows[i] > most) most = set.rows[i];
         ok = ok && set.rows[i] % 4 == 0 && set.out_bs[i] % 4 == 0;
     }
-    if (!ok) {
-        for (int i = 0; i < count; ++i) {
-            const hipError_t e = launch_gemv(dtype, set.g.W[i], set.g.bias[i], in, set.g.out[i], set.rows[i], cols, batch, in_bs,
-                                             set.out_bs[i], 0, st);
+    if (!ok) {                                           // matrices of one shape (the layers') share a launch
+        for (int i = 0, n; i < count; i += n) {
+            GemvSet part{};
+            for (n = 0; i + n < count && set.rows[i + n] == set.rows[i] && set.out_bs[i + n] == set.out_bs[i]; ++n) {
+                part.W[n] = set.g.W[i + n]; part.bias[n] = set.g.bias[i + n]; part.out[n] = set.g.out[i + n];
+            }
+            const hipError_t e = launch_gemv_set(dtype, part, n, in, set.rows[i], cols, batch, in_bs, set.out_bs[i], 0, st);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;

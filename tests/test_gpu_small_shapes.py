@@ -1,5 +1,6 @@
 """Kernels for few tokens and for fp32 operands at the sizes where they can go wrong: edges of 64 x 64 tiles, K pieces of
 unequal length, pieces added by the following LayerNorm, ragged keys, more predictor steps than one conditioning chunk."""
+import ctypes
 import math
 
 import numpy as np
@@ -125,9 +126,32 @@ def test_run_longer_than_one_conditioning_chunk(mode, batched, S, m, cyc):
     assert torch.equal(out, x0) and torch.equal(sums2, sums)
 
 
+def graph_nodes(call):
+    """How many kernels a call enqueues: the nodes of the graph it is captured into."""
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        call()
+    n = ctypes.c_size_t()
+    hip = next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64.so" in l)      # the runtime that is in use
+    assert ctypes.CDLL(hip).hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+def test_modulation_off_the_matrix_path_is_one_launch_per_32_layers():
+    """40 layers: the matrix kernel takes 41 matrices in 2 launches; time_embed_dim 72 takes 32 + 8 + the final one."""
+    def nodes(Dt):
+        cfg = I.CONFIGS["tiny_text"].with_(time_embed_dim=Dt, layers=40)
+        d = B.dit_create(cfg, B.weights_to_device(cfg, I.make_weights(cfg, 1001, "unit"), DEV))
+        x, ctx = torch.from_numpy(I.make_latent(cfg, 1)).to(DEV), torch.from_numpy(I.make_context(cfg, 1)).to(DEV)
+        return graph_nodes(lambda: B.dit_forward(d, x, ctx, [500]))
+    assert nodes(72) == nodes(64) + 1
+
+
 @pytest.mark.parametrize("Dt", [64, 72, 1024])
 def test_modulation_widths_on_and_off_the_matrix_path(Dt):
-    """time_embed_dim a multiple of 64 up to 1000 takes the matrix kernel, others one vector product per matrix."""
+    """time_embed_dim a multiple of 64 up to 1000 takes the matrix kernel, others vector products."""
     cfg = I.CONFIGS["tiny_text"].with_(time_embed_dim=Dt)
     W = I.make_weights(cfg, 1001, "unit")
     d = B.dit_create(cfg, B.weights_to_device(cfg, W, DEV))
