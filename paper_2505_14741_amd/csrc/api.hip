@@ -730,21 +730,21 @@ int sampler_run_steps(dit* d, const sampler_schedule* s, sampler_state* state, i
     // computed again when they are used up.  `need` steps from `step` on are asked for together.
     Conditioning cd{(float*)(base + w.sinus), (float*)(base + w.hid), (float*)(base + w.cvec), (float*)(base + w.mod),
                     (float*)(base + w.modf), (float*)(base + w.rope)};
-    std::vector<int> cond_steps;
+    int cond_steps[MAX_BATCH], conds = 0;                // (no container: entry points do not throw)
     bool rope_done = false;
     auto conditioned = [&](int step, int need, Conditioning* out) -> int {
-        size_t at = 0;
-        while (at < cond_steps.size() && cond_steps[at] != step) ++at;
-        if (at + need > cond_steps.size()) {
+        int at = 0;
+        while (at < conds && cond_steps[at] != step) ++at;
+        if (at + need > conds) {
             int32_t ts[MAX_BATCH];
-            cond_steps.clear();
-            for (int j = step; j < stop_step && (int)cond_steps.size() < w.cond_steps; ++j) {
+            conds = 0;
+            for (int j = step; j < stop_step && conds < w.cond_steps; ++j) {
                 int c2, r2;
                 if (s->mode == 1 && position_of(plan, j, &c2, &r2) && r2 != 0) continue;   // direct reuse: no call there
-                ts[cond_steps.size()] = s->timesteps[j];
-                cond_steps.push_back(j);
+                ts[conds] = s->timesteps[j];
+                cond_steps[conds++] = j;
             }
-            const int rc2 = condition(d, ts, (int)cond_steps.size(), cd, !rope_done, st);
+            const int rc2 = condition(d, ts, conds, cd, !rope_done, st);
             if (rc2 != PS_OK) return rc2;
             rope_done = true;
             at = 0;
