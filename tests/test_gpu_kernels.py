@@ -159,8 +159,10 @@ def test_attention_fp32_matches_oracle(N, d):
     assert_close_fp32(host(o), O.attn3d(q, k, v, scale))
 
 
-@pytest.mark.parametrize("N", [1, 31, 63, 64, 65, 127, 129, 255, 257, 1000])
+@pytest.mark.parametrize("N", [1, 31, 63, 64, 65, 127, 129, 255, 257, 512, 513, 543, 575, 576, 577, 639, 767, 769, 1000])
 def test_attention_bf16_mfma_matches_oracle(N):
+    """Up to 512 keys one kernel that tracks a softmax reference, beyond it the one without and its fallback: ragged last
+    key tiles of both."""
     print(f"attn3d bf16 N={N}", flush=True)
     q, k, v = I.make_qkv(2, N, 3, 64, dtype="bf16")
     o = B.attn3d(dev(q, torch.bfloat16), dev(k, torch.bfloat16), dev(v, torch.bfloat16), 0.125)
@@ -170,9 +172,9 @@ def test_attention_bf16_mfma_matches_oracle(N):
     assert r < 8e-3      # bf16 rounding of P and of the output only
 
 
-def test_attention_bf16_large_logits_and_poisoned_workspace():
-    """Logit std ~ 4 (sharp softmax), NaN-filled scratch and output must not leak."""
-    N = 333
+@pytest.mark.parametrize("N", [333, 700])
+def test_attention_bf16_large_logits_and_poisoned_workspace(N):
+    """Logit std ~ 4 (sharp softmax), NaN-filled scratch and output must not leak (333 keys need no scratch)."""
     q, k, v = I.make_qkv(1, N, 2, 64, dtype="bf16", scale=2.0)
     qd, kd, vd = (dev(a, torch.bfloat16) for a in (q, k, v))
     out = torch.full_like(qd, float("nan"))
@@ -182,6 +184,43 @@ def test_attention_bf16_large_logits_and_poisoned_workspace():
     torch.cuda.synchronize()
     assert torch.isfinite(o).all()
     assert_close_bf16(host(o), O.attn3d(q, k, v, 0.125), 2e-2)
+
+
+def test_attention_bf16_split_items_marked_heads_and_poisoned_workspace_in_a_batch():
+    """513 keys x 200 heads: 600 items of 256 queries on 512 slots, the last 88 of each sample (heads 170.7 to 199) in key
+    pieces.  The scratch (flags and pieces) is full of NaN; heads 3, 180 and 199 of sample 1 overflow and go to the kernel
+    that tracks a reference, split items among them.  Against the oracle, against another scratch and against single calls."""
+    N, H, heads = 513, 200, (0, 3, 170, 171, 180, 198, 199)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(11)
+    q, k, v = (torch.randn(2, N, H, 64, generator=g, device=DEV) for _ in range(3))
+    for h in (3, 180, 199):
+        q[1, :, h] *= 16.0
+        k[1, :, h] *= 16.0                            # exponents ~ N(0, 370^2)
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+
+    def call(q, k, v, fill):
+        L, out = B.lib(), torch.full_like(q, float("nan"))
+        n = L.attn3d_workspace_bytes(q.shape[0], N, H, 64, 1)
+        assert n > 4 * H * 256                        # the plan does split
+        ws = torch.full((n // 4,), fill, device=DEV)
+        ptr = lambda t: t.data_ptr()
+        rc = L.attn3d(ptr(q), ptr(k), ptr(v), ptr(out), q.shape[0], N, H, 64, 0.125, 1, 0, ptr(ws), n,
+                      torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        torch.cuda.synchronize()
+        return out
+
+    out = call(q, k, v, float("nan"))
+    assert torch.isfinite(out).all()
+    assert torch.equal(out, call(q, k, v, 0.0))
+    for b in range(2):
+        assert torch.equal(call(q[b:b + 1], k[b:b + 1], v[b:b + 1], float("nan"))[0], out[b]), b
+        sel = torch.tensor(heads, device=DEV)
+        ref = O.attn3d(*(host(t[b:b + 1].index_select(2, sel)) for t in (q, k, v)), 0.125)
+        got = host(out[b:b + 1].index_select(2, sel))
+        for i, h in enumerate(heads):
+            assert_close_bf16(got[:, :, i], ref[:, :, i], 2e-2, max_tol=4e-2)
 
 
 @pytest.mark.parametrize("case", ["huge_everywhere", "small_first_tile_then_huge", "all_far_below_zero",
@@ -459,6 +498,10 @@ def test_linear_small_shapes_both_dtypes(M, Nn, K, act):
             assert_close_fp32(out, ref)
         else:
             assert_close_bf16(out, ref, 5e-3, max_tol=1e-2)
+            # the automatic choice is a kernel of 64 x 64 tiles here; the tile variants give the same bits
+            for variant in (1, 2, 3, 4):
+                forced = host(B.dit_linear(dev(a, td), dev(w, td), dev(bias), act, kernel_path=variant << 8))
+                assert np.array_equal(forced, out), variant
 
 
 @pytest.mark.parametrize("variant", [0, 3, 4])

@@ -80,11 +80,12 @@ def test_attention_bf16_around_the_one_launch_limit_and_with_few_items(N):
     out = B.attn3d(q, k, v, 0.125)
     assert torch.equal(B.attn3d(q[1:], k[1:], v[1:], 0.125)[0], out[1])
     rows = torch.tensor([0, 1, N // 2, N - 1])
-    for h in range(4):
-        kd, vd = k[0, :, h].double().cpu(), v[0, :, h].double().cpu()
-        ref = (torch.softmax(q[0, rows, h].double().cpu() @ kd.t() * 0.125, -1) @ vd).numpy()
-        # probabilities and result in bf16: two roundings of 2^-9
-        assert rel(ref, out[0, rows, h].double().cpu().numpy()) <= 2 * 2.0 ** -8
+    for b in range(2):
+        for h in range(4):
+            kd, vd = k[b, :, h].double().cpu(), v[b, :, h].double().cpu()
+            ref = (torch.softmax(q[b, rows, h].double().cpu() @ kd.t() * 0.125, -1) @ vd).numpy()
+            # probabilities and result in bf16: two roundings of 2^-9
+            assert rel(ref, out[b, rows, h].double().cpu().numpy()) <= 2 * 2.0 ** -9
 
 
 @pytest.mark.parametrize("text", [0, 6, 70])
@@ -149,6 +150,30 @@ def test_modulation_off_the_matrix_path_is_one_launch_per_32_layers():
     assert nodes(72) == nodes(64) + 1
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_modulation_of_many_layers_equals_that_of_one(dtype):
+    """Beyond 200000 rows of modulation matrices (9 layers of width 1920) a wave takes 32 rows at a time instead of 16, with
+    the same values: of 9 layers all but one add nothing, wherever that one stands the network equals it alone bit for bit."""
+    one = I.CONFIGS["reduced"].with_(layers=1, frames=1, height=2, width=6, text_tokens=8, dtype=dtype)
+    nine = one.with_(layers=9)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    td = B.torch_dtype(dtype)
+    rand = [torch.randn(shape, generator=g, device=DEV).mul_(shape[1] ** -0.5).to(td) if len(shape) == 2
+            else torch.randn(shape, generator=g, device=DEV) for _, shape in I.weight_shapes(one)]
+    head, layer, tail = rand[:6], rand[6:16], rand[16:]
+    # order of a layer: W_mod b_mod W_qkv b_qkv W_o b_o W_1 b_1 W_2 b_2; without output projections it adds nothing
+    idle = [torch.zeros_like(t) if i in (4, 5, 8, 9) else t for i, t in enumerate(layer)]
+    x = torch.randn(3, *one.latent_shape, generator=g, device=DEV)
+    ctx = torch.randn(3, 8, one.hidden, generator=g, device=DEV).to(td)
+    t = [900, 400, 20]
+    ref = B.dit_forward(B.dit_create(one, rand), x, ctx, t).clone()
+    assert torch.isfinite(ref).all()
+    for at in (0, 4, 8):
+        w = head + [t for l in range(9) for t in (layer if l == at else idle)] + tail
+        assert torch.equal(B.dit_forward(B.dit_create(nine, w), x, ctx, t), ref), at
+
+
 @pytest.mark.parametrize("Dt", [64, 72, 1024])
 def test_modulation_widths_on_and_off_the_matrix_path(Dt):
     """time_embed_dim a multiple of 64 up to 1000 takes the matrix kernel, others vector products."""
@@ -178,14 +203,15 @@ def test_update_and_rel_mae_on_one_and_two_workgroups(n):
     assert torch.isnan(B.rel_mae(torch.zeros(n, device=DEV), torch.zeros(n, device=DEV))[2])
 
 
-@pytest.mark.parametrize("rows,cols", [(1, 3), (6, 8), (12, 20), (18, 28), (24, 32), (30, 43), (36, 43), (40, 51), (48, 54)])
-@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+BATCH_GRIDS = [(1, 3), (6, 8), (12, 20), (18, 28), (24, 32), (30, 43), (36, 43), (40, 51), (48, 54)]
+
+
+@pytest.mark.parametrize("dtype,rows,cols", [("bf16", *g) for g in BATCH_GRIDS] + [("f32", *g) for g in BATCH_GRIDS[:5]])
 def test_forward_of_a_batch_equals_single_calls_whatever_kernels_the_batch_takes(dtype, rows, cols):
     """One block of width 1920.  What runs a projection or a LayerNorm depends on the rows of the whole batch (K pieces in
     workgroups of their own or in registers, 64- or 128-wide tiles, a row per workgroup or per wave), its values do not:
-    samples of 11 to 2600 tokens, batches of 1, 2, 5 and 16, bit for bit."""
-    if dtype == "f32" and rows > 18:
-        pytest.skip("one kernel for every fp32 size")
+    samples of 11 to 2600 tokens (fp32, one kernel
+    for every size: to 776), batches of 1, 2, 5 and 16, bit for bit."""
     cfg = I.CONFIGS["reduced"].with_(layers=1, frames=1, height=2 * rows, width=2 * cols, text_tokens=8, dtype=dtype)
     g = torch.Generator(device=DEV)
     g.manual_seed(rows * cols)
