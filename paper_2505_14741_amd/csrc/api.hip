@@ -316,7 +316,7 @@ int dit_create(const dit_config* cfg, const void* const* weights, int n_weights,
     if (c.in_channels < 1 || c.patch < 1 || c.frames < 1 || c.height < 1 || c.width < 1) return PS_ERR_SHAPE;
     if (c.height % c.patch || c.width % c.patch) return PS_ERR_SHAPE;
     if (c.text_tokens < 0 || c.time_embed_dim < 1) return PS_ERR_SHAPE;
-    // the patch-embedding kernel stages 16 patch vectors in LDS (64 bytes per patch value, 64 KB at most)
+    // the documented limit of the interface (no kernel depends on it: patch vectors are staged 64 values at a time)
     if ((long)c.in_channels * c.patch * c.patch > 1024) return PS_ERR_SHAPE;
     if (!(c.ln_eps > 0.f) || !(c.rope_theta > 1.f)) return PS_ERR_SHAPE;
     if ((long)c.in_channels * c.frames * c.height * c.width % 4 != 0) return PS_ERR_SHAPE;

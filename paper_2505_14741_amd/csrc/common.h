@@ -56,11 +56,11 @@ struct Epilogue {
     int rope_F, rope_Hp, rope_Wp;
     int head_dim;
     float q_scale;            // factor applied to the q columns (col < D) after the rotation
-    // EPI_UNPATCHIFY (bf16 MFMA kernel only): columns are (c, dy, dx) of a video token's patch; rows of text
+    // EPI_UNPATCHIFY (matrix kernels only): columns are (c, dy, dx) of a video token's patch; rows of text
     // tokens are dropped; resid is the fp32 output latent [B, C, F, H, W]
     PatchGeom pg;
-    // optional scratch for the bf16 MFMA kernel: with it, the output tiles of the last, partial round of
-    // workgroups are split along K and their fp32 partial sums pass through this buffer
+    // optional scratch for the matrix kernels: with it, output tiles that do not fill the chip (the last, partial round of
+    // workgroups where K is long, all tiles of few tokens) are summed in K pieces whose fp32 sums may pass through this buffer
     float* split_ws;
     size_t split_ws_bytes;
 };
@@ -68,8 +68,8 @@ struct Epilogue {
 // Kernel path: a per-call selector handed down from the entry points (a field of the `dit` handle, an argument of
 // the stand-alone calls); nothing process-wide selects kernels.  Low byte = mode: 0 the fastest kernel for each
 // shape, 1 the generic fp32-FMA kernels, 2 bf16 attention without the key split of its last partial round,
-// 3 bf16 head-dim-64 attention always through the kernel that tracks a softmax reference, 4 projections whose
-// last partial round is not divided along K.  Bits 8-11: tile variant of the bf16 MFMA GEMM (0 automatic,
+// 3 bf16 head-dim-64 attention always through the kernel that tracks a softmax reference, 4 projections not
+// divided along K.  Bits 8-11: tile variant of the bf16 MFMA GEMM (0 automatic,
 // 1: 256x256, 2: 128x128, 3: 192x256, 4: 192x128).
 constexpr int PS_PATH_MAX_VARIANT = 4;
 inline bool kernel_path_valid(int path) {

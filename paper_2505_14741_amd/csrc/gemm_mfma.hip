@@ -702,8 +702,9 @@ static int best_variant(int samples, int tokens, int Nn, int K, bool may_split) 
 }
 
 // The variant for tiles that add up their own `pieces`: 128 x 128 in registers, or 192 x 256, whose sums wait in memory (a
-// fifth of a round per piece), where that saves a round.  4 samples of 1442 tokens, 1920 x 7680 in 2 pieces: 720 tiles, two
-// rounds, 204 us; 256, one round, 160.  16 of 256 tokens in 4 pieces: 480 and 256 tiles, one round each, 117 and 229.
+// fifth of a round per piece), where that saves a round.  4 samples of 1442 tokens, 1920 x 7680 in 2 pieces: 720 tiles are
+// two rounds, 256 one (forward of 4 layers 2893 against 2764 us).  16 of 256 tokens in 4 pieces: 480 and 256 tiles, one
+// round each (1900 against 2347).
 static int inreg_variant(int samples, int tokens, int Nn, int pieces) {
     const int cus = gemm_compute_units();
     auto estimate = [&](const TileVariant& t) {

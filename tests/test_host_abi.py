@@ -140,7 +140,7 @@ def test_kernel_path_is_a_property_of_the_handle():
 
 def test_dit_create_rejects_shapes_no_kernel_serves():
     cfg = I.CONFIGS["tiny"]
-    assert _create(_cfg_struct(cfg, in_channels=300))[0] == -2                    # 1200 patch values: LDS staging
+    assert _create(_cfg_struct(cfg, in_channels=300))[0] == -2                    # 1200 patch values: the documented limit
     assert _create(_cfg_struct(cfg, in_channels=256))[0] == 0
     # bf16: a sample's widest activation must stay below 2^31 elements (32-bit offsets in the MFMA projections)
     big = dict(hidden=2048, heads=32, head_dim=64, mlp_ratio=8, frames=33, height=128, width=128, patch=2)
