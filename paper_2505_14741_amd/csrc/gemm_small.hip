@@ -120,8 +120,7 @@ __device__ __forceinline__ void epilogue_quad(const Epilogue& ep, T* __restrict_
 // Workgroup -> (sample, tile, K piece).  Ids that share an XCD are contiguous (see the remap in the kernel); the row
 // tiles of all samples that read one W panel come first, so the panel is fetched into that XCD's L2 once.  With more
 // than 8 row tiles the tiles go in bands of 8 rows instead.
-// pieces: workgroups along K per tile, nsplit or 1.
-struct SmallGrid { int batch, tiles_m, tiles_n, nsplit, pieces; };
+struct SmallGrid { int batch, tiles_m, tiles_n, nsplit; };
 
 // INREG: one workgroup per tile walks all of K and adds the nsplit pieces up in registers, in the order and with the
 // roundings of the reduction.
@@ -130,7 +129,7 @@ __global__ void __launch_bounds__(256, NST == 3 ? 3 : NST == 4 ? 2 : 1)
 gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict__ C, int Nn, int K, SmallGrid g,
                   Epilogue ep) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
-    const int tokens = ep.geom.tokens;
+    const int tokens = ep.geom.tokens, pieces = INREG ? 1 : g.nsplit;    // workgroups along K per tile
     int id, sample, piece, m0, n0;
     {
         const int total = gridDim.x, per = total / 8, rem = total % 8, x = blockIdx.x % 8;
@@ -139,18 +138,18 @@ gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restric
     if (g.tiles_m <= 8) {
         m0 = id % g.tiles_m * TILE; id /= g.tiles_m;
         sample = id % g.batch;      id /= g.batch;
-        piece = id % g.pieces;      n0 = id / g.pieces * TILE;
+        piece = id % pieces;      n0 = id / pieces * TILE;
     } else {
         const int tiles = g.tiles_m * g.tiles_n, tile = id % tiles;
         id /= tiles;
-        piece = id % g.pieces; sample = id / g.pieces;
+        piece = id % pieces; sample = id / pieces;
         const int band = tile / (8 * g.tiles_n), in_band = tile % (8 * g.tiles_n);
         const int rows_here = min(8, g.tiles_m - band * 8);
         m0 = (band * 8 + in_band % rows_here) * TILE;
         n0 = in_band / rows_here * TILE;
     }
     const int nk = K / (ROWB / (int)sizeof(T));
-    const int k0 = nk * piece / g.pieces, nkt = nk * (piece + 1) / g.pieces - k0;
+    const int k0 = nk * piece / pieces, nkt = nk * (piece + 1) / pieces - k0;
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, kgrp = lane >> 4;
@@ -206,7 +205,7 @@ gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restric
     // the epilogue's operands are requested now, with the first stages, and not when the sums are done
     // (rows and columns past the edge: clamped, not stored)
     EpiOperands eo[2][2];
-    if (g.pieces == 1) {
+    if (pieces == 1) {
 #pragma unroll
         for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -276,7 +275,7 @@ gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restric
             const int col = n0 + wn * 32 + y * 16 + kgrp * 4;
             if (col >= Nn) continue;
             const f32x4_t sum = INREG ? total[y][x] : piece_sum(y, x);
-            if (g.pieces > 1)                            // [piece][row][column]
+            if (pieces > 1)                              // [piece][row][column]
                 *reinterpret_cast<f32x4_t*>(ep.split_ws + (((long)piece * g.batch + sample) * tokens + n) * Nn + col) = sum;
             else
                 epilogue_quad<KIND, T>(ep, C, Nn, sample, n, col, sum, eo[x][y]);
@@ -303,8 +302,9 @@ gemm_small_reduce_kernel(T* __restrict__ C, int Nn, SmallGrid g, Epilogue ep) {
 template <typename T, int KIND>
 static hipError_t launch_small_kind(const T* A, const T* W, T* C, int batch, int tokens, int Nn, int K, const FewPlan& p,
                                     bool inreg, const Epilogue& ep, int* deferred, hipStream_t st) {
-    const SmallGrid g{batch, p.tiles_m, p.tiles_n, p.nsplit, inreg ? 1 : p.nsplit};
-    const long blocks = (long)batch * p.tiles_m * p.tiles_n * g.pieces;
+    const SmallGrid g{batch, p.tiles_m, p.tiles_n, p.nsplit};
+    const int pieces = inreg ? 1 : p.nsplit;
+    const long blocks = (long)batch * p.tiles_m * p.tiles_n * pieces;
     if (blocks >= (1L << 31)) return hipErrorInvalidValue;
     auto go = [&](auto kernel) { kernel<<<(int)blocks, 256, 0, st>>>(A, W, C, Nn, K, g, ep); };
     // as deep a ring as lets every workgroup start at once (with two per CU, 513 to 768 are a second, nearly empty round:
@@ -318,7 +318,7 @@ static hipError_t launch_small_kind(const T* A, const T* W, T* C, int batch, int
     };
     if (inreg && p.nsplit > 1) ring(std::true_type{}); else ring(std::false_type{});
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || g.pieces == 1) return e;
+    if (e != hipSuccess || pieces == 1) return e;
     if (deferred) { *deferred = p.nsplit; return e; }
     const long quads = (long)batch * tokens * (Nn / 4);
     gemm_small_reduce_kernel<T, KIND><<<(int)((quads + 255) / 256), 256, 0, st>>>(C, Nn, g, ep);
