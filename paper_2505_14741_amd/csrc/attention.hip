@@ -1072,18 +1072,6 @@ attn_sp_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const
 // Split plan for the bf16 head-dim-64 kernels (see AttnGrid): per sample, how many work items run whole and how
 // many ways the rest is split along the keys.
 struct AttnPlan { int qblocks, items_ps, full_ps, tail_ps, nsplit, bq; };
-static int compute_units() {
-    // per device, asked once (a constant of the device, not a setting)
-    static int cached[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    if (cached[dev] == 0) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
-        cached[dev] = cus;
-    }
-    return cached[dev];
-}
 // Up to this many keys the launches cost more than the faster loop gains, and the reference-tracking kernel does every
 // head alone: one launch instead of two (three outside a network).  30 heads: 112 keys 7.6 us against 10.5, 512 keys 16.0
 // against 18.2; at 1500 keys 36.5 against 36.1.

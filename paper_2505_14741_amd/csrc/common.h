@@ -76,6 +76,9 @@ inline bool kernel_path_valid(int path) {
     return path >= 0 && (path & ~0xfff) == 0 && (path & 0xff) <= 4 && ((path >> 8) & 0xf) <= PS_PATH_MAX_VARIANT;
 }
 
+// compute units of the current device
+int compute_units();
+
 // The M rows of a projection are `batch` samples of `tokens` rows each; every sample is tiled on its own, so a
 // sample's result is bit-identical whatever batch it is computed in.
 // scratch that lets launch_gemm split its last partial round along K (0: the shape does not profit)

@@ -1,0 +1,120 @@
+// Epilogues of the few-token kernels: a lane holds 4 adjacent output columns of one row.
+#pragma once
+#include "common.h"
+
+namespace ps {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+
+__device__ __forceinline__ float gelu_of(float x, float) { return gelu_tanh_f(x); }
+// where the result is rounded to bf16: x * sigmoid(2u), u = sqrt(2/pi)(x + 0.044715 x^3)
+__device__ __forceinline__ float gelu_of(float x, bf16_t) {
+    const float c0 = -2.0f * 0.7978845608028654f * 1.4426950408889634f;
+    const float t = x * (c0 + c0 * 0.044715f * x * x);
+    return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
+}
+
+__device__ __forceinline__ void store_quad(float* p, f32x4_t v) { *reinterpret_cast<f32x4_t*>(p) = v; }
+__device__ __forceinline__ void store_quad(bf16_t* p, f32x4_t v) {
+    *reinterpret_cast<bf16x4_t*>(p) = __builtin_convertvector(v, bf16x4_t);
+}
+
+// A row of the batch's rows: sample and token, and for the rotation the position on the three axes.
+struct EpiRow { int sample, n, pos[3]; };
+template <int KIND>
+__device__ __forceinline__ EpiRow epilogue_row(const Epilogue& ep, int row) {
+    EpiRow r;
+    r.sample = row / ep.geom.tokens;
+    r.n = row - r.sample * ep.geom.tokens;
+    if constexpr (KIND == EPI_QKV_ROPE) {
+        const int nv = r.n - ep.geom.text_tokens, q1 = nv / ep.rope_Wp, q2 = q1 / ep.rope_Hp;
+        r.pos[0] = q2; r.pos[1] = q1 - q2 * ep.rope_Hp; r.pos[2] = nv - q1 * ep.rope_Wp;
+    }
+    return r;
+}
+
+// What the epilogue of 4 adjacent columns of a row reads besides the sum; aux: the residual, or (cos, sin) of both pairs.
+struct EpiOperands { f32x4_t bias, gate, aux; };
+template <int KIND>
+__device__ __forceinline__ EpiOperands epilogue_operands(const Epilogue& ep, int Nn, const EpiRow& r, int row, int col) {
+    EpiOperands o;
+    o.bias = *reinterpret_cast<const f32x4_t*>(ep.bias + col);
+    o.gate = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    o.aux = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if constexpr (KIND == EPI_GATE_RESIDUAL) {
+        o.gate = *reinterpret_cast<const f32x4_t*>(ep.mod_layer + r.sample * ep.mod_batch_stride +
+                                                   (long)(ep.gate_chunk + (r.n < ep.geom.text_tokens ? 6 : 0)) * ep.D + col);
+        o.aux = *reinterpret_cast<const f32x4_t*>(ep.resid + (long)row * Nn + col);
+    }
+    if constexpr (KIND == EPI_QKV_ROPE) {
+        if (r.n >= ep.geom.text_tokens && col < 2 * ep.D) {
+            const int pr = (col % ep.head_dim) >> 1;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const RopeAxis ra = rope_axis_of(pr + c, ep.head_dim, ep.rope_F, ep.rope_Hp);
+                const f32x2_t cs = *reinterpret_cast<const f32x2_t*>(
+                    ep.rope_cs + ra.base + (ra.axis == 0 ? r.pos[0] : ra.axis == 1 ? r.pos[1] : r.pos[2]) * ra.stride);
+                o.aux[2 * c] = cs[0];
+                o.aux[2 * c + 1] = cs[1];
+            }
+        }
+    }
+    return o;
+}
+
+// x is the finished sum.
+template <int KIND, typename T>
+__device__ __forceinline__ void epilogue_quad(const Epilogue& ep, T* __restrict__ C, int Nn, const EpiRow& r, int row, int col,
+                                              f32x4_t x, const EpiOperands& o) {
+    x += o.bias;
+    if constexpr (KIND == EPI_BIAS_GELU) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[c] = gelu_of(x[c], T{});
+    }
+    if constexpr (KIND == EPI_GATE_RESIDUAL) {
+        *reinterpret_cast<f32x4_t*>(ep.resid + (long)row * Nn + col) = o.aux + o.gate * x;
+        return;
+    }
+    if constexpr (KIND == EPI_UNPATCHIFY) {
+        const int text = ep.geom.text_tokens;
+        if (r.n < text) return;
+        const PatchGeom& g = ep.pg;
+        const int Hp = g.H / g.patch, Wp = g.W / g.patch, nv = r.n - text;
+        const int pj = nv % Wp, pi = (nv / Wp) % Hp, f = nv / (Wp * Hp);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int q = col + c;
+            const int dx = q % g.patch, dy = (q / g.patch) % g.patch, ch = q / (g.patch * g.patch);
+            ep.resid[((((long)r.sample * g.C + ch) * g.F + f) * g.H + (pi * g.patch + dy)) * g.W + (pj * g.patch + dx)] = x[c];
+        }
+        return;
+    }
+    if constexpr (KIND == EPI_QKV_ROPE) {
+        const f32x4_t t = o.aux;
+        if (r.n >= ep.geom.text_tokens && col < 2 * ep.D)
+            x = f32x4_t{x[0] * t[0] - x[1] * t[1], x[1] * t[0] + x[0] * t[1], x[2] * t[2] - x[3] * t[3], x[3] * t[2] + x[2] * t[3]};
+        if (col < ep.D) x *= ep.q_scale;
+    }
+    store_quad(C + (long)row * Nn + col, x);
+}
+
+// Adds the K pieces ([piece][row][column]) in order and applies the epilogue: one thread per 4 adjacent columns.
+template <typename T, int KIND>
+__global__ void __launch_bounds__(256)
+gemm_small_reduce_kernel(T* __restrict__ C, int Nn, long rows, int nsplit, Epilogue ep) {
+    const int quads = Nn / 4;
+    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= rows * quads) return;
+    const long row = idx / quads;
+    const int col = (int)(idx - row * quads) * 4;
+    f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int p = 0; p < nsplit; ++p) s += *reinterpret_cast<const f32x4_t*>(ep.split_ws + (p * rows + row) * Nn + col);
+    const EpiRow r = epilogue_row<KIND>(ep, (int)row);
+    epilogue_quad<KIND, T>(ep, C, Nn, r, (int)row, col, s, epilogue_operands<KIND>(ep, Nn, r, (int)row, col));
+}
+
+}  // namespace ps

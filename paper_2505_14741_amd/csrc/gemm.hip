@@ -7,6 +7,19 @@
 
 namespace ps {
 
+int compute_units() {
+    // per device, asked once (a constant of the device, not a setting)
+    static int cached[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    if (cached[dev] == 0) {
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
+        cached[dev] = cus;
+    }
+    return cached[dev];
+}
+
 // 64x64 output tile, 16-deep K slices, 256 threads, 4x4 outputs per thread.
 template <typename T, int KIND>
 __global__ void __launch_bounds__(256)
@@ -79,8 +92,8 @@ bool gemm_mfma_supported(int tokens, int Nn, int K);
 hipError_t launch_gemm_mfma(const bf16_t* A, const bf16_t* W, bf16_t* C, int batch, int tokens, int Nn, int K,
                             const Epilogue& ep, int path, int pieces, hipStream_t st);
 size_t gemm_tiles_workspace_bytes(int batch, int tokens, int Nn, int K, int path, int pieces);
-hipError_t launch_gemm_small(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K,
-                             const Epilogue& ep, const FewPlan& plan, bool inreg, int* deferred, hipStream_t st);
+hipError_t launch_gemm_few(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K, int tile,
+                           int nsplit, bool inreg, const Epilogue& ep, int* deferred, hipStream_t st);
 
 static bool uses_tiles(int dtype, int tokens, int Nn, int K, int path) {
     return dtype == PS_BF16 && (path & 0xff) != 1 && gemm_mfma_supported(tokens, Nn, K);
@@ -110,9 +123,13 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, void* C, int bat
     if (few.use && !forced_tiles(dtype, path)) {
         if (epi.split_ws == nullptr || epi.split_ws_bytes < few_workspace_bytes(bf16, few, batch, tokens, Nn, K)) few.nsplit = 1;
         const FewHow how = few_how(bf16, few, batch, K);
-        if (how != FEW_TILES)
-            return launch_gemm_small(dtype, A, W, C, batch, tokens, Nn, K, epi, few, how == FEW_INREG, deferred, st);
-        return launch_gemm_mfma((const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C, batch, tokens, Nn, K, epi, path, few.nsplit, st);
+        if (how == FEW_TILES && few.nsplit == 1)         // (whole sums: the fastest tile of either kernel)
+            return launch_gemm_mfma((const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C, batch, tokens, Nn, K, epi, path, 1, st);
+        const bool apart = how == FEW_PIECES;
+        const int tile = bf16 ? best_tile(FEW_64x64, FEW_TILE_KINDS - 1, (long)batch * tokens, Nn, K, apart ? few.nsplit : 1,
+                                          epi.kind == EPI_GATE_RESIDUAL && !apart, compute_units())
+                              : FEW_64x64;
+        return launch_gemm_few(dtype, A, W, C, batch, tokens, Nn, K, tile, few.nsplit, !apart, epi, deferred, st);
     }
     const bool mfma = uses_tiles(dtype, tokens, Nn, K, path);
     if (epi.kind == EPI_UNPATCHIFY && !mfma) return hipErrorInvalidValue;

@@ -15,35 +15,85 @@ constexpr MergeRow merge_row(int block, int thread, int bq) {
     return MergeRow{rowid / bq, rowid % bq, thread & 15};
 }
 
-// ---- projections of few tokens and of fp32 operands (gemm_small.hip): C[tokens, Nn] = A[tokens, K] * W[Nn, K]^T per sample
-constexpr int FEW_TILE = 64;                             // output rows and columns of a workgroup
+// ---- projections: C[rows, Nn] = A[rows, K] * W[Nn, K]^T, rows = all samples of the batch
+// Output tiles of the matrix kernels: gemm_few.hip (any K pieces; fp32 and bf16) and gemm_mfma.hip (bf16).
+enum TileId { FEW_64x64, FEW_128x64, FEW_128x128, FEW_192x128, FEW_256x128, FEW_192x192, FEW_TILE_KINDS,
+              WIDE_256x256 = FEW_TILE_KINDS, WIDE_128x128, WIDE_192x256, WIDE_192x128, TILE_KINDS };
+// Measured us of a round of workgroups, one tile each: fixed + stages of 64 k * stage.  per_cu = 2: two workgroups share a
+// CU; `half`: a round that leaves at most one to each.  (bf16, operands that change from call to call, 32 to 9000 rows x
+// 1920 to 7680 columns x K = 1920 and 7680.)
+struct Tile { int bm, bn, per_cu; float half_fixed, half_stage, fixed, stage; };
+constexpr Tile kTiles[TILE_KINDS] = {
+    {64, 64, 2, 3.0f, 0.235f, 4.5f, 0.40f},              // 8 waves of 16 x 32
+    {128, 64, 1, 0.f, 0.f, 4.0f, 0.30f},                 // 8 waves of 32 x 32
+    {128, 128, 1, 0.f, 0.f, 6.0f, 0.47f},                // 8 waves of 32 x 64
+    {192, 128, 1, 0.f, 0.f, 7.0f, 0.60f},                // 8 waves of 48 x 64
+    {256, 128, 1, 0.f, 0.f, 8.7f, 0.76f},                // 8 waves of 64 x 64
+    {192, 192, 1, 0.f, 0.f, 9.0f, 0.90f},                // 8 waves of 48 x 96
+    {256, 256, 1, 0.f, 0.f, 7.3f, 1.34f},                // gemm_mfma.hip: 8 waves of 128 x 64
+    {128, 128, 2, 2.0f, 0.80f, 4.0f, 0.90f},             // 4 waves of 64 x 64
+    {192, 256, 1, 0.f, 0.f, 8.7f, 1.13f},                // 8 waves of 96 x 64
+    {192, 128, 2, 2.0f, 0.88f, 4.6f, 1.30f},             // 4 waves of 96 x 64
+};
+constexpr long tile_count(int id, long rows, int Nn) {
+    return (rows + kTiles[id].bm - 1) / kTiles[id].bm * ((Nn + kTiles[id].bn - 1) / kTiles[id].bn);
+}
+// Estimated us of `wgs` workgroups of `stages` stages each on `cus` compute units (without what launching takes).  gated: the
+// epilogue reads and writes an fp32 residual, 0.23 ns per output of a CU (17776 rows x 1920: 184, 164 and 168 us on the tiles
+// of 256 x 256, 192 x 256 and 192 x 128, with a plain epilogue 0.12 to 0.14 ms).
+constexpr float tile_time(int id, long wgs, float stages, bool gated, int cus) {
+    const Tile& t = kTiles[id];
+    const long slots = (long)cus * t.per_cu, tail = wgs % slots;
+    const float epi = gated ? 2.3e-4f * t.bm * t.bn : 0.f;
+    // (gemm_few.hip over more than two rounds: the chip at its power limit, and its smaller wave tiles read more LDS per
+    // product: 41728 rows, 1920 x 7680 on 256 x 128 tiles 1323 us, on 192 x 256 of gemm_mfma.hip 1229)
+    const float many = id < FEW_TILE_KINDS && wgs > 2 * slots ? 1.15f : 1.f;
+    const float full = many * (t.fixed + stages * t.stage) + epi * t.per_cu, half = t.half_fixed + stages * t.half_stage + epi;
+    return (float)(wgs / slots) * full + (tail == 0 ? 0.f : t.per_cu == 2 && tail <= cus ? half : full);
+}
+// The bf16 tile with the least estimated time: `pieces` workgroups per tile along K; [first, last]: the kinds to choose from.
+// At the sizes above it misses the fastest one by 1 % on average and 6 % at most.
+constexpr int best_tile(int first, int last, long rows, int Nn, int K, int pieces, bool gated, int cus) {
+    int best = first;
+    float least = 0.f;
+    for (int id = first; id <= last; ++id) {
+        const float t = tile_time(id, tile_count(id, rows, Nn) * pieces, (float)(K / 64) / pieces, gated, cus);
+        if (id == first || t < least) { best = id; least = t; }
+    }
+    return best;
+}
+
+// ---- projections of few tokens and of fp32 operands (gemm_few.hip)
 constexpr int FEW_ROW_BYTES = 128;                       // bytes of an operand row per stage: 64 bf16 or 32 fp32
 
-// A sample's plan: a function of the sample's shape alone, so that its result does not depend on the batch.
-//   bf16: up to 640 tiles of 64 x 64; beyond that the 128-wide tiles of the other kernel win by reading less per output.
-//     Weights cold / in cache, against 128 x 128 tiles: 5760 x 1920 weights at 440 tokens (630 tiles) 27.4 / 20.7 against
-//     29.9 / 22.7 us; 7680 x 1920 at 300 (600) 27.5 / 20.5 against 29.5 / 22.1; 1920 x 1920 at 1340 (630) 21.2 / 21.1
-//     against 23.0 / 23.0, at 1500 (720) 26.4 against 24.3 cold.
-//     K >= 4096: up to 512.  Beyond, no tile has a second K piece here, while 128 x 128 tiles are cut: 1920 x 7680 at 1100
-//     tokens (540 tiles) 78.9 / 76.8 whole here, 58.5 / 54.6 in 3 pieces there; at 1000 (480) 61.1 / 49.0 here.
+// A sample's plan: a function of the sample's shape alone, so that its result does not depend on the batch.  tiles_m x
+// tiles_n tiles of 64 x 64.
+//   bf16: up to 640 of them, 512 with K >= 4096, where a sample is cut into K pieces that wider tiles would also need.
 //   fp32: every size (the matrix instructions bind, 32 cycles per 2048 operations, not the LDS reads).
-// K pieces: as many as bring the workgroups to 256 (one per compute unit) where K is short, 512 where it is long (60
-// stages and more), 8 at most (fp32 16) and each at least 5 stages.  1920 x 1920 bf16 at 112 tokens (60 tiles): 1 piece 14.2 us,
-// 4 pieces 11.5, 6 pieces 12.2 with the reduction launch; 1920 x 7680: 42.8, 19.0 (4 pieces), 18.5 (8).
+// K pieces, short K: as many as bring the workgroups to 256 (one per compute unit), 8 at most (fp32 16) and each at least 5
+// stages.  1920 x 1920 bf16 at 112 tokens (60 tiles), without / with the launch that adds them: 1 piece 10.3 us, 4 pieces
+// 5.8 / 9.7, 8 pieces 6.2 / 11.1.
+// Long K (60 stages and more), fp32 and up to 128 tokens: to 512.  1920 x 7680 bf16 at 112 tokens: 8 pieces (128 x 64
+// tiles) 15.2, 4 pieces 16.1, 3 pieces 18.9.  More tokens: as many as bring 192 x 128 tiles to 256, 4 at most, up to 128
+// tiles of 128 x 128 (1024 tokens), beyond which those run whole.  us in 2 / 3 / 4 / 8 pieces, the fastest tile of each: 224
+// tokens 23.7 / 23.7 / 20.3 / 20.7, 448 29.6 / 31.2 / 27.4 / 30.3, 768 44.2 / 41.2 / 36.2 / -, 900 40.8 / 40.6 / 40.9 / -.
 // path: kernel path (low byte 1: generic kernels, 4: no K pieces).
 struct FewPlan { bool use; int tiles_m, tiles_n, nsplit; };
 constexpr FewPlan few_plan(bool bf16, int tokens, int Nn, int K, int path) {
     FewPlan p{false, 0, 0, 1};
     const long row_bytes = (long)K * (bf16 ? 2 : 4);
     if ((path & 0xff) == 1 || row_bytes % FEW_ROW_BYTES != 0 || Nn % 4 != 0 || tokens < 1) return p;
-    p.tiles_m = (tokens + FEW_TILE - 1) / FEW_TILE;
-    p.tiles_n = (Nn + FEW_TILE - 1) / FEW_TILE;
+    p.tiles_m = (tokens + 63) / 64;
+    p.tiles_n = (Nn + 63) / 64;
     const long tiles = (long)p.tiles_m * p.tiles_n, nk = row_bytes / FEW_ROW_BYTES;
     if (bf16 && (Nn < 64 || tiles > (K >= 4096 ? 512 : 640))) return p;
     p.use = true;
     if ((path & 0xff) == 4) return p;
-    const long most = bf16 ? 8 : 16;
-    long ns = (nk >= 60 ? 512 : 256) / tiles;
+    long most = bf16 ? 8 : 16, ns = (nk >= 60 ? 512 : 256) / tiles;
+    if (bf16 && nk >= 60 && tokens > 128) {
+        most = 4;
+        ns = tile_count(FEW_128x128, tokens, Nn) <= 128 ? 256 / tile_count(FEW_192x128, tokens, Nn) : 1;
+    }
     ns = ns < most ? ns : most;
     ns = ns < nk / 5 ? ns : nk / 5;
     p.nsplit = ns > 1 ? (int)ns : 1;
@@ -52,17 +102,15 @@ constexpr FewPlan few_plan(bool bf16, int tokens, int Nn, int K, int path) {
 
 // What runs a batch of samples of one plan.  It counts the tiles of the whole batch; the values are the same either way (same
 // instruction, same order of k, pieces added in the same order, same epilogue).
-//   FEW_PIECES  a workgroup per 64 x 64 tile and K piece; the pieces pass through memory
-//   FEW_INREG   a workgroup per 64 x 64 tile, which adds its pieces in registers
-//   FEW_TILES   128-wide tiles of the other kernel, pieces in registers (bf16)
+//   FEW_PIECES  a workgroup per tile and K piece; the pieces pass through memory
+//   FEW_INREG   a workgroup per tile, which adds its pieces in registers
+//   FEW_TILES   the same, and where there is one piece (bf16) the tiles of gemm_mfma.hip are candidates too
 // Pieces of their own pay until the tiles alone occupy the chip.  Layer with cold weights, us, pieces apart / in registers:
 // 1920 x 1920 and the LayerNorm that adds the pieces, 112 tokens: 3 samples (180 tiles) 19.3 / 21.5, 4 (240) 23.1 / 22.0,
 // 8 (480) 37.1 / 26.3; 1920 x 7680, 4 samples (240) 42.1 / 50.2, 6 (360) 57.5 / 62.4, 8 (480) 74.1 / 62.2.  fp32 is bound by
 // the matrix instructions and takes finer pieces longer: 1920 x 7680 at 320 tokens, 4 samples (600 tiles) 358 / 393, 8 (1200)
 // 674 / 654.
-// 128-wide tiles need 512 of themselves for a round and take about as long for fewer; 64-wide ones, 0.036 us each: 5760 x
-// 1920, 112 tokens, 4 samples (720 tiles) 28.2 against 32.9, 6 (1080) 39.1 / 34.3, 16 (2880) 96.3 / 68.9.  In samples of up
-// to 64 tokens a 128-row tile is at least half empty: 16 of 32 tokens (1440) 42.4 / 56.7.
+// The tiles of gemm_mfma.hip are never the fastest up to 768 tiles of 64 x 64 (5760 x 1920, 512 rows).
 enum FewHow { FEW_PIECES, FEW_INREG, FEW_TILES };
 constexpr long few_spread_tiles(bool bf16, int K) { return !bf16 ? 640 : K >= 60 * 64 ? 384 : 256; }
 constexpr FewHow few_how(bool bf16, const FewPlan& p, int batch, int K) {

@@ -54,6 +54,25 @@ def test_linear_on_both_sides_of_the_tile_limit(N):
         assert rel(ref, B.dit_linear(a, w, bias, 0).double().cpu().numpy()) <= 2.0 ** -9
 
 
+TILE_SIZES = [(0, 300, 1908, 1920), (1, 700, 1908, 1920), (2, 1290, 1908, 1920), (3, 2500, 1908, 1920), (4, 3300, 1908, 7680),
+              (5, 4500, 1908, 7680)]
+
+
+@pytest.mark.parametrize("kind,M,Nn,K", TILE_SIZES)
+def test_every_tile_of_the_few_token_kernel_at_ragged_edges(kind, M, Nn, K):
+    """Rows and columns that end inside a tile, more row tiles than a band of 8; whole sums, so a forced tile of the other
+    kernel gives the same bits.  One rounding of the result to bf16."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M)
+    a = torch.randn(M, K, generator=g, device=DEV).bfloat16()
+    w = (torch.randn(Nn, K, generator=g, device=DEV) / math.sqrt(K)).bfloat16()
+    bias = torch.randn(Nn, generator=g, device=DEV)
+    out = B.dit_linear(a, w, bias, 0)
+    ref = a.double() @ w.double().t() + bias.double()
+    assert rel(ref.cpu().numpy(), out.double().cpu().numpy()) <= 2.0 ** -9
+    assert torch.equal(out, B.dit_linear(a, w, bias, 0, kernel_path=0x204))
+
+
 @pytest.mark.parametrize("N", [1, 15, 16, 17, 63, 64, 65, 200])
 @pytest.mark.parametrize("d", [16, 32, 64])
 def test_attention_fp32_math_ragged(N, d):

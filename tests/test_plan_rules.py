@@ -20,6 +20,10 @@ extern "C" int few(int bf16, int tokens, int n, int k, int path) {   // 0: anoth
 extern "C" int how(int bf16, int tokens, int n, int k, int batch) {
     return ps::few_how(bf16 != 0, ps::few_plan(bf16 != 0, tokens, n, k, 0), batch, k);
 }
+extern "C" int best(int first, int last, long rows, int n, int k, int pieces, int gated) {
+    return ps::best_tile(first, last, rows, n, k, pieces, gated != 0, 256);
+}
+extern "C" int kinds(int* few) { *few = ps::FEW_TILE_KINDS; return ps::TILE_KINDS; }
 extern "C" long scratch(int bf16, int tokens, int n, int k, int batch) {
     return (long)ps::few_workspace_bytes(bf16 != 0, ps::few_plan(bf16 != 0, tokens, n, k, 0), batch, tokens, n, k);
 }
@@ -89,3 +93,25 @@ def test_scratch_of_few_token_projections_serves_every_smaller_batch(rules, bf16
                 if pieces > 1 and rules.how(bf16, tokens, n, k, b) == PIECES:
                     assert size[b - 1] >= 4 * pieces * b * tokens * n
                 assert size[b - 1] <= 4 * max(pieces, 1) * tokens * n * b
+
+
+FASTEST = [  # rows, columns, K, pieces (1920 columns: with the gated residual update): kinds within 6 % of the fastest measured one (0-5: gemm_few.hip, 6-9: gemm_mfma.hip)
+    (112, 5760, 1920, 1, [0]), (224, 7680, 1920, 1, [1]), (448, 5760, 1920, 1, [2]), (640, 7680, 1920, 1, [3]),
+    (1306, 5760, 1920, 1, [7]), (2048, 5760, 1920, 1, [9, 8]), (2600, 5760, 1920, 1, [6]), (4516, 7680, 1920, 1, [9, 8]),
+    (17776, 5760, 1920, 1, [6]), (17776, 1920, 1920, 1, [8]), (33976, 1920, 1920, 1, [9, 7]), (8326, 1920, 1920, 1, [7]),
+    (3600, 1920, 7680, 1, [4, 5]), (4516, 1920, 7680, 1, [5]),
+    (112, 1920, 7680, 8, [1]), (448, 1920, 7680, 4, [2]), (768, 1920, 7680, 4, [3])]
+
+
+@pytest.mark.parametrize("rows,n,k,pieces,kinds", FASTEST)
+def test_tiles_are_the_fastest_measured(rules, rows, n, k, pieces, kinds):
+    few = C.c_int()
+    total = rules.kinds(C.byref(few))
+    assert (few.value, total) == (6, 10)
+    assert rules.best(0, (few.value if pieces > 1 else total) - 1, C.c_long(rows), n, k, pieces, n == 1920 and pieces == 1) in kinds
+
+
+def test_sizes_of_the_tile_tests_take_the_tiles_they_name(rules):
+    from test_gpu_small_shapes import TILE_SIZES
+    for kind, rows, n, k in TILE_SIZES:
+        assert rules.best(0, 9, C.c_long(rows), n, k, 1, 0) == kind
