@@ -12,6 +12,8 @@
 //    three-stage LDS ring (global_load_lds_dwordx4), shared by the 4 waves of a
 //    workgroup, each wave owning 64 queries; V stays in its natural [key][d] layout and
 //    its transposed fragments come from ds_read_b64_tr_b16.
+//  * attn_sp_kernel: the same tiles, software-pipelined and without a softmax reference; checks its results
+//    and has what fails recomputed by the loop of attn_mfma_kernel.
 #include "common.h"
 #include "plan.h"
 #include <type_traits>
@@ -445,33 +447,22 @@ __device__ __forceinline__ float rowsum_bf16x8(bf16x8_t p, float acc) {
     return acc;
 }
 
-template <int QT, bool PRESCALED>   // QT: 32-query column tiles per wave
-__global__ void __launch_bounds__(256, 2)
-attn_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
-                 bf16_t* __restrict__ o, int seq, float scale_log2e, AttnStrides s, AttnGrid grid,
-                 float* __restrict__ part, const unsigned* __restrict__ fail, MergeTail mt) {
-    if ((int)blockIdx.x < mt.blocks) {                      // whole workgroup: before any barrier
-        attn_merge_rows(blockIdx.x, mt.part, o, seq, mt.g, mt.nitems, mt.cexp, mt.bq, s, fail);
-        return;
-    }
-    const int heads = grid.heads;
+// The loop that tracks a reference: four waves of QT 32-query column tiles each, key tiles [jt0, jt1) of one (batch, head).
+// q0: first query of this wave; lds: TRACKED_LDS bytes; store: whether this wave writes its rows (wave-uniform; every wave
+// takes part in the loads and barriers); piece >= 0: partial sums to `part`.
+constexpr int TRACKED_LDS = 3 * 2 * 64 * 128;
+template <int QT, bool PRESCALED>
+__device__ __forceinline__ void
+attn_tracked(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, bf16_t* __restrict__ o,
+             int seq, float scale_log2e, const AttnStrides& s, int b, int h, int q0, int jt0, int jt1, int piece,
+             float* __restrict__ part, bool store, unsigned char* lds) {
     constexpr int KV = 64;
     constexpr int BQ = 4 * QT * 32;
     constexpr int NST = 3;                       // LDS ring depth
     constexpr int STAGE = 2 * KV * 128;          // K tile then V tile, 128-byte rows
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
-
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform values stay in scalar registers
     const int col = lane & 31, half = lane >> 5;
-    // workgroup -> (batch*head, query block), see AttnGrid.  A whole item takes one workgroup over all keys; a
-    // piece of a split item leaves unnormalised sums, row sum and reference in `part` for the merge.
-    int bh, qb, piece, jt0, jt1;
-    attn_item(grid, blockIdx.x - mt.blocks, (seq + KV - 1) / KV, bh, qb, piece, jt0, jt1);
-    // with `fail` given, only the heads attn_sp_kernel marked are (re)computed here
-    if (fail != nullptr && fail[bh] == 0u) return;
-    const int b = bh / heads, h = bh % heads;
-    const int q0 = qb * BQ + wave * (QT * 32);
 
     const bf16_t* kbase = k + b * s.k_batch + h * s.k_head;
     const bf16_t* vbase = v + b * s.v_batch + h * s.v_head;
@@ -736,6 +727,7 @@ attn_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, con
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // drain the look-ahead loads before exit
 
+    if (!store) return;
     // finish: total row sum = both halves; O[query][d] = O^T / l
     if (piece >= 0) {
         // partial result of a key range: [piece][row in block][64 sums | row sum | reference | pad]
@@ -775,6 +767,28 @@ attn_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, con
     }
 }
 
+template <int QT, bool PRESCALED>
+__global__ void __launch_bounds__(256, 2)
+attn_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
+                 bf16_t* __restrict__ o, int seq, float scale_log2e, AttnStrides s, AttnGrid grid,
+                 float* __restrict__ part, const unsigned* __restrict__ fail, MergeTail mt) {
+    if ((int)blockIdx.x < mt.blocks) {                      // whole workgroup: before any barrier
+        attn_merge_rows(blockIdx.x, mt.part, o, seq, mt.g, mt.nitems, mt.cexp, mt.bq, s, fail);
+        return;
+    }
+    const int heads = grid.heads;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[TRACKED_LDS];
+    // workgroup -> (batch*head, query block), see AttnGrid.  A whole item takes one workgroup over all keys; a
+    // piece of a split item leaves unnormalised sums, row sum and reference in `part` for the merge.
+    int bh, qb, piece, jt0, jt1;
+    attn_item(grid, blockIdx.x - mt.blocks, (seq + 63) / 64, bh, qb, piece, jt0, jt1);
+    // with `fail` given, only the heads attn_sp_kernel marked are (re)computed here
+    if (fail != nullptr && fail[bh] == 0u) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    attn_tracked<QT, PRESCALED>(q, k, v, o, seq, scale_log2e, s, bh / heads, bh % heads, (qb * 4 + wave) * (QT * 32), jt0,
+                                   jt1, piece, part, true, lds);
+}
+
 // The kernel without a softmax reference (see SP_SUM_MIN above): p = 2^(c s), the result checks itself at the end.
 // Work split and LDS layout as in attn_mfma_kernel (4 waves x 64 queries, K/V tiles of 64 keys straight into
 // an LDS ring, two workgroups per CU), but the loop is software-pipelined over 32-key half tiles.  In
@@ -793,14 +807,24 @@ attn_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, con
 //   A: S(j,b)    | softmax(j,a)  | PV(j-1,b)
 //   B: S(j+1,a)  | softmax(j,b)  | PV(j,a)
 // so tiles j-1, j, j+1 are read during iteration j and tile j+2 is being loaded: four ring slots.
-template <bool PRESCALED>
+//
+// END says what becomes of a result that fails its check:
+//   SP_FLAGS  its (batch, head) is marked in `fail` and attn_mfma_kernel recomputes the head
+//   SP_ALONE  (whole items) the waves concerned compute their queries again, with a tracked reference, in this kernel
+//   SP_NANS   (whole items) its 32 queries are written as NaN -- a result that passes is finite -- for attn_redo_kernel
+// SP_ALONE and SP_NANS redo the same 32 queries with the same arithmetic, so which one runs changes no bit.
+// QT = 1 is for items that do not fill the chip: 128 queries per workgroup, four waves of 32 each.  30 heads, whole calls, QT =
+// 2 and three launches against QT = 1 alone: 112 keys 7.9 -> 6.4 us, 512 16.3 -> 11.5, 1000 28.5 -> 19.7, 2000 50.3 -> 42.9; 4
+// heads x 4200 keys 78 -> 59.  (8 waves of 32 queries: 23.8 and 42.8 us at 1000 and 2000 keys, 2 waves 20.1 and 62.3.)
+enum SpEnd { SP_FLAGS, SP_ALONE, SP_NANS };
+template <int QT, int END, bool PRESCALED>   // QT: 32-query column tiles per wave
 __global__ void __launch_bounds__(256, 2)
 attn_sp_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
                bf16_t* __restrict__ o, int seq, float scale_log2e, AttnStrides s, AttnGrid grid,
                float* __restrict__ part, unsigned* __restrict__ fail) {
-    constexpr int QT = 2;                        // 32-query column tiles per wave
     constexpr int KV = 64;                       // keys per tile
-    constexpr int BQ = 4 * QT * 32;              // queries per workgroup
+    constexpr int NW = 4;                        // waves
+    constexpr int BQ = NW * QT * 32;             // queries per workgroup
     constexpr int NST = 4;                       // LDS ring depth
     constexpr int STAGE = 2 * KV * 128;          // K tile then V tile, 128-byte rows
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
@@ -1017,21 +1041,24 @@ attn_sp_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const
     // the result checks itself (see SP_SUM_MIN): key sums out of range or accumulators that are not finite mark the
     // head for attn_mfma_kernel.  (A key range of a split item is held to the same limits as a whole row: a range
     // whose keys all lie far below the row's maximum sends the head to the other kernel, which costs time only.)
-    {
-        bool bad = false;
+    bool bad[QT];
 #pragma unroll
-        for (int t = 0; t < QT; ++t) {
-            const float l = rowsum_of(t);
-            float mag = 0.f;
+    for (int t = 0; t < QT; ++t) {
+        const float l = rowsum_of(t);
+        float mag = 0.f;
 #pragma unroll
-            for (int dt = 0; dt < 2; ++dt)
+        for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) mag += fabsf(oacc[dt][t][e]);
-            bad = bad || !(l >= SP_SUM_MIN && l <= SP_SUM_MAX) || !(mag < INFINITY);
-        }
-        if (__any(bad) && lane == 0) fail[bh] = 1u;
+            for (int e = 0; e < 16; ++e) mag += fabsf(oacc[dt][t][e]);
+        bad[t] = !(l >= SP_SUM_MIN && l <= SP_SUM_MAX) || !(mag < INFINITY);
     }
-    if (piece >= 0) {
+    if constexpr (END == SP_FLAGS) {
+        bool any = false;
+#pragma unroll
+        for (int t = 0; t < QT; ++t) any = any || bad[t];
+        if (__any(any) && lane == 0) fail[bh] = 1u;
+    }
+    if (END == SP_FLAGS && piece >= 0) {
         // partial result of a key range, reference 0: [piece][row in block][64 sums | row sum | 0 | pad]
         float* pp = part + (long)piece * BQ * PART_STRIDE;
 #pragma unroll
@@ -1053,6 +1080,7 @@ attn_sp_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const
     for (int t = 0; t < QT; ++t) {
         float l = rowsum_of(t);
         float inv = 1.0f / l;
+        if (END == SP_NANS && __any(bad[t])) inv = __builtin_nanf("");
         int qi = q0 + t * 32 + col;
         if (qi < seq) {
             bf16_t* op = o + b * s.o_batch + (long)qi * s.o_tok + h * s.o_head;
@@ -1067,17 +1095,38 @@ attn_sp_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const
                 }
         }
     }
+    if constexpr (END == SP_ALONE) {
+        static_assert(QT == 1, "the queries of a wave are redone together");
+        const bool redo = __any(bad[0]);
+        if (__syncthreads_or(redo))                      // (every wave has left the ring by now)
+            attn_tracked<1, PRESCALED>(q, k, v, o, seq, scale_log2e, s, b, h, q0, 0, (seq + KV - 1) / KV, -1, nullptr, redo, lds);
+    }
+}
+
+// Computes the groups of 32 queries again that attn_sp_kernel<.., SP_NANS, ..> wrote as NaN: 128 queries per workgroup.
+template <bool PRESCALED>
+__global__ void __launch_bounds__(256, 2)
+attn_redo_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
+                 bf16_t* __restrict__ o, int seq, float scale_log2e, AttnStrides s, int qblocks, int heads) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[TRACKED_LDS];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int bh = blockIdx.x / qblocks, b = bh / heads, h = bh % heads;
+    const int q0 = (blockIdx.x % qblocks * 4 + wave) * 32;
+    bool redo = false;
+    if (q0 < seq) redo = !(fabsf(to_f32(o[b * s.o_batch + (long)q0 * s.o_tok + h * s.o_head])) <= __builtin_inff());
+    if (__syncthreads_or(redo))
+        attn_tracked<1, PRESCALED>(q, k, v, o, seq, scale_log2e, s, b, h, q0, 0, (seq + 63) / 64, -1, nullptr, redo, lds);
 }
 
 // Split plan for the bf16 head-dim-64 kernels (see AttnGrid): per sample, how many work items run whole and how
 // many ways the rest is split along the keys.
 struct AttnPlan { int qblocks, items_ps, full_ps, tail_ps, nsplit, bq; };
-// Up to this many keys the launches cost more than the faster loop gains, and the reference-tracking kernel does every
-// head alone: one launch instead of two (three outside a network).  30 heads: 112 keys 7.6 us against 10.5, 512 keys 16.0
-// against 18.2; at 1500 keys 36.5 against 36.1.
+// Where the items of one sample fill the chip (256 heads and more) and up to this many keys, the second launch costs more
+// than the faster loop gains, and the reference-tracking kernel does every head alone.
 static constexpr int TRACKED_ONLY_KEYS = 512;
 // kernel path 3 sends every head to the reference-tracking kernel; otherwise every head first takes the
-// software-pipelined kernel without a reference, which marks the heads it could not do
+// software-pipelined kernel without a reference, which marks the heads it could not do (samples of fewer items: see
+// attention_spread_path)
 static bool attention_checked_path(int path, int seq) { return (path & 0xff) != 3 && seq > TRACKED_ONLY_KEYS; }
 static AttnPlan attention_plan(int seq, int heads) {
     constexpr int KV = 64;
@@ -1099,6 +1148,26 @@ static AttnPlan attention_plan(int seq, int heads) {
     return p;
 }
 
+// Samples whose items of 256 queries do not fill the chip: no split, no flags (see SpEnd).
+static bool attention_spread_path(int path, const AttnPlan& p) { return (path & 0xff) != 3 && p.items_ps < compute_units() * 2; }
+
+template <bool PRESCALED>
+static hipError_t launch_spread_as(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* o, int batch, int seq, int heads,
+                                   float c, const AttnStrides& s, hipStream_t st) {
+    const int wide = (seq + 255) / 256, narrow = (seq + 127) / 128;
+    if (attn_narrow_items((long)batch * heads, seq, compute_units())) {
+        const AttnGrid g{narrow, heads, narrow * heads, 0, 1, batch * narrow * heads};
+        attn_sp_kernel<1, SP_ALONE, PRESCALED><<<g.all_full, 256, 0, st>>>(q, k, v, o, seq, c, s, g, nullptr, nullptr);
+        return hipGetLastError();
+    }
+    const AttnGrid g{wide, heads, wide * heads, 0, 1, batch * wide * heads};
+    attn_sp_kernel<2, SP_NANS, PRESCALED><<<g.all_full, 256, 0, st>>>(q, k, v, o, seq, c, s, g, nullptr, nullptr);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    attn_redo_kernel<PRESCALED><<<batch * heads * narrow, 256, 0, st>>>(q, k, v, o, seq, c, s, narrow, heads);
+    return hipGetLastError();
+}
+
 static size_t flags_bytes(int batch, int heads) { return (((size_t)batch * heads * sizeof(unsigned)) + 255) & ~(size_t)255; }
 
 // workspace of the bf16 head-dim-64 kernels: [one flag per (batch, head) | key-split pieces]
@@ -1116,7 +1185,9 @@ bool attention_uses_mfma(int dtype, int head_dim, int path) {
 float* attention_head_flags(int dtype, int batch, int seq, int heads, int head_dim, void* ws, int path, hipStream_t st,
                             bool clear, int* count) {
     if (count) *count = 0;
-    if (!ws || !attention_uses_mfma(dtype, head_dim, path) || !attention_checked_path(path, seq)) return nullptr;
+    if (!ws || !attention_uses_mfma(dtype, head_dim, path) || !attention_checked_path(path, seq) ||
+        attention_spread_path(path, attention_plan(seq, heads)))
+        return nullptr;
     const int nb = batch * heads;
     if (count) *count = nb;
     if (!clear) return (float*)ws;
@@ -1133,6 +1204,11 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
         if (s.k_tok >= (1 << 24) || s.v_tok >= (1 << 24)) return hipErrorInvalidValue;   // 32-bit in-tile offsets
         const bool checked = attention_checked_path(path, seq);
         AttnPlan p = attention_plan(seq, heads);
+        if (attention_spread_path(path, p))
+            return q_prescaled ? launch_spread_as<true>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, batch,
+                                                        seq, heads, scale * 1.4426950408889634f, s, st)
+                               : launch_spread_as<false>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, batch,
+                                                         seq, heads, scale * 1.4426950408889634f, s, st);
         if ((path & 0xff) == 2) { p.full_ps = p.items_ps; p.tail_ps = 0; p.nsplit = 1; }
         const float c = scale * 1.4426950408889634f;
         const float cexp = q_prescaled ? 1.0f : c;
@@ -1152,9 +1228,9 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
                 attn_flags_clear_kernel<<<(nb + 255) / 256, 256, 0, st>>>(flags, nb);
             }
             if (q_prescaled)
-                attn_sp_kernel<true><<<split_blocks, 256, 0, st>>>(qq, kk, vv, (bf16_t*)o, seq, c, s, split, part, flags);
+                attn_sp_kernel<2, SP_FLAGS, true><<<split_blocks, 256, 0, st>>>(qq, kk, vv, (bf16_t*)o, seq, c, s, split, part, flags);
             else
-                attn_sp_kernel<false><<<split_blocks, 256, 0, st>>>(qq, kk, vv, (bf16_t*)o, seq, c, s, split, part, flags);
+                attn_sp_kernel<2, SP_FLAGS, false><<<split_blocks, 256, 0, st>>>(qq, kk, vv, (bf16_t*)o, seq, c, s, split, part, flags);
             // then the reference-tracking kernel (unsplit) for the other heads; the merge of attn_sp_kernel's pieces
             // rides on that launch as workgroups in front of the items
             MergeTail mt{part, 0, nitems, bq, cexp, split};

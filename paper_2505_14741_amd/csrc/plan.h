@@ -15,6 +15,23 @@ constexpr MergeRow merge_row(int block, int thread, int bq) {
     return MergeRow{rowid / bq, rowid % bq, thread & 15};
 }
 
+// ---- bf16 attention of samples whose items of 256 queries do not fill the chip: whether workgroups of 128 queries, alone, are
+// faster than workgroups of 256 and the launch that looks their results through.  `bh`: (batch, head) pairs.
+// Measured us per tile of 64 keys: 512 workgroups of 128 queries 1.25, up to 256 of them 0.98; of 256 queries 2.27 and 1.29.
+// A launch more costs 3 us; over several rounds the narrow ones, which read K and V twice as often, lose another 6 %.  Whole
+// calls, 30 heads, narrow / wide: 2608 keys 84 / 88, two samples 132 / 136, four 255 / 249; 1000 keys, 4 and 8 samples 46.8 /
+// 48.5 and 87.7 / 85.2; 3600 keys 132 / 122.
+constexpr bool attn_narrow_items(long bh, int seq, int cus) {
+    const long slots = 2L * cus, narrow = bh * ((seq + 127) / 128), wide = bh * ((seq + 255) / 256);
+    const auto rounds = [slots, cus](long n, float full, float half) {
+        const long tail = n % slots;
+        return (float)(n / slots) * full + (tail == 0 ? 0.f : tail <= cus ? half : full);
+    };
+    const float tiles = (float)((seq + 63) / 64);
+    const float a = tiles * rounds(narrow, 1.25f, 0.98f) * (narrow > 2 * slots ? 1.06f : 1.f);
+    return a <= tiles * rounds(wide, 2.27f, 1.29f) + 3.f;
+}
+
 // ---- projections: C[rows, Nn] = A[rows, K] * W[Nn, K]^T, rows = all samples of the batch
 // Output tiles of the matrix kernels: gemm_few.hip (any K pieces; fp32 and bf16) and gemm_mfma.hip (bf16).
 enum TileId { FEW_64x64, FEW_128x64, FEW_128x128, FEW_192x128, FEW_256x128, FEW_192x192, FEW_TILE_KINDS,

@@ -107,6 +107,32 @@ def test_attention_bf16_around_the_one_launch_limit_and_with_few_items(N):
             assert rel(ref, out[b, rows, h].double().cpu().numpy()) <= 2 * 2.0 ** -9
 
 
+@pytest.mark.parametrize("N", [31, 129, 300, 1000])
+def test_attention_queries_that_overflow_are_redone_alone(N):
+    """Logits far beyond what fits without a softmax reference, in some queries of one head: the workgroups of 128 queries
+    redo theirs on the spot, those of 256 (16 samples of 1000 keys) leave them to a second launch; the other queries of the
+    workgroup keep their values, and the batch changes no bit."""
+    H = 16
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N)
+    q, k, v = (torch.randn(16, N, H, 64, generator=g, device=DEV).bfloat16() for _ in range(3))
+    plain = B.attn3d(q, k, v, 0.125).clone()
+    big = [r for r in (5, 30, 128, 299, 700) if r < N]
+    q[3, big, 2] *= 200.0
+    q[3, big[:1], 2] = -q[3, big[:1], 2]
+    out = B.attn3d(q, k, v, 0.125)
+    for b in (2, 3, 15):
+        assert torch.equal(B.attn3d(q[b:b + 1], k[b:b + 1], v[b:b + 1], 0.125)[0], out[b]), b
+    ref = torch.softmax(q[3, :, 2].double().cpu() @ k[3, :, 2].double().cpu().t() * 0.125, -1) @ v[3, :, 2].double().cpu()
+    assert rel(ref.numpy(), out[3, :, 2].double().cpu().numpy()) <= 2 * 2.0 ** -9
+    near = {r // 32 for r in big}                        # the groups of 32 queries that are redone
+    same = [r for r in range(N) if r // 32 not in near]
+    assert torch.equal(out[3, same, 2], plain[3, same, 2])
+    assert torch.equal(out[:3], plain[:3]) and torch.equal(out[4:], plain[4:])
+    v[3, :, 2] = float("nan")                            # a head that stays NaN, and no other
+    assert torch.isnan(B.attn3d(q, k, v, 0.125)[3, :, 2]).all()
+
+
 @pytest.mark.parametrize("text", [0, 6, 70])
 @pytest.mark.parametrize("frames,rows,cols", [(1, 3, 3), (2, 8, 8), (3, 5, 7)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])

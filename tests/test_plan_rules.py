@@ -23,6 +23,7 @@ extern "C" int how(int bf16, int tokens, int n, int k, int batch) {
 extern "C" int best(int first, int last, long rows, int n, int k, int pieces, int gated) {
     return ps::best_tile(first, last, rows, n, k, pieces, gated != 0, 256);
 }
+extern "C" int narrow(long bh, int seq) { return ps::attn_narrow_items(bh, seq, 256); }
 extern "C" int kinds(int* few) { *few = ps::FEW_TILE_KINDS; return ps::TILE_KINDS; }
 extern "C" long scratch(int bf16, int tokens, int n, int k, int batch) {
     return (long)ps::few_workspace_bytes(bf16 != 0, ps::few_plan(bf16 != 0, tokens, n, k, 0), batch, tokens, n, k);
@@ -115,3 +116,12 @@ def test_sizes_of_the_tile_tests_take_the_tiles_they_name(rules):
     from test_gpu_small_shapes import TILE_SIZES
     for kind, rows, n, k in TILE_SIZES:
         assert rules.best(0, 9, C.c_long(rows), n, k, 1, 0) == kind
+
+
+def test_attention_workgroups_of_128_queries_where_they_are_faster(rules):
+    """(batch, head) pairs and keys on both sides, as measured; 16 samples of 16 heads and 1000 keys are what the test of
+    overflowing queries takes to the wider kernel."""
+    narrow = lambda bh, n: rules.narrow(C.c_long(bh), n)
+    assert narrow(30, 112) and narrow(60, 1000) and narrow(30, 2000) and narrow(30, 2608) and narrow(4, 4200) and narrow(240, 520)
+    assert not narrow(30, 3600) and not narrow(240, 1000) and not narrow(256, 1000)
+    assert narrow(16, 1000) and narrow(256, 31) and narrow(256, 129)
