@@ -34,9 +34,11 @@ __device__ __forceinline__ void sinusoid_entry(const TList& tl, float* __restric
     out[(long)b * D + half + j] = (float)sin(ang);
 }
 
-// One wave per GEMV_ROWS consecutive output rows (8 for a single input vector, 4 for batches); weights stream once from HBM (16 bytes per lane and load when
-// the row length allows, the loads of the wave's rows in flight together), inputs stay in cache and are read once
-// for the wave's rows.  Each row's sum is formed as if the wave had that row alone (same lanes, same order).
+// One wave per GEMV_ROWS consecutive output rows; weights stream once from HBM (16 bytes per lane and load when the row
+// length allows, the loads of the wave's rows in flight together), inputs stay in cache and are read once for the wave's
+// rows.  Each row's sum is formed as if the wave had that row alone (same lanes, same order).  Few rows in all (a time MLP
+// layer: 512) take a wave each, which spreads the loads and the six shuffles per row and vector over the chip: 512 rows of
+// 1920 bf16 weights, one vector 9.0 -> 5.3 us (8 rows per wave), 64 rows of 64 fp32, nine vectors 20 -> 5.
 // blockIdx.y picks one of up to GEMV_SET matrices of the same shape applied to the same input.
 template <typename T, int MAXB, int GEMV_ROWS>
 __global__ void gemv_kernel(GemvSet set, const float* __restrict__ in, int rows,
@@ -58,6 +60,7 @@ __global__ void gemv_kernel(GemvSet set, const float* __restrict__ in, int rows,
         for (int b = 0; b < MAXB; ++b) acc[r][b] = 0.f;
     constexpr int VEC = 16 / sizeof(T);                      // elements per 16-byte load
     if (cols % VEC == 0 && in_bs % 4 == 0) {
+#pragma unroll 4
         for (int c = lane * VEC; c < cols; c += WAVE * VEC) {
             float wv[GEMV_ROWS][VEC];
 #pragma unroll
@@ -114,6 +117,8 @@ __global__ void gemv_kernel(GemvSet set, const float* __restrict__ in, int rows,
     }
 }
 
+static constexpr long GEMV_FEW_ROWS = 4096;              // waves, half of what the chip holds
+
 hipError_t launch_gemv_set(int dtype, const GemvSet& set, int count, const float* in, int rows, int cols, int batch,
                            long in_bs, long out_bs, int act, hipStream_t st) {
     if (count < 1 || count > GEMV_SET) return hipErrorInvalidValue;
@@ -124,6 +129,19 @@ hipError_t launch_gemv_set(int dtype, const GemvSet& set, int count, const float
         kernel<<<blocks, threads, 0, st>>>(set, in, rows, cols, batch, in_bs, out_bs, act);
     };
     if (batch < 1 || batch > 16) return hipErrorInvalidValue;
+    if ((long)rows * count <= GEMV_FEW_ROWS) {
+        threads = 64;
+        if (dtype == PS_BF16) {
+            if (batch == 1) go(gemv_kernel<bf16_t, 1, 1>, 1);
+            else if (batch <= 4) go(gemv_kernel<bf16_t, 4, 1>, 1);
+            else go(gemv_kernel<bf16_t, 16, 1>, 1);
+        } else {
+            if (batch == 1) go(gemv_kernel<float, 1, 1>, 1);
+            else if (batch <= 4) go(gemv_kernel<float, 4, 1>, 1);
+            else go(gemv_kernel<float, 16, 1>, 1);
+        }
+        return hipGetLastError();
+    }
     if (dtype == PS_BF16) {
         if (batch == 1) go(gemv_kernel<bf16_t, 1, 8>, 8);
         else if (batch <= 4) go(gemv_kernel<bf16_t, 4, 4>, 4);
@@ -402,10 +420,134 @@ patch_embed_kernel(const float* __restrict__ x, const T* __restrict__ ctx, const
     }
 }
 
+// The same for bf16 weights and patch vectors of up to 64 values, on bf16 matrix instructions: a pixel is split into three
+// bf16 numbers whose sum it is exactly (8 of its 24 significand bits each), so products and sums are those of fp32 at a
+// fifth of the matrix time (six 16 x 16 x 32 instructions of 16 cycles for sixteen 16 x 16 x 4 of 32).  A wave keeps the
+// patches of 64 tokens in registers and walks its columns, 32 at a time (whole lines of X), whose weights come straight from
+// global memory in operand layout; writing X is the bound.
+// (One workgroup per 64 x 64 outputs gathered the pixels once per 64 columns, in fp32 products: 13.4 us at 112 tokens x 1920,
+// 31 at 4516, 100 at 17776; this takes 7.4, 20 and 58.)
+__global__ void __launch_bounds__(256)
+patch_embed64_kernel(const float* __restrict__ x, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ W_pe,
+                     const float* __restrict__ b_pe, float* __restrict__ X, int C, int F, int H, int Wd, int patch,
+                     int text_tokens, int D, long ctx_bs, int cols) {
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    typedef __attribute__((ext_vector_type(8))) __bf16 b8;
+    constexpr int TILE = 64, LD = TILE + 4;              // (rows 16-byte aligned, 4 banks apart)
+    __shared__ __attribute__((aligned(16))) float pt[TILE * LD];
+    const int Hp = H / patch, Wp = Wd / patch, N = text_tokens + F * Hp * Wp, P = C * patch * patch;
+    const int n0 = blockIdx.x * TILE, d0 = blockIdx.y * cols, d1 = min(d0 + cols, D), b = blockIdx.z;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, kgrp = lane >> 4;
+    if (n0 < text_tokens) {                              // text rows of the tile: widened copies
+        const int rows = min(TILE, text_tokens - n0), quads = (d1 - d0) / 4;
+        for (int e = threadIdx.x; e < rows * quads; e += 256) {
+            const int r = e / quads, col = d0 + (e - r * quads) * 4;
+            const bf16_t* cp = ctx + b * ctx_bs + (long)(n0 + r) * D + col;
+            *reinterpret_cast<f4*>(X + ((long)b * N + n0 + r) * D + col) = f4{to_f32(cp[0]), to_f32(cp[1]), to_f32(cp[2]), to_f32(cp[3])};
+        }
+        if (n0 + TILE <= text_tokens) return;            // (whole workgroup)
+    }
+    {
+        const int n = n0 + lane, nv = n - text_tokens;   // lane = token while staging: neighbours read adjacent pixels
+        const bool video = n < N && nv >= 0;
+        const int j = nv % Wp, i = (nv / Wp) % Hp, f = nv / (Wp * Hp);
+        const float* xp = x + (((long)b * C * F + f) * H + (long)i * patch) * Wd + (long)j * patch;
+        // where patch value `lane` lies, one division per lane; read from that lane below
+        const int lc = lane / (patch * patch), lr = lane - lc * patch * patch, ly = lr / patch;
+        const int in_plane = ly * Wd + (lr - ly * patch);
+        float pv[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {                   // patch value wave + 4u of every token (uniform per wave)
+            const int c = __builtin_amdgcn_readlane(lc, wave + 4 * u);
+            const int at = __builtin_amdgcn_readlane(in_plane, wave + 4 * u);
+            pv[u] = video && wave + 4 * u < P ? xp[(long)c * F * H * Wd + at] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) pt[lane * LD + wave + 4 * u] = pv[u];
+    }
+    // lane l of step s: k = 16 * (l / 16) + 8s .. + 7, of a token in one operand and of a column in the other
+    auto weights = [&](int col0, b8 (&w)[2][2]) {
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+            const bf16_t* wp = W_pe + (long)min(col0 + y * 16 + l16, D - 1) * P + kgrp * 16;
+            if (P == 64) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) w[y][s] = reinterpret_cast<const b8*>(wp)[s];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) w[y][e / 8][e % 8] = (__bf16)(kgrp * 16 + e < P ? to_f32(wp[e]) : 0.f);
+            }
+        }
+    };
+    b8 w[2][2], wn[2][2];
+    int c0 = d0 + wave * 32;
+    if (c0 < d1) weights(c0, w);
+    __syncthreads();
+    b8 p[4][2][3];                                       // [16 tokens][step][part]
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float v = pt[(t * 16 + l16) * LD + kgrp * 16 + s * 8 + e];
+                // (infinities and NaN: all in the first part)
+                const auto top = [](float u) { return __uint_as_float(__float_as_uint(u) & 0xffff0000u); };
+                const float hi = v == v ? top(v) : v, rest = fabsf(v) < __builtin_inff() ? v - hi : 0.f, mid = top(rest);
+                p[t][s][0][e] = (__bf16)hi; p[t][s][1][e] = (__bf16)mid; p[t][s][2][e] = (__bf16)(rest - mid);
+            }
+    for (; c0 < d1; c0 += 128) {
+        if (c0 + 128 < d1) weights(c0 + 128, wn);
+        f4 acc[4][2];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[t][y] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int part = 2; part >= 0; --part)            // small parts first
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int y = 0; y < 2; ++y)
+                        acc[t][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[y][s], p[t][s][part], acc[t][y], 0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int n = n0 + t * 16 + l16;
+            if (n < text_tokens || n >= N) continue;
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                const int col = c0 + y * 16 + kgrp * 4;  // D % 4 == 0: inside or outside together
+                if (col < d1) *reinterpret_cast<f4*>(X + ((long)b * N + n) * D + col) = acc[t][y] + *reinterpret_cast<const f4*>(b_pe + col);
+            }
+        }
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) w[y][s] = wn[y][s];
+    }
+}
+
 hipError_t launch_patch_embed(int dtype, const float* x, const void* ctx, const void* W_pe,
                               const float* b_pe, float* X, int batch, int C, int F, int H, int Wd,
                               int patch, int text_tokens, int D, long ctx_bs, hipStream_t st) {
     const long N = text_tokens + (long)F * (H / patch) * (Wd / patch);
+    if (dtype == PS_BF16 && C * patch * patch <= 64) {
+        // Two workgroups of four waves per compute unit, and four or more per tile of tokens, so that their writes start and
+        // end at different times; none with fewer than 128 columns.  4516 tokens in 4 / 8 / 15 pieces: 26 / 20 / 23 us,
+        // 17776 tokens in 1 / 2 / 4 / 8 / 15: 98 / 68 / 58 / 59 / 72.
+        const long tiles = (N + 63) / 64 * batch, most = (D + 127) / 128;
+        long split = (2L * compute_units() + tiles - 1) / tiles;
+        if (split < 4) split = 4;
+        if (split > most) split = most;
+        const int cols = (int)((most + split - 1) / split) * 128;
+        const dim3 g((unsigned)((N + 63) / 64), (D + cols - 1) / cols, batch);
+        patch_embed64_kernel<<<g, 256, 0, st>>>(x, (const bf16_t*)ctx, (const bf16_t*)W_pe, b_pe, X, C, F, H, Wd, patch, text_tokens,
+                                                D, ctx_bs, cols);
+        return hipGetLastError();
+    }
     dim3 grid((unsigned)((N + 63) / 64 * ((D + 63) / 64)), batch);   // at most 2^18 x 2^5
     if (dtype == PS_BF16)
         patch_embed_kernel<bf16_t><<<grid, 256, 0, st>>>(x, (const bf16_t*)ctx, (const bf16_t*)W_pe,

@@ -154,6 +154,25 @@ def test_forward_few_tokens(dtype, frames, rows, cols, text):
         assert torch.equal(one[0], eps[b])
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("channels,patch", [(1, 2), (4, 2), (3, 4), (16, 2), (20, 2), (4, 1)])
+def test_patch_vectors_of_any_length(dtype, channels, patch):
+    """bf16 weights: up to 64 values per patch as three bf16 parts of every pixel, longer ones (80) and fp32 weights in fp32
+    products.  Pixels from 2^-12 to 2^12; 77 columns of patches and 70 text rows end inside a tile.  Output projections of
+    zero leave the embedding to the final layer, whose rounding to bf16 is one in 2^9 per value."""
+    cfg = I.CONFIGS["reduced"].with_(layers=1, frames=1, height=4 * patch, width=77 * patch, in_channels=channels, patch=patch,
+                                     text_tokens=70, dtype=dtype)
+    W = [(n, w * 0 if n.split(".")[0] in ("W_o", "b_o", "W_2", "b_2") else w) for n, w in I.make_weights(cfg, 1001, "unit")]
+    assert sum(float(np.abs(w).max()) == 0 for _, w in W) == 4
+    d = B.dit_create(cfg, B.weights_to_device(cfg, W, DEV))
+    rng = np.random.default_rng(channels * patch)
+    x = (I.make_latent(cfg, 2) * 2.0 ** rng.integers(-12, 13, size=(2,) + tuple(cfg.latent_shape))).astype(np.float32)
+    ctx = I.make_context(cfg, 2)
+    eps = B.dit_forward(d, torch.from_numpy(x).to(DEV), torch.from_numpy(ctx).to(DEV).to(B.torch_dtype(dtype)), [900, 20])
+    ref = O.dit_forward(cfg, dict(W), x, ctx, [900, 20])
+    assert rel(ref, eps.cpu().numpy()) <= (1e-5 if dtype == "f32" else 2.0 ** -8)
+
+
 @pytest.mark.parametrize("mode,batched,S,m,cyc", [(0, False, 37, 3, [4] * 9), (1, False, 37, 1, [3] * 12), (0, True, 37, 2, [7] * 5)])
 def test_run_longer_than_one_conditioning_chunk(mode, batched, S, m, cyc):
     """More predictor calls than the 16 whose modulation is computed together: step by step (one at a time) equals the whole
