@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "common.h"
+#include "slim.h"
 
 using namespace ps;
 
@@ -44,7 +45,7 @@ struct dit {
 namespace {
 
 struct WsLayout {
-    size_t X, H, QKV, mod, modf, sinus, hid, cvec, rope, attn, gemm, gemm_bytes, total;
+    size_t X, H, QKV, qkv2, mod, modf, sinus, hid, cvec, rope, attn, gemm, gemm_bytes, total;
 };
 
 WsLayout ws_layout(const dit* d, int batch) {
@@ -57,6 +58,8 @@ WsLayout ws_layout(const dit* d, int batch) {
     w.H = take(M * D * d->esize);                                  // LN output / attention output
     size_t wide = (size_t)(c.mlp_ratio > 3 ? c.mlp_ratio : 3);
     w.QKV = take(M * wide * D * d->esize);                         // qkv, later the MLP hidden
+    // narrow networks: q, k, v of the layer after the current one
+    w.qkv2 = take(slim_network(c.dtype, c.hidden, c.head_dim, c.mlp_ratio, d->P, d->N) ? M * 3 * D * 4 : 0);
     w.mod = take((size_t)batch * c.layers * 12 * D * 4);
     w.modf = take((size_t)batch * 2 * D * 4);
     w.sinus = take((size_t)batch * D * 4);
@@ -197,6 +200,24 @@ int forward_impl(dit* d, const float* x, const void* ctx, const int32_t* t_host,
     } else {
         mod = cond->mod; modf = cond->modf; rope = cond->rope;
     }
+    const int P = c.in_channels * c.patch * c.patch;
+    if ((path & 0xff) != 1 && slim_network(dt, D, c.head_dim, c.mlp_ratio, P, N)) {
+        SlimLayer layers[MAX_LAYERS];
+        for (int l = 0; l < L; ++l) {
+            const LayerW& lw = d->layers[l];
+            layers[l] = SlimLayer{(const float*)lw.W_qkv, (const float*)lw.W_o, (const float*)lw.W_1, (const float*)lw.W_2,
+                                  lw.b_qkv, lw.b_o, lw.b_1, lw.b_2};
+        }
+        SlimArgs g{};
+        g.x = x; g.ctx = (const float*)ctx; g.ctx_bs = ctx_shared ? 0L : (long)c.text_tokens * D;
+        g.W_pe = (const float*)d->W_pe; g.b_pe = d->b_pe; g.W_out = (const float*)d->W_out; g.b_out = d->b_out;
+        g.mod = mod; g.mod_bs = mod_bs; g.modf = modf; g.rope = rope; g.X = X; g.eps_out = eps_out;
+        g.pg = PatchGeom{c.in_channels, c.frames, c.height, c.width, c.patch};
+        g.tokens = N; g.text_tokens = c.text_tokens; g.head_dim = c.head_dim;
+        g.eps = c.ln_eps; g.scale = 1.0f / sqrtf((float)c.head_dim);
+        PS_TIMED(KC_OTHER, launch_slim(g, D, layers, L, batch, (float*)QKV, (float*)(base + w.qkv2), st));
+        return PS_OK;
+    }
     PS_TIMED(KC_OTHER, launch_patch_embed(dt, x, ctx, d->W_pe, d->b_pe, X, batch, c.in_channels, c.frames,
                                           c.height, c.width, c.patch, c.text_tokens, D,
                                           ctx_shared ? 0L : (long)c.text_tokens * D, st));
@@ -211,7 +232,6 @@ int forward_impl(dit* d, const float* x, const void* ctx, const int32_t* t_host,
     // the MFMA attention kernel takes queries that already carry scale*log2(e); the QKV
     // projection applies the factor in fp32, before its single rounding to bf16
     const bool prescale = attention_uses_mfma(dt, c.head_dim, path);
-    const int P = c.in_channels * c.patch * c.patch;
     const bool final_gemm = gemm_uses_mfma(dt, N, P, D, path);
     // a gated projection of few tokens leaves its K pieces to the LayerNorm that follows
     PendingResidual pend{};

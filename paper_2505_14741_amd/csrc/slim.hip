@@ -1,0 +1,331 @@
+// A whole forward of a narrow fp32 network (see slim_network) in layers + 1 launches.
+//
+// In such a network every operation of a layer is a few microseconds of latency: a launch, the loads of its operands, a
+// short chain of products (2 layers of 64 on 32 tokens: 17 launches of 3.3 to 6.5 us).  Everything but attention's keys and
+// values belongs to one token, and 16 tokens' rows fit LDS many times over, so a workgroup of four waves takes 16 tokens
+// through all that lies between two attentions: attention itself (a wave per head, keys and values straight from memory
+// into operand layout), output projection, LayerNorm, MLP, and the next layer's LayerNorm and q, k, v -- or, after the last
+// layer, the final projection.  The first launch embeds and does the first layer's q, k, v.  Weights come from L2 in operand
+// layout, requested a phase ahead, across the barrier in front of their use.
+// fp32 products and sums on v_mfma_f32_16x16x4_f32 throughout; instruction e of a 16-deep step multiplies k = 4 * (lane / 16)
+// + e, even and odd steps have sums of their own.
+// us per forward of 2 layers of hidden 64 with the launches of the conditioning, a launch per operation and this: 32 tokens
+// 99 and 48, 134 tokens 109 and 56, 416 tokens 125 and 71.
+#include "few_epilogue.h"
+#include "slim.h"
+
+namespace ps {
+
+namespace {
+
+constexpr int ROWS = 16;                                 // tokens of a workgroup
+__device__ __forceinline__ f32x4_t quad(const float* p) { return *reinterpret_cast<const f32x4_t*>(p); }
+
+// One wave's share of out = in * W^T: 16-column blocks wave, wave + 4, ... (NF of them, `blocks` in all), K = 16 * KB.
+// The weights of the first blocks are requested by request(), the others when their turn comes.
+template <int KB, int NF>
+struct Project {
+    static constexpr int G = KB >= 16 ? 1 : NF * KB <= 16 ? NF : 16 / KB;
+    f32x4_t pre[G][KB];
+    const float* W;
+    int wave, blocks;
+    __device__ __forceinline__ void load(int j, f32x4_t (&w)[KB]) const {
+        const int lane = threadIdx.x & 63, col = min(wave + 4 * j, blocks - 1) * 16 + (lane & 15);
+        const float* p = W + (long)col * (16 * KB) + (lane >> 4) * 4;
+#pragma unroll
+        for (int i = 0; i < KB; ++i) w[i] = quad(p + i * 16);
+    }
+    __device__ __forceinline__ void request(const float* weights, int w, int n) {
+        W = weights; wave = w; blocks = n;
+#pragma unroll
+        for (int j = 0; j < G; ++j) load(j, pre[j]);
+    }
+    // in: LDS, this lane's row (lane % 16); epi(first of the lane's 4 columns, sums)
+    template <class Epi>
+    __device__ __forceinline__ void run(const float* in, Epi epi) const {
+        const int kgrp = (threadIdx.x & 63) >> 4;
+        f32x4_t a[KB];
+#pragma unroll
+        for (int i = 0; i < KB; ++i) a[i] = quad(in + i * 16 + kgrp * 4);
+#pragma unroll
+        for (int j = 0; j < NF; ++j) {
+            if (wave + 4 * j >= blocks) break;
+            f32x4_t later[KB], s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+            if (j >= G) load(j, later);
+#pragma unroll
+            for (int i = 0; i < KB; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    s[i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(j < G ? pre[j < G ? j : 0][i][e] : later[i][e], a[i][e], s[i & 1], 0, 0, 0);
+            epi((wave + 4 * j) * 16 + kgrp * 4, s[0] + s[1]);
+        }
+    }
+};
+
+// sum over the 16 lanes that share a row
+__device__ __forceinline__ float row_sum(float v) {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// out = LN(in) * (1 + scale) + shift for rows 4 * wave + lane / 16; shift, scale: of that row
+template <int D>
+__device__ __forceinline__ void slim_norm(const float* in, float* out, const float* shift, const float* scale, float eps) {
+    constexpr int V = D / 16;
+    const int l16 = threadIdx.x & 15;
+    float v[V], h[V], k[V], s = 0.f, q = 0.f;
+#pragma unroll
+    for (int i = 0; i < V; ++i) { h[i] = shift[l16 + 16 * i]; k[i] = scale[l16 + 16 * i]; }
+#pragma unroll
+    for (int i = 0; i < V; ++i) { v[i] = in[l16 + 16 * i]; s += v[i]; }
+    const float mean = row_sum(s) / (float)D;
+#pragma unroll
+    for (int i = 0; i < V; ++i) q += (v[i] - mean) * (v[i] - mean);
+    const float rstd = 1.0f / sqrtf(row_sum(q) / (float)D + eps);
+#pragma unroll
+    for (int i = 0; i < V; ++i) out[l16 + 16 * i] = (v[i] - mean) * rstd * (1.f + k[i]) + h[i];
+}
+
+// q, k, v of a row block: bias, rotation, store
+template <int D>
+__device__ __forceinline__ void slim_qkv(const SlimArgs& g, const SlimLayer& w, const Project<D / 16, (3 * D / 16 + 3) / 4>& pj,
+                                         const float* in, int b, int n) {
+    Epilogue ep{};
+    ep.kind = EPI_QKV_ROPE; ep.bias = w.b_qkv; ep.D = D; ep.geom = TokenGeom{g.tokens, g.text_tokens};
+    ep.rope_cs = g.rope; ep.rope_F = g.pg.F; ep.rope_Hp = g.pg.H / g.pg.patch; ep.rope_Wp = g.pg.W / g.pg.patch;
+    ep.head_dim = g.head_dim; ep.q_scale = 1.0f;
+    const int row = b * g.tokens + min(n, g.tokens - 1);
+    const EpiRow r = epilogue_row<EPI_QKV_ROPE>(ep, row);
+    pj.run(in, [&](int col, f32x4_t x) {
+        const EpiOperands o = epilogue_operands<EPI_QKV_ROPE>(ep, 3 * D, r, row, col);
+        if (n < g.tokens) epilogue_quad<EPI_QKV_ROPE, float>(ep, g.qkv_out, 3 * D, r, row, col, x, o);
+    });
+}
+
+// Embedding, first LayerNorm and q, k, v.  P = 16 * PB values per patch.
+template <int D, int PB>
+__global__ void __launch_bounds__(256, 1) slim_begin_kernel(SlimArgs g, SlimLayer w) {
+    constexpr int LD = D + 4, P = 16 * PB, LP = P + 4;   // rows 16-byte aligned, 4 banks apart
+    __shared__ __attribute__((aligned(16))) float pt[ROWS * LP], xt[ROWS * LD], ht[ROWS * LD];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15;
+    const int n0 = blockIdx.x * ROWS, b = blockIdx.y, N = g.tokens, L = g.text_tokens;
+    const int n = n0 + l16;                              // this lane's row in the projections
+    Project<PB, (D / 16 + 3) / 4> embed;
+    embed.request(g.W_pe, wave, D / 16);
+    Project<D / 16, (3 * D / 16 + 3) / 4> qkv;
+    qkv.request(w.W_qkv, wave, 3 * D / 16);
+    const PatchGeom& pg = g.pg;
+    const int Hp = pg.H / pg.patch, Wp = pg.W / pg.patch, ps2 = pg.patch * pg.patch;
+    for (int e = threadIdx.x; e < ROWS * P; e += 256) {
+        const int r = e & 15, p = e >> 4, nv = n0 + r - L;
+        float v = 0.f;
+        if (nv >= 0 && n0 + r < N) {
+            const int j = nv % Wp, i = (nv / Wp) % Hp, f = nv / (Wp * Hp), c = p / ps2, dy = p % ps2 / pg.patch, dx = p % pg.patch;
+            v = g.x[(((long)b * pg.C + c) * pg.F + f) * pg.H * pg.W + (long)(i * pg.patch + dy) * pg.W + j * pg.patch + dx];
+        }
+        pt[r * LP + p] = v;
+    }
+    __syncthreads();
+    embed.run(pt + l16 * LP, [&](int col, f32x4_t x) {
+        x += quad(g.b_pe + col);
+        if (n < L) x = quad(g.ctx + b * g.ctx_bs + (long)n * D + col);
+        *reinterpret_cast<f32x4_t*>(xt + l16 * LD + col) = x;
+        if (n < N) *reinterpret_cast<f32x4_t*>(g.X + ((long)b * N + n) * D + col) = x;
+    });
+    __syncthreads();
+    {
+        const int r = wave * 4 + (lane >> 4);
+        const float* m = g.mod + b * g.mod_bs + (n0 + r < L ? 6 * D : 0);
+        slim_norm<D>(xt + r * LD, ht + r * LD, m, m + D, g.eps);
+    }
+    __syncthreads();
+    slim_qkv<D>(g, w, qkv, ht + l16 * LD, b, n);
+}
+
+// One layer from its attention on; `next`: the following layer's q, k, v, or after the last layer the final projection.
+template <int D, int HD, bool LAST>
+__global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLayer w, SlimLayer next) {
+    constexpr int LD = D + 4, F = 4 * D, LF = F + 4, NB = HD / 16, HEADS = D / HD;
+    __shared__ __attribute__((aligned(16))) float xt[ROWS * LD], ht[ROWS * LD], ut[ROWS * LF];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kgrp = lane >> 4;
+    const int n0 = blockIdx.x * ROWS, b = blockIdx.y, N = g.tokens, L = g.text_tokens;
+    const int n = n0 + l16;
+    const float* mod = g.mod + b * g.mod_bs + (long)g.layer * 12 * D;
+    const float* gates = mod + (n < L ? 6 * D : 0);      // of this lane's row
+    Project<D / 16, (D / 16 + 3) / 4> po;
+    po.request(w.W_o, wave, D / 16);
+    for (int e = threadIdx.x; e < ROWS * (D / 4); e += 256) {
+        const int r = e / (D / 4), c = e % (D / 4) * 4;
+        *reinterpret_cast<f32x4_t*>(xt + r * LD + c) = quad(g.X + ((long)b * N + min(n0 + r, N - 1)) * D + c);
+    }
+    // attention: a wave per head, its 16 queries in lane % 16.  S^T = K Q^T leaves keys 4 * (lane / 16) + i of every 16-key
+    // block, the layout the second operand of O^T = V^T P^T wants: the probabilities stay in their registers, in fp32.
+    const float* base = g.qkv + (long)b * N * 3 * D;
+    for (int h = wave; h < HEADS; h += 4) {
+        f32x4_t qf[NB], acc[NB];
+#pragma unroll
+        for (int d = 0; d < NB; ++d) {
+            qf[d] = quad(base + (long)min(n, N - 1) * 3 * D + h * HD + d * 16 + kgrp * 4) * g.scale;
+            acc[d] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+        f32x4_t kn[4][NB];                               // the next 64 keys; values past the end are zero
+        float vn[4][4][NB];
+        auto fetch = [&](int k0) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int d = 0; d < NB; ++d) {
+                    kn[t][d] = quad(base + (long)min(k0 + t * 16 + l16, N - 1) * 3 * D + D + h * HD + d * 16 + kgrp * 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int key = k0 + t * 16 + kgrp * 4 + e;
+                        const float u = base[(long)min(key, N - 1) * 3 * D + 2 * D + h * HD + d * 16 + l16];
+                        vn[t][e][d] = key < N ? u : 0.f;
+                    }
+                }
+        };
+        float m = -INFINITY, l = 0.f;                    // l: over this lane's keys only
+        fetch(0);
+        for (int k0 = 0; k0 < N; k0 += 64) {
+            f32x4_t kf[4][NB], sc[4];
+            float vf[4][4][NB];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int d = 0; d < NB; ++d) {
+                    kf[t][d] = kn[t][d];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) vf[t][e][d] = vn[t][e][d];
+                }
+            if (k0 + 64 < N) fetch(k0 + 64);
+            float tmax = -INFINITY;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                sc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int d = 0; d < NB; ++d)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][d][e], qf[d][e], sc[t], 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (k0 + t * 16 + kgrp * 4 + i >= N) sc[t][i] = -INFINITY;
+                    tmax = fmaxf(tmax, sc[t][i]);
+                }
+            }
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+            const float mn = fmaxf(m, tmax), alpha = expf(m - mn);   // exp(-inf) = 0 on the first keys
+            m = mn;
+            l *= alpha;
+#pragma unroll
+            for (int d = 0; d < NB; ++d) acc[d] *= alpha;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                if (k0 + t * 16 >= N) continue;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    sc[t][i] = expf(sc[t][i] - mn);      // masked keys: exp(-inf) = 0
+                    l += sc[t][i];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int d = 0; d < NB; ++d) acc[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][e][d], sc[t][e], acc[d], 0, 0, 0);
+            }
+        }
+        l += __shfl_xor(l, 16, 64);
+        l += __shfl_xor(l, 32, 64);
+        const float inv = 1.0f / l;
+#pragma unroll
+        for (int d = 0; d < NB; ++d) *reinterpret_cast<f32x4_t*>(ht + l16 * LD + h * HD + d * 16 + kgrp * 4) = acc[d] * inv;
+    }
+    __syncthreads();
+    Project<D / 16, D / 16> p1;
+    p1.request(w.W_1, wave, F / 16);
+    auto residual = [&](const float* bias, const float* gate) {
+        return [=](int col, f32x4_t x) {
+            float* at = xt + l16 * LD + col;
+            *reinterpret_cast<f32x4_t*>(at) = quad(at) + quad(gate + col) * (x + quad(bias + col));
+        };
+    };
+    po.run(ht + l16 * LD, residual(w.b_o, gates + 2 * D));
+    __syncthreads();
+    const int nr = wave * 4 + kgrp;                      // this lane's row in the LayerNorms
+    {
+        const float* m = mod + (n0 + nr < L ? 6 * D : 0);
+        slim_norm<D>(xt + nr * LD, ht + nr * LD, m + 3 * D, m + 4 * D, g.eps);
+    }
+    __syncthreads();
+    Project<F / 16, (D / 16 + 3) / 4> p2;
+    p2.request(w.W_2, wave, D / 16);
+    p1.run(ht + l16 * LD, [&](int col, f32x4_t x) {
+        x += quad(w.b_1 + col);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[c] = gelu_tanh_f(x[c]);
+        *reinterpret_cast<f32x4_t*>(ut + l16 * LF + col) = x;
+    });
+    __syncthreads();
+    p2.run(ut + l16 * LF, residual(w.b_2, gates + 5 * D));
+    Project<D / 16, LAST ? 1 : (3 * D / 16 + 3) / 4> pn;
+    pn.request(LAST ? g.W_out : next.W_qkv, wave, LAST ? g.pg.C * g.pg.patch * g.pg.patch / 16 : 3 * D / 16);
+    __syncthreads();
+    if constexpr (LAST) {
+        const float* m = g.modf + b * 2 * D;
+        slim_norm<D>(xt + nr * LD, ht + nr * LD, m, m + D, g.eps);
+        __syncthreads();
+        Epilogue ep{};
+        ep.kind = EPI_UNPATCHIFY; ep.bias = g.b_out; ep.resid = g.eps_out; ep.geom = TokenGeom{N, L}; ep.pg = g.pg;
+        const int P = g.pg.C * g.pg.patch * g.pg.patch, row = b * N + min(n, N - 1);
+        const EpiRow r = epilogue_row<EPI_UNPATCHIFY>(ep, row);
+        pn.run(ht + l16 * LD, [&](int col, f32x4_t x) {
+            if (n < N) epilogue_quad<EPI_UNPATCHIFY, float>(ep, nullptr, P, r, row, col, x, epilogue_operands<EPI_UNPATCHIFY>(ep, P, r, row, col));
+        });
+    } else {
+        for (int e = threadIdx.x; e < ROWS * (D / 4); e += 256) {
+            const int r = e / (D / 4), c = e % (D / 4) * 4;
+            if (n0 + r < N) *reinterpret_cast<f32x4_t*>(g.X + ((long)b * N + n0 + r) * D + c) = quad(xt + r * LD + c);
+        }
+        const float* m = mod + 12 * D + (n0 + nr < L ? 6 * D : 0);
+        slim_norm<D>(xt + nr * LD, ht + nr * LD, m, m + D, g.eps);
+        __syncthreads();
+        slim_qkv<D>(g, next, pn, ht + l16 * LD, b, n);
+    }
+}
+
+template <int D, int HD>
+hipError_t launch_slim_as(SlimArgs g, const SlimLayer* layers, int count, int batch, float* qkv_even, float* qkv_odd, hipStream_t st) {
+    const dim3 grid((g.tokens + ROWS - 1) / ROWS, batch);
+    const int P = g.pg.C * g.pg.patch * g.pg.patch;
+    g.qkv_out = qkv_even;
+    switch (P / 16) {
+        case 1: slim_begin_kernel<D, 1><<<grid, 256, 0, st>>>(g, layers[0]); break;
+        case 2: slim_begin_kernel<D, 2><<<grid, 256, 0, st>>>(g, layers[0]); break;
+        case 3: slim_begin_kernel<D, 3><<<grid, 256, 0, st>>>(g, layers[0]); break;
+        case 4: slim_begin_kernel<D, 4><<<grid, 256, 0, st>>>(g, layers[0]); break;
+        default: return hipErrorInvalidValue;
+    }
+    for (int l = 0; l < count; ++l) {
+        g.layer = l;
+        g.qkv = l % 2 ? qkv_odd : qkv_even;              // a workgroup's next q, k, v must not overwrite keys others still read
+        g.qkv_out = l % 2 ? qkv_even : qkv_odd;
+        if (l + 1 < count) slim_layer_kernel<D, HD, false><<<grid, 256, 0, st>>>(g, layers[l], layers[l + 1]);
+        else slim_layer_kernel<D, HD, true><<<grid, 256, 0, st>>>(g, layers[l], layers[l]);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_slim(const SlimArgs& g, int hidden, const SlimLayer* layers, int count, int batch, float* qkv_even,
+                       float* qkv_odd, hipStream_t st) {
+    switch (hidden * 100 + g.head_dim) {
+        case 3216: return launch_slim_as<32, 16>(g, layers, count, batch, qkv_even, qkv_odd, st);
+        case 3232: return launch_slim_as<32, 32>(g, layers, count, batch, qkv_even, qkv_odd, st);
+        case 6416: return launch_slim_as<64, 16>(g, layers, count, batch, qkv_even, qkv_odd, st);
+        case 6432: return launch_slim_as<64, 32>(g, layers, count, batch, qkv_even, qkv_odd, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace ps

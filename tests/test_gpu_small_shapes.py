@@ -295,3 +295,25 @@ def test_forward_of_a_batch_equals_single_calls_whatever_kernels_the_batch_takes
         out = B.dit_forward(d, x[:n].contiguous(), ctx[:n].contiguous(), t[:n])
         for b in range(n):
             assert torch.equal(out[b], one[b]), (n, b)
+
+
+@pytest.mark.parametrize("hidden,heads,channels,patch", [(32, 1, 4, 2), (32, 2, 16, 1), (64, 2, 12, 2), (64, 4, 16, 2)])
+@pytest.mark.parametrize("frames,rows,cols,text", [(1, 1, 4, 0), (1, 3, 5, 0), (1, 4, 4, 16), (2, 7, 9, 17), (16, 8, 8, 0)])
+@pytest.mark.parametrize("layers", [1, 3])
+def test_narrow_network_in_one_launch_per_layer(hidden, heads, channels, patch, frames, rows, cols, text, layers):
+    """Row blocks of 16 tokens that end inside, at and before the last token, text and video rows in one block, keys past a
+    tile of 64, 1 to 4 blocks of patch values, up to the 1024 tokens it serves: against the oracle, and the batch changes no
+    bit."""
+    cfg = I.CONFIGS["tiny_text"].with_(layers=layers, hidden=hidden, heads=heads, head_dim=hidden // heads, frames=frames,
+                                       height=rows * patch, width=cols * patch, in_channels=channels, patch=patch, text_tokens=text)
+    W = I.make_weights(cfg, 1001, "unit")
+    d = B.dit_create(cfg, B.weights_to_device(cfg, W, DEV))
+    x, ctx = I.make_latent(cfg, 2), I.make_context(cfg, 2) if text else None
+    xd, cd = torch.from_numpy(x).to(DEV), torch.from_numpy(ctx).to(DEV) if text else None
+    eps = B.dit_forward(d, xd, cd, [900, 20])
+    ref = O.dit_forward(cfg, dict(W), x, ctx, [900, 20])
+    for b in range(2):
+        assert O.rel_mae(ref[b], eps[b].cpu().numpy())[2] <= 1e-5          # fp32 sums of up to 256 and 1024 terms, 3 layers
+        one = B.dit_forward(d, xd[b:b + 1].contiguous(), None if cd is None else cd[b:b + 1].contiguous(), [[900, 20][b]])
+        assert torch.equal(one[0], eps[b])
+    assert graph_nodes(lambda: B.dit_forward(d, xd, cd, [900, 20])) == 4 + 1 + layers
