@@ -9,6 +9,7 @@ library handle -- there is no CPU fallback.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import List, Optional, Sequence
 
@@ -111,11 +112,23 @@ def _check(status: int, where: str):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return C.c_void_p(0 if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()      # (void* arguments take an int as it is)
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of torch's current stream on the current device."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+@functools.lru_cache(maxsize=1024)
+def _bytes_on(device: int, entry: str, *args) -> int:
+    return getattr(lib(), entry)(*args)
+
+
+def _bytes(entry: str, *args) -> int:
+    """What a workspace-size function of the library returns for these sizes on the current device (asking it through
+    ctypes is a microsecond)."""
+    return _bytes_on(torch._C._cuda_getDevice(), entry, *args)
 
 
 def _dt(name: str) -> int:
@@ -215,7 +228,7 @@ def attn3d(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, scale: float,
     dt = PS_BF16 if q.dtype == torch.bfloat16 else PS_F32
     if out is None:
         out = torch.empty_like(q)
-    n = lib().attn3d_workspace_bytes(B, N, H, d, dt)
+    n = _bytes("attn3d_workspace_bytes", B, N, H, d, dt)
     ws = _workspace(n, q.device)
     _check(lib().attn3d(_ptr(q), _ptr(k), _ptr(v), _ptr(out), B, N, H, d, float(scale), dt, int(kernel_path),
                         _ptr(ws), n, _stream()), "attn3d")
@@ -229,7 +242,7 @@ def dit_linear(a: torch.Tensor, w: torch.Tensor, bias: torch.Tensor, act: int = 
     dt = PS_BF16 if a.dtype == torch.bfloat16 else PS_F32
     if out is None:
         out = torch.empty(M, Nn, dtype=a.dtype, device=a.device)
-    nb = lib().dit_linear_workspace_bytes(M, Nn, K, dt, int(kernel_path)) if use_workspace else 0
+    nb = _bytes("dit_linear_workspace_bytes", M, Nn, K, dt, int(kernel_path)) if use_workspace else 0
     ws = _workspace(nb, a.device)
     _check(lib().dit_linear(_ptr(a), _ptr(w), _ptr(bias), _ptr(out), M, Nn, K, int(act), dt, int(kernel_path),
                             _ptr(ws), nb, _stream()), "dit_linear")
@@ -243,7 +256,7 @@ def sampler_step(x: torch.Tensor, eps: torch.Tensor, eps_prev: Optional[torch.Te
     if x_out is None:
         x_out = torch.empty_like(x)
     sums = torch.empty(4, dtype=torch.float32, device=x.device) if want_sums else None
-    nb = lib().sampler_step_workspace_bytes(n) if want_sums else 0
+    nb = _bytes("sampler_step_workspace_bytes", n) if want_sums else 0
     ws = _workspace(nb, x.device)
     _check(lib().sampler_step(_ptr(x), _ptr(eps), _ptr(eps_prev), _ptr(x_out), float(a), float(b), n, _ptr(sums),
                               _ptr(ws), nb, _stream()), "sampler_step")
@@ -261,7 +274,7 @@ def sampler_step_noalloc(x: torch.Tensor, eps: torch.Tensor, eps_prev: Optional[
 def rel_mae(a: torch.Tensor, b: torch.Tensor) -> torch.Tensor:
     n = a.numel()
     out = torch.empty(3, dtype=torch.float32, device=a.device)
-    nb = lib().rel_mae_workspace_bytes(n)
+    nb = _bytes("rel_mae_workspace_bytes", n)
     ws = _workspace(nb, a.device)
     _check(lib().rel_mae(_ptr(a), _ptr(b), n, _ptr(out), _ptr(ws), nb, _stream()), "rel_mae")
     return out
