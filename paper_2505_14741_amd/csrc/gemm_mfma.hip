@@ -4,7 +4,7 @@
 // row) is a single 16-byte LDS read.  A workgroup computes a BM x BN tile with WR x WC
 // waves, every wave owning (BM/WR) x (BN/WC) outputs as 16x16 v_mfma_f32_16x16x32_bf16 products
 // (a loop of nothing but these sustains 2.1 PFLOP/s on MI355X, the 32x32x16 form 1.85).
-// K is consumed 64 at a time through a two-stage LDS ring filled by direct global->LDS
+// K is consumed 64 at a time through an LDS ring of two stages (three of A on the wide tiles of a long K) filled by direct global->LDS
 // loads (global_load_lds_dwordx4: no staging registers, no ds_write): the loads of slice
 // k+1 are in flight while slice k is multiplied, one barrier per slice.  The A fragments
 // of the next 32-deep step are read into the registers of the current ones as soon as
@@ -268,8 +268,9 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 // One BM x BN output tile (rows m0.., columns n0..), k-tiles k0..k1-1 of 64, by the WR x WC waves of a workgroup,
 // each owning (BM/WR) x (BN/WC) outputs.  piece >= 0: a K-split piece, accumulators go to ep.split_ws.
-// BK: K depth of an LDS stage; NST: ring depth; lds: NST * (BM + BN) * 2 * BK bytes, 1024-aligned.
-template <int BM, int BN, int WR, int WC, int BK, int NST, int KIND>
+// BK: K depth of an LDS stage; lds: 1024-aligned.
+// NSA, NSW: stages in the LDS rings of A and of W; lds: (NSA * BM + NSW * BN) * 2 * BK bytes.
+template <int BM, int BN, int WR, int WC, int BK, int NSA, int NSW, int KIND>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, bf16_t* __restrict__ C,
                                           int M, int Nn, int K, int m0, int n0, int k0, int k1, int piece,
                                           const Epilogue& ep, unsigned char* lds) {
@@ -282,12 +283,15 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
     constexpr int CPR = ROWB / 16;                       // 16-byte chunks per row (8 or 4)
     constexpr int GROUPS = (BM + BN) / RPI;
     constexpr int GPW = GROUPS / NW;                     // load instructions per wave per stage
-    constexpr int STAGE = (BM + BN) * ROWB;
+    constexpr int STA = BM * ROWB, STW = BN * ROWB;      // bytes of an operand's stage
+    constexpr int GA = BM / RPI / NW, GB = BN / RPI / NW;            // load instructions per wave, stage and operand
+    constexpr int AHEAD = (NSA - 2) * GA + (NSW - 2) * GB;           // loads that may be out when the next stage is due
+    static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0 && NSA >= 2 && NSW == 2, "rings");
     static_assert(TN == 2 || TN == 4, "the epilogue handles strips of 64 columns");
     static_assert(GROUPS % NW == 0, "rows must split evenly over waves");
     static_assert(BM % RPI == 0, "a load group must not straddle the A/W boundary");
-    static_assert((NST - 1) * GPW <= 63, "vmcnt range");
-    static_assert(NW * EPI_LDS_FLOATS * 4 <= NST * STAGE, "epilogue patches reuse the stage memory");
+    static_assert(AHEAD + 8 <= 63, "vmcnt range");
+    static_assert(NW * EPI_LDS_FLOATS * 4 <= NSA * STA + NSW * STW, "epilogue patches reuse the stage memory");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -315,15 +319,20 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
         }
     }
     const unsigned lds_base = (unsigned)(size_t)PS_LDS_PTR(lds);
-    auto issue_one = [&](int kt, int i) {                // kt counts from k0; ring slot kt % NST; load group i of the wave
-        const int kc = k0 + kt < k1 ? k0 + kt : k1 - 1;  // (the prologue of a one-stage piece may ask past the end)
-        const unsigned st = lds_base + (kt % NST) * STAGE;
-        const int g = wave + NW * i;
-        lds_dma16(gp[i] + (long)kc * BK, __builtin_amdgcn_readfirstlane(st + g * 1024));
+    // load group i of the wave (A groups first), stage kt counted from k0, into ring slot `slot`
+    auto issue_one = [&](int kt, int slot, int i) {
+        const int kc = k0 + kt < k1 ? k0 + kt : k1 - 1;  // (the prologue of a short piece may ask past the end)
+        const unsigned at = i < GA ? lds_base + slot * STA + (wave + NW * i) * 1024
+                                   : lds_base + NSA * STA + slot * STW + (wave + NW * (i - GA)) * 1024;
+        lds_dma16(gp[i] + (long)kc * BK, __builtin_amdgcn_readfirstlane(at));
     };
-    auto issue = [&](int kt) {
+    auto issue_a = [&](int kt, int slot) {
 #pragma unroll
-        for (int i = 0; i < GPW; ++i) issue_one(kt, i);
+        for (int i = 0; i < GA; ++i) issue_one(kt, slot, i);
+    };
+    auto issue_w = [&](int kt, int slot) {
+#pragma unroll
+        for (int i = GA; i < GPW; ++i) issue_one(kt, slot, i);
     };
     // (Measured and dropped: a cache prefetch two or four stages ahead of the direct loads -- one 4-byte-per-lane
     // direct load per thread and stage into an LDS area nobody reads, lane r touching the line of row r.  It doubles
@@ -349,7 +358,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
 #pragma unroll
     for (int x = 0; x < FA; ++x) aoff[x] = (wm * WM + x * 16 + l16) * ROWB;
 #pragma unroll
-    for (int y = 0; y < FB; ++y) boff[y] = (BM + wn * WN + y * 16 + l16) * ROWB;
+    for (int y = 0; y < FB; ++y) boff[y] = NSA * STA + (wn * WN + y * 16 + l16) * ROWB;
     const int sw = (l16 >> 1) & 7;                       // the row offsets above are multiples of 16
     auto slot_of = [&](int ks) { return ((ks * 4 + kgrp) ^ sw) << 4; };
 
@@ -359,10 +368,14 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
     // whose operands are already in registers.
     bf16x8_t fa[FA], fb[2][FB];
 #pragma unroll
-    for (int p = 0; p < NST - 1; ++p) issue(p);
-    wait_vmcnt<(NST - 2) * GPW>();                       // own share of stage 0
+    for (int p = 0; p < NSA - 1; ++p) {                  // W of a stage before the A stages beyond it: loads return in order
+        if (p == 0) issue_w(0, 0);
+        issue_a(p, p);
+    }
+    wait_vmcnt<AHEAD>();                                 // own share of stage 0
     __syncthreads();
-    issue(NST - 1);
+    issue_w(1, 1);
+    issue_a(NSA - 1, NSA - 1);
     // Gated residual update on the narrow tile: the residual values of the wave's outputs are requested ahead of
     // the epilogue and sit in registers through the last stages (this tile has registers to spare).  Fetched in the
     // epilogue one strip ahead, their latency was exposed strip by strip: 32 us of the out-projection's 178, 45 us
@@ -383,15 +396,16 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
 #pragma unroll
         for (int y = 0; y < FB; ++y) fb[0][y] = *reinterpret_cast<const bf16x8_t*>(lds + boff[y] + slot);
     }
+    int slot_a = 0;                                      // ring slot of A of stage kt
     for (int kt = 0; kt < nkt; ++kt) {
-        const unsigned char* st = lds + (kt % NST) * STAGE;
-        const unsigned char* nx = lds + ((kt + 1) % NST) * STAGE;
+        const int sa = slot_a, sw_ = kt & 1, na = sa + 1 == NSA ? 0 : sa + 1;
+        slot_a = na;
         // no stage follows the last one: no hand-over there, and no loads for stages past the end (the fragment
         // reads of the last step then fetch stale, unused data from the other slot)
-        const bool more = kt + 1 < nkt, fill = kt + NST < nkt;
+        const bool more = kt + 1 < nkt, fill_a = kt + NSA < nkt, fill_w = kt + 2 < nkt;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            const unsigned char* src = st;               // where the next step's fragments come from
+            int from_a = sa * STA, from_w = sw_ * STW;   // where the next step's fragments come from
             // Direct loads into the slot the barrier frees: one workgroup per CU (8 waves) spreads them over the
             // fragment rounds of the stage's last step (in one block after the barrier they held this wave's MFMAs
             // back for ~30 instructions: QKV / fc1 shapes 6 % faster spread out); with two co-resident workgroups
@@ -399,11 +413,16 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
             constexpr bool SPREAD = NW >= 8;
             if (ks == 1) {
                 if (more) {
-                    if (PRE && have_pre && kt == nkt - 2) wait_vmcnt<(NST - 2) * GPW + 8>();   // strip 0's loads may stay out
-                    else wait_vmcnt<(NST - 2) * GPW>();  // own share of stage kt+1 has landed
+                    // own share of stage kt+1 has landed; A of later stages, and strip 0's loads, may stay out
+                    if (PRE && have_pre && kt == nkt - 2) wait_vmcnt<8>();
+                    else if (AHEAD > 0 && kt + 2 < nkt) wait_vmcnt<AHEAD>();
+                    else wait_vmcnt<0>();
                     __syncthreads();                     // ... everyone's; and nobody reads stage kt any more
                 }
-                if constexpr (!SPREAD) { if (fill) issue(kt + NST); }   // into the slot stage kt occupied
+                if constexpr (!SPREAD) {                 // into the slots stage kt occupied
+                    if (fill_w) issue_w(kt + 2, sw_);
+                    if (fill_a) issue_a(kt + NSA, sa);
+                }
                 if constexpr (PRE) {
                     if (have_pre && kt >= nkt - 3 && kt <= nkt - 2) {
                         const bool first = kt == nkt - 3;
@@ -414,19 +433,19 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
                         }
                     }
                 }
-                src = nx;
+                from_a = na * STA; from_w = (sw_ ^ 1) * STW;
                 __builtin_amdgcn_sched_barrier(0);       // hand-over code stays ahead of the MFMAs
             }
             const int slot = slot_of(ks ^ 1);
             if constexpr (!SPREAD) {
 #pragma unroll
                 for (int x = 0; x < FA; ++x) {
-                    if (x < FB) fb[ks ^ 1][x] = *reinterpret_cast<const bf16x8_t*>(src + boff[x] + slot);
+                    if (x < FB) fb[ks ^ 1][x] = *reinterpret_cast<const bf16x8_t*>(lds + from_w + boff[x] + slot);
 #pragma unroll
                     for (int y = 0; y < FB; ++y)
                         acc[x >> 1][y >> 1][(x & 1) * 2 + (y & 1)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                             fa[x], fb[ks][y], acc[x >> 1][y >> 1][(x & 1) * 2 + (y & 1)], 0, 0, 0);
-                    fa[x] = *reinterpret_cast<const bf16x8_t*>(src + aoff[x] + slot);
+                    fa[x] = *reinterpret_cast<const bf16x8_t*>(lds + from_a + aoff[x] + slot);
                 }
 #pragma unroll
                 for (int x = 0; x < FA; ++x) {           // FB MFMAs, then the LDS reads of the round
@@ -446,12 +465,15 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
                 for (int y = 0; y < FB; ++y)
                     acc[x >> 1][y >> 1][(x & 1) * 2 + (y & 1)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                         fa[x], fb[ks][y], acc[x >> 1][y >> 1][(x & 1) * 2 + (y & 1)], 0, 0, 0);
-                if (x < FB) fb[ks ^ 1][x] = *reinterpret_cast<const bf16x8_t*>(src + boff[x] + slot);
-                fa[x] = *reinterpret_cast<const bf16x8_t*>(src + aoff[x] + slot);
-                if (ks == 1 && fill) {
+                if (x < FB) fb[ks ^ 1][x] = *reinterpret_cast<const bf16x8_t*>(lds + from_w + boff[x] + slot);
+                fa[x] = *reinterpret_cast<const bf16x8_t*>(lds + from_a + aoff[x] + slot);
+                if (ks == 1) {                           // W first (see the prologue)
 #pragma unroll
-                    for (int d = 0; d < DPR; ++d)
-                        if (x * DPR + d < GPW) issue_one(kt + NST, x * DPR + d);
+                    for (int d = 0; d < DPR; ++d) {
+                        const int i = x * DPR + d;
+                        if (i < GB) { if (fill_w) issue_one(kt + 2, sw_, GA + i); }
+                        else if (i < GPW) { if (fill_a) issue_one(kt + NSA, sa, i - GB); }
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -514,11 +536,11 @@ __device__ __forceinline__ void shift_to_sample(Epilogue& ep, int sample, int to
     }
 }
 
-template <int BM, int BN, int WR, int WC, int BK, int NST, int KIND>
+template <int BM, int BN, int WR, int WC, int BK, int NSA, int KIND>
 __global__ void __launch_bounds__(WR * WC * 64, (WR * WC == 4 && BM * BN <= 192 * 128) ? 2 : 1)
 gemm_mfma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, bf16_t* __restrict__ C,
                  int Nn, int K, GemmGrid g, Epilogue ep) {
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * (BM + BN) * BK * 2];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[(NSA * BM + 2 * BN) * BK * 2];
     const int nk = K / BK;
     const int all_full = g.batch * g.full_tiles;
     int sample, tile, piece = -1, k0 = 0, k1 = nk;
@@ -542,7 +564,7 @@ gemm_mfma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, bf1
     shift_to_sample<KIND>(ep, sample, g.tokens, Nn);
     int m0, n0;
     tile_origin(tile, g.tiles_m, g.tiles_n, BM, BN, m0, n0);
-    gemm_tile<BM, BN, WR, WC, BK, NST, KIND>(A, W, C, g.tokens, Nn, K, m0, n0, k0, k1, piece, ep, lds);
+    gemm_tile<BM, BN, WR, WC, BK, NSA, 2, KIND>(A, W, C, g.tokens, Nn, K, m0, n0, k0, k1, piece, ep, lds);
 }
 
 // Sums the K-split pieces of the tail tiles (fixed order: deterministic) and applies the epilogue; one single-wave
@@ -649,28 +671,28 @@ size_t gemm_tiles_workspace_bytes(int batch, int tokens, int Nn, int K, int path
 hipError_t launch_gemm_few(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K, int tile,
                            int nsplit, bool inreg, const Epilogue& ep, int* deferred, hipStream_t st);
 
-template <int BM, int BN, int WR, int WC, int BK, int NST, int KIND>
+template <int BM, int BN, int WR, int WC, int BK, int NSA, int KIND>
 static hipError_t launch_kind(const bf16_t* A, const bf16_t* W, bf16_t* C, int batch, int tokens, int Nn, int K,
                               const GemmPlan& p, const Epilogue& ep, hipStream_t st) {
     dim3 block(WR * WC * 64);
     const GemmGrid g{tokens, batch, p.tiles_m, p.tiles_n, p.full, p.tail, p.nsplit};
     const int grid = batch * (p.full + p.tail * p.nsplit);
-    gemm_mfma_kernel<BM, BN, WR, WC, BK, NST, KIND><<<grid, block, 0, st>>>(A, W, C, Nn, K, g, ep);
+    gemm_mfma_kernel<BM, BN, WR, WC, BK, NSA, KIND><<<grid, block, 0, st>>>(A, W, C, Nn, K, g, ep);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.tail == 0) return e;
     gemm_tail_kernel<BM, BN, WR, WC, KIND><<<batch * p.tail * (WR * WC) * (BM / WR / 32), 64, 0, st>>>(C, Nn, g, ep);
     return hipGetLastError();
 }
 
-template <int BM, int BN, int WR, int WC, int BK, int NST>
+template <int BM, int BN, int WR, int WC, int BK, int NSA>
 static hipError_t launch_tile(const bf16_t* A, const bf16_t* W, bf16_t* C, int batch, int tokens, int Nn, int K,
                               const GemmPlan& p, const Epilogue& ep, hipStream_t st) {
     switch (ep.kind) {
-        case EPI_BIAS: return launch_kind<BM, BN, WR, WC, BK, NST, EPI_BIAS>(A, W, C, batch, tokens, Nn, K, p, ep, st);
-        case EPI_BIAS_GELU: return launch_kind<BM, BN, WR, WC, BK, NST, EPI_BIAS_GELU>(A, W, C, batch, tokens, Nn, K, p, ep, st);
-        case EPI_GATE_RESIDUAL: return launch_kind<BM, BN, WR, WC, BK, NST, EPI_GATE_RESIDUAL>(A, W, C, batch, tokens, Nn, K, p, ep, st);
-        case EPI_QKV_ROPE: return launch_kind<BM, BN, WR, WC, BK, NST, EPI_QKV_ROPE>(A, W, C, batch, tokens, Nn, K, p, ep, st);
-        case EPI_UNPATCHIFY: return launch_kind<BM, BN, WR, WC, BK, NST, EPI_UNPATCHIFY>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+        case EPI_BIAS: return launch_kind<BM, BN, WR, WC, BK, NSA, EPI_BIAS>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+        case EPI_BIAS_GELU: return launch_kind<BM, BN, WR, WC, BK, NSA, EPI_BIAS_GELU>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+        case EPI_GATE_RESIDUAL: return launch_kind<BM, BN, WR, WC, BK, NSA, EPI_GATE_RESIDUAL>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+        case EPI_QKV_ROPE: return launch_kind<BM, BN, WR, WC, BK, NSA, EPI_QKV_ROPE>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+        case EPI_UNPATCHIFY: return launch_kind<BM, BN, WR, WC, BK, NSA, EPI_UNPATCHIFY>(A, W, C, batch, tokens, Nn, K, p, ep, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -696,10 +718,19 @@ hipError_t launch_gemm_mfma(const bf16_t* A, const bf16_t* W, bf16_t* C, int bat
         p.tiles_n = (Nn + kTiles[p.tile].bn - 1) / kTiles[p.tile].bn;
         p.full = p.tiles_m * p.tiles_n;
     }
+    const bool long_k = K >= 4096;
     switch (p.tile - WIDE_256x256 + 1) {
-        case 1: return launch_tile<256, 256, 2, 4, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 8 waves, 128x64 each
+        // The wide tiles of a long K keep three stages of A in flight beside two of W, all of a CU's LDS (or most): A comes from
+        // further away, W is shared by the row tiles of a band.  1920 x 7680: 495 -> 477 us at 17776 rows, 921 -> 868 at
+        // 33976 on 256 x 256 tiles, 507 -> 482 and 1005 -> 962 on 192 x 256.  Not with K = 1920 (5760 and 7680 columns, 17776
+        // rows: 359 -> 362, 447 -> 453 us) nor where two workgroups share a CU (128 x 128, 1920 x 7680: 523 -> 558).
+        case 1:                                                                                          // 8 waves, 128x64 each
+            if (long_k) return launch_tile<256, 256, 2, 4, 64, 3>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+            return launch_tile<256, 256, 2, 4, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);
         case 2: return launch_tile<128, 128, 2, 2, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 4 waves, 64x64 each, 2 per CU
-        case 3: return launch_tile<192, 256, 2, 4, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 8 waves, 96x64 each
+        case 3:                                                                                          // 8 waves, 96x64 each
+            if (long_k) return launch_tile<192, 256, 2, 4, 64, 3>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+            return launch_tile<192, 256, 2, 4, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);
         case 4: return launch_tile<192, 128, 2, 2, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 4 waves, 96x64 each, 2 per CU
         // Measured and dropped: 4 waves of 128x128 outputs on the 256x256 tile (fewer LDS reads per MFMA; with the
         // 32x32x16 MFMA one wave per SIMD issued one only every ~48 cycles: 5-15 % slower; with 16x16x32 the 256
