@@ -38,38 +38,44 @@ enum TileId { FEW_64x64, FEW_128x64, FEW_128x128, FEW_192x128, FEW_256x128, FEW_
               WIDE_256x256 = FEW_TILE_KINDS, WIDE_128x128, WIDE_192x256, WIDE_192x128, TILE_KINDS };
 // Measured us of a round of workgroups, one tile each: fixed + stages of 64 k * stage.  per_cu = 2: two workgroups share a
 // CU; `half`: a round that leaves at most one to each.  (bf16, operands that change from call to call, 32 to 9000 rows x
-// 1920 to 7680 columns x K = 1920 and 7680.)
-struct Tile { int bm, bn, per_cu; float half_fixed, half_stage, fixed, stage; };
+// 1920 to 7680 columns x K = 1920 and 7680.)  gated: what an epilogue that reads and writes an fp32 residual adds to a round
+// (17776 rows x 1920, K = 1920: 184, 170, 164 and 168 us on the tiles of gemm_mfma.hip in their order below).
+struct Tile { int bm, bn, per_cu; float half_fixed, half_stage, fixed, stage, gated; };
 constexpr Tile kTiles[TILE_KINDS] = {
-    {64, 64, 2, 3.0f, 0.235f, 4.5f, 0.40f},              // 8 waves of 16 x 32
-    {128, 64, 1, 0.f, 0.f, 4.0f, 0.30f},                 // 8 waves of 32 x 32
-    {128, 128, 1, 0.f, 0.f, 6.0f, 0.47f},                // 8 waves of 32 x 64
-    {192, 128, 1, 0.f, 0.f, 7.0f, 0.60f},                // 8 waves of 48 x 64
-    {256, 128, 1, 0.f, 0.f, 8.7f, 0.76f},                // 8 waves of 64 x 64
-    {192, 192, 1, 0.f, 0.f, 9.0f, 0.90f},                // 8 waves of 48 x 96
-    {256, 256, 1, 0.f, 0.f, 7.3f, 1.34f},                // gemm_mfma.hip: 8 waves of 128 x 64
-    {128, 128, 2, 2.0f, 0.80f, 4.0f, 0.90f},             // 4 waves of 64 x 64
-    {192, 256, 1, 0.f, 0.f, 8.7f, 1.13f},                // 8 waves of 96 x 64
-    {192, 128, 2, 2.0f, 0.88f, 4.6f, 1.30f},             // 4 waves of 96 x 64
+    {64, 64, 2, 3.0f, 0.235f, 4.5f, 0.40f, 1.9f},        // 8 waves of 16 x 32
+    {128, 64, 1, 0.f, 0.f, 4.0f, 0.30f, 1.9f},           // 8 waves of 32 x 32
+    {128, 128, 1, 0.f, 0.f, 6.0f, 0.47f, 3.8f},          // 8 waves of 32 x 64
+    {192, 128, 1, 0.f, 0.f, 7.0f, 0.60f, 5.7f},          // 8 waves of 48 x 64
+    {256, 128, 1, 0.f, 0.f, 8.7f, 0.76f, 7.5f},          // 8 waves of 64 x 64
+    {192, 192, 1, 0.f, 0.f, 9.0f, 0.90f, 8.5f},          // 8 waves of 48 x 96
+    {256, 256, 1, 0.f, 0.f, 7.3f, 1.34f, 15.f},          // gemm_mfma.hip: 8 waves of 128 x 64
+    {128, 128, 2, 2.0f, 0.80f, 4.0f, 0.92f, 7.5f},       // 4 waves of 64 x 64
+    {192, 256, 1, 0.f, 0.f, 8.7f, 1.14f, 11.3f},         // 8 waves of 96 x 64
+    {192, 128, 2, 2.0f, 0.88f, 3.0f, 1.367f, 16.f},      // 4 waves of 96 x 64
 };
 constexpr long tile_count(int id, long rows, int Nn) {
     return (rows + kTiles[id].bm - 1) / kTiles[id].bm * ((Nn + kTiles[id].bn - 1) / kTiles[id].bn);
 }
-// Estimated us of `wgs` workgroups of `stages` stages each on `cus` compute units (without what launching takes).  gated: the
-// epilogue reads and writes an fp32 residual, 0.23 ns per output of a CU (17776 rows x 1920: 184, 164 and 168 us on the tiles
-// of 256 x 256, 192 x 256 and 192 x 128, with a plain epilogue 0.12 to 0.14 ms).
+// Estimated us of `wgs` workgroups of `stages` stages each on `cus` compute units (without what launching takes).
 constexpr float tile_time(int id, long wgs, float stages, bool gated, int cus) {
     const Tile& t = kTiles[id];
     const long slots = (long)cus * t.per_cu, tail = wgs % slots;
-    const float epi = gated ? 2.3e-4f * t.bm * t.bn : 0.f;
+    const float epi = gated ? t.gated : 0.f;
     // (gemm_few.hip over more than two rounds: the chip at its power limit, and its smaller wave tiles read more LDS per
     // product: 41728 rows, 1920 x 7680 on 256 x 128 tiles 1323 us, on 192 x 256 of gemm_mfma.hip 1229)
     const float many = id < FEW_TILE_KINDS && wgs > 2 * slots ? 1.15f : 1.f;
-    const float full = many * (t.fixed + stages * t.stage) + epi * t.per_cu, half = t.half_fixed + stages * t.half_stage + epi;
-    return (float)(wgs / slots) * full + (tail == 0 ? 0.f : t.per_cu == 2 && tail <= cus ? half : full);
+    const float full = many * (t.fixed + stages * t.stage) + epi;
+    const float half = t.half_fixed + stages * t.half_stage + 0.5f * epi;
+    float last = tail == 0 ? 0.f : full;
+    if (t.per_cu == 2 && tail > 0) {                     // two per CU do not start a last round together
+        const float share = (float)(tail <= cus ? tail : tail - cus) / cus;
+        if (wgs < slots) last = tail <= cus ? half : 0.9f * full;
+        else last = tail <= cus ? half * (0.5f + 0.5f * share) : half + (full - half) * share;
+    }
+    return (float)(wgs / slots) * full + last;
 }
 // The bf16 tile with the least estimated time: `pieces` workgroups per tile along K; [first, last]: the kinds to choose from.
-// At the sizes above it misses the fastest one by 1 % on average and 6 % at most.
+// At the sizes above it misses the fastest one by 0.4 % on average and 6 % at most.
 constexpr int best_tile(int first, int last, long rows, int Nn, int K, int pieces, bool gated, int cus) {
     int best = first;
     float least = 0.f;
