@@ -4,7 +4,7 @@
 // row) is a single 16-byte LDS read.  A workgroup computes a BM x BN tile with WR x WC
 // waves, every wave owning (BM/WR) x (BN/WC) outputs as 16x16 v_mfma_f32_16x16x32_bf16 products
 // (a loop of nothing but these sustains 2.1 PFLOP/s on MI355X, the 32x32x16 form 1.85).
-// K is consumed 64 at a time through an LDS ring of two stages (three of A on the wide tiles of a long K) filled by direct global->LDS
+// K is consumed 64 at a time through an LDS ring of two stages (three of one operand on wide tiles) filled by direct global->LDS
 // loads (global_load_lds_dwordx4: no staging registers, no ds_write): the loads of slice
 // k+1 are in flight while slice k is multiplied, one barrier per slice.  The A fragments
 // of the next 32-deep step are read into the registers of the current ones as soon as
@@ -269,7 +269,11 @@ __device__ __forceinline__ void wait_vmcnt() {
 // One BM x BN output tile (rows m0.., columns n0..), k-tiles k0..k1-1 of 64, by the WR x WC waves of a workgroup,
 // each owning (BM/WR) x (BN/WC) outputs.  piece >= 0: a K-split piece, accumulators go to ep.split_ws.
 // BK: K depth of an LDS stage; lds: 1024-aligned.
-// NSA, NSW: stages in the LDS rings of A and of W; lds: (NSA * BM + NSW * BN) * 2 * BK bytes.
+// NSA, NSW: stages in the LDS rings of A and of W, at most one of them above two.  lds: (NSA * BM + NSW * BN) * 2 * BK bytes.
+// Rings of one depth keep A and W of a stage together, so that one slot offset serves both (256 x 256 tiles, 4516 and 8326
+// rows, K = 1920: 1 % faster than rings of their own); of two depths, the shallow ring's loads of a stage are requested
+// before the deep ring's of the next, because loads return in order.  Else W is requested first, it comes from further away
+// (5760 x 1920, 2992 rows, weights that change from call to call: 79.8 -> 76.8 us).
 template <int BM, int BN, int WR, int WC, int BK, int NSA, int NSW, int KIND>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, bf16_t* __restrict__ C,
                                           int M, int Nn, int K, int m0, int n0, int k0, int k1, int piece,
@@ -285,8 +289,12 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
     constexpr int GPW = GROUPS / NW;                     // load instructions per wave per stage
     constexpr int STA = BM * ROWB, STW = BN * ROWB;      // bytes of an operand's stage
     constexpr int GA = BM / RPI / NW, GB = BN / RPI / NW;            // load instructions per wave, stage and operand
-    constexpr int AHEAD = (NSA - 2) * GA + (NSW - 2) * GB;           // loads that may be out when the next stage is due
-    static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0 && NSA >= 2 && NSW == 2, "rings");
+    constexpr int AHEAD = (NSA - 2) * GA + (NSW - 2) * GB;              // loads that may be out when the next stage is due
+    constexpr bool JOINT = NSA == NSW;
+    constexpr int DEEP = NSW > 2 ? NSW : NSA;
+    constexpr int STEP_A = JOINT ? STA + STW : STA, STEP_W = JOINT ? STA + STW : STW;   // bytes from slot to slot
+    constexpr int BASE_W = JOINT ? STA : NSA * STA;      // where W's slot 0 begins
+    static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0 && NSA >= 2 && NSW >= 2 && (NSA == 2 || NSW == 2), "rings");
     static_assert(TN == 2 || TN == 4, "the epilogue handles strips of 64 columns");
     static_assert(GROUPS % NW == 0, "rows must split evenly over waves");
     static_assert(BM % RPI == 0, "a load group must not straddle the A/W boundary");
@@ -322,8 +330,8 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
     // load group i of the wave (A groups first), stage kt counted from k0, into ring slot `slot`
     auto issue_one = [&](int kt, int slot, int i) {
         const int kc = k0 + kt < k1 ? k0 + kt : k1 - 1;  // (the prologue of a short piece may ask past the end)
-        const unsigned at = i < GA ? lds_base + slot * STA + (wave + NW * i) * 1024
-                                   : lds_base + NSA * STA + slot * STW + (wave + NW * (i - GA)) * 1024;
+        const unsigned at = i < GA ? lds_base + slot * STEP_A + (wave + NW * i) * 1024
+                                   : lds_base + BASE_W + slot * STEP_W + (wave + NW * (i - GA)) * 1024;
         lds_dma16(gp[i] + (long)kc * BK, __builtin_amdgcn_readfirstlane(at));
     };
     auto issue_a = [&](int kt, int slot) {
@@ -358,7 +366,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
 #pragma unroll
     for (int x = 0; x < FA; ++x) aoff[x] = (wm * WM + x * 16 + l16) * ROWB;
 #pragma unroll
-    for (int y = 0; y < FB; ++y) boff[y] = NSA * STA + (wn * WN + y * 16 + l16) * ROWB;
+    for (int y = 0; y < FB; ++y) boff[y] = BASE_W + (wn * WN + y * 16 + l16) * ROWB;
     const int sw = (l16 >> 1) & 7;                       // the row offsets above are multiples of 16
     auto slot_of = [&](int ks) { return ((ks * 4 + kgrp) ^ sw) << 4; };
 
@@ -368,14 +376,15 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
     // whose operands are already in registers.
     bf16x8_t fa[FA], fb[2][FB];
 #pragma unroll
-    for (int p = 0; p < NSA - 1; ++p) {                  // W of a stage before the A stages beyond it: loads return in order
-        if (p == 0) issue_w(0, 0);
-        issue_a(p, p);
+    for (int p = 0; p < DEEP - 1; ++p) {
+        if (NSW > NSA && p < NSA - 1) issue_a(p, p);
+        if (p < NSW - 1) issue_w(p, p);
+        if (NSW <= NSA && p < NSA - 1) issue_a(p, p);
     }
     wait_vmcnt<AHEAD>();                                 // own share of stage 0
     __syncthreads();
-    issue_w(1, 1);
-    issue_a(NSA - 1, NSA - 1);
+    if constexpr (NSW > NSA) { issue_a(NSA - 1, NSA - 1); issue_w(NSW - 1, NSW - 1); }
+    else { issue_w(NSW - 1, NSW - 1); issue_a(NSA - 1, NSA - 1); }
     // Gated residual update on the narrow tile: the residual values of the wave's outputs are requested ahead of
     // the epilogue and sit in registers through the last stages (this tile has registers to spare).  Fetched in the
     // epilogue one strip ahead, their latency was exposed strip by strip: 32 us of the out-projection's 178, 45 us
@@ -396,16 +405,17 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
 #pragma unroll
         for (int y = 0; y < FB; ++y) fb[0][y] = *reinterpret_cast<const bf16x8_t*>(lds + boff[y] + slot);
     }
-    int slot_a = 0;                                      // ring slot of A of stage kt
+    int slot_d = 0;                                      // deep ring's slot of stage kt
     for (int kt = 0; kt < nkt; ++kt) {
-        const int sa = slot_a, sw_ = kt & 1, na = sa + 1 == NSA ? 0 : sa + 1;
-        slot_a = na;
+        const int s2 = kt & 1, sd = JOINT ? s2 : slot_d, nd = JOINT ? s2 ^ 1 : sd + 1 == DEEP ? 0 : sd + 1;
+        const int sa = NSA > 2 ? sd : s2, na = NSA > 2 ? nd : s2 ^ 1, sw_ = NSW > 2 ? sd : s2, nw = NSW > 2 ? nd : s2 ^ 1;
+        slot_d = nd;
         // no stage follows the last one: no hand-over there, and no loads for stages past the end (the fragment
         // reads of the last step then fetch stale, unused data from the other slot)
-        const bool more = kt + 1 < nkt, fill_a = kt + NSA < nkt, fill_w = kt + 2 < nkt;
+        const bool more = kt + 1 < nkt, fill_a = kt + NSA < nkt, fill_w = kt + NSW < nkt;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            int from_a = sa * STA, from_w = sw_ * STW;   // where the next step's fragments come from
+            int from_a = sa * STEP_A, from_w = sw_ * STEP_W;   // where the next step's fragments come from
             // Direct loads into the slot the barrier frees: one workgroup per CU (8 waves) spreads them over the
             // fragment rounds of the stage's last step (in one block after the barrier they held this wave's MFMAs
             // back for ~30 instructions: QKV / fc1 shapes 6 % faster spread out); with two co-resident workgroups
@@ -420,8 +430,8 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
                     __syncthreads();                     // ... everyone's; and nobody reads stage kt any more
                 }
                 if constexpr (!SPREAD) {                 // into the slots stage kt occupied
-                    if (fill_w) issue_w(kt + 2, sw_);
-                    if (fill_a) issue_a(kt + NSA, sa);
+                    static_assert(SPREAD || JOINT, "rings of one depth");
+                    if (fill_a) { issue_w(kt + NSW, sw_); issue_a(kt + NSA, sa); }
                 }
                 if constexpr (PRE) {
                     if (have_pre && kt >= nkt - 3 && kt <= nkt - 2) {
@@ -433,7 +443,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
                         }
                     }
                 }
-                from_a = na * STA; from_w = (sw_ ^ 1) * STW;
+                from_a = na * STEP_A; from_w = nw * STEP_W;
                 __builtin_amdgcn_sched_barrier(0);       // hand-over code stays ahead of the MFMAs
             }
             const int slot = slot_of(ks ^ 1);
@@ -467,12 +477,12 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
                         fa[x], fb[ks][y], acc[x >> 1][y >> 1][(x & 1) * 2 + (y & 1)], 0, 0, 0);
                 if (x < FB) fb[ks ^ 1][x] = *reinterpret_cast<const bf16x8_t*>(lds + from_w + boff[x] + slot);
                 fa[x] = *reinterpret_cast<const bf16x8_t*>(lds + from_a + aoff[x] + slot);
-                if (ks == 1) {                           // W first (see the prologue)
+                if (ks == 1) {
 #pragma unroll
                     for (int d = 0; d < DPR; ++d) {
                         const int i = x * DPR + d;
-                        if (i < GB) { if (fill_w) issue_one(kt + 2, sw_, GA + i); }
-                        else if (i < GPW) { if (fill_a) issue_one(kt + NSA, sa, i - GB); }
+                        const int g = NSW > NSA ? i : i < GB ? GA + i : i - GB;
+                        if (i < GPW && (g < GA ? fill_a : fill_w)) issue_one(kt + (g < GA ? NSA : NSW), g < GA ? sa : sw_, g);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -536,11 +546,11 @@ __device__ __forceinline__ void shift_to_sample(Epilogue& ep, int sample, int to
     }
 }
 
-template <int BM, int BN, int WR, int WC, int BK, int NSA, int KIND>
+template <int BM, int BN, int WR, int WC, int BK, int NSA, int NSW, int KIND>
 __global__ void __launch_bounds__(WR * WC * 64, (WR * WC == 4 && BM * BN <= 192 * 128) ? 2 : 1)
 gemm_mfma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, bf16_t* __restrict__ C,
                  int Nn, int K, GemmGrid g, Epilogue ep) {
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[(NSA * BM + 2 * BN) * BK * 2];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[(NSA * BM + NSW * BN) * BK * 2];
     const int nk = K / BK;
     const int all_full = g.batch * g.full_tiles;
     int sample, tile, piece = -1, k0 = 0, k1 = nk;
@@ -564,7 +574,7 @@ gemm_mfma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, bf1
     shift_to_sample<KIND>(ep, sample, g.tokens, Nn);
     int m0, n0;
     tile_origin(tile, g.tiles_m, g.tiles_n, BM, BN, m0, n0);
-    gemm_tile<BM, BN, WR, WC, BK, NSA, 2, KIND>(A, W, C, g.tokens, Nn, K, m0, n0, k0, k1, piece, ep, lds);
+    gemm_tile<BM, BN, WR, WC, BK, NSA, NSW, KIND>(A, W, C, g.tokens, Nn, K, m0, n0, k0, k1, piece, ep, lds);
 }
 
 // Sums the K-split pieces of the tail tiles (fixed order: deterministic) and applies the epilogue; one single-wave
@@ -671,28 +681,28 @@ size_t gemm_tiles_workspace_bytes(int batch, int tokens, int Nn, int K, int path
 hipError_t launch_gemm_few(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K, int tile,
                            int nsplit, bool inreg, const Epilogue& ep, int* deferred, hipStream_t st);
 
-template <int BM, int BN, int WR, int WC, int BK, int NSA, int KIND>
+template <int BM, int BN, int WR, int WC, int BK, int NSA, int NSW, int KIND>
 static hipError_t launch_kind(const bf16_t* A, const bf16_t* W, bf16_t* C, int batch, int tokens, int Nn, int K,
                               const GemmPlan& p, const Epilogue& ep, hipStream_t st) {
     dim3 block(WR * WC * 64);
     const GemmGrid g{tokens, batch, p.tiles_m, p.tiles_n, p.full, p.tail, p.nsplit};
     const int grid = batch * (p.full + p.tail * p.nsplit);
-    gemm_mfma_kernel<BM, BN, WR, WC, BK, NSA, KIND><<<grid, block, 0, st>>>(A, W, C, Nn, K, g, ep);
+    gemm_mfma_kernel<BM, BN, WR, WC, BK, NSA, NSW, KIND><<<grid, block, 0, st>>>(A, W, C, Nn, K, g, ep);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.tail == 0) return e;
     gemm_tail_kernel<BM, BN, WR, WC, KIND><<<batch * p.tail * (WR * WC) * (BM / WR / 32), 64, 0, st>>>(C, Nn, g, ep);
     return hipGetLastError();
 }
 
-template <int BM, int BN, int WR, int WC, int BK, int NSA>
+template <int BM, int BN, int WR, int WC, int BK, int NSA, int NSW = 2>
 static hipError_t launch_tile(const bf16_t* A, const bf16_t* W, bf16_t* C, int batch, int tokens, int Nn, int K,
                               const GemmPlan& p, const Epilogue& ep, hipStream_t st) {
     switch (ep.kind) {
-        case EPI_BIAS: return launch_kind<BM, BN, WR, WC, BK, NSA, EPI_BIAS>(A, W, C, batch, tokens, Nn, K, p, ep, st);
-        case EPI_BIAS_GELU: return launch_kind<BM, BN, WR, WC, BK, NSA, EPI_BIAS_GELU>(A, W, C, batch, tokens, Nn, K, p, ep, st);
-        case EPI_GATE_RESIDUAL: return launch_kind<BM, BN, WR, WC, BK, NSA, EPI_GATE_RESIDUAL>(A, W, C, batch, tokens, Nn, K, p, ep, st);
-        case EPI_QKV_ROPE: return launch_kind<BM, BN, WR, WC, BK, NSA, EPI_QKV_ROPE>(A, W, C, batch, tokens, Nn, K, p, ep, st);
-        case EPI_UNPATCHIFY: return launch_kind<BM, BN, WR, WC, BK, NSA, EPI_UNPATCHIFY>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+        case EPI_BIAS: return launch_kind<BM, BN, WR, WC, BK, NSA, NSW, EPI_BIAS>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+        case EPI_BIAS_GELU: return launch_kind<BM, BN, WR, WC, BK, NSA, NSW, EPI_BIAS_GELU>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+        case EPI_GATE_RESIDUAL: return launch_kind<BM, BN, WR, WC, BK, NSA, NSW, EPI_GATE_RESIDUAL>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+        case EPI_QKV_ROPE: return launch_kind<BM, BN, WR, WC, BK, NSA, NSW, EPI_QKV_ROPE>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+        case EPI_UNPATCHIFY: return launch_kind<BM, BN, WR, WC, BK, NSA, NSW, EPI_UNPATCHIFY>(A, W, C, batch, tokens, Nn, K, p, ep, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -724,13 +734,17 @@ hipError_t launch_gemm_mfma(const bf16_t* A, const bf16_t* W, bf16_t* C, int bat
         // further away, W is shared by the row tiles of a band.  1920 x 7680: 495 -> 477 us at 17776 rows, 921 -> 868 at
         // 33976 on 256 x 256 tiles, 507 -> 482 and 1005 -> 962 on 192 x 256.  Not with K = 1920 (5760 and 7680 columns, 17776
         // rows: 359 -> 362, 447 -> 453 us) nor where two workgroups share a CU (128 x 128, 1920 x 7680: 523 -> 558).
+        // K = 1920 on 192 x 256: three stages of W, whose weights come from memory once per layer while A was just written.
+        // Weights that change from call to call: 7680 columns, 4516 rows 134.4 -> 127.6 us, 5760, 6016 rows 129.1 -> 121.9
+        // (192 x 128 tiles: 131.5 and 125.5); the same weights in every call 126.3 -> 127.5 and 120.3 -> 122.2.  Not on 256 x
+        // 256 (7680 columns, 4516 rows 145 -> 151 us; 17776 rows 465 -> 470).
         case 1:                                                                                          // 8 waves, 128x64 each
             if (long_k) return launch_tile<256, 256, 2, 4, 64, 3>(A, W, C, batch, tokens, Nn, K, p, ep, st);
             return launch_tile<256, 256, 2, 4, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);
         case 2: return launch_tile<128, 128, 2, 2, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 4 waves, 64x64 each, 2 per CU
         case 3:                                                                                          // 8 waves, 96x64 each
             if (long_k) return launch_tile<192, 256, 2, 4, 64, 3>(A, W, C, batch, tokens, Nn, K, p, ep, st);
-            return launch_tile<192, 256, 2, 4, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+            return launch_tile<192, 256, 2, 4, 64, 2, 3>(A, W, C, batch, tokens, Nn, K, p, ep, st);
         case 4: return launch_tile<192, 128, 2, 2, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 4 waves, 96x64 each, 2 per CU
         // Measured and dropped: 4 waves of 128x128 outputs on the 256x256 tile (fewer LDS reads per MFMA; with the
         // 32x32x16 MFMA one wave per SIMD issued one only every ~48 cycles: 5-15 % slower; with 16x16x32 the 256

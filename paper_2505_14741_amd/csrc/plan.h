@@ -50,8 +50,8 @@ constexpr Tile kTiles[TILE_KINDS] = {
     {192, 192, 1, 0.f, 0.f, 9.0f, 0.90f, 8.5f},          // 8 waves of 48 x 96
     {256, 256, 1, 0.f, 0.f, 7.3f, 1.34f, 15.f},          // gemm_mfma.hip: 8 waves of 128 x 64
     {128, 128, 2, 2.0f, 0.80f, 4.0f, 0.92f, 7.5f},       // 4 waves of 64 x 64
-    {192, 256, 1, 0.f, 0.f, 8.7f, 1.14f, 11.3f},         // 8 waves of 96 x 64
-    {192, 128, 2, 2.0f, 0.88f, 3.0f, 1.367f, 16.f},      // 4 waves of 96 x 64
+    {192, 256, 1, 0.f, 0.f, 7.4f, 1.14f, 12.6f},         // 8 waves of 96 x 64
+    {192, 128, 2, 2.0f, 0.88f, 4.0f, 1.367f, 15.f},      // 4 waves of 96 x 64
 };
 constexpr long tile_count(int id, long rows, int Nn) {
     return (rows + kTiles[id].bm - 1) / kTiles[id].bm * ((Nn + kTiles[id].bn - 1) / kTiles[id].bn);
