@@ -728,22 +728,26 @@ hipError_t launch_gemm_mfma(const bf16_t* A, const bf16_t* W, bf16_t* C, int bat
         p.tiles_n = (Nn + kTiles[p.tile].bn - 1) / kTiles[p.tile].bn;
         p.full = p.tiles_m * p.tiles_n;
     }
-    const bool long_k = K >= 4096;
+    const bool long_k = K >= 4096, rounds = (long)batch * p.tiles_m * p.tiles_n > compute_units();
     switch (p.tile - WIDE_256x256 + 1) {
         // The wide tiles of a long K keep three stages of A in flight beside two of W, all of a CU's LDS (or most): A comes from
         // further away, W is shared by the row tiles of a band.  1920 x 7680: 495 -> 477 us at 17776 rows, 921 -> 868 at
         // 33976 on 256 x 256 tiles, 507 -> 482 and 1005 -> 962 on 192 x 256.  Not with K = 1920 (5760 and 7680 columns, 17776
         // rows: 359 -> 362, 447 -> 453 us) nor where two workgroups share a CU (128 x 128, 1920 x 7680: 523 -> 558).
+        // Workgroups of the only round keep step, each operand is asked for by all of them at once and two stages do: 1920 x
+        // 7680 at 6016 rows (256 tiles of 192 x 256) 141 us against 147 with three of A, weights from memory 150 against 153; at
+        // 8326 rows 241 against 234.
         // K = 1920 on 192 x 256: three stages of W, whose weights come from memory once per layer while A was just written.
         // Weights that change from call to call: 7680 columns, 4516 rows 134.4 -> 127.6 us, 5760, 6016 rows 129.1 -> 121.9
         // (192 x 128 tiles: 131.5 and 125.5); the same weights in every call 126.3 -> 127.5 and 120.3 -> 122.2.  Not on 256 x
         // 256 (7680 columns, 4516 rows 145 -> 151 us; 17776 rows 465 -> 470).
         case 1:                                                                                          // 8 waves, 128x64 each
-            if (long_k) return launch_tile<256, 256, 2, 4, 64, 3>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+            if (long_k && rounds) return launch_tile<256, 256, 2, 4, 64, 3>(A, W, C, batch, tokens, Nn, K, p, ep, st);
             return launch_tile<256, 256, 2, 4, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);
         case 2: return launch_tile<128, 128, 2, 2, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 4 waves, 64x64 each, 2 per CU
         case 3:                                                                                          // 8 waves, 96x64 each
-            if (long_k) return launch_tile<192, 256, 2, 4, 64, 3>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+            if (long_k && rounds) return launch_tile<192, 256, 2, 4, 64, 3>(A, W, C, batch, tokens, Nn, K, p, ep, st);
+            if (long_k) return launch_tile<192, 256, 2, 4, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);
             return launch_tile<192, 256, 2, 4, 64, 2, 3>(A, W, C, batch, tokens, Nn, K, p, ep, st);
         case 4: return launch_tile<192, 128, 2, 2, 64, 2>(A, W, C, batch, tokens, Nn, K, p, ep, st);   // 4 waves, 96x64 each, 2 per CU
         // Measured and dropped: 4 waves of 128x128 outputs on the 256x256 tile (fewer LDS reads per MFMA; with the

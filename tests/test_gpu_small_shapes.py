@@ -73,6 +73,23 @@ def test_every_tile_of_the_few_token_kernel_at_ragged_edges(kind, M, Nn, K):
     assert torch.equal(out, B.dit_linear(a, w, bias, 0, kernel_path=0x204))
 
 
+@pytest.mark.parametrize("M,Nn,K", [(300, 260, 64), (300, 260, 128), (300, 260, 192), (300, 260, 4032), (300, 260, 4096),
+                                    (3300, 4100, 4032), (3300, 4100, 4096), (4200, 4100, 4160)])
+def test_rings_of_the_wide_tiles(M, Nn, K):
+    """Two and three stages of either operand: K of one to three stages, short and long K on both sides of the line, one round of
+    workgroups and more; whole sums, so every ring gives the bits of the 128 x 128 tile.  One rounding of the result to bf16."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + K)
+    a = torch.randn(M, K, generator=g, device=DEV).bfloat16()
+    w = (torch.randn(Nn, K, generator=g, device=DEV) / math.sqrt(K)).bfloat16()
+    bias = torch.randn(Nn, generator=g, device=DEV)
+    out = B.dit_linear(a, w, bias, 0, kernel_path=0x204)
+    ref = a[-300:].double() @ w.double().t() + bias.double()
+    assert rel(ref.cpu().numpy(), out[-300:].double().cpu().numpy()) <= 2.0 ** -9
+    for variant in (1, 3):
+        assert torch.equal(out, B.dit_linear(a, w, bias, 0, kernel_path=variant << 8 | 4)), variant
+
+
 @pytest.mark.parametrize("N", [1, 15, 16, 17, 63, 64, 65, 200])
 @pytest.mark.parametrize("d", [16, 32, 64])
 def test_attention_fp32_math_ragged(N, d):
