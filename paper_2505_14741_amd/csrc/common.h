@@ -79,8 +79,8 @@ inline bool kernel_path_valid(int path) {
 // compute units of the current device
 int compute_units();
 
-// The M rows of a projection are `batch` samples of `tokens` rows each; every sample is tiled on its own, so a
-// sample's result is bit-identical whatever batch it is computed in.
+// The M rows of a projection are `batch` samples of `tokens` rows each; a sample's shape alone says which of its sums are
+// made in pieces, so its result is bit-identical whatever batch it is computed in.
 // scratch that lets launch_gemm split its last partial round along K (0: the shape does not profit)
 size_t gemm_split_workspace_bytes(int dtype, int batch, int tokens, int Nn, int K, int path);
 // whether launch_gemm sends a shape to one of the matrix kernels (EPI_UNPATCHIFY exists only there)

@@ -104,7 +104,7 @@ __device__ __forceinline__ void epilogue_quad(const Epilogue& ep, T* __restrict_
 // Adds the K pieces ([piece][row][column]) in order and applies the epilogue: one thread per 4 adjacent columns.
 template <typename T, int KIND>
 __global__ void __launch_bounds__(256)
-gemm_small_reduce_kernel(T* __restrict__ C, int Nn, long rows, int nsplit, Epilogue ep) {
+gemm_few_reduce_kernel(T* __restrict__ C, int Nn, long rows, int nsplit, Epilogue ep) {
     const int quads = Nn / 4;
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
     if (idx >= rows * quads) return;

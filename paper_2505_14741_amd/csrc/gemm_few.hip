@@ -271,7 +271,7 @@ static hipError_t launch_few_kind(int tile, const T* A, const T* W, T* C, int ro
     if (e != hipSuccess || nsplit == 1) return e;
     if (deferred && KIND == EPI_GATE_RESIDUAL) { *deferred = nsplit; return e; }
     const long quads = (long)rows * (Nn / 4);
-    gemm_small_reduce_kernel<T, KIND><<<(int)((quads + 255) / 256), 256, 0, st>>>(C, Nn, rows, nsplit, ep);
+    gemm_few_reduce_kernel<T, KIND><<<(int)((quads + 255) / 256), 256, 0, st>>>(C, Nn, rows, nsplit, ep);
     return hipGetLastError();
 }
 

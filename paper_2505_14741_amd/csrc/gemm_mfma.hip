@@ -521,11 +521,11 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
     }
 }
 
-// Every sample of a batch (rows [b * tokens, (b+1) * tokens) of the operands) is tiled on its own: a tile never
-// holds rows of two samples, and which of its tiles are summed in K pieces depends on the sample's shape alone,
-// so a sample's result does not depend on the batch it is computed in (Section 3.3: the batched step must
-// reproduce the per-step process).  A workgroup shifts the operand, output, residual and modulation
-// pointers to its sample and from then on works on a [tokens, Nn] problem.
+// A sample's result does not depend on the batch it is computed in (Section 3.3: the batched step must reproduce the
+// per-step process): which of its tiles are summed in K pieces follows from its shape alone.  Where there are such tiles
+// every sample (rows [b * tokens, (b+1) * tokens) of the operands) is tiled on its own: a workgroup shifts the operand,
+// output, residual and modulation pointers to its sample and from then on works on a [tokens, Nn] problem.  Whole sums have
+// the same value on every tile, and the rows of all samples are tiled as one matrix (see launch_gemm_mfma).
 //
 // The first batch * full_tiles workgroups compute one BM x BN output tile each.  The tiles beyond them -- the last,
 // partial round of the chip's workgroup slots, per sample -- can be shared out so that the round is shorter: with
@@ -646,15 +646,16 @@ static GemmPlan gemm_plan(int tokens, int Nn, int K, bool allow_split, int force
         // (for the kind of epilogue that follows a long K, whichever the call's is: the plan belongs to the shape)
         p.tile = best_tile(0, TILE_KINDS - 1, tokens, Nn, K, 1, true, cus);
         float best = tile_time(p.tile, tile_count(p.tile, tokens, Nn), (float)(K / 64), true, cus);
-        // The last partial round of a long K in pieces, which count as 1/pieces of a round plus a fifth of one for the
+        // The last partial round of a long K in pieces, which count as 1/pieces of a round plus a third of one for the
         // partial sums (two passes over tile-size fp32 per piece) and the second launch -- measured at 17776 tokens: worth
-        // it with a long K (1920 x 7680: 0.62 -> 0.57 ms on 128 x 128 tiles), not with K = 1920 (0.188 -> 0.196 ms)
+        // it with a long K (1920 x 7680: 0.62 -> 0.57 ms on 128 x 128 tiles), not with K = 1920 (0.188 -> 0.196 ms); 1920 x
+        // 7680 at 13000 rows: 192 x 256 tiles in two rounds and 32 tiles of 8 pieces 351 us, 192 x 128 whole 332
         bool split = false;
         for (int id = WIDE_256x256; id < TILE_KINDS && pieces == 0; ++id) {
             const long tiles = tile_count(id, tokens, Nn), slots = slots_of(id);
             const int ns = tail_split(tiles, slots, K, allow_split);
             if (ns == 1 || tiles < slots) continue;
-            const float t = tile_time(id, slots, (float)(K / 64), true, cus) * (tiles / slots + 1.0f / ns + 0.2f);
+            const float t = tile_time(id, slots, (float)(K / 64), true, cus) * (tiles / slots + 1.0f / ns + 0.35f);
             if (t < best) { best = t; p.tile = id; split = true; }
         }
         allow_split = split;

@@ -47,11 +47,11 @@ constexpr Tile kTiles[TILE_KINDS] = {
     {128, 128, 1, 0.f, 0.f, 6.0f, 0.47f, 3.8f},          // 8 waves of 32 x 64
     {192, 128, 1, 0.f, 0.f, 7.0f, 0.60f, 5.7f},          // 8 waves of 48 x 64
     {256, 128, 1, 0.f, 0.f, 8.7f, 0.76f, 7.5f},          // 8 waves of 64 x 64
-    {192, 192, 1, 0.f, 0.f, 9.0f, 0.90f, 8.5f},          // 8 waves of 48 x 96
+    {192, 192, 1, 0.f, 0.f, 10.f, 0.90f, 7.5f},          // 8 waves of 48 x 96
     {256, 256, 1, 0.f, 0.f, 7.3f, 1.34f, 15.f},          // gemm_mfma.hip: 8 waves of 128 x 64
     {128, 128, 2, 2.0f, 0.80f, 4.0f, 0.92f, 7.5f},       // 4 waves of 64 x 64
-    {192, 256, 1, 0.f, 0.f, 7.4f, 1.14f, 12.6f},         // 8 waves of 96 x 64
-    {192, 128, 2, 2.0f, 0.88f, 4.0f, 1.367f, 15.f},      // 4 waves of 96 x 64
+    {192, 256, 1, 0.f, 0.f, 5.4f, 1.14f, 14.6f},         // 8 waves of 96 x 64
+    {192, 128, 2, 4.2f, 0.88f, 6.0f, 1.34f, 13.f},       // 4 waves of 96 x 64
 };
 constexpr long tile_count(int id, long rows, int Nn) {
     return (rows + kTiles[id].bm - 1) / kTiles[id].bm * ((Nn + kTiles[id].bn - 1) / kTiles[id].bn);
@@ -75,7 +75,7 @@ constexpr float tile_time(int id, long wgs, float stages, bool gated, int cus) {
     return (float)(wgs / slots) * full + last;
 }
 // The bf16 tile with the least estimated time: `pieces` workgroups per tile along K; [first, last]: the kinds to choose from.
-// At the sizes above it misses the fastest one by 0.4 % on average and 6 % at most.
+// At the sizes above it misses the fastest one by about 1 % on average and 6 % at most.
 constexpr int best_tile(int first, int last, long rows, int Nn, int K, int pieces, bool gated, int cus) {
     int best = first;
     float least = 0.f;
