@@ -122,7 +122,7 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, void* C, int bat
     FewPlan few = few_plan(bf16, tokens, Nn, K, path);
     if (few.use && !forced_tiles(dtype, path)) {
         if (epi.split_ws == nullptr || epi.split_ws_bytes < few_workspace_bytes(bf16, few, batch, tokens, Nn, K)) few.nsplit = 1;
-        const FewHow how = few_how(bf16, few, batch, K);
+        const FewHow how = few_how(bf16, few, batch, tokens, Nn, K);
         if (how == FEW_TILES && few.nsplit == 1)         // (whole sums: the fastest tile of either kernel)
             return launch_gemm_mfma((const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C, batch, tokens, Nn, K, epi, path, 1, st);
         const bool apart = how == FEW_PIECES;

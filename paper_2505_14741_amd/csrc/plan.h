@@ -89,17 +89,43 @@ constexpr int best_tile(int first, int last, long rows, int Nn, int K, int piece
 // ---- projections of few tokens and of fp32 operands (gemm_few.hip)
 constexpr int FEW_ROW_BYTES = 128;                       // bytes of an operand row per stage: 64 bf16 or 32 fp32
 
+// Whether `pieces` workgroups per tile are one round, a compute unit each, on some tile of gemm_few.hip.
+constexpr int FEW_CUS = 256;                             // (a plan must not depend on the device's count)
+constexpr bool few_one_round(long rows, int Nn, int pieces) {
+    for (int id = 0; id < FEW_TILE_KINDS; ++id)
+        if (tile_count(id, rows, Nn) * pieces <= FEW_CUS) return true;
+    return false;
+}
+// K pieces of a sample of more than 128 tokens and a long K (bf16): 4 or 3, whichever is estimated faster, where that is one
+// round; 3 on 192 x 192 tiles excepted.  1920 x 7680, weights from memory, us apart / one workgroup per tile: 450 tokens 27.6 /
+// 36.1, 768 35.7 / 49.2, 800 39.0 / 42.6, 960 42.5 / 44.4, 1024 42.7 / 49.5, 1100 45.0 / 65, 1200 49.8 / 62, 1280 49.6 / 68.5.
+// From 1281 tokens on (3 pieces, 192 x 192: 1400 53.2 / 68) a batch would lose more than that: its pieces stay on tiles of
+// gemm_few.hip, four samples of 1500 168 us, on wider tiles whole 146.  (Up to there it loses little: a layer of one sample
+// of 1104 / 1264 tokens, whole and in pieces, 212 -> 188 / 225 -> 201 us, of four 475 -> 478 / 557 -> 569, of six 722 -> 740
+// / 761 -> 779.)
+constexpr int few_long_pieces(int tokens, int Nn, int nk) {
+    int best = 1;
+    float least = 0.f;
+    for (int n = 4; n >= 3; --n)
+        for (int id = 0; id < (n == 4 ? (int)FEW_TILE_KINDS : (int)FEW_192x192); ++id) {
+            const long wgs = tile_count(id, tokens, Nn) * n;
+            if (wgs > FEW_CUS) continue;
+            const float t = tile_time(id, wgs, (float)nk / n, false, FEW_CUS);
+            if (best == 1 || t < least) { best = n; least = t; }
+        }
+    return best;
+}
+
 // A sample's plan: a function of the sample's shape alone, so that its result does not depend on the batch.  tiles_m x
 // tiles_n tiles of 64 x 64.
-//   bf16: up to 640 of them, 512 with K >= 4096, where a sample is cut into K pieces that wider tiles would also need.
+//   bf16: up to 640 of them, 512 with K >= 4096, where a sample is cut into K pieces that wider tiles would also need, and
+//     beyond as long as it is cut.
 //   fp32: every size (the matrix instructions bind, 32 cycles per 2048 operations, not the LDS reads).
 // K pieces, short K: as many as bring the workgroups to 256 (one per compute unit), 8 at most (fp32 16) and each at least 5
 // stages.  1920 x 1920 bf16 at 112 tokens (60 tiles), without / with the launch that adds them: 1 piece 10.3 us, 4 pieces
 // 5.8 / 9.7, 8 pieces 6.2 / 11.1.
 // Long K (60 stages and more), fp32 and up to 128 tokens: to 512.  1920 x 7680 bf16 at 112 tokens: 8 pieces (128 x 64
-// tiles) 15.2, 4 pieces 16.1, 3 pieces 18.9.  More tokens: as many as bring 192 x 128 tiles to 256, 4 at most, up to 128
-// tiles of 128 x 128 (1024 tokens), beyond which those run whole.  us in 2 / 3 / 4 / 8 pieces, the fastest tile of each: 224
-// tokens 23.7 / 23.7 / 20.3 / 20.7, 448 29.6 / 31.2 / 27.4 / 30.3, 768 44.2 / 41.2 / 36.2 / -, 900 40.8 / 40.6 / 40.9 / -.
+// tiles) 15.2, 4 pieces 16.1, 3 pieces 18.9.  More tokens: few_long_pieces().
 // path: kernel path (low byte 1: generic kernels, 4: no K pieces).
 struct FewPlan { bool use; int tiles_m, tiles_n, nsplit; };
 constexpr FewPlan few_plan(bool bf16, int tokens, int Nn, int K, int path) {
@@ -109,14 +135,13 @@ constexpr FewPlan few_plan(bool bf16, int tokens, int Nn, int K, int path) {
     p.tiles_m = (tokens + 63) / 64;
     p.tiles_n = (Nn + 63) / 64;
     const long tiles = (long)p.tiles_m * p.tiles_n, nk = row_bytes / FEW_ROW_BYTES;
-    if (bf16 && (Nn < 64 || tiles > (K >= 4096 ? 512 : 640))) return p;
+    if (bf16 && Nn < 64) return p;
+    const long most = bf16 ? 8 : 16;
+    long ns = (nk >= 60 ? 512 : 256) / tiles;
+    if (bf16 && nk >= 60 && tokens > 128) ns = few_long_pieces(tokens, Nn, (int)nk);
+    if ((path & 0xff) == 4) ns = 1;
+    if (bf16 && ns <= 1 && tiles > (K >= 4096 ? 512 : 640)) return p;
     p.use = true;
-    if ((path & 0xff) == 4) return p;
-    long most = bf16 ? 8 : 16, ns = (nk >= 60 ? 512 : 256) / tiles;
-    if (bf16 && nk >= 60 && tokens > 128) {
-        most = 4;
-        ns = tile_count(FEW_128x128, tokens, Nn) <= 128 ? 256 / tile_count(FEW_192x128, tokens, Nn) : 1;
-    }
     ns = ns < most ? ns : most;
     ns = ns < nk / 5 ? ns : nk / 5;
     p.nsplit = ns > 1 ? (int)ns : 1;
@@ -128,25 +153,26 @@ constexpr FewPlan few_plan(bool bf16, int tokens, int Nn, int K, int path) {
 //   FEW_PIECES  a workgroup per tile and K piece; the pieces pass through memory
 //   FEW_INREG   a workgroup per tile, which adds its pieces in registers
 //   FEW_TILES   the same, and where there is one piece (bf16) the tiles of gemm_mfma.hip are candidates too
-// Pieces of their own pay until the tiles alone occupy the chip.  Layer with cold weights, us, pieces apart / in registers:
-// 1920 x 1920 and the LayerNorm that adds the pieces, 112 tokens: 3 samples (180 tiles) 19.3 / 21.5, 4 (240) 23.1 / 22.0,
-// 8 (480) 37.1 / 26.3; 1920 x 7680, 4 samples (240) 42.1 / 50.2, 6 (360) 57.5 / 62.4, 8 (480) 74.1 / 62.2.  fp32 is bound by
-// the matrix instructions and takes finer pieces longer: 1920 x 7680 at 320 tokens, 4 samples (600 tiles) 358 / 393, 8 (1200)
-// 674 / 654.
+// Pieces of their own pay until the tiles alone occupy the chip: with a short K up to 256 tiles of 64 x 64, with a long one as
+// long as the pieces are one round; a single sample's always are (its plan counts the same tiles).  Layer with cold weights,
+// us, pieces apart / in registers: 1920 x 1920 and the LayerNorm that adds the pieces, 112 tokens: 3 samples (180 tiles) 19.3 /
+// 21.5, 4 (240) 23.1 / 22.0, 8 (480) 37.1 / 26.3; 1920 x 7680 in 8 pieces, 112 tokens: 4 samples 28.8 / 37.6, 5 32.4 / 42.7,
+// 6 (no longer one round) 47.9 / 42.1, 8 55.0 / 49.4; in 4 pieces 1040 rows 43.2 / 58.7, 1200 62.2 / 61.2, 1350 68.0 / 63.7.
+// fp32 is bound by the matrix instructions and takes finer pieces longer: 1920 x 7680 at 320 tokens, 4 samples (600 tiles)
+// 358 / 393, 8 (1200) 674 / 654.
 // The tiles of gemm_mfma.hip are never the fastest up to 768 tiles of 64 x 64 (5760 x 1920, 512 rows).
 enum FewHow { FEW_PIECES, FEW_INREG, FEW_TILES };
-constexpr long few_spread_tiles(bool bf16, int K) { return !bf16 ? 640 : K >= 60 * 64 ? 384 : 256; }
-constexpr FewHow few_how(bool bf16, const FewPlan& p, int batch, int K) {
+constexpr FewHow few_how(bool bf16, const FewPlan& p, int batch, int tokens, int Nn, int K) {
     const long tiles = (long)batch * p.tiles_m * p.tiles_n;
-    if (p.nsplit > 1 && tiles < few_spread_tiles(bf16, K)) return FEW_PIECES;
+    if (p.nsplit > 1 && (bf16 && K >= 60 * 64 ? few_one_round((long)batch * tokens, Nn, p.nsplit) : tiles < (bf16 ? 256 : 640)))
+        return FEW_PIECES;
     return bf16 && tiles > 768 && p.tiles_m > 1 ? FEW_TILES : FEW_INREG;
 }
 
-// scratch for the K pieces, [piece][row][column] in fp32; does not shrink with the batch
+// scratch for the K pieces, [piece][row][column] in fp32, of the largest batch up to `batch` whose pieces pass through memory
 constexpr size_t few_workspace_bytes(bool bf16, const FewPlan& p, int batch, int tokens, int Nn, int K) {
-    if (p.nsplit == 1) return 0;
-    const long most = (few_spread_tiles(bf16, K) - 1) / ((long)p.tiles_m * p.tiles_n);   // the largest batch of FEW_PIECES
-    return (size_t)p.nsplit * (batch < most ? batch : most) * tokens * Nn * sizeof(float);
+    while (batch > 0 && few_how(bf16, p, batch, tokens, Nn, K) != FEW_PIECES) --batch;
+    return (size_t)p.nsplit * batch * tokens * Nn * sizeof(float);
 }
 
 }  // namespace ps

@@ -40,10 +40,11 @@ def test_linear_few_rows_split_and_whole(M, Nn, K, act):
             assert rel(ref, B.dit_linear(a, w, bias, act, **kw).double().cpu().numpy()) <= bound, (td, kw)
 
 
-@pytest.mark.parametrize("N", [1088, 1152, 1344, 1408])
+@pytest.mark.parametrize("N", [768, 769, 960, 961, 1088, 1152, 1153, 1280, 1281, 1344, 1408])
 def test_linear_on_both_sides_of_the_tile_limit(N):
-    """1920 columns are 30 column tiles: 17 and 18 row tiles are 510 and 540 of them, around the limit of 512 for K = 7680
-    (whole below, 128-wide tiles in K pieces above), 21 and 22 are 630 and 660, around the limit of 640 for K = 1920."""
+    """1920 columns are 30 column tiles of 64: 21 and 22 row tiles are 630 and 660, around the limit of 640 for K = 1920.  K =
+    7680 is cut in 4 pieces up to 768 rows and from 961 to 1152, in 3 between and up to 1280, and not beyond; the tiles of the
+    other kernel, forced, add the same pieces.  One rounding of the result to bf16."""
     g = torch.Generator(device=DEV)
     g.manual_seed(N)
     for K in (1920, 7680):
@@ -51,7 +52,11 @@ def test_linear_on_both_sides_of_the_tile_limit(N):
         w = (torch.randn(1920, K, generator=g, device=DEV) / math.sqrt(K)).bfloat16()
         bias = torch.randn(1920, generator=g, device=DEV)
         ref = (a.double() @ w.double().t() + bias.double()).cpu().numpy()
-        assert rel(ref, B.dit_linear(a, w, bias, 0).double().cpu().numpy()) <= 2.0 ** -9
+        out = B.dit_linear(a, w, bias, 0)
+        assert rel(ref, out.double().cpu().numpy()) <= 2.0 ** -9
+        assert rel(ref, B.dit_linear(a, w, bias, 0, use_workspace=False).double().cpu().numpy()) <= 2.0 ** -9
+        if N <= 1280 or K == 1920:                       # (above, 128 x 128 tiles have a last round of their own to cut)
+            assert torch.equal(out, B.dit_linear(a, w, bias, 0, kernel_path=0x200))
 
 
 TILE_SIZES = [(0, 300, 1908, 1920), (1, 700, 1908, 1920), (2, 1290, 1908, 1920), (3, 2500, 1908, 1920), (4, 3300, 1908, 7680),
@@ -284,7 +289,7 @@ def test_update_and_rel_mae_on_one_and_two_workgroups(n):
     assert torch.isnan(B.rel_mae(torch.zeros(n, device=DEV), torch.zeros(n, device=DEV))[2])
 
 
-BATCH_GRIDS = [(1, 3), (6, 8), (12, 20), (18, 28), (24, 32), (30, 43), (36, 43), (40, 51), (48, 54)]
+BATCH_GRIDS = [(1, 3), (6, 8), (12, 20), (18, 28), (24, 32), (28, 39), (28, 44), (30, 43), (36, 43), (40, 51), (48, 54)]
 
 
 @pytest.mark.parametrize("dtype,rows,cols", [("bf16", *g) for g in BATCH_GRIDS] + [("f32", *g) for g in BATCH_GRIDS[:5]])

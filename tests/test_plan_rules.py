@@ -18,7 +18,7 @@ extern "C" int few(int bf16, int tokens, int n, int k, int path) {   // 0: anoth
     return p.use ? p.nsplit : 0;
 }
 extern "C" int how(int bf16, int tokens, int n, int k, int batch) {
-    return ps::few_how(bf16 != 0, ps::few_plan(bf16 != 0, tokens, n, k, 0), batch, k);
+    return ps::few_how(bf16 != 0, ps::few_plan(bf16 != 0, tokens, n, k, 0), batch, tokens, n, k);
 }
 extern "C" int best(int first, int last, long rows, int n, int k, int pieces, int gated) {
     return ps::best_tile(first, last, rows, n, k, pieces, gated != 0, 256);
@@ -57,9 +57,9 @@ def test_merge_rows_of_many_items(rules, nitems):
 
 def test_few_token_projections_end_where_wider_tiles_are_faster(rules):
     few = lambda *a: rules.few(1, *a, 0)
-    # K = 1920: 640 tiles of 64 x 64; long K: 512, beyond which only 128-wide tiles are cut along K
+    # K = 1920: 640 tiles of 64 x 64; long K: as long as pieces are one round of workgroups
     assert few(1344, 1920, 1920) == 1 and few(1345, 1920, 1920) == 0
-    assert few(1088, 1920, 7680) == 1 and few(1089, 1920, 7680) == 0
+    assert few(1088, 1920, 7680) > 1 and few(1280, 1920, 7680) > 1 and few(1281, 1920, 7680) == 0
     assert few(112, 1920, 7680) == 8 and few(112, 1920, 1920) == 4 and few(112, 5760, 1920) == 1
     assert few(1344, 1920, 4032) == 1 and few(1344, 1920, 4096) == 0     # where 128-wide tiles start to be cut
     assert rules.few(0, 4096, 1920, 7680, 0) == 1                        # fp32: every size
@@ -74,7 +74,7 @@ def test_a_batch_that_fills_the_chip_takes_wide_tiles_and_no_pieces_of_its_own(r
     how = lambda *a: rules.how(1, *a)
     assert how(112, 1920, 1920, 1) == PIECES and how(112, 1920, 1920, 4) == PIECES      # 60 tiles, 240
     assert how(112, 1920, 1920, 8) == INREG and how(112, 1920, 1920, 16) == TILES       # 480, 960
-    assert how(112, 1920, 7680, 6) == PIECES and how(112, 1920, 7680, 8) == INREG       # 360, 480
+    assert how(112, 1920, 7680, 5) == PIECES and how(112, 1920, 7680, 6) == INREG       # 192 x 192 x 8 pieces: 240, 320
     assert how(256, 7680, 1920, 1) == INREG and how(256, 7680, 1920, 8) == TILES
     assert how(1300, 1920, 1920, 1) == INREG and how(1300, 1920, 1920, 2) == TILES      # 630, 1260
     assert how(64, 7680, 1920, 16) == INREG                                             # a 128-row tile would be half empty
@@ -82,10 +82,22 @@ def test_a_batch_that_fills_the_chip_takes_wide_tiles_and_no_pieces_of_its_own(r
 
 
 @pytest.mark.parametrize("bf16", [0, 1])
+def test_pieces_that_are_planned_are_spread(rules, bf16):
+    """A single sample's K pieces are workgroups of their own, with scratch to pass them: a tile that walks all of K has no use
+    for pieces, and a call without scratch would be summed in another order."""
+    for tokens in (*range(1, 2000, 13), 64, 128, 129, 768, 769, 960, 961, 1024, 1088, 1089, 1152, 1153, 1280, 1281):
+        for n, k in ((64, 4096), (196, 1984), (1024, 4096), (1536, 6144), (1920, 1920), (1920, 7680), (2048, 8192), (7680, 3840)):
+            pieces = rules.few(bf16, tokens, n, k, 0)
+            if pieces > 1:
+                assert rules.how(bf16, tokens, n, k, 1) == PIECES, (tokens, n, k)
+                assert rules.scratch(bf16, tokens, n, k, 1) == 4 * pieces * tokens * n
+
+
+@pytest.mark.parametrize("bf16", [0, 1])
 def test_scratch_of_few_token_projections_serves_every_smaller_batch(rules, bf16):
     """A workspace sized for a batch is used for smaller ones (the last cycle of a step-batched run), and a batch whose pieces
     stay in registers needs no more than the largest one whose pieces do not."""
-    for tokens in (1, 32, 64, 65, 112, 256, 520, 1040, 1300):
+    for tokens in (1, 32, 64, 65, 112, 256, 520, 1040, 1200, 1300):
         for n, k in ((64, 1920), (1920, 1920), (5760, 1920), (7680, 1920), (1920, 7680), (196, 1984)):
             pieces = rules.few(bf16, tokens, n, k, 0)
             size = [rules.scratch(bf16, tokens, n, k, b) for b in range(1, 17)]
