@@ -736,8 +736,10 @@ hipError_t launch_gemm_mfma(const bf16_t* A, const bf16_t* W, bf16_t* C, int bat
         // 33976 on 256 x 256 tiles, 507 -> 482 and 1005 -> 962 on 192 x 256.  Not with K = 1920 (5760 and 7680 columns, 17776
         // rows: 359 -> 362, 447 -> 453 us) nor where two workgroups share a CU (128 x 128, 1920 x 7680: 523 -> 558).
         // Workgroups of the only round keep step, each operand is asked for by all of them at once and two stages do: 1920 x
-        // 7680 at 6016 rows (256 tiles of 192 x 256) 141 us against 147 with three of A, weights from memory 150 against 153; at
-        // 8326 rows 241 against 234.
+        // 7680 at 6016 rows (256 tiles of 192 x 256) 141 us against 147 with three of A, weights from memory 150 against 153.
+        // Two rounds of 192 x 256 tiles are faster with three inside the network (us of a layer's fc2 with two / three: 11000
+        // tokens 319 / 314, 12000 325 / 324) and where both operands come from memory (11000 rows 309 / 298); where a call
+        // repeats itself on the same operands they lose 4 % (11000 rows 265 / 276, 12000 277 / 288).
         // K = 1920 on 192 x 256: three stages of W, whose weights come from memory once per layer while A was just written.
         // Weights that change from call to call: 7680 columns, 4516 rows 134.4 -> 127.6 us, 5760, 6016 rows 129.1 -> 121.9
         // (192 x 128 tiles: 131.5 and 125.5); the same weights in every call 126.3 -> 127.5 and 120.3 -> 122.2.  Not on 256 x
