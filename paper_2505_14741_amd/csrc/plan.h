@@ -17,19 +17,22 @@ constexpr MergeRow merge_row(int block, int thread, int bq) {
 
 // ---- bf16 attention of samples whose items of 256 queries do not fill the chip: whether workgroups of 128 queries, alone, are
 // faster than workgroups of 256 and the launch that looks their results through.  `bh`: (batch, head) pairs.
-// Measured us per tile of 64 keys: 512 workgroups of 128 queries 1.25, up to 256 of them 0.98; of 256 queries 2.27 and 1.29.
-// A launch more costs 3 us; over several rounds the narrow ones, which read K and V twice as often, lose another 6 %.  Whole
-// calls, 30 heads, narrow / wide: 2608 keys 84 / 88, two samples 132 / 136, four 255 / 249; 1000 keys, 4 and 8 samples 46.8 /
-// 48.5 and 87.7 / 85.2; 3600 keys 132 / 122.
+// Measured us per tile of 64 keys: 512 workgroups of 128 queries 1.25, up to 256 of them 0.98; of 256 queries 2.27 and 1.29; a
+// single round that puts two on some compute units only is between them, nearer the full one.  A launch more costs 4 us; over
+// several rounds the narrow ones, which read K and V twice as often, lose another 6 %.  Whole calls, narrow / wide us: 30 heads,
+// 1000 keys, 4 and 8 samples 46.8 / 48.5 and 87.7 / 85.2, 2608 keys 88 / 90, two samples 131 / 130, four 245 / 243, 3600 keys 135 / 117;
+// 16 heads, 3000 keys 59 / 60, 4200 keys 127 / 119; 4 heads, 6000 keys 84 / 107, 17776 keys 503 / 461.
+// (On 278 shapes of 32 to 17776 keys and 1 to 3200 (batch, head) pairs the one picked is 3.2 % slower than the other at most.)
 constexpr bool attn_narrow_items(long bh, int seq, int cus) {
     const long slots = 2L * cus, narrow = bh * ((seq + 127) / 128), wide = bh * ((seq + 255) / 256);
     const auto rounds = [slots, cus](long n, float full, float half) {
         const long tail = n % slots;
+        if (n < slots && tail > cus) return full * (0.92f + 0.08f * (float)(tail - cus) / cus);
         return (float)(n / slots) * full + (tail == 0 ? 0.f : tail <= cus ? half : full);
     };
     const float tiles = (float)((seq + 63) / 64);
     const float a = tiles * rounds(narrow, 1.25f, 0.98f) * (narrow > 2 * slots ? 1.06f : 1.f);
-    return a <= tiles * rounds(wide, 2.27f, 1.29f) + 3.f;
+    return a <= tiles * rounds(wide, 2.27f, 1.29f) + 4.f;
 }
 
 // ---- projections: C[rows, Nn] = A[rows, K] * W[Nn, K]^T, rows = all samples of the batch

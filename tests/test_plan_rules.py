@@ -137,3 +137,5 @@ def test_attention_workgroups_of_128_queries_where_they_are_faster(rules):
     assert narrow(30, 112) and narrow(60, 1000) and narrow(30, 2000) and narrow(30, 2608) and narrow(4, 4200) and narrow(240, 520)
     assert not narrow(30, 3600) and not narrow(240, 1000) and not narrow(256, 1000)
     assert narrow(16, 1000) and narrow(256, 31) and narrow(256, 129)
+    assert not narrow(16, 4200) and not narrow(16, 6000) and not narrow(8, 12000) and not narrow(4, 17776)
+    assert narrow(8, 4200) and narrow(4, 6000) and narrow(4, 12000) and narrow(128, 700)
