@@ -125,11 +125,15 @@ PS_API int dit_forward(dit* d, const float* x, const void* ctx, const int32_t* t
 
 /* Optional per-kernel-class timing of dit_forward with HIP events on its stream.
  * Classes: 0 attention, 1 qkv GEMM, 2 out-proj GEMM, 3 fc1 GEMM, 4 fc2 GEMM,
- * 5 LayerNorm+modulate, 6 everything else.  dit_profile_read synchronises the
- * recorded events and returns accumulated milliseconds and launch counts since the
- * last dit_profile_enable(d, on > 0); both arrays are HOST [7].
+ * 5 LayerNorm+modulate, 6 everything else.  Narrow fp32 networks (hidden 32 or 64 in heads of
+ * 16 or 32, mlp_ratio 4, in_channels*patch^2 16, 32, 48 or 64, up to 1024 tokens) run a whole
+ * layer in one launch, which counts as 6: classes 0 to 5 stay empty unless their kernel path is 1.
+ * dit_profile_read synchronises the recorded events and returns accumulated milliseconds and
+ * counts (launches; a projection or attention call of several launches is one) since the last
+ * dit_profile_enable(d, on > 0); both arrays are HOST [7].
  * on: 0 off, 1 every class (two events per launch: about 1.5 % of a 30-layer forward at
- * 17776 tokens), 2 the attention class only (0.3 %); other values: PS_ERR_SHAPE. */
+ * 17776 tokens), 2 the attention class only (0.3 %; nothing for the narrow networks above);
+ * other values: PS_ERR_SHAPE. */
 PS_API int dit_profile_enable(dit* d, int on);
 PS_API int dit_profile_read(dit* d, double* ms_out, int64_t* launches_out);
 

@@ -14,7 +14,7 @@ struct SlimArgs {
     float eps, scale;
 };
 
-// What launch_slim takes: fp32, hidden 32 or 64 in heads of 16 or 32, mlp_ratio 4, whole 16-value blocks of up to 64 values
+// What slim.hip takes: fp32, hidden 32 or 64 in heads of 16 or 32, mlp_ratio 4, whole 16-value blocks of up to 64 values
 // per patch, up to 1024 tokens.  us per forward of 2 layers, a launch per operation / this: hidden 64, 4 heads: 32 tokens 99 /
 // 48, 416 tokens 125 / 71, 976 tokens 159 / 103 (16 samples 428 / 300).  A head of 64 keeps one wave per workgroup busy for
 // long (416 tokens 156 / 183), and a hidden size of 128 has too much to do per token for one workgroup (416 tokens, 8 heads
@@ -25,8 +25,11 @@ constexpr bool slim_network(int dtype, int hidden, int head_dim, int mlp_ratio, 
            patch_values <= 64 && tokens <= SLIM_TOKENS;
 }
 
-// One forward; the conditioning (mod, modf, rope) is there already.  qkv_even / qkv_odd: [batch * tokens, 3 * hidden] each.
-hipError_t launch_slim(const SlimArgs& args, int hidden, const SlimLayer* layers, int count, int batch, float* qkv_even,
-                       float* qkv_odd, hipStream_t st);
+// A forward is launch_slim_begin and one launch_slim_layer per layer; the conditioning (mod, modf, rope) is there already.
+// g.qkv_out: where the launch leaves the q, k, v [batch * tokens, 3 * hidden] of the layer that follows; g.qkv: where a
+// layer's own were left, other memory (a workgroup's next ones must not overwrite keys others still read).
+hipError_t launch_slim_begin(const SlimArgs& g, int hidden, const SlimLayer& first, int batch, hipStream_t st);
+// layer number g.layer; next: the one after it, NULL after the last
+hipError_t launch_slim_layer(const SlimArgs& g, int hidden, const SlimLayer& layer, const SlimLayer* next, int batch, hipStream_t st);
 
 }  // namespace ps

@@ -293,37 +293,43 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
     }
 }
 
-template <int D, int HD>
-hipError_t launch_slim_as(SlimArgs g, const SlimLayer* layers, int count, int batch, float* qkv_even, float* qkv_odd, hipStream_t st) {
+template <int D>
+hipError_t launch_begin_as(const SlimArgs& g, const SlimLayer& w, int batch, hipStream_t st) {
     const dim3 grid((g.tokens + ROWS - 1) / ROWS, batch);
-    const int P = g.pg.C * g.pg.patch * g.pg.patch;
-    g.qkv_out = qkv_even;
-    switch (P / 16) {
-        case 1: slim_begin_kernel<D, 1><<<grid, 256, 0, st>>>(g, layers[0]); break;
-        case 2: slim_begin_kernel<D, 2><<<grid, 256, 0, st>>>(g, layers[0]); break;
-        case 3: slim_begin_kernel<D, 3><<<grid, 256, 0, st>>>(g, layers[0]); break;
-        case 4: slim_begin_kernel<D, 4><<<grid, 256, 0, st>>>(g, layers[0]); break;
+    switch (g.pg.C * g.pg.patch * g.pg.patch / 16) {
+        case 1: slim_begin_kernel<D, 1><<<grid, 256, 0, st>>>(g, w); break;
+        case 2: slim_begin_kernel<D, 2><<<grid, 256, 0, st>>>(g, w); break;
+        case 3: slim_begin_kernel<D, 3><<<grid, 256, 0, st>>>(g, w); break;
+        case 4: slim_begin_kernel<D, 4><<<grid, 256, 0, st>>>(g, w); break;
         default: return hipErrorInvalidValue;
     }
-    for (int l = 0; l < count; ++l) {
-        g.layer = l;
-        g.qkv = l % 2 ? qkv_odd : qkv_even;              // a workgroup's next q, k, v must not overwrite keys others still read
-        g.qkv_out = l % 2 ? qkv_even : qkv_odd;
-        if (l + 1 < count) slim_layer_kernel<D, HD, false><<<grid, 256, 0, st>>>(g, layers[l], layers[l + 1]);
-        else slim_layer_kernel<D, HD, true><<<grid, 256, 0, st>>>(g, layers[l], layers[l]);
-    }
+    return hipGetLastError();
+}
+
+template <int D, int HD>
+hipError_t launch_layer_as(const SlimArgs& g, const SlimLayer& w, const SlimLayer* next, int batch, hipStream_t st) {
+    const dim3 grid((g.tokens + ROWS - 1) / ROWS, batch);
+    if (next) slim_layer_kernel<D, HD, false><<<grid, 256, 0, st>>>(g, w, *next);
+    else slim_layer_kernel<D, HD, true><<<grid, 256, 0, st>>>(g, w, w);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_slim(const SlimArgs& g, int hidden, const SlimLayer* layers, int count, int batch, float* qkv_even,
-                       float* qkv_odd, hipStream_t st) {
+hipError_t launch_slim_begin(const SlimArgs& g, int hidden, const SlimLayer& first, int batch, hipStream_t st) {
+    switch (hidden) {
+        case 32: return launch_begin_as<32>(g, first, batch, st);
+        case 64: return launch_begin_as<64>(g, first, batch, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_slim_layer(const SlimArgs& g, int hidden, const SlimLayer& layer, const SlimLayer* next, int batch, hipStream_t st) {
     switch (hidden * 100 + g.head_dim) {
-        case 3216: return launch_slim_as<32, 16>(g, layers, count, batch, qkv_even, qkv_odd, st);
-        case 3232: return launch_slim_as<32, 32>(g, layers, count, batch, qkv_even, qkv_odd, st);
-        case 6416: return launch_slim_as<64, 16>(g, layers, count, batch, qkv_even, qkv_odd, st);
-        case 6432: return launch_slim_as<64, 32>(g, layers, count, batch, qkv_even, qkv_odd, st);
+        case 3216: return launch_layer_as<32, 16>(g, layer, next, batch, st);
+        case 3232: return launch_layer_as<32, 32>(g, layer, next, batch, st);
+        case 6416: return launch_layer_as<64, 16>(g, layer, next, batch, st);
+        case 6432: return launch_layer_as<64, 32>(g, layer, next, batch, st);
         default: return hipErrorInvalidValue;
     }
 }

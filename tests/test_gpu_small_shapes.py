@@ -339,3 +339,28 @@ def test_narrow_network_in_one_launch_per_layer(hidden, heads, channels, patch, 
         one = B.dit_forward(d, xd[b:b + 1].contiguous(), None if cd is None else cd[b:b + 1].contiguous(), [[900, 20][b]])
         assert torch.equal(one[0], eps[b])
     assert graph_nodes(lambda: B.dit_forward(d, xd, cd, [900, 20])) == 4 + 1 + layers
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+def test_profile_of_a_narrow_network_and_of_one_that_is_not(mode):
+    """A narrow network's launches -- tables, two layers of the time MLP, modulation, embedding, one per layer -- all count as
+    "everything else", on the generic kernels and in a wider network a layer's operations count one by one; profiling changes
+    no value."""
+    narrow = I.CONFIGS["tiny_text"].with_(layers=3)
+    for cfg, path, one_launch in ((narrow, 0, True), (narrow, 1, False), (narrow.with_(hidden=128, heads=8), 0, False)):
+        d = B.dit_create(cfg, B.weights_to_device(cfg, I.make_weights(cfg, 1001, "unit"), DEV))
+        B.dit_set_kernel_path(d, path)
+        x, ctx = torch.from_numpy(I.make_latent(cfg, 1)).to(DEV), torch.from_numpy(I.make_context(cfg, 1)).to(DEV)
+        plain = B.dit_forward(d, x, ctx, [500]).clone()
+        B.dit_profile_enable(d, mode)
+        assert torch.equal(B.dit_forward(d, x, ctx, [500]), plain)
+        prof = B.dit_profile_read(d)
+        B.dit_profile_enable(d, 0)
+        for name, (ms, count) in prof.items():
+            layers = 0 if one_launch else 3
+            want = layers if name == "attention" else 0 if mode == 2 else None if name in ("ln_modulate", "other") else layers
+            assert (ms > 0) == (count > 0), name
+            assert want is None or count == want, (name, count)
+        if mode == 1:
+            assert prof["ln_modulate"][1] == 0 if one_launch else prof["ln_modulate"][1] >= 6
+            assert prof["other"][1] == 4 + 1 + 3 if one_launch else prof["other"][1] > 0
