@@ -14,8 +14,8 @@
 //    its transposed fragments come from ds_read_b64_tr_b16.
 //  * attn_sp_kernel: the same tiles, software-pipelined and without a softmax reference; checks its results
 //    and has what fails recomputed by the loop of attn_mfma_kernel.
-#include "common.h"
 #include "plan.h"
+#include "tile_ops.h"
 #include <type_traits>
 
 namespace ps {
@@ -226,15 +226,9 @@ static hipError_t launch_f32_attn(const T* q, const T* k, const T* v, T* o, int 
 }
 
 // --------------------------------------------------------------------------------- MFMA
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(2))) int i32x2_t;
-
-#define PS_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
-#define PS_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
 
 // ds_read_b64_tr_b16: within each group of 16 lanes, lane i receives, for e = 0..3, the
 // 16-bit element (i%4) of the 8 bytes addressed by lane 4*e + i/4 of the same group.
@@ -417,24 +411,17 @@ struct MergeTail {
     AttnGrid g;
 };
 
-// global->LDS load of 16 bytes per lane: lane j's bytes land at lds_addr + 16*j (lds_addr
-// wave-uniform, passed through M0).  _base: scalar 64-bit base + per-lane 32-bit byte offset;
-// _ptr: per-lane 64-bit address.
 // XOR applied to the 16-byte chunk index of V row r in LDS (low three bits of r matter): bits 0-1 = r & 3,
 // bit 2 = bit 1 of r.  A transposing fragment read covers rows 4m..4m+3 with 32 lanes per cycle; rows r and
 // r + 2 start in the same bank, and the flipped bit 2 keeps their 64-byte windows apart (with r & 7 instead
 // every such read took twice as long: measured as LDS bank conflict cycles).
 __device__ __forceinline__ int v_swizzle(int r) { return (r & 3) | ((r & 2) << 1); }
 
+// lds_dma16 from a scalar 64-bit base + per-lane 32-bit byte offset
 __device__ __forceinline__ void lds_dma16_base(unsigned voff, const void* sbase, unsigned lds_addr) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_addr)
                  : "memory", "m0");
 }
-__device__ __forceinline__ void lds_dma16_ptr(const void* gptr, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_addr)
-                 : "memory", "m0");
-}
-
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 // acc + sum of eight bf16 values (v_dot2c_f32_bf16 against packed ones)
 __device__ __forceinline__ float rowsum_bf16x8(bf16x8_t p, float acc) {
@@ -553,8 +540,8 @@ attn_tracked(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const b
                 int kr = tile * KV + g * 8 + lr;
                 kr = kr < seq ? kr : seq - 1;        // rows past the end re-read the last key (masked later)
                 const int lc_k = (lane & 7) ^ (((g & 1) << 2) | (lane >> 4));
-                lds_dma16_ptr(kbase + (long)kr * s.k_tok + lc_k * 8, st + g * 1024);
-                lds_dma16_ptr(vbase + (long)kr * s.v_tok + lc_v * 8, st + KV * 128 + g * 1024);
+                lds_dma16(kbase + (long)kr * s.k_tok + lc_k * 8, st + g * 1024);
+                lds_dma16(vbase + (long)kr * s.v_tok + lc_v * 8, st + KV * 128 + g * 1024);
             }
         }
     };
@@ -913,8 +900,8 @@ attn_sp_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const
                 int kr = tile * KV + g * 8 + lr;
                 kr = kr < seq ? kr : seq - 1;        // rows past the end re-read the last key (masked later)
                 const int lc_k = (lane & 7) ^ (((g & 1) << 2) | (lane >> 4));
-                lds_dma16_ptr(kbase + (long)kr * s.k_tok + lc_k * 8, st + g * 1024);
-                lds_dma16_ptr(vbase + (long)kr * s.v_tok + lc_v * 8, st + KV * 128 + g * 1024);
+                lds_dma16(kbase + (long)kr * s.k_tok + lc_k * 8, st + g * 1024);
+                lds_dma16(vbase + (long)kr * s.v_tok + lc_v * 8, st + KV * 128 + g * 1024);
             }
         }
     };

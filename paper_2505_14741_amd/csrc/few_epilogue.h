@@ -1,21 +1,11 @@
 // Epilogues of the few-token kernels: a lane holds 4 adjacent output columns of one row.
 #pragma once
-#include "common.h"
+#include "tile_ops.h"
 
 namespace ps {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-typedef __attribute__((ext_vector_type(2))) float f32x2_t;
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
-
 __device__ __forceinline__ float gelu_of(float x, float) { return gelu_tanh_f(x); }
-// where the result is rounded to bf16: x * sigmoid(2u), u = sqrt(2/pi)(x + 0.044715 x^3)
-__device__ __forceinline__ float gelu_of(float x, bf16_t) {
-    const float c0 = -2.0f * 0.7978845608028654f * 1.4426950408889634f;
-    const float t = x * (c0 + c0 * 0.044715f * x * x);
-    return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
-}
+__device__ __forceinline__ float gelu_of(float x, bf16_t) { return gelu_fast(x); }
 
 __device__ __forceinline__ void store_quad(float* p, f32x4_t v) { *reinterpret_cast<f32x4_t*>(p) = v; }
 __device__ __forceinline__ void store_quad(bf16_t* p, f32x4_t v) {
@@ -75,7 +65,7 @@ __device__ __forceinline__ void epilogue_quad(const Epilogue& ep, T* __restrict_
         for (int c = 0; c < 4; ++c) x[c] = gelu_of(x[c], T{});
     }
     if constexpr (KIND == EPI_GATE_RESIDUAL) {
-        *reinterpret_cast<f32x4_t*>(ep.resid + (long)row * Nn + col) = o.aux + o.gate * x;
+        *reinterpret_cast<f32x4_t*>(ep.resid + (long)row * Nn + col) = gated_sum(o.aux, o.gate, x);
         return;
     }
     if constexpr (KIND == EPI_UNPATCHIFY) {
@@ -93,9 +83,7 @@ __device__ __forceinline__ void epilogue_quad(const Epilogue& ep, T* __restrict_
         return;
     }
     if constexpr (KIND == EPI_QKV_ROPE) {
-        const f32x4_t t = o.aux;
-        if (r.n >= ep.geom.text_tokens && col < 2 * ep.D)
-            x = f32x4_t{x[0] * t[0] - x[1] * t[1], x[1] * t[0] + x[0] * t[1], x[2] * t[2] - x[3] * t[3], x[3] * t[2] + x[2] * t[3]};
+        if (r.n >= ep.geom.text_tokens && col < 2 * ep.D) x = rotate_quad(x, o.aux);
         if (col < ep.D) x *= ep.q_scale;
     }
     store_quad(C + (long)row * Nn + col, x);

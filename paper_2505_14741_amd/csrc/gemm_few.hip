@@ -25,12 +25,6 @@ namespace ps {
 
 static constexpr int ROWB = FEW_ROW_BYTES;               // bytes of an operand row per stage: 64 bf16 or 32 fp32
 
-// global->LDS load of 16 bytes per lane; lane j's bytes land at lds_addr + 16*j (lds_addr wave-uniform)
-__device__ __forceinline__ void lds_dma16(const void* gptr, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_addr)
-                 : "memory", "m0");
-}
-
 // the loads of at most `stages` stages (G instructions each) may stay in flight
 template <int G>
 __device__ __forceinline__ void wait_stages(int stages) {
@@ -43,8 +37,8 @@ __device__ __forceinline__ void wait_stages(int stages) {
     }
 }
 
-// pieces: workgroups along K per tile; nsplit: K pieces per output (INREG: one workgroup adds them up in registers, in the
-// order and with the roundings of the reduction).
+// nsplit: K pieces per output, a workgroup each (INREG: one workgroup per tile adds them up in registers, in the order and with
+// the roundings of the reduction).
 struct FewGrid { int rows, tiles_m, tiles_n, nsplit; };
 
 // WR x WC waves; a wave computes TM x TN blocks of 16 x 16 outputs.  NST: stages in the LDS ring.
@@ -57,11 +51,8 @@ gemm_few_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict_
     static_assert(NST >= 2 && NST <= 4, "wait_stages counts to 3");
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
     const int M = g.rows, pieces = INREG ? 1 : g.nsplit;
-    int id, piece, m0, n0;
-    {   // ids that share an XCD are contiguous, so that the row tiles of one W panel fetch it into that XCD's L2 once
-        const int total = gridDim.x, per = total / 8, rem = total % 8, x = blockIdx.x % 8;
-        id = x * per + (x < rem ? x : rem) + blockIdx.x / 8;
-    }
+    int id = xcd_remap(blockIdx.x, gridDim.x), piece, m0, n0;
+    // (ids that share an XCD are contiguous, so that the row tiles of one W panel fetch it into that XCD's L2 once)
     if (g.tiles_m <= 8) {
         m0 = id % g.tiles_m * BM; id /= g.tiles_m;
         piece = id % pieces;    n0 = id / pieces * BN;
@@ -91,7 +82,7 @@ gemm_few_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict_
                                     : reinterpret_cast<const char*>(W) + (long)min(n0 + row - AROWS, Nn - 1) * row_bytes;
         gp[i] = base + chunk * 16 + (long)k0 * ROWB;
     }
-    const unsigned lds_base = (unsigned)(size_t)((__attribute__((address_space(3))) void*)lds);
+    const unsigned lds_base = (unsigned)(size_t)PS_LDS_PTR(lds);
     auto issue_one = [&](int kt, int slot, int i) {
         lds_dma16(gp[i] + (long)kt * ROWB, __builtin_amdgcn_readfirstlane(lds_base + slot * STAGE + (wave + NW * i) * 1024));
     };

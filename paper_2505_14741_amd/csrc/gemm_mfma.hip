@@ -27,24 +27,10 @@
 // on 16-byte pieces: one 8-byte bf16 store (or 16-byte fp32 store) per 4 outputs, whole
 // 128-byte lines per row, the residual / rotary-table operands fetched as 16- / 8-byte loads
 // one 32-row strip ahead.
-#include "common.h"
 #include "plan.h"
+#include "tile_ops.h"
 
 namespace ps {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-
-#define PS_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
-#define PS_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
-
-// Consecutive workgroup ids go to different XCDs (8 of them, each with its own L2).
-// Give each XCD a contiguous range of tiles so co-resident workgroups share operand panels.
-__device__ __forceinline__ int xcd_remap(int id, int total) {
-    int per = total / 8, rem = total % 8;
-    int x = id % 8, j = id / 8;
-    return x * per + (x < rem ? x : rem) + j;
-}
 
 // Tile id -> first row and column of the tile.  Tiles walk down the 8 tile rows of a band, column after column, so
 // the workgroups resident on one XCD (a contiguous range of ids, about one band) cover a compact block of the
@@ -59,19 +45,6 @@ __device__ __forceinline__ void tile_origin(int tile, int tiles_m, int tiles_n, 
     m0 = (band * GM + in_band % rows_here) * bm;
     n0 = ((in_band / rows_here + band * max(1, tiles_n / 8)) % tiles_n) * bn;
 }
-
-// tanh-form GELU written as x * sigmoid(2u), u = sqrt(2/pi)(x + 0.044715 x^3): two
-// transcendentals and four FMAs; used where the result is rounded to bf16.
-__device__ __forceinline__ float gelu_fast(float x) {
-    const float c0 = -2.0f * 0.7978845608028654f * 1.4426950408889634f;
-    const float c1 = c0 * 0.044715f;
-    float t = x * (c0 + c1 * x * x);
-    return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
-}
-
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-typedef __attribute__((ext_vector_type(2))) float f32x2_t;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
 
 constexpr int EPI_LDS_STRIDE = 68;                       // floats per row of a wave's 32 x 64 patch (68 * 4 rows = 16 banks mod 64)
 constexpr int EPI_LDS_FLOATS = 32 * EPI_LDS_STRIDE;
@@ -212,8 +185,7 @@ __device__ __forceinline__ void wave_epilogue(f32x4_t (&acc)[TM][TN][4], const E
             }
             if constexpr (KIND == EPI_QKV_ROPE) {
                 // t = (cos0, sin0, cos1, sin1); identity for text tokens and v columns
-                x = f32x4_t{x[0] * t[0] - x[1] * t[1], x[1] * t[0] + x[0] * t[1],
-                            x[2] * t[2] - x[3] * t[3], x[3] * t[2] + x[2] * t[3]} * qs;
+                x = rotate_quad(x, t) * qs;
             }
             if (CHECK && (m >= M || !col_ok)) continue;
             if constexpr (KIND == EPI_UNPATCHIFY) {
@@ -244,7 +216,7 @@ __device__ __forceinline__ void wave_epilogue(f32x4_t (&acc)[TM][TN][4], const E
                     const float* g = ep.mod_layer + b * ep.mod_batch_stride + col;
                     gate = *reinterpret_cast<const f32x4_t*>(g + (ep.gate_chunk + (n < text ? 6 : 0)) * ep.D);
                 }
-                *reinterpret_cast<f32x4_t*>(ep.resid + off) = t + gate * x;
+                *reinterpret_cast<f32x4_t*>(ep.resid + off) = gated_sum(t, gate, x);
             } else {
                 *reinterpret_cast<bf16x4_t*>(reinterpret_cast<unsigned short*>(C) + off) =
                     __builtin_convertvector(x, bf16x4_t);
@@ -253,14 +225,6 @@ __device__ __forceinline__ void wave_epilogue(f32x4_t (&acc)[TM][TN][4], const E
     }
 }
 
-// global->LDS load of 16 bytes per lane, issued from inline asm: lane j's bytes land at
-// lds_addr + 16*j (lds_addr wave-uniform, passed through M0).  The compiler does not see the
-// LDS write, so it never orders LDS reads of other stages behind loads still in flight; the
-// explicit vmcnt waits and barriers in the kernel make a stage visible before it is read.
-__device__ __forceinline__ void lds_dma16(const void* gptr, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_addr)
-                 : "memory", "m0");
-}
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
