@@ -585,62 +585,12 @@ bool gemm_mfma_supported(int tokens, int Nn, int K) {
     return K % 64 == 0 && Nn % 4 == 0 && tokens >= 1 && Nn >= 64 && K >= 64 && (long)tokens * Nn < (1L << 31);
 }
 
-// How a sample's [tokens, Nn] output is spread over the chip: which tile, how many tiles run whole and how the rest is
-// split along K.  A function of the sample's shape only (never of the batch): see gemm_mfma_kernel.
-struct GemmPlan { int tile, tiles_m, tiles_n, full, tail, nsplit; size_t ws_bytes_per_sample; };
-
-// the K split of the last partial round: pieces per tail tile (1: none)
-static int tail_split(long tiles, long slots, int K, bool allow_split) {
-    const long tail = tiles % slots, nk = K / 64;
-    if (!allow_split || K < 4096 || tail == 0) return 1;
-    long ns = slots / tail;
-    if (ns > 8) ns = 8;
-    if (ns > nk / 2) ns = nk / 2;
-    return ns >= 2 ? (int)ns : 1;
-}
-
-// pieces > 0: every tile is summed in that many K pieces (1: whole), which the caller has fixed for the sample's shape.
-static GemmPlan gemm_plan(int tokens, int Nn, int K, bool allow_split, int forced_variant, int pieces) {
-    GemmPlan p{};
-    const int cus = compute_units();
-    const auto slots_of = [&](int tile) { return (long)cus * kTiles[tile].per_cu; };
-    if (forced_variant >= 1 && forced_variant <= 4) {
-        p.tile = WIDE_256x256 + forced_variant - 1;
-    } else {
-        // (for the kind of epilogue that follows a long K, whichever the call's is: the plan belongs to the shape)
-        p.tile = best_tile(0, TILE_KINDS - 1, tokens, Nn, K, 1, true, cus);
-        float best = tile_time(p.tile, tile_count(p.tile, tokens, Nn), (float)(K / 64), true, cus);
-        // The last partial round of a long K in pieces, which count as 1/pieces of a round plus a third of one for the
-        // partial sums (two passes over tile-size fp32 per piece) and the second launch -- measured at 17776 tokens: worth
-        // it with a long K (1920 x 7680: 0.62 -> 0.57 ms on 128 x 128 tiles), not with K = 1920 (0.188 -> 0.196 ms); 1920 x
-        // 7680 at 13000 rows: 192 x 256 tiles in two rounds and 32 tiles of 8 pieces 351 us, 192 x 128 whole 332
-        bool split = false;
-        for (int id = WIDE_256x256; id < TILE_KINDS && pieces == 0; ++id) {
-            const long tiles = tile_count(id, tokens, Nn), slots = slots_of(id);
-            const int ns = tail_split(tiles, slots, K, allow_split);
-            if (ns == 1 || tiles < slots) continue;
-            const float t = tile_time(id, slots, (float)(K / 64), true, cus) * (tiles / slots + 1.0f / ns + 0.35f);
-            if (t < best) { best = t; p.tile = id; split = true; }
-        }
-        allow_split = split;
-    }
-    const Tile& t = kTiles[p.tile];
-    p.tiles_m = (tokens + t.bm - 1) / t.bm;
-    p.tiles_n = (Nn + t.bn - 1) / t.bn;
-    const int tiles = p.tiles_m * p.tiles_n;
-    p.nsplit = pieces > 0 ? pieces : tail_split(tiles, slots_of(p.tile), K, allow_split);
-    p.tail = p.nsplit == 1 ? 0 : pieces > 0 ? tiles : (int)(tiles % slots_of(p.tile));
-    p.full = tiles - p.tail;
-    p.ws_bytes_per_sample = (size_t)p.tail * p.nsplit * t.bm * t.bn * sizeof(float);
-    return p;
-}
-
 // kernel path: low byte = mode (4: never split a tail along K), bits 8-11 = forced tile variant (0: automatic)
 static int forced_variant_of(int path) { return (path >> 8) & 0xf; }
 
 size_t gemm_tiles_workspace_bytes(int batch, int tokens, int Nn, int K, int path, int pieces) {
     if ((path & 0xff) == 4 || (pieces == 0 && K < 4096)) return 0;
-    return gemm_plan(tokens, Nn, K, true, forced_variant_of(path), pieces).ws_bytes_per_sample * (size_t)batch;
+    return gemm_plan(tokens, Nn, K, true, forced_variant_of(path), pieces, compute_units()).ws_bytes_per_sample * (size_t)batch;
 }
 
 hipError_t launch_gemm_few(int dtype, const void* A, const void* W, void* C, int batch, int tokens, int Nn, int K, int tile,
@@ -678,9 +628,9 @@ hipError_t launch_gemm_mfma(const bf16_t* A, const bf16_t* W, bf16_t* C, int bat
     const int fv = forced_variant_of(path);
     Epilogue ep = epi;
     ep.geom.tokens = tokens;                             // (the plain kinds leave it unset)
-    GemmPlan p = gemm_plan(tokens, Nn, K, ep.split_ws != nullptr && tails, fv, pieces);
+    GemmPlan p = gemm_plan(tokens, Nn, K, ep.split_ws != nullptr && tails, fv, pieces, compute_units());
     if (p.ws_bytes_per_sample * (size_t)batch > (ep.split_ws ? ep.split_ws_bytes : 0))
-        p = gemm_plan(tokens, Nn, K, false, fv, pieces > 0 ? 1 : 0);
+        p = gemm_plan(tokens, Nn, K, false, fv, pieces > 0 ? 1 : 0, compute_units());
     if (p.nsplit == 1) {
         // Whole sums have the same values on every tile: the rows of all samples are one matrix (while its offsets fit 32
         // bits), tiles may hold rows of two samples, and the choice counts the whole batch.  (4 samples of 2608 tokens,

@@ -89,6 +89,56 @@ constexpr int best_tile(int first, int last, long rows, int Nn, int K, int piece
     return best;
 }
 
+// ---- bf16 projections on the tiles of gemm_mfma.hip
+// How a sample's [tokens, Nn] output is spread over the chip: which tile, how many tiles run whole and how the rest is
+// split along K.  A function of the sample's shape only (never of the batch): see gemm_mfma_kernel.
+struct GemmPlan { int tile, tiles_m, tiles_n, full, tail, nsplit; size_t ws_bytes_per_sample; };
+
+// the K split of the last partial round: pieces per tail tile (1: none)
+constexpr int gemm_tail_split(long tiles, long slots, int K, bool allow_split) {
+    const long tail = tiles % slots, nk = K / 64;
+    if (!allow_split || K < 4096 || tail == 0) return 1;
+    long ns = slots / tail;
+    if (ns > 8) ns = 8;
+    if (ns > nk / 2) ns = nk / 2;
+    return ns >= 2 ? (int)ns : 1;
+}
+
+// pieces > 0: every tile is summed in that many K pieces (1: whole), which the caller has fixed for the sample's shape.
+constexpr GemmPlan gemm_plan(int tokens, int Nn, int K, bool allow_split, int forced_variant, int pieces, int cus) {
+    GemmPlan p{};
+    const auto slots_of = [cus](int tile) { return (long)cus * kTiles[tile].per_cu; };
+    if (forced_variant >= 1 && forced_variant <= 4) {
+        p.tile = WIDE_256x256 + forced_variant - 1;
+    } else {
+        // (for the kind of epilogue that follows a long K, whichever the call's is: the plan belongs to the shape)
+        p.tile = best_tile(0, TILE_KINDS - 1, tokens, Nn, K, 1, true, cus);
+        float best = tile_time(p.tile, tile_count(p.tile, tokens, Nn), (float)(K / 64), true, cus);
+        // The last partial round of a long K in pieces, which count as 1/pieces of a round plus a third of one for the
+        // partial sums (two passes over tile-size fp32 per piece) and the second launch -- measured at 17776 tokens: worth
+        // it with a long K (1920 x 7680: 0.62 -> 0.57 ms on 128 x 128 tiles), not with K = 1920 (0.188 -> 0.196 ms); 1920 x
+        // 7680 at 13000 rows: 192 x 256 tiles in two rounds and 32 tiles of 8 pieces 351 us, 192 x 128 whole 332
+        bool split = false;
+        for (int id = WIDE_256x256; id < TILE_KINDS && pieces == 0; ++id) {
+            const long tiles = tile_count(id, tokens, Nn), slots = slots_of(id);
+            const int ns = gemm_tail_split(tiles, slots, K, allow_split);
+            if (ns == 1 || tiles < slots) continue;
+            const float t = tile_time(id, slots, (float)(K / 64), true, cus) * (tiles / slots + 1.0f / ns + 0.35f);
+            if (t < best) { best = t; p.tile = id; split = true; }
+        }
+        allow_split = split;
+    }
+    const Tile& t = kTiles[p.tile];
+    p.tiles_m = (tokens + t.bm - 1) / t.bm;
+    p.tiles_n = (Nn + t.bn - 1) / t.bn;
+    const int tiles = p.tiles_m * p.tiles_n;
+    p.nsplit = pieces > 0 ? pieces : gemm_tail_split(tiles, slots_of(p.tile), K, allow_split);
+    p.tail = p.nsplit == 1 ? 0 : pieces > 0 ? tiles : (int)(tiles % slots_of(p.tile));
+    p.full = tiles - p.tail;
+    p.ws_bytes_per_sample = (size_t)p.tail * p.nsplit * t.bm * t.bn * sizeof(float);
+    return p;
+}
+
 // ---- projections of few tokens and of fp32 operands (gemm_few.hip)
 constexpr int FEW_ROW_BYTES = 128;                       // bytes of an operand row per stage: 64 bf16 or 32 fp32
 

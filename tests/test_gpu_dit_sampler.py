@@ -327,14 +327,38 @@ def test_step_batched_round_at_full_shape_equals_one_call_per_step_bitwise():
 
 
 def test_forward_batch_invariance_at_the_block_shape_bitwise():
-    """One block at 4516 tokens (attention splits its last 28 work items, fc2 its last tiles along K), batch 3 with
-    different timesteps against three single calls."""
+    """One block at 4516 tokens (attention splits its last 28 work items; every projection's sums are whole, on tiles that the
+    rows of the whole batch choose), batch 3 with different timesteps against three single calls."""
     cfg, W, d = setup("block", "unit")
     x, ctx = dev(I.make_latent(cfg, 3)), dev(I.make_context(cfg, 3), torch.bfloat16)
     t = [900, 500, 20]
     full = B.dit_forward(d, x, ctx, t).clone()
     for b in range(3):
         one = B.dit_forward(d, x[b:b + 1].contiguous(), ctx[b:b + 1].contiguous(), t[b:b + 1])
+        assert torch.equal(one[0], full[b]), b
+
+
+SPLIT_GRIDS = [(10, 20, 50, 8), (16, 32, 32, 16)]        # frames, rows, columns, text: 10008 and 16400 tokens
+
+
+@pytest.mark.parametrize("frames,rows,cols,text", SPLIT_GRIDS)
+def test_forward_batch_invariance_where_fc2_splits_its_last_tiles_bitwise(frames, rows, cols, text):
+    """One block of width 1920 whose 1920 x 7680 projection runs its last, partial round of 256 x 256 tiles in K pieces, 64
+    tiles in 4 and 8 in 8, each sample its own: a batch of 2 against single calls."""
+    cfg = I.CONFIGS["reduced"].with_(layers=1, frames=frames, height=2 * rows, width=2 * cols, text_tokens=text)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    w = []
+    for _, shape in I.weight_shapes(cfg):
+        t = torch.randn(shape, generator=g, device="cuda")
+        w.append((t * shape[1] ** -0.5).bfloat16() if len(shape) == 2 else t)
+    d = B.dit_create(cfg, w)
+    x = torch.randn(2, *cfg.latent_shape, generator=g, device="cuda")
+    ctx = torch.randn(2, text, cfg.hidden, generator=g, device="cuda").bfloat16()
+    full = B.dit_forward(d, x, ctx, [700, 30]).clone()
+    assert torch.isfinite(full).all()
+    for b in range(2):
+        one = B.dit_forward(d, x[b:b + 1].contiguous(), ctx[b:b + 1].contiguous(), [[700, 30][b]])
         assert torch.equal(one[0], full[b]), b
 
 

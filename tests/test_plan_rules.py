@@ -23,6 +23,10 @@ extern "C" int how(int bf16, int tokens, int n, int k, int batch) {
 extern "C" int best(int first, int last, long rows, int n, int k, int pieces, int gated) {
     return ps::best_tile(first, last, rows, n, k, pieces, gated != 0, 256);
 }
+extern "C" void wide(int tokens, int n, int k, int* out) {
+    const ps::GemmPlan p = ps::gemm_plan(tokens, n, k, true, 0, 0, 256);
+    out[0] = p.tile; out[1] = p.full; out[2] = p.tail; out[3] = p.nsplit;
+}
 extern "C" int narrow(long bh, int seq) { return ps::attn_narrow_items(bh, seq, 256); }
 extern "C" int kinds(int* few) { *few = ps::FEW_TILE_KINDS; return ps::TILE_KINDS; }
 extern "C" long scratch(int bf16, int tokens, int n, int k, int batch) {
@@ -106,6 +110,16 @@ def test_scratch_of_few_token_projections_serves_every_smaller_batch(rules, bf16
                 if pieces > 1 and rules.how(bf16, tokens, n, k, b) == PIECES:
                     assert size[b - 1] >= 4 * pieces * b * tokens * n
                 assert size[b - 1] <= 4 * max(pieces, 1) * tokens * n * b
+
+
+def test_sizes_of_the_batch_tests_split_where_they_say_so(rules):
+    from test_gpu_dit_sampler import SPLIT_GRIDS
+    plan = lambda tokens: (rules.wide(tokens, 1920, 7680, out), list(out))[1]
+    out = (C.c_int * 4)()
+    tails = [plan(text + f * r * c) for f, r, c, text in SPLIT_GRIDS]
+    assert [t[2:] for t in tails] == [[64, 4], [8, 8]] and all(t[1] % 256 == 0 for t in tails)
+    assert plan(17776)[2] > 0 and plan(17776)[3] > 1     # the 30-layer run
+    assert plan(4516)[2:] == [0, 1]                      # the block
 
 
 FASTEST = [  # rows, columns, K, pieces (1920 columns: with the gated residual update): kinds within 6 % of the fastest measured one (0-5: gemm_few.hip, 6-9: gemm_mfma.hip)
