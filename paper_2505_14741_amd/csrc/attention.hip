@@ -1105,44 +1105,12 @@ attn_redo_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, con
         attn_tracked<1, PRESCALED>(q, k, v, o, seq, scale_log2e, s, b, h, q0, 0, (seq + 63) / 64, -1, nullptr, redo, lds);
 }
 
-// Split plan for the bf16 head-dim-64 kernels (see AttnGrid): per sample, how many work items run whole and how
-// many ways the rest is split along the keys.
-struct AttnPlan { int qblocks, items_ps, full_ps, tail_ps, nsplit, bq; };
-// Where the items of one sample fill the chip (256 heads and more) and up to this many keys, the second launch costs more
-// than the faster loop gains, and the reference-tracking kernel does every head alone.
-static constexpr int TRACKED_ONLY_KEYS = 512;
-// kernel path 3 sends every head to the reference-tracking kernel; otherwise every head first takes the
-// software-pipelined kernel without a reference, which marks the heads it could not do (samples of fewer items: see
-// attention_spread_path)
-static bool attention_checked_path(int path, int seq) { return (path & 0xff) != 3 && seq > TRACKED_ONLY_KEYS; }
-static AttnPlan attention_plan(int seq, int heads) {
-    constexpr int KV = 64;
-    AttnPlan p;
-    p.bq = 256;
-    p.qblocks = (seq + p.bq - 1) / p.bq;
-    p.items_ps = p.qblocks * heads;
-    const int slots = compute_units() * 2;               // two resident workgroups per CU
-    const int tail = p.items_ps % slots;
-    const int ntiles = (seq + KV - 1) / KV;
-    // Fewer items than slots are never split: the plan must not depend on the batch, and a batch that fills the chip by
-    // itself pays 70 KB of partial sums per piece for nothing.  (4 heads x 4096 keys in two pieces: 74 -> 49 us alone, but
-    // 80 -> 94 for four samples and 256 -> 330 for sixteen; 16 heads x 1000 keys, four samples: 30 -> 50.)
-    int ns = tail > 0 ? slots / tail : 1;
-    if (ns > 8) ns = 8;
-    if (ns > ntiles / 2) ns = ntiles / 2;
-    if (tail == 0 || p.items_ps < slots || ns < 2) { p.full_ps = p.items_ps; p.tail_ps = 0; p.nsplit = 1; }
-    else { p.full_ps = p.items_ps - tail; p.tail_ps = tail; p.nsplit = ns; }
-    return p;
-}
-
-// Samples whose items of 256 queries do not fill the chip: no split, no flags (see SpEnd).
-static bool attention_spread_path(int path, const AttnPlan& p) { return (path & 0xff) != 3 && p.items_ps < compute_units() * 2; }
-
+// Samples whose items do not fill the chip, in workgroups of 128 or of 256 queries (see SpEnd).
 template <bool PRESCALED>
-static hipError_t launch_spread_as(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* o, int batch, int seq, int heads,
-                                   float c, const AttnStrides& s, hipStream_t st) {
+static hipError_t launch_spread_as(bool by128, const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* o, int batch, int seq,
+                                   int heads, float c, const AttnStrides& s, hipStream_t st) {
     const int wide = (seq + 255) / 256, narrow = (seq + 127) / 128;
-    if (attn_narrow_items((long)batch * heads, seq, compute_units())) {
+    if (by128) {
         const AttnGrid g{narrow, heads, narrow * heads, 0, 1, batch * narrow * heads};
         attn_sp_kernel<1, SP_ALONE, PRESCALED><<<g.all_full, 256, 0, st>>>(q, k, v, o, seq, c, s, g, nullptr, nullptr);
         return hipGetLastError();
@@ -1160,7 +1128,7 @@ static size_t flags_bytes(int batch, int heads) { return (((size_t)batch * heads
 // workspace of the bf16 head-dim-64 kernels: [one flag per (batch, head) | key-split pieces]
 size_t attention_workspace_bytes(int dtype, int batch, int seq, int heads, int head_dim) {
     if (dtype != PS_BF16 || head_dim != 64 || batch < 1 || seq < 1 || heads < 1) return 0;
-    const AttnPlan p = attention_plan(seq, heads);
+    const AttnPlan p = attention_plan(seq, heads, compute_units());
     const size_t need = (size_t)batch * p.tail_ps * p.nsplit * p.bq * PART_STRIDE * sizeof(float);
     return flags_bytes(batch, heads) + need;
 }
@@ -1172,8 +1140,7 @@ bool attention_uses_mfma(int dtype, int head_dim, int path) {
 float* attention_head_flags(int dtype, int batch, int seq, int heads, int head_dim, void* ws, int path, hipStream_t st,
                             bool clear, int* count) {
     if (count) *count = 0;
-    if (!ws || !attention_uses_mfma(dtype, head_dim, path) || !attention_checked_path(path, seq) ||
-        attention_spread_path(path, attention_plan(seq, heads)))
+    if (!ws || !attention_uses_mfma(dtype, head_dim, path) || attention_route(batch, seq, heads, path, compute_units()) != ATTN_FLAGS)
         return nullptr;
     const int nb = batch * heads;
     if (count) *count = nb;
@@ -1189,13 +1156,14 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
     if (attention_uses_mfma(dtype, head_dim, path)) {
         if (ws == nullptr) return hipErrorInvalidValue;
         if (s.k_tok >= (1 << 24) || s.v_tok >= (1 << 24)) return hipErrorInvalidValue;   // 32-bit in-tile offsets
-        const bool checked = attention_checked_path(path, seq);
-        AttnPlan p = attention_plan(seq, heads);
-        if (attention_spread_path(path, p))
-            return q_prescaled ? launch_spread_as<true>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, batch,
-                                                        seq, heads, scale * 1.4426950408889634f, s, st)
-                               : launch_spread_as<false>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, batch,
-                                                         seq, heads, scale * 1.4426950408889634f, s, st);
+        const AttnRoute route = attention_route(batch, seq, heads, path, compute_units());
+        if (route == ATTN_BY_128 || route == ATTN_BY_256) {
+            const float c = scale * 1.4426950408889634f;
+            const auto launch = q_prescaled ? launch_spread_as<true> : launch_spread_as<false>;
+            return launch(route == ATTN_BY_128, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, batch, seq, heads,
+                          c, s, st);
+        }
+        AttnPlan p = attention_plan(seq, heads, compute_units());
         if ((path & 0xff) == 2) { p.full_ps = p.items_ps; p.tail_ps = 0; p.nsplit = 1; }
         const float c = scale * 1.4426950408889634f;
         const float cexp = q_prescaled ? 1.0f : c;
@@ -1207,7 +1175,7 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
         const AttnGrid whole{p.qblocks, heads, p.items_ps, 0, 1, batch * p.items_ps};
         const int split_blocks = batch * (p.full_ps + p.tail_ps * p.nsplit);
         const int nitems = batch * p.tail_ps;
-        if (checked) {
+        if (route == ATTN_FLAGS) {
             // the kernel without a reference for every head (it marks the heads whose sums left the safe range),
             // then the reference-tracking kernel (unsplit) for the marked heads; each of its workgroups looks its head up
             if (!flags_cleared) {

@@ -35,6 +35,49 @@ constexpr bool attn_narrow_items(long bh, int seq, int cus) {
     return a <= tiles * rounds(wide, 2.27f, 1.29f) + 4.f;
 }
 
+// Split plan of the bf16 head-dim-64 kernels: per sample, how many work items of 256 queries run whole and how many ways the
+// rest is split along the keys.
+struct AttnPlan { int qblocks, items_ps, full_ps, tail_ps, nsplit, bq; };
+constexpr AttnPlan attention_plan(int seq, int heads, int cus) {
+    constexpr int KV = 64;
+    AttnPlan p{};
+    p.bq = 256;
+    p.qblocks = (seq + p.bq - 1) / p.bq;
+    p.items_ps = p.qblocks * heads;
+    const int slots = cus * 2;                           // two resident workgroups per CU
+    const int tail = p.items_ps % slots;
+    const int ntiles = (seq + KV - 1) / KV;
+    // Fewer items than slots are never split: the plan must not depend on the batch, and a batch that fills the chip by
+    // itself pays 70 KB of partial sums per piece for nothing.  (4 heads x 4096 keys in two pieces: 74 -> 49 us alone, but
+    // 80 -> 94 for four samples and 256 -> 330 for sixteen; 16 heads x 1000 keys, four samples: 30 -> 50.)
+    int ns = tail > 0 ? slots / tail : 1;
+    if (ns > 8) ns = 8;
+    if (ns > ntiles / 2) ns = ntiles / 2;
+    if (tail == 0 || p.items_ps < slots || ns < 2) { p.full_ps = p.items_ps; p.tail_ps = 0; p.nsplit = 1; }
+    else { p.full_ps = p.items_ps - tail; p.tail_ps = tail; p.nsplit = ns; }
+    return p;
+}
+
+// Which kernels a bf16 head-dim-64 call takes.
+//   ATTN_BY_128   attn_sp_kernel alone, 128 queries per workgroup, which redoes its own failures
+//   ATTN_BY_256   attn_sp_kernel with 256 queries per workgroup, then attn_redo_kernel
+//   ATTN_FLAGS    attn_sp_kernel marks the (batch, head) pairs it could not do, attn_mfma_kernel redoes those; key pieces
+//   ATTN_TRACKED  attn_mfma_kernel for every head
+// Samples whose items do not fill the chip take one of the first two: no split, no flags; the values of the two are the same,
+// so the whole batch may decide between them.  Which samples these are must not depend on the batch, and a large batch of short
+// ones is slower so than it was on attn_mfma_kernel alone: 30 heads x 512 keys, 16 samples 49.2 -> 51.4 us, 200 keys 22.5 ->
+// 23.9 (one sample 17.7 -> 12.6 and 12.1 -> 8.7).
+// Samples of 512 items and more (256 heads and more) of up to 512 keys: the second launch of ATTN_FLAGS costs more than the
+// faster loop gains.
+// path: kernel path (low byte 3: ATTN_TRACKED always).
+enum AttnRoute { ATTN_BY_128, ATTN_BY_256, ATTN_FLAGS, ATTN_TRACKED };
+constexpr AttnRoute attention_route(int batch, int seq, int heads, int path, int cus) {
+    if ((path & 0xff) == 3) return ATTN_TRACKED;
+    if (attention_plan(seq, heads, cus).items_ps < cus * 2)
+        return attn_narrow_items((long)batch * heads, seq, cus) ? ATTN_BY_128 : ATTN_BY_256;
+    return seq > 512 ? ATTN_FLAGS : ATTN_TRACKED;
+}
+
 // ---- projections: C[rows, Nn] = A[rows, K] * W[Nn, K]^T, rows = all samples of the batch
 // Output tiles of the matrix kernels: gemm_few.hip (any K pieces; fp32 and bf16) and gemm_mfma.hip (bf16).
 enum TileId { FEW_64x64, FEW_128x64, FEW_128x128, FEW_192x128, FEW_256x128, FEW_192x192, FEW_TILE_KINDS,

@@ -161,8 +161,7 @@ def test_attention_fp32_matches_oracle(N, d):
 
 @pytest.mark.parametrize("N", [1, 31, 63, 64, 65, 127, 129, 255, 257, 512, 513, 543, 575, 576, 577, 639, 767, 769, 1000])
 def test_attention_bf16_mfma_matches_oracle(N):
-    """Up to 512 keys one kernel that tracks a softmax reference, beyond it the one without and its fallback: ragged last
-    key tiles of both."""
+    """Three heads do not fill the chip: workgroups of 128 queries without a softmax reference, ragged last key tiles."""
     print(f"attn3d bf16 N={N}", flush=True)
     q, k, v = I.make_qkv(2, N, 3, 64, dtype="bf16")
     o = B.attn3d(dev(q, torch.bfloat16), dev(k, torch.bfloat16), dev(v, torch.bfloat16), 0.125)
@@ -174,7 +173,7 @@ def test_attention_bf16_mfma_matches_oracle(N):
 
 @pytest.mark.parametrize("N", [333, 700])
 def test_attention_bf16_large_logits_and_poisoned_workspace(N):
-    """Logit std ~ 4 (sharp softmax), NaN-filled scratch and output must not leak (333 keys need no scratch)."""
+    """Logit std ~ 4 (sharp softmax), NaN-filled scratch and output must not leak."""
     q, k, v = I.make_qkv(1, N, 2, 64, dtype="bf16", scale=2.0)
     qd, kd, vd = (dev(a, torch.bfloat16) for a in (q, k, v))
     out = torch.full_like(qd, float("nan"))
@@ -226,11 +225,12 @@ def test_attention_bf16_split_items_marked_heads_and_poisoned_workspace_in_a_bat
 @pytest.mark.parametrize("case", ["huge_everywhere", "small_first_tile_then_huge", "all_far_below_zero",
                                   "moderate_above_window", "common_offset_plus_70", "common_offset_minus_30"])
 def test_attention_bf16_reference_shifts(case):
-    """The kernel without a softmax reference checks its own sums and hands heads it cannot do to the kernel that
-    tracks a reference, which keeps that reference at 0 while it safely can; these inputs overflow 2^(c s)
-    everywhere, only from a later tile on, or underflow it (all handed over, the reference moves on the first tile,
-    on a later tile, downwards), or stay inside the range the first kernel accepts although every exponent is
-    far from zero (+70, -30: no hand-over, sums of 2^80 and 2^-20)."""
+    """The kernel without a softmax reference checks its own sums, and queries it cannot do are computed again with a
+    tracked reference, which stays at 0 while it safely can -- in this shape (two heads) by their own workgroups of 128
+    queries, see the next test for the others; these inputs overflow 2^(c s) everywhere, only from a later tile on, or
+    underflow it (all redone, the reference moves on the first tile, on a later tile, downwards), or stay inside the range
+    the first kernel accepts although every exponent is far from zero (+70, -30: nothing redone, sums of 2^80 and
+    2^-20)."""
     N = 700
     print(f"attn3d bf16 reference case {case}", flush=True)
     q, k, v = I.make_qkv(1, N, 2, 64, dtype="bf16")
@@ -257,6 +257,74 @@ def test_attention_bf16_reference_shifts(case):
     torch.cuda.synchronize()
     assert torch.isfinite(o).all()
     assert_close_bf16(host(o), O.attn3d(q, k, v, scale), 2e-2, max_tol=3e-2)
+
+
+# (batch, keys, heads) by the kernels they take: workgroups of 256 queries and a launch that redoes what they could not do,
+# heads marked and redone whole, every head with a tracked reference
+BY_256, FLAGS, TRACKED = 1, 2, 3
+ROUTE_SIZES = ([(BY_256, 16, n, 16) for n in (700, 703, 704, 705, 767, 768, 769, 1000, 1023, 1025)] +
+               [(FLAGS, 1, n, 200) for n in (513, 543, 575, 576, 577, 600, 639, 640, 641, 700, 767, 769)] +
+               [(FLAGS, 1, 513, 256)] + [(TRACKED, 1, n, 256) for n in (257, 300, 447, 448, 449, 511, 512)] +
+               [(TRACKED, 1, n, 512) for n in (1, 31, 63, 64, 65, 127, 129, 255)])
+
+
+def attention_inputs(batch, N, heads, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    return tuple(torch.randn(batch, N, heads, 64, generator=g, device=DEV) for _ in range(3))
+
+
+def assert_heads_match_oracle(out, q, k, v, scale, picks, max_tol):
+    for b, h in picks:
+        ref = O.attn3d(*(host(t[b:b + 1, :, h:h + 1]) for t in (q, k, v)), scale)
+        assert_close_bf16(host(out[b:b + 1, :, h:h + 1]), ref, 2e-2, max_tol=max_tol)
+
+
+@pytest.mark.parametrize("case", ["huge_everywhere", "small_first_tile_then_huge", "all_far_below_zero",
+                                  "moderate_above_window", "common_offset_plus_70", "common_offset_minus_30"])
+@pytest.mark.parametrize("batch,N,heads", [(16, 1000, 16), (1, 700, 200)])
+def test_attention_bf16_reference_shifts_in_workgroups_of_256_queries(case, batch, N, heads):
+    """The inputs of the test before at shapes whose workgroups take 256 queries: 16 samples of 16 heads leave what they could
+    not do, 32 queries at a time, to a second launch; 200 heads fill the chip, mark whole heads and run the last 88 items of
+    256 queries (heads from 170 on) in key pieces."""
+    print(f"attn3d bf16 reference case {case} {batch} x {N} x {heads}", flush=True)
+    q, k, v = attention_inputs(batch, N, heads, 5)
+    scale = 1.0
+    if case == "huge_everywhere":
+        scale = 8.0
+    elif case == "small_first_tile_then_huge":
+        scale = 8.0
+        k[:, :64] *= 0.01
+    elif case == "all_far_below_zero":
+        q, k = q * 0.125, k * 0.125
+        q[..., 0], k[..., 0] = 8.0, -8.0
+    elif case.startswith("common_offset"):
+        q, k = q * 0.125, k * 0.125
+        a = 7.0 if case.endswith("plus_70") else 4.56
+        q[..., 0], k[..., 0] = a, (a if case.endswith("plus_70") else -a)
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    o = B.attn3d(q, k, v, scale)
+    assert torch.isfinite(o).all()
+    picks = [(0, 0), (0, 15), (7, 3), (15, 15)] if batch > 1 else [(0, h) for h in (0, 99, 170, 171, 199)]
+    assert_heads_match_oracle(o, q, k, v, scale, picks, 3e-2)
+
+
+@pytest.mark.parametrize("route,batch,N,heads", ROUTE_SIZES)
+def test_attention_bf16_ragged_keys_on_every_route(route, batch, N, heads):
+    """Last key tiles of every kind of remainder in the kernels that the shape above does not reach; two heads of 16, apart,
+    overflow and the others keep what they have alone."""
+    print(f"attn3d bf16 {batch} x {N} x {heads}", flush=True)
+    q, k, v = attention_inputs(batch, N, heads, N)
+    last = (batch - 1, heads - 1)
+    for b, h in ((0, 3), last):
+        q[b, :, h] *= 16.0
+        k[b, :, h] *= 16.0
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    o = B.attn3d(q, k, v, 0.125)
+    assert torch.isfinite(o).all()
+    assert_heads_match_oracle(o, q, k, v, 0.125, [(0, 0), (0, 3), (0, heads - 2), (batch // 2, heads // 2), last], 4e-2)
+    b = batch - 1
+    assert torch.equal(B.attn3d(q[b:].contiguous(), k[b:].contiguous(), v[b:].contiguous(), 0.125)[0], o[b])
 
 
 @pytest.mark.parametrize("N", [64, 300, 1000])
@@ -321,9 +389,9 @@ def test_attention_bf16_batch_invariance_at_a_shape_that_splits():
             assert torch.equal(one[0], full[b]), (path, b)
 
 
-def test_attention_bf16_marked_head_in_one_sample_of_a_batch():
-    """A head whose scores overflow in sample 1 only: that (sample, head) alone is handed to the reference-tracking
-    kernel, every sample still equals its single call bit for bit, and all agree with the oracle."""
+def test_attention_bf16_overflowing_head_in_one_sample_of_a_batch():
+    """A head whose scores overflow in sample 1 only: its queries alone are computed again with a tracked reference, every
+    sample still equals its single call bit for bit, and all agree with the oracle."""
     N, H = 700, 3
     q, k, v = I.make_qkv(3, N, H, 64, dtype="bf16")
     q[1, :, 2, :] *= 16.0
@@ -339,14 +407,14 @@ def test_attention_bf16_marked_head_in_one_sample_of_a_batch():
         assert torch.equal(one[0], full[b]), b
         for h in range(H):
             assert_close_bf16(host(full)[b, :, h], ref[b, :, h], 2e-2, max_tol=3e-2)
-    # the overflowing head really needs the other kernel: forced through it, the result is the same
+    # the overflowing head really needs a reference: forced through the kernel that tracks one, the result is the same
     forced = B.attn3d(qd[1:2].contiguous(), kd[1:2].contiguous(), vd[1:2].contiguous(), 0.125, kernel_path=3)
     assert torch.equal(forced[0, :, 2], full[1, :, 2])
 
 
-def test_attention_bf16_mixed_heads_take_different_kernels():
-    """One head with huge scores (its key sums overflow without a softmax reference) next to ordinary heads: the
-    first kernel marks that head, the reference-tracking kernel redoes it, and all agree with the oracle."""
+def test_attention_bf16_huge_head_next_to_ordinary_heads():
+    """One head with huge scores (its key sums overflow without a softmax reference) next to ordinary heads: its
+    workgroups redo its queries with a tracked reference, and all agree with the oracle."""
     N = 700
     q, k, v = I.make_qkv(1, N, 3, 64, dtype="bf16")
     q[:, :, 1, :] *= 16.0

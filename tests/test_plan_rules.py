@@ -28,6 +28,7 @@ extern "C" void wide(int tokens, int n, int k, int* out) {
     out[0] = p.tile; out[1] = p.full; out[2] = p.tail; out[3] = p.nsplit;
 }
 extern "C" int narrow(long bh, int seq) { return ps::attn_narrow_items(bh, seq, 256); }
+extern "C" int route(int batch, int seq, int heads, int path) { return ps::attention_route(batch, seq, heads, path, 256); }
 extern "C" int kinds(int* few) { *few = ps::FEW_TILE_KINDS; return ps::TILE_KINDS; }
 extern "C" long scratch(int bf16, int tokens, int n, int k, int batch) {
     return (long)ps::few_workspace_bytes(bf16 != 0, ps::few_plan(bf16 != 0, tokens, n, k, 0), batch, tokens, n, k);
@@ -153,3 +154,20 @@ def test_attention_workgroups_of_128_queries_where_they_are_faster(rules):
     assert narrow(16, 1000) and narrow(256, 31) and narrow(256, 129)
     assert not narrow(16, 4200) and not narrow(16, 6000) and not narrow(8, 12000) and not narrow(4, 17776)
     assert narrow(8, 4200) and narrow(4, 6000) and narrow(4, 12000) and narrow(128, 700)
+
+
+def test_sizes_of_the_attention_tests_take_the_kernels_they_name(rules):
+    from test_gpu_kernels import BY_256, FLAGS, ROUTE_SIZES, TRACKED
+    BY_128 = 0
+    for route, batch, keys, heads in ROUTE_SIZES:
+        assert rules.route(batch, keys, heads, 0) == route, (batch, keys, heads)
+        assert rules.route(batch, keys, heads, 3) == TRACKED
+    assert rules.route(16, 1000, 16, 0) == BY_256 and rules.route(1, 700, 200, 0) == FLAGS and rules.route(2, 513, 200, 0) == FLAGS
+    assert rules.route(1, 4516, 30, 0) == FLAGS and rules.route(1, 17776, 30, 0) == FLAGS
+    for batch, keys, heads in ((1, 700, 2), (3, 700, 3), (2, 1000, 3), (2, 1, 3), (2, 4096, 4), (1, 1000, 16)):
+        assert rules.route(batch, keys, heads, 0) == BY_128, (batch, keys, heads)
+    # samples of fewer than 512 items of 256 queries never take the last two, whatever the batch
+    for heads in (1, 30, 200, 255):
+        for keys in (1, 64, 300, 512, 513, 2000, 17776):
+            small = heads * -(-keys // 256) < 512
+            assert all((rules.route(b, keys, heads, 0) < FLAGS) == small for b in (1, 2, 16, 1024))
