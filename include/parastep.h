@@ -19,10 +19,10 @@
  *    default stream) and the call returns without synchronising; outputs, including
  *    device-side sums, are valid once the caller has synchronised that stream;
  *  - results are deterministic: no floating-point atomics, fixed reduction order;
- *  - a sample's result does not depend on the batch it is computed in: every sample of a
- *    batch is tiled and summed exactly as if it were alone (Section 3.3: the batched step
- *    must reproduce the per-step process), so dit_forward on B samples equals B calls bit
- *    for bit;
+ *  - a sample's result does not depend on the batch it is computed in: every sum is formed
+ *    exactly as if the sample were alone, whichever workgroup forms it (Section 3.3: the
+ *    batched step must reproduce the per-step process), so dit_forward on B samples equals
+ *    B calls bit for bit;
  *  - the library keeps no process-wide mutable state: kernels are selected per call from
  *    the shapes and from the kernel path of the handle (dit_set_kernel_path) or of the
  *    call (attn3d, dit_linear);
@@ -151,11 +151,13 @@ PS_API int ps_mfma_probe(int iters, float* sink, double* flops_out, void* hip_st
  * the inputs.  seq >= 1, scale > 0, head_dim in {16, 32, 64}; rows past the end are never
  * read, but V must be finite (masked keys multiply V by an exact 0).
  * workspace: DEVICE, 256-byte aligned, >= attn3d_workspace_bytes(...) (may be NULL when
- * that is 0); scratch only.  It is non-zero for bf16 with head_dim 64: the kernel that needs no
- * running maximum (sequences beyond 512) checks its own sums and marks, per (batch, head), what it could not do there
- * (a second kernel that tracks a softmax reference recomputes those heads), and the workgroups
- * that split their keys in the last, partial round leave their partial sums there (merged by
- * that second launch).
+ * that is 0); scratch only.  It is non-zero for bf16 with head_dim 64, whose kernel needs no running
+ * maximum and checks its own sums: where a sample's blocks of 256 queries fill the chip (beyond
+ * 512 keys), it marks in the scratch, per (batch, head), what it could not do (a second kernel that
+ * tracks a softmax reference recomputes those heads), and the workgroups that split their keys in
+ * the last, partial round leave their partial sums there (merged by that second launch).  Samples
+ * that do not fill the chip redo groups of 32 queries with a tracked reference and leave the
+ * scratch alone.
  * kernel_path: as for dit_set_kernel_path (0 = default); the workspace size does not depend on it. */
 PS_API size_t attn3d_workspace_bytes(int batch, int seq, int heads, int head_dim, int dtype);
 PS_API int attn3d(const void* q, const void* k, const void* v, void* o,
@@ -168,9 +170,11 @@ PS_API int attn3d(const void* q, const void* k, const void* v, void* o,
  * 16-byte aligned.  n_out even, k % 8 == 0; bf16 shapes of the MFMA kernel (k % 64 == 0,
  * n_out % 4 == 0, n_out >= 64) need m * n_out < 2^31.
  * workspace: DEVICE scratch, 256-byte aligned, or NULL.  With at least
- * dit_linear_workspace_bytes(...) of it, shapes whose output tiles do not fill the chip, or the
- * last round of workgroups on it, split those tiles along k (fp32 partial sums pass through the workspace and
- * are added in a fixed order); with NULL or less the call computes the same product unsplit.
+ * dit_linear_workspace_bytes(...) of it, shapes whose output tiles occupy a part of the chip (few
+ * rows; bf16 to 128 tiles of 64 x 64 with a short k, to 1280 rows of 1920 columns with k = 7680) split
+ * all tiles along k, and with k >= 4096 some larger ones the tiles of the last, partial round of
+ * workgroups (fp32 partial sums pass through the workspace and are added in a fixed order); with
+ * NULL or less the call computes the same product unsplit.  The size is 0 for shapes that are never split.
  * The two differ only in summation order.
  * kernel_path: as for dit_set_kernel_path (0 = default); it enters the workspace size. */
 PS_API size_t dit_linear_workspace_bytes(int m, int n_out, int k, int dtype, int kernel_path);

@@ -306,14 +306,16 @@ __device__ __forceinline__ float sum_across_halves(float v) {
 // attn_sp_kernel accumulates sum_j 2^(c s_j) v_j and sum_j 2^(c s_j) as they are: the quotient is the softmax
 // whenever no term overflows and the sum does not vanish, which is the case for every head whose exponents c*s
 // stay within roughly +-100 of zero.  It does not look for maxima; it checks its result instead.  A query row
-// whose key sum l is outside [2^-40, 2^100], or whose accumulators are not finite, marks its (batch, head) in
-// a flag array; the launch of attn_mfma_kernel that follows recomputes exactly the marked heads with a tracked
-// reference and overwrites them.  (l >= 2^-40 also bounds what flushing tiny terms to zero can cost: with
+// whose key sum l is outside [2^-40, 2^100], or whose accumulators are not finite, is computed again with a tracked
+// reference: with its whole (batch, head), marked in a flag array, by the launch of attn_mfma_kernel that follows, or with the
+// 32 queries of its wave (see SpEnd).  (l >= 2^-40 also bounds what flushing tiny terms to zero can cost: with
 // l >= 2^-40 the largest term is at least 2^-40 / N, and the terms below the smallest normal number, 2^-126,
 // sum to less than N * 2^-126, i.e. a fraction below 2^-58 of l for any sequence this kernel accepts.)
 // The check is exact about what went wrong, where a bound on the exponents from the largest query and key
 // norms (Cauchy-Schwarz) would send every head with large norms, however harmless its scores, to the slower kernel;
-// heads that really overflow are computed twice.
+// what really overflows is computed twice.  (30 heads, us with a tracked reference at once / after the check, where every
+// query overflows: 112 keys 9.4 / 11.6, 300 keys 18.1 / 18.9, 512 keys 25.8 / 25.4, four samples of 300 and 512 keys 18.9 / 26.8
+// and 28.3 / 37.7; where none does 9.5 / 7.8, 14.7 / 10.4, 17.7 / 12.6, 16.0 / 14.1 and 20.3 / 18.8.)
 constexpr float SP_SUM_MIN = 0x1p-40f, SP_SUM_MAX = 0x1p+100f;
 
 __global__ void attn_flags_clear_kernel(unsigned* __restrict__ flags, int n) {
@@ -1025,9 +1027,9 @@ attn_sp_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const
     pv(pb, (jt1 - 1 - jt0) & (NST - 1), 1);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // drain the look-ahead loads before exit
 
-    // the result checks itself (see SP_SUM_MIN): key sums out of range or accumulators that are not finite mark the
-    // head for attn_mfma_kernel.  (A key range of a split item is held to the same limits as a whole row: a range
-    // whose keys all lie far below the row's maximum sends the head to the other kernel, which costs time only.)
+    // the result checks itself (see SP_SUM_MIN): key sums out of range or accumulators that are not finite are redone, as END
+    // says.  (A key range of a split item is held to the same limits as a whole row: a range whose keys all lie far below the
+    // row's maximum sends the head to the other kernel, which costs time only.)
     bool bad[QT];
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
