@@ -195,6 +195,44 @@ def test_patch_vectors_of_any_length(dtype, channels, patch):
     assert rel(ref, eps.cpu().numpy()) <= (1e-5 if dtype == "f32" else 2.0 ** -8)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("channels,patch", [(1, 2), (4, 2), (3, 4), (16, 2), (20, 2)])
+def test_embedding_loses_nothing_of_a_pixel(dtype, channels, patch):
+    """The residual stream, at the head of the workspace, holds the embedding itself where the layer's output projections are
+    zero.  One pixel per patch: its product with a weight, rounded to fp32 (one step of the last place, 2^-23, for a sum that is
+    rounded otherwise); a pixel without its last 8 bits would be off by up to 2^-15.  All pixels: fp32 sums of at most 3 * 80
+    terms, sqrt(240) * 2^-24 of the result's norm; without the last 8 bits of the pixels it would be 2^-17.  Text rows exactly."""
+    cfg = I.CONFIGS["reduced"].with_(layers=1, frames=1, height=4 * patch, width=77 * patch, in_channels=channels, patch=patch,
+                                     text_tokens=70, dtype=dtype)
+    td, P = B.torch_dtype(dtype), cfg.patch_dim
+    g = torch.Generator(device=DEV)
+    g.manual_seed(channels)
+    rand = lambda *shape: torch.randn(shape, generator=g, device=DEV)
+    named = [(n, rand(*shape)) for n, shape in I.weight_shapes(cfg)]
+    named = [(n, w * 0 if n.split(".")[0] in ("W_o", "b_o", "W_2", "b_2", "b_pe") else w) for n, w in named]
+    assert sum(not w.any() for _, w in named) == 5
+    weights = [(w * w.shape[1] ** -0.5).to(td) if w.dim() == 2 else w for _, w in named]
+    W_pe = dict(zip([n for n, _ in named], weights))["W_pe"].double()
+    d = B.dit_create(cfg, weights)
+    ctx = rand(2, 70, cfg.hidden).to(td)
+    patches = rand(2, cfg.video_tokens, P) * 2.0 ** torch.randint(-6, 7, (2, cfg.video_tokens, P), generator=g, device=DEV)
+    one = torch.zeros_like(patches)
+    token = torch.arange(cfg.video_tokens, device=DEV)
+    one[:, token, token % P] = patches[:, token, token % P]
+    for p, whole in ((one, False), (patches, True)):
+        Hp, Wp = cfg.height // patch, cfg.width // patch
+        x = p.view(2, 1, Hp, Wp, channels, patch, patch).permute(0, 4, 1, 2, 5, 3, 6).reshape(2, *cfg.latent_shape).contiguous()
+        B.dit_forward(d, x, ctx, [900, 20])
+        X = d.workspace(2)[:8 * cfg.tokens * cfg.hidden].view(torch.float32).view(2, cfg.tokens, cfg.hidden)
+        assert torch.equal(X[:, :70], ctx.float())
+        ref = torch.matmul(p.double().view(-1, P), W_pe.t()).view(2, cfg.video_tokens, cfg.hidden)
+        err = (X[:, 70:].double() - ref).abs()
+        if whole:
+            assert err.norm() <= 240 ** 0.5 * 2.0 ** -24 * ref.norm()
+        else:
+            assert (err <= 2.0 ** -23 * ref.abs()).all()
+
+
 @pytest.mark.parametrize("mode,batched,S,m,cyc", [(0, False, 37, 3, [4] * 9), (1, False, 37, 1, [3] * 12), (0, True, 37, 2, [7] * 5)])
 def test_run_longer_than_one_conditioning_chunk(mode, batched, S, m, cyc):
     """More predictor calls than the 16 whose modulation is computed together: step by step (one at a time) equals the whole
