@@ -121,7 +121,9 @@ constexpr float tile_time(int id, long wgs, float stages, bool gated, int cus) {
     return (float)(wgs / slots) * full + last;
 }
 // The bf16 tile with the least estimated time: `pieces` workgroups per tile along K; [first, last]: the kinds to choose from.
-// At the sizes above it misses the fastest one by about 1 % on average and 6 % at most.
+// Inside the network, 26 token counts from 64 to 33976 x the four projections of a layer, the one picked is 0.6 % slower than
+// the fastest on average, and 7 % at most but for QKV and fc1 at 1024 tokens (128 x 128 of gemm_mfma.hip 43.0 and 41.4 us, 256 x
+// 128 here 37.3 and 35.3).
 constexpr int best_tile(int first, int last, long rows, int Nn, int K, int pieces, bool gated, int cus) {
     int best = first;
     float least = 0.f;

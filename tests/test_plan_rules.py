@@ -123,26 +123,61 @@ def test_sizes_of_the_batch_tests_split_where_they_say_so(rules):
     assert plan(4516)[2:] == [0, 1]                      # the block
 
 
-FASTEST = [  # rows, columns, K, pieces (1920 columns: with the gated residual update): kinds within 6 % of the fastest measured one (0-5: gemm_few.hip, 6-9: gemm_mfma.hip)
-    (112, 5760, 1920, 1, [0]), (224, 7680, 1920, 1, [1]), (448, 5760, 1920, 1, [2]), (640, 7680, 1920, 1, [3]),
-    (1306, 5760, 1920, 1, [7]), (2048, 5760, 1920, 1, [9, 8]), (2600, 5760, 1920, 1, [6]), (4516, 7680, 1920, 1, [9, 8]),
-    (17776, 5760, 1920, 1, [6]), (17776, 1920, 1920, 1, [8]), (33976, 1920, 1920, 1, [9, 7]), (8326, 1920, 1920, 1, [7]),
-    (3600, 1920, 7680, 1, [4, 5]), (4516, 1920, 7680, 1, [5]),
-    (112, 1920, 7680, 8, [1]), (448, 1920, 7680, 4, [2]), (768, 1920, 7680, 4, [3])]
+SHAPES = {"qkv": (5760, 1920, 0), "o": (1920, 1920, 1), "fc1": (7680, 1920, 0), "fc2": (1920, 7680, 1)}   # gated: o, fc2
+# us of a projection on every kind of tile (0-5: gemm_few.hip, 6-9: gemm_mfma.hip), whole inside the network, and in K pieces
+# (the kinds of gemm_few.hip, stand-alone with weights from memory)
+MEASURED = [
+    (112, "qkv", 1, [13.5, 18.1, 25.8, 28.9, 32.6, 36.7, 54.8, 32.6, 39.4, 36.6]),
+    (200, "fc1", 1, [18.4, 15.7, 22.5, 25.8, 31.9, 33.6, 55.5, 32.0, 38.4, 33.2]),
+    (448, "qkv", 1, [29.3, 29.9, 23.9, 29.3, 36.0, 38.4, 56.1, 33.0, 40.9, 35.9]),
+    (640, "o", 1, [19.6, 17.1, 24.4, 26.5, 32.7, 34.9, 56.4, 33.8, 41.2, 36.6]),
+    (800, "qkv", 1, [41.5, 41.9, 42.6, 30.1, 35.5, 38.8, 55.0, 34.4, 41.6, 36.5]),
+    (800, "fc1", 1, [50.8, 50.3, 39.9, 48.1, 34.3, 35.5, 52.3, 34.2, 40.6, 42.4]),
+    (1306, "o", 1, [27.5, 27.5, 22.1, 29.9, 33.2, 37.3, 56.0, 33.6, 42.1, 38.8]),
+    (1306, "fc2", 1, [85.6, 81.6, 59.7, 86.0, 91.9, 104, 173, 106, 161, 119]),
+    (1700, "fc1", 1, [88.8, 95.1, 78.6, 76.9, 65.8, 71.1, 55.4, 65.2, 77.5, 68.6]),
+    (2048, "qkv", 1, [95.4, 91.8, 71.8, 61.1, 73.7, 76.0, 56.7, 62.7, 46.6, 50.0]),
+    (2600, "o", 1, [39.8, 41.6, 39.8, 29.6, 34.3, 36.9, 56.2, 35.9, 42.7, 38.9]),
+    (2600, "fc1", 1, [132, 132, 106, 99.3, 95.3, 99.6, 102, 91.6, 80.4, 82.8]),
+    (3000, "qkv", 1, [115, 123, 103, 90.2, 106, 80.8, 98.5, 87.4, 82.0, 77.6]),
+    (3600, "fc2", 1, [180, 178, 127, 158, 105, 106, 169, 112, 150, 139]),
+    (4516, "o", 1, [66.0, 68.3, 60.7, 53.6, 65.8, 41.9, 57.6, 61.7, 45.5, 48.7]),
+    (4516, "fc1", 1, [214, 217, 167, 148, 157, 137, 142, 142, 119, 124]),
+    (4516, "fc2", 1, [224, 212, 184, 160, 199, 118, 177, 198, 152, 144]),
+    (6000, "qkv", 1, [226, 230, 183, 171, 176, 156, 150, 147, 127, 129]),
+    (8326, "o", 1, [118, 121, 94.1, 86.2, 77.5, 80.2, 110, 75.3, 93.3, 87.6]),
+    (8326, "fc2", 1, [428, 378, 280, 258, 225, 227, 351, 236, 290, 254]),
+    (9500, "fc1", 1, [442, 442, 331, 300, 287, 273, 242, 269, 240, 244]),
+    (12000, "qkv", 1, [440, 448, 346, 324, 303, 297, 248, 262, 244, 250]),
+    (12000, "fc2", 1, [630, 535, 401, 355, 340, 356, 372, 358, 320, 331]),
+    (17776, "qkv", 1, [653, 643, 512, 472, 452, 422, 348, 387, 375, 362]),
+    (17776, "o", 1, [258, 243, 200, 183, 190, 175, 185, 172, 169, 173]),
+    (17776, "fc1", 1, [826, 810, 612, 551, 530, 512, 436, 487, 455, 451]),
+    (24000, "fc2", 1, [1202, 1120, 847, 769, 783, 660, 624, 738, 663, 701]),
+    (33976, "qkv", 1, [1302, 1337, 1043, 952, 898, 863, 660, 770, 728, 727]),
+    (112, "fc2", 8, [16.9, 15.2, 18.4, 18.9, 20.4, 22.1]), (448, "fc2", 8, [46.4, 51.9, 37.6, 39.4, 28.8, 30.2]),
+    (450, "fc2", 4, [39.0, 35.5, 27.6, 31.2, 36.1, 36.9]), (768, "fc2", 4, [55.7, 59.0, 51.8, 35.7, 39.2, 40.6]),
+    (1040, "fc2", 4, [72.6, 76.8, 64.2, 59.1, 64.6, 43.2]), (1280, "fc2", 3, [84.2, 79.9, 63.4, 73.7, 49.6, 50.6])]
 
 
-@pytest.mark.parametrize("rows,n,k,pieces,kinds", FASTEST)
-def test_tiles_are_the_fastest_measured(rules, rows, n, k, pieces, kinds):
+def test_tiles_are_about_the_fastest_measured(rules):
     few = C.c_int()
     total = rules.kinds(C.byref(few))
-    assert (few.value, total) == (6, 10)
-    assert rules.best(0, (few.value if pieces > 1 else total) - 1, C.c_long(rows), n, k, pieces, n == 1920 and pieces == 1) in kinds
+    lost = []
+    for rows, name, pieces, us in MEASURED:
+        n, k, gated = SHAPES[name]
+        assert len(us) == (total if pieces == 1 else few.value)
+        kind = rules.best(0, len(us) - 1, C.c_long(rows), n, k, pieces, gated if pieces == 1 else 0)
+        lost.append(us[kind] / min(us))
+        assert lost[-1] <= 1.07, (rows, name, kind)
+    assert sum(lost) / len(lost) <= 1.01
 
 
-def test_sizes_of_the_tile_tests_take_the_tiles_they_name(rules):
+def test_sizes_of_the_tile_tests_reach_every_tile(rules):
     from test_gpu_small_shapes import TILE_SIZES
-    for kind, rows, n, k in TILE_SIZES:
-        assert rules.best(0, 9, C.c_long(rows), n, k, 1, 0) == kind
+    few = C.c_int()
+    rules.kinds(C.byref(few))
+    assert {rules.best(0, 9, C.c_long(rows), n, k, 1, 0) for rows, n, k in TILE_SIZES} >= set(range(few.value))
 
 
 def test_attention_workgroups_of_128_queries_where_they_are_faster(rules):
