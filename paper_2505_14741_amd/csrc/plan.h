@@ -200,7 +200,7 @@ constexpr bool few_one_round(long rows, int Nn, int pieces) {
 // From 1281 tokens on (3 pieces, 192 x 192: 1400 53.2 / 68) a batch would lose more than that: its pieces stay on tiles of
 // gemm_few.hip, four samples of 1500 168 us, on wider tiles whole 146.  (Up to there it loses little: a layer of one sample
 // of 1104 / 1264 tokens, whole and in pieces, 212 -> 188 / 225 -> 201 us, of four 475 -> 478 / 557 -> 569, of six 722 -> 740
-// / 761 -> 779.)
+// / 761 -> 779; two layers of twelve of 1264 3150 -> 3340, of sixteen 4210 -> 4330.)
 constexpr int few_long_pieces(int tokens, int Nn, int nk) {
     int best = 1;
     float least = 0.f;
