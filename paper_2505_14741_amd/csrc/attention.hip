@@ -419,11 +419,6 @@ struct MergeTail {
 // every such read took twice as long: measured as LDS bank conflict cycles).
 __device__ __forceinline__ int v_swizzle(int r) { return (r & 3) | ((r & 2) << 1); }
 
-// lds_dma16 from a scalar 64-bit base + per-lane 32-bit byte offset
-__device__ __forceinline__ void lds_dma16_base(unsigned voff, const void* sbase, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_addr)
-                 : "memory", "m0");
-}
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 // acc + sum of eight bf16 values (v_dot2c_f32_bf16 against packed ones)
 __device__ __forceinline__ float rowsum_bf16x8(bf16x8_t p, float acc) {

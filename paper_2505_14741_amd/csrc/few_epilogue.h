@@ -26,12 +26,12 @@ __device__ __forceinline__ EpiRow epilogue_row(const Epilogue& ep, int row) {
     return r;
 }
 
-// What the epilogue of 4 adjacent columns of a row reads besides the sum; aux: the residual, or (cos, sin) of both pairs.
-struct EpiOperands { f32x4_t bias, gate, aux; };
+// What the epilogue of 4 adjacent columns of a row reads besides the sum and the bias; aux: the residual, or (cos, sin) of both
+// pairs.
+struct EpiOperands { f32x4_t gate, aux; };
 template <int KIND>
 __device__ __forceinline__ EpiOperands epilogue_operands(const Epilogue& ep, int Nn, const EpiRow& r, int row, int col) {
     EpiOperands o;
-    o.bias = *reinterpret_cast<const f32x4_t*>(ep.bias + col);
     o.gate = f32x4_t{0.f, 0.f, 0.f, 0.f};
     o.aux = f32x4_t{0.f, 0.f, 0.f, 0.f};
     if constexpr (KIND == EPI_GATE_RESIDUAL) {
@@ -58,8 +58,8 @@ __device__ __forceinline__ EpiOperands epilogue_operands(const Epilogue& ep, int
 // x is the finished sum.
 template <int KIND, typename T>
 __device__ __forceinline__ void epilogue_quad(const Epilogue& ep, T* __restrict__ C, int Nn, const EpiRow& r, int row, int col,
-                                              f32x4_t x, const EpiOperands& o) {
-    x += o.bias;
+                                              f32x4_t x, f32x4_t bias, const EpiOperands& o) {
+    x += bias;
     if constexpr (KIND == EPI_BIAS_GELU) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) x[c] = gelu_of(x[c], T{});
@@ -102,7 +102,7 @@ gemm_few_reduce_kernel(T* __restrict__ C, int Nn, long rows, int nsplit, Epilogu
 #pragma unroll 4
     for (int p = 0; p < nsplit; ++p) s += *reinterpret_cast<const f32x4_t*>(ep.split_ws + (p * rows + row) * Nn + col);
     const EpiRow r = epilogue_row<KIND>(ep, (int)row);
-    epilogue_quad<KIND, T>(ep, C, Nn, r, (int)row, col, s, epilogue_operands<KIND>(ep, Nn, r, (int)row, col));
+    epilogue_quad<KIND, T>(ep, C, Nn, r, (int)row, col, s, *reinterpret_cast<const f32x4_t*>(ep.bias + col), epilogue_operands<KIND>(ep, Nn, r, (int)row, col));
 }
 
 }  // namespace ps

@@ -14,7 +14,9 @@
 // us, weights cold, before (64 x 64 tiles of 4 waves without this pipelining; 128 x 128 of 4 waves from 640 tiles of 64 x 64
 // on) and after: 7680 x 1920 at 112 / 224 / 448 / 640 rows 14.6 / 19.5 / 30.5 / 30.9 -> 12.8 / 16.3 / 22.4 / 27.7; 1920 x
 // 7680 in K pieces (without the reduction) 13.5 / 18.6 / 38.6 / 60.7 -> 11.7 / 16.8 / 22.9 / 28.3; 1920 x 1920 at 4516 rows
-// 48.3 -> 37.5.
+// 48.3 -> 37.5.  Then stages without branches and epilogues that request what they read for all their blocks at once: 448 rows x
+// 7680 22.4 -> 21.1, 640 rows 27.6 -> 24.8, 1306 rows x 1920 19.1 -> 17.1, 4516 rows 37.5 -> 33.9, K = 7680 at 1306 rows 58.2 ->
+// 55.4.  (Not faster: rings of 5 to 8 stages; fragments read a whole stage ahead, 2 to 9 % slower.)
 // fp32 (v_mfma_f32_16x16x4_f32: full fp32 products and sums) is bound by the matrix instructions and takes 64 x 64 tiles at
 // every size: 5760 x 1920 at 112 tokens 40 us, at 400 101 us (88 TFLOP/s).
 #include "few_epilogue.h"
@@ -25,16 +27,11 @@ namespace ps {
 
 static constexpr int ROWB = FEW_ROW_BYTES;               // bytes of an operand row per stage: 64 bf16 or 32 fp32
 
-// the loads of at most `stages` stages (G instructions each) may stay in flight
-template <int G>
-__device__ __forceinline__ void wait_stages(int stages) {
-    static_assert(3 * G <= 63, "vmcnt range");
-    switch (stages) {
-        case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
-        case 1: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(G) : "memory"); break;
-        case 2: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * G) : "memory"); break;
-        default: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * G) : "memory"); break;
-    }
+// at most N direct loads may stay in flight
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+    static_assert(N >= 0 && N <= 63, "vmcnt range");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 // nsplit: K pieces per output, a workgroup each (INREG: one workgroup per tile adds them up in registers, in the order and with
@@ -70,21 +67,26 @@ gemm_few_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict_
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WC, wn = wave % WC, l16 = lane & 15, kgrp = lane >> 4;
 
-    // load group q = 8 rows of the stage [A rows | W rows]; slot p of row r holds 16-byte chunk p ^ ((r >> 1) & 7),
+    // Waves take neighbouring load groups, so that one's loads are all of A, which is in the caches, or all of W, which may come
+    // from memory (alternate groups, 7680 x 1920 at 448 rows, weights from memory: 22.1 -> 21.1 us).
+    // A load group = 8 rows of the stage [A rows | W rows]; slot p of row r holds 16-byte chunk p ^ ((r >> 1) & 7),
     // so the 16 rows of a fragment read fall into 16 different bank groups; rows past the edge re-read the last one
-    const char* gp[GPW];
+    // (a group's rows are all of A or all of W: scalar base of the tile, 32-bit offsets inside it)
+    const char* base[GPW];
+    unsigned off[GPW];
     const long row_bytes = (long)K * sizeof(T);
 #pragma unroll
     for (int i = 0; i < GPW; ++i) {
-        const int row = (wave + NW * i) * 8 + (lane >> 3);
+        const int group = wave * GPW + i, row = group * 8 + (lane >> 3);
         const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-        const char* base = row < AROWS ? reinterpret_cast<const char*>(A) + (long)min(m0 + row, M - 1) * row_bytes
-                                    : reinterpret_cast<const char*>(W) + (long)min(n0 + row - AROWS, Nn - 1) * row_bytes;
-        gp[i] = base + chunk * 16 + (long)k0 * ROWB;
+        const bool of_a = group * 8 < AROWS;
+        base[i] = (of_a ? reinterpret_cast<const char*>(A) + (long)m0 * row_bytes : reinterpret_cast<const char*>(W) + (long)n0 * row_bytes) +
+                  (long)k0 * ROWB;
+        off[i] = (unsigned)(of_a ? min(row, M - 1 - m0) : min(row - AROWS, Nn - 1 - n0)) * (unsigned)row_bytes + chunk * 16;
     }
     const unsigned lds_base = (unsigned)(size_t)PS_LDS_PTR(lds);
     auto issue_one = [&](int kt, int slot, int i) {
-        lds_dma16(gp[i] + (long)kt * ROWB, __builtin_amdgcn_readfirstlane(lds_base + slot * STAGE + (wave + NW * i) * 1024));
+        lds_dma16_base(off[i], base[i] + (long)kt * ROWB, __builtin_amdgcn_readfirstlane(lds_base + slot * STAGE + (wave * GPW + i) * 1024));
     };
     auto issue = [&](int kt) {                           // (prologue: stage kt goes to slot kt)
 #pragma unroll
@@ -116,19 +118,23 @@ gemm_few_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict_
             for (int x = 0; x < TM; ++x) total[y][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
 
-    // Small tiles request the epilogue's operands now, with the first stages, and not when the sums are done
-    // (rows and columns past the edge: clamped, not stored).  Larger ones have no registers for them.
+    // The bias, and on small tiles all that the epilogue reads besides the sums, is requested now, with the first stages, and
+    // not when the sums are done (rows and columns past the edge: clamped, not stored).
     constexpr bool EARLY = TM * TN <= 4;
+    auto col_of = [&](int y) { return n0 + (wn * TN + y) * 16 + kgrp * 4; };
+    auto row_of = [&](int x) { return m0 + (wm * TM + x) * 16 + l16; };
+    f32x4_t bias[TN];
     EpiOperands eo[EARLY ? TM : 1][EARLY ? TN : 1];
-    if constexpr (EARLY) {
-        if (pieces == 1) {
+    if (pieces == 1) {
+#pragma unroll
+        for (int y = 0; y < TN; ++y) bias[y] = *reinterpret_cast<const f32x4_t*>(ep.bias + min(col_of(y), Nn - 4));
+        if constexpr (EARLY) {
 #pragma unroll
             for (int x = 0; x < TM; ++x) {
-                const int row = min(m0 + (wm * TM + x) * 16 + l16, M - 1);
+                const int row = min(row_of(x), M - 1);
                 const EpiRow r = epilogue_row<KIND>(ep, row);
 #pragma unroll
-                for (int y = 0; y < TN; ++y)
-                    eo[x][y] = epilogue_operands<KIND>(ep, Nn, r, row, min(n0 + (wn * TN + y) * 16 + kgrp * 4, Nn - 4));
+                for (int y = 0; y < TN; ++y) eo[x][y] = epilogue_operands<KIND>(ep, Nn, r, row, min(col_of(y), Nn - 4));
             }
         }
     }
@@ -136,7 +142,8 @@ gemm_few_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict_
 #pragma unroll
     for (int p = 0; p < NST - 1; ++p)
         if (p < nkt) issue(p);
-    wait_stages<GPW>(min(NST - 1, nkt) - 1);             // own share of stage 0
+    if (nkt >= NST - 1) wait_loads<(NST - 2) * GPW>();   // own share of stage 0
+    else wait_loads<0>();
     __syncthreads();
     if (NST - 1 < nkt) issue(NST - 1);
     const int aoff = (wm * TM * 16 + l16) * ROWB, woff = (AROWS + wn * TN * 16 + l16) * ROWB, sw = (l16 >> 1) & 7;
@@ -155,15 +162,18 @@ gemm_few_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict_
     }
     constexpr int LPR = (GPW + TM - 1) / TM, WPR = (TN + TM - 1) / TM;     // direct loads and W reads per fragment round
     int cur = 0;                                         // ring slot of stage kt
-    for (int kt = 0; kt < nkt; ++kt) {
+    // One stage.  LEFT: stages after it, NST or more: any number, which is the steady state and has no branch inside.  (Waits and
+    // loads behind run-time conditions, seven branches per stage, cost 250 of its cycles: barriers and matrix instructions
+    // alone, 128 x 128 tile 0.34 -> 0.24 us per stage, 64 x 64 0.148 -> 0.055, i.e. the matrix rate.)
+    auto stage = [&](int kt, auto left_c) {
+        constexpr int LEFT = decltype(left_c)::value;
         const int nxt = cur + 1 == NST ? 0 : cur + 1;
-        const bool more = kt + 1 < nkt, fill = kt + NST < nkt;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             const unsigned char* src = lds + cur * STAGE;            // where the next step's fragments come from
             if (ks == 1) {
-                if (more) {
-                    wait_stages<GPW>(min(NST - 2, nkt - 2 - kt));    // own share of stage kt + 1 has landed
+                if constexpr (LEFT > 0) {
+                    wait_loads<(LEFT - 1 < NST - 2 ? LEFT - 1 : NST - 2) * GPW>();   // own share of stage kt + 1 has landed
                     __syncthreads();                     // ... everyone's; and nobody reads stage kt any more
                 }
                 src = lds + nxt * STAGE;                 // (after the last stage: stale, unused)
@@ -186,9 +196,11 @@ gemm_few_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict_
                 for (int y = x * WPR; y < (x + 1) * WPR && y < TN; ++y)
                     fw[ks ^ 1][y] = *reinterpret_cast<const frag_t*>(src + woff + y * 16 * ROWB + slot);
                 fa[x] = *reinterpret_cast<const frag_t*>(src + aoff + x * 16 * ROWB + slot);
-                if (ks == 1 && fill) {                   // into the slot stage kt occupied
+                if constexpr (LEFT >= NST) {             // into the slot stage kt occupied
+                    if (ks == 1) {
 #pragma unroll
-                    for (int i = x * LPR; i < (x + 1) * LPR && i < GPW; ++i) issue_one(kt + NST, cur, i);
+                        for (int i = x * LPR; i < (x + 1) * LPR && i < GPW; ++i) issue_one(kt + NST, cur, i);
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -208,24 +220,52 @@ gemm_few_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict_
                 piece_end = nk * piece_no / g.nsplit;
             }
         }
+    };
+    int kt = 0;
+    for (; kt + NST < nkt; ++kt) stage(kt, std::integral_constant<int, NST>{});
+    if (NST > 3 && kt + 3 < nkt) stage(kt++, std::integral_constant<int, 3>{});
+    if (kt + 2 < nkt) stage(kt++, std::integral_constant<int, 2>{});
+    if (kt + 1 < nkt) stage(kt++, std::integral_constant<int, 1>{});
+    stage(kt, std::integral_constant<int, 0>{});
+
+    auto sum_of = [&](int y, int x) {
+        if constexpr (INREG) return total[y][x]; else return piece_sum(y, x);
+    };
+    if (pieces > 1) {                                    // [piece][row][column]
+#pragma unroll
+        for (int x = 0; x < TM; ++x)
+#pragma unroll
+            for (int y = 0; y < TN; ++y)
+                if (row_of(x) < M && col_of(y) < Nn)     // Nn % 4 == 0: a quad is inside or outside
+                    *reinterpret_cast<f32x4_t*>(ep.split_ws + ((long)piece * M + row_of(x)) * Nn + col_of(y)) = sum_of(y, x);
+        return;
     }
+    // Larger tiles: what the epilogue reads is requested for several rows at once (one 16 x 16 block after the other, each
+    // waiting for its own: 2 us on 8 blocks per wave, 4 on 16).
+    constexpr int CHUNK = EARLY ? TM : TM * TN <= 12 ? TM : 2;
 #pragma unroll
-    for (int x = 0; x < TM; ++x) {
-        const int row = m0 + (wm * TM + x) * 16 + l16;
-        if (row >= M) continue;
-        const EpiRow r = epilogue_row<KIND>(ep, row);
+    for (int x0 = 0; x0 < TM; x0 += CHUNK) {
+        EpiRow rows[CHUNK];
+        EpiOperands late[EARLY ? 1 : CHUNK][EARLY ? 1 : TN];
 #pragma unroll
-        for (int y = 0; y < TN; ++y) {
-            const int col = n0 + (wn * TN + y) * 16 + kgrp * 4;      // Nn % 4 == 0: inside or outside together
-            if (col >= Nn) continue;
-            f32x4_t sum;
-            if constexpr (INREG) sum = total[y][x]; else sum = piece_sum(y, x);
-            if (pieces > 1) {                            // [piece][row][column]
-                *reinterpret_cast<f32x4_t*>(ep.split_ws + ((long)piece * M + row) * Nn + col) = sum;
-                continue;
+        for (int c = 0; c < CHUNK; ++c) {
+            if (x0 + c >= TM) break;
+            const int row = min(row_of(x0 + c), M - 1);
+            rows[c] = epilogue_row<KIND>(ep, row);
+            if constexpr (!EARLY) {
+#pragma unroll
+                for (int y = 0; y < TN; ++y) late[c][y] = epilogue_operands<KIND>(ep, Nn, rows[c], row, min(col_of(y), Nn - 4));
             }
-            if constexpr (EARLY) epilogue_quad<KIND, T>(ep, C, Nn, r, row, col, sum, eo[x][y]);
-            else epilogue_quad<KIND, T>(ep, C, Nn, r, row, col, sum, epilogue_operands<KIND>(ep, Nn, r, row, col));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < CHUNK; ++c) {
+            if (x0 + c >= TM) break;
+#pragma unroll
+            for (int y = 0; y < TN; ++y)
+                if (row_of(x0 + c) < M && col_of(y) < Nn)
+                    epilogue_quad<KIND, T>(ep, C, Nn, rows[c], row_of(x0 + c), col_of(y), sum_of(y, x0 + c), bias[y],
+                                           EARLY ? eo[EARLY ? x0 + c : 0][EARLY ? y : 0] : late[EARLY ? 0 : c][EARLY ? 0 : y]);
         }
     }
 }

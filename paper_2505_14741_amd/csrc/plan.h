@@ -184,6 +184,9 @@ constexpr GemmPlan gemm_plan(int tokens, int Nn, int K, bool allow_split, int fo
     return p;
 }
 
+// Longest operand row the tile kernels take: a load's offset inside a tile's rows (256 at most) is 32 bits.
+constexpr long TILE_MAX_ROW_BYTES = 1L << 23;
+
 // ---- projections of few tokens and of fp32 operands (gemm_few.hip)
 constexpr int FEW_ROW_BYTES = 128;                       // bytes of an operand row per stage: 64 bf16 or 32 fp32
 
@@ -229,7 +232,7 @@ struct FewPlan { bool use; int tiles_m, tiles_n, nsplit; };
 constexpr FewPlan few_plan(bool bf16, int tokens, int Nn, int K, int path) {
     FewPlan p{false, 0, 0, 1};
     const long row_bytes = (long)K * (bf16 ? 2 : 4);
-    if ((path & 0xff) == 1 || row_bytes % FEW_ROW_BYTES != 0 || Nn % 4 != 0 || tokens < 1) return p;
+    if ((path & 0xff) == 1 || row_bytes % FEW_ROW_BYTES != 0 || row_bytes > TILE_MAX_ROW_BYTES || Nn % 4 != 0 || tokens < 1) return p;
     p.tiles_m = (tokens + 63) / 64;
     p.tiles_n = (Nn + 63) / 64;
     const long tiles = (long)p.tiles_m * p.tiles_n, nk = row_bytes / FEW_ROW_BYTES;

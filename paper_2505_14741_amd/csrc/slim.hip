@@ -99,7 +99,7 @@ __device__ __forceinline__ void slim_qkv(const SlimArgs& g, const SlimLayer& w, 
     const EpiRow r = epilogue_row<EPI_QKV_ROPE>(ep, row);
     pj.run(in, [&](int col, f32x4_t x) {
         const EpiOperands o = epilogue_operands<EPI_QKV_ROPE>(ep, 3 * D, r, row, col);
-        if (n < g.tokens) epilogue_quad<EPI_QKV_ROPE, float>(ep, g.qkv_out, 3 * D, r, row, col, x, o);
+        if (n < g.tokens) epilogue_quad<EPI_QKV_ROPE, float>(ep, g.qkv_out, 3 * D, r, row, col, x, quad(w.b_qkv + col), o);
     });
 }
 
@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
         const int P = g.pg.C * g.pg.patch * g.pg.patch, row = b * N + min(n, N - 1);
         const EpiRow r = epilogue_row<EPI_UNPATCHIFY>(ep, row);
         pn.run(ht + l16 * LD, [&](int col, f32x4_t x) {
-            if (n < N) epilogue_quad<EPI_UNPATCHIFY, float>(ep, nullptr, P, r, row, col, x, epilogue_operands<EPI_UNPATCHIFY>(ep, P, r, row, col));
+            if (n < N) epilogue_quad<EPI_UNPATCHIFY, float>(ep, nullptr, P, r, row, col, x, quad(g.b_out + col), epilogue_operands<EPI_UNPATCHIFY>(ep, P, r, row, col));
         });
     } else {
         for (int e = threadIdx.x; e < ROWS * (D / 4); e += 256) {

@@ -19,6 +19,12 @@ __device__ __forceinline__ void lds_dma16(const void* gptr, unsigned lds_addr) {
                  : "memory", "m0");
 }
 
+// lds_dma16 from a scalar 64-bit base + per-lane 32-bit byte offset
+__device__ __forceinline__ void lds_dma16_base(unsigned voff, const void* sbase, unsigned lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_addr)
+                 : "memory", "m0");
+}
+
 // Consecutive workgroup ids go to different XCDs (8 of them, each with its own L2).
 // Give each XCD a contiguous range of tiles so co-resident workgroups share operand panels.
 __device__ __forceinline__ int xcd_remap(unsigned id, unsigned total) {

@@ -95,6 +95,24 @@ def test_rings_of_the_wide_tiles(M, Nn, K):
         assert torch.equal(out, B.dit_linear(a, w, bias, 0, kernel_path=variant << 8 | 4)), variant
 
 
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 320, 384])
+@pytest.mark.parametrize("M,Nn", [(40, 196), (300, 3900), (600, 3900)])
+def test_fewer_stages_than_the_ring_and_a_few_more(M, Nn, K):
+    """The stages after the steady state are written out: K of one to six stages on 64 x 64, 128 x 64 and 128 x 128 tiles of the
+    few-token kernel and on every tile of the other (same bits), fp32 on its own.  One rounding of the result to bf16; fp32 sums
+    as above."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + K)
+    for td, bound in ((torch.float32, 5e-6), (torch.bfloat16, 2.0 ** -9)):
+        a = torch.randn(M, K, generator=g, device=DEV).to(td)
+        w = (torch.randn(Nn, K, generator=g, device=DEV) / math.sqrt(K)).to(td)
+        bias = torch.randn(Nn, generator=g, device=DEV)
+        out = B.dit_linear(a, w, bias, 0)
+        assert rel((a.double() @ w.double().t() + bias.double()).cpu().numpy(), out.double().cpu().numpy()) <= bound
+        for variant in (1, 2, 3, 4) if td == torch.bfloat16 and M > 40 else ():      # (few rows: in K pieces)
+            assert torch.equal(out, B.dit_linear(a, w, bias, 0, kernel_path=variant << 8)), variant
+
+
 @pytest.mark.parametrize("N", [1, 15, 16, 17, 63, 64, 65, 200])
 @pytest.mark.parametrize("d", [16, 32, 64])
 def test_attention_fp32_math_ragged(N, d):
