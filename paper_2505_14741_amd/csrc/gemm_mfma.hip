@@ -29,6 +29,7 @@
 // one 32-row strip ahead.
 #include "plan.h"
 #include "tile_ops.h"
+#include <type_traits>
 
 namespace ps {
 
@@ -272,39 +273,34 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
 
     // direct loads: lane j of load group g lands at group base + 16j = row RPI*g + j/CPR, slot j%CPR; the slot
     // holds chunk (j%CPR) ^ swizzle(row) of the row (applied on the global side):
-    //   128-byte rows: slot p of row r holds chunk p ^ ((r>>1)&7);  64-byte rows: chunk p ^ ((r>>2)&3)
+    //   slot p of row r holds chunk p ^ ((r>>1)&7)
+    // Scalar base of the tile's rows, 32-bit offsets inside it.
     const int lr = lane / CPR;
-    const bf16_t* gp[GPW];
+    const long row_bytes = (long)K * 2;
+    const char* const base_a = reinterpret_cast<const char*>(A) + m0 * row_bytes + (long)k0 * ROWB;
+    const char* const base_w = reinterpret_cast<const char*>(W) + n0 * row_bytes + (long)k0 * ROWB;
+    unsigned off[GPW];
 #pragma unroll
     for (int i = 0; i < GPW; ++i) {
-        const int g = wave + NW * i;
-        const int row = g * RPI + lr;                    // row within [A rows | W rows]
-        const int lc = BK == 64 ? ((lane & 7) ^ ((row >> 1) & 7)) : ((lane & 3) ^ ((row >> 2) & 3));
-        if (row < BM) {
-            int r = m0 + row;
-            r = r < M ? r : M - 1;
-            gp[i] = A + (long)r * K + lc * 8;
-        } else {
-            int r = n0 + row - BM;
-            r = r < Nn ? r : Nn - 1;
-            gp[i] = W + (long)r * K + lc * 8;
-        }
+        const int row = (wave + NW * (i < GA ? i : i - GA)) * RPI + lr;   // within the operand's rows of the tile
+        const int lc = (lane & 7) ^ ((row >> 1) & 7);
+        off[i] = (unsigned)min(row, i < GA ? M - 1 - m0 : Nn - 1 - n0) * (unsigned)row_bytes + lc * 16;
     }
     const unsigned lds_base = (unsigned)(size_t)PS_LDS_PTR(lds);
+    const int nkt = k1 - k0;
     // load group i of the wave (A groups first), stage kt counted from k0, into ring slot `slot`
     auto issue_one = [&](int kt, int slot, int i) {
-        const int kc = k0 + kt < k1 ? k0 + kt : k1 - 1;  // (the prologue of a short piece may ask past the end)
         const unsigned at = i < GA ? lds_base + slot * STEP_A + (wave + NW * i) * 1024
                                    : lds_base + BASE_W + slot * STEP_W + (wave + NW * (i - GA)) * 1024;
-        lds_dma16(gp[i] + (long)kc * BK, __builtin_amdgcn_readfirstlane(at));
+        lds_dma16_base(off[i], (i < GA ? base_a : base_w) + (long)kt * ROWB, __builtin_amdgcn_readfirstlane(at));
     };
-    auto issue_a = [&](int kt, int slot) {
+    auto issue_a = [&](int kt, int slot) {               // (the prologue of a short piece may ask past the end)
 #pragma unroll
-        for (int i = 0; i < GA; ++i) issue_one(kt, slot, i);
+        for (int i = 0; i < GA; ++i) issue_one(min(kt, nkt - 1), slot, i);
     };
     auto issue_w = [&](int kt, int slot) {
 #pragma unroll
-        for (int i = GA; i < GPW; ++i) issue_one(kt, slot, i);
+        for (int i = GA; i < GPW; ++i) issue_one(min(kt, nkt - 1), slot, i);
     };
     // (Measured and dropped: a cache prefetch two or four stages ahead of the direct loads -- one 4-byte-per-lane
     // direct load per thread and stage into an LDS area nobody reads, lane r touching the line of row r.  It doubles
@@ -360,7 +356,6 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
     // needs more than a stage to return and then every one of those hand-overs stalls.)
     constexpr bool PRE = KIND == EPI_GATE_RESIDUAL && TN == 2 && TM == 2 && NW == 4;
     f32x4_t pre[PRE ? TM : 1][8];
-    const int nkt = k1 - k0;
     const bool have_pre = PRE && piece < 0 && nkt >= 3;
     {
         const int slot = slot_of(0);
@@ -370,13 +365,16 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
         for (int y = 0; y < FB; ++y) fb[0][y] = *reinterpret_cast<const bf16x8_t*>(lds + boff[y] + slot);
     }
     int slot_d = 0;                                      // deep ring's slot of stage kt
-    for (int kt = 0; kt < nkt; ++kt) {
+    // One stage.  LEFT: stages after it, DEEP or more: any number, which is the steady state and has no branch inside (with the
+    // waits and loads behind run-time conditions and a 64-bit vector address per load, us at 17776 rows: 5760 x 1920 329 ->
+    // 316, 7680 x 1920 449 -> 436, 1920 x 7680 467 -> 441, 1920 x 1920 126 -> 117; at 4516 rows 92.5 -> 90.4, 127.7 -> 123.6,
+    // 117.9 -> 110.7, 37.9 -> 34.4).  No stage follows the last one: no hand-over there, and no loads for stages past the end
+    // (the fragment reads of the last step then fetch stale, unused data from the other slot).
+    auto stage = [&](int kt, auto left_c) {
+        constexpr int LEFT = decltype(left_c)::value;
         const int s2 = kt & 1, sd = JOINT ? s2 : slot_d, nd = JOINT ? s2 ^ 1 : sd + 1 == DEEP ? 0 : sd + 1;
         const int sa = NSA > 2 ? sd : s2, na = NSA > 2 ? nd : s2 ^ 1, sw_ = NSW > 2 ? sd : s2, nw = NSW > 2 ? nd : s2 ^ 1;
         slot_d = nd;
-        // no stage follows the last one: no hand-over there, and no loads for stages past the end (the fragment
-        // reads of the last step then fetch stale, unused data from the other slot)
-        const bool more = kt + 1 < nkt, fill_a = kt + NSA < nkt, fill_w = kt + NSW < nkt;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             int from_a = sa * STEP_A, from_w = sw_ * STEP_W;   // where the next step's fragments come from
@@ -386,25 +384,23 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
             // of 4 waves the block form measured 2-3 % faster, the other workgroup covers it.
             constexpr bool SPREAD = NW >= 8;
             if (ks == 1) {
-                if (more) {
+                if constexpr (LEFT > 0) {
                     // own share of stage kt+1 has landed; A of later stages, and strip 0's loads, may stay out
-                    if (PRE && have_pre && kt == nkt - 2) wait_vmcnt<8>();
-                    else if (AHEAD > 0 && kt + 2 < nkt) wait_vmcnt<AHEAD>();
-                    else wait_vmcnt<0>();
+                    if (PRE && LEFT == 1 && have_pre) wait_vmcnt<8>();
+                    else wait_vmcnt<(LEFT >= 2 ? AHEAD : 0)>();
                     __syncthreads();                     // ... everyone's; and nobody reads stage kt any more
                 }
                 if constexpr (!SPREAD) {                 // into the slots stage kt occupied
                     static_assert(SPREAD || JOINT, "rings of one depth");
-                    if (fill_a) { issue_w(kt + NSW, sw_); issue_a(kt + NSA, sa); }
-                }
-                if constexpr (PRE) {
-                    if (have_pre && kt >= nkt - 3 && kt <= nkt - 2) {
-                        const bool first = kt == nkt - 3;
+                    if constexpr (LEFT >= NSA) {
 #pragma unroll
-                        for (int k = 0; k < 8; ++k) {
-                            const f32x4_t v = resid_fetch(ep, M, Nn, m0 + wm * WM, n0 + wn * WN, lane, first ? 0 : 1, k);
-                            if (first) pre[0][k] = v; else pre[1][k] = v;
-                        }
+                        for (int i = 0; i < GPW; ++i) { const int g = i < GB ? GA + i : i - GB; issue_one(kt + NSA, sa, g); }
+                    }
+                }
+                if constexpr (PRE && (LEFT == 1 || LEFT == 2)) {
+                    if (have_pre) {
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) pre[LEFT == 2 ? 0 : 1][k] = resid_fetch(ep, M, Nn, m0 + wm * WM, n0 + wn * WN, lane, LEFT == 2 ? 0 : 1, k);
                     }
                 }
                 from_a = na * STEP_A; from_w = nw * STEP_W;
@@ -446,14 +442,19 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
                     for (int d = 0; d < DPR; ++d) {
                         const int i = x * DPR + d;
                         const int g = NSW > NSA ? i : i < GB ? GA + i : i - GB;
-                        if (i < GPW && (g < GA ? fill_a : fill_w)) issue_one(kt + (g < GA ? NSA : NSW), g < GA ? sa : sw_, g);
+                        if (i < GPW && LEFT >= (g < GA ? NSA : NSW)) issue_one(kt + (g < GA ? NSA : NSW), g < GA ? sa : sw_, g);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-    }
+    };
+    int kt = 0;
+    for (; kt + DEEP < nkt; ++kt) stage(kt, std::integral_constant<int, DEEP>{});
+    if (DEEP > 2 && kt + 2 < nkt) stage(kt++, std::integral_constant<int, 2>{});
+    if (kt + 1 < nkt) stage(kt++, std::integral_constant<int, 1>{});
+    stage(kt, std::integral_constant<int, 0>{});
     wait_vmcnt<0>();                                     // the look-ahead loads past the end have landed
     __syncthreads();                                     // ... in every wave: the stage memory is free
 
@@ -580,9 +581,10 @@ gemm_tail_kernel(bf16_t* __restrict__ C, int Nn, GemmGrid g, Epilogue ep) {
         wave_epilogue<1, TN, 2, KIND, true>(acc, ep, C, M, Nn, wrow0, n0 + wn * WN + 64, lane, patch);
 }
 
-// `tokens` rows per sample; offsets inside a sample are 32-bit element indices
+// `tokens` rows per sample; offsets inside a sample are 32-bit element indices, inside a tile's rows 32-bit byte offsets
 bool gemm_mfma_supported(int tokens, int Nn, int K) {
-    return K % 64 == 0 && Nn % 4 == 0 && tokens >= 1 && Nn >= 64 && K >= 64 && (long)tokens * Nn < (1L << 31);
+    return K % 64 == 0 && Nn % 4 == 0 && tokens >= 1 && Nn >= 64 && K >= 64 && K <= TILE_MAX_ROW_BYTES / 2 &&
+           (long)tokens * Nn < (1L << 31);
 }
 
 // kernel path: low byte = mode (4: never split a tail along K), bits 8-11 = forced tile variant (0: automatic)
