@@ -14,6 +14,7 @@
 //    its transposed fragments come from ds_read_b64_tr_b16.
 //  * attn_sp_kernel: the same tiles, software-pipelined and without a softmax reference; checks its results
 //    and has what fails recomputed by the loop of attn_mfma_kernel.
+#include "lane_sums.h"
 #include "plan.h"
 #include "tile_ops.h"
 #include <type_traits>
@@ -180,8 +181,7 @@ attn_f32_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __res
                 tmax = fmaxf(tmax, sc[g][i]);
             }
         }
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+        tmax = max_xor32(max_xor16(tmax));
         const float mn = fmaxf(m, tmax), alpha = expf(m - mn);   // exp(-inf) = 0 on the first tile
         m = mn;
         l *= alpha;
@@ -203,8 +203,7 @@ attn_f32_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __res
                                                                   acc[d], 0, 0, 0);
         }
     }
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
+    l = sum_xor32(sum_xor16(l));
     if (qi >= seq) return;
     const float inv = 1.0f / l;
     T* op = o + b * s.o_batch + (long)qi * s.o_tok + h * s.o_head + kgrp * 4;
@@ -274,16 +273,6 @@ __device__ __forceinline__ void lds_wait_v_frags(i32x2_t (&f)[16]) {
 __device__ __forceinline__ bf16x4_t lds_read_tr16(const unsigned char* p) {
     s16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(p));
     return __builtin_bit_cast(bf16x4_t, v);
-}
-
-// max over a query's keys held by lanes l and l^32
-__device__ __forceinline__ float max_across_halves(float v) {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
-    return fmaxf(__int_as_float(r[0]), __int_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_across_halves(float v) {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
-    return __int_as_float(r[0]) + __int_as_float(r[1]);
 }
 
 // Softmax bookkeeping.  Every query keeps a reference value r (bf16-representable) and the
@@ -659,7 +648,7 @@ attn_tracked(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const b
                 for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sacc[0][t][e]);
 #pragma unroll
                 for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[1][t][e]);
-                mx = max_across_halves(mx);                       // finite: every tile has a valid key
+                mx = max_xor32(mx);                       // finite: every tile has a valid key
                 if (j > jt0) mx = fmaxf(mx, 0.f);                 // the reference never moves down
                 // first tile: keep the reference at 0 while the maximum is within 2^+-REF_WINDOW of it
                 if (j == jt0 && fabsf(mx * cexp) <= REF_WINDOW) mx = 0.f;
@@ -718,7 +707,7 @@ attn_tracked(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const b
         float* pp = part + (long)piece * BQ * PART_STRIDE;
 #pragma unroll
         for (int t = 0; t < QT; ++t) {
-            const float l = sum_across_halves(lsum[t]);
+            const float l = sum_xor32(lsum[t]);
             float* pr = pp + (long)(wave * (QT * 32) + t * 32 + col) * PART_STRIDE;
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt)
@@ -733,7 +722,7 @@ attn_tracked(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const b
     }
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
-        float l = sum_across_halves(lsum[t]);
+        float l = sum_xor32(lsum[t]);
         float inv = 1.0f / l;
         int qi = q0 + t * 32 + col;
         if (qi < seq) {

@@ -1,24 +1,13 @@
 // HBM-bound kernels of the denoising step: time conditioning, patch embedding,
 // LayerNorm + adaLN modulation, final projection, the fused DDIM update with the
 // relative-MAE sums of paper Eq. (1), and the stand-alone relative MAE.
-#include "common.h"
+#include "lane_sums.h"
 
 #include <mutex>
 
 namespace ps {
 
 static constexpr int WAVE = 64;
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-    return v;
-}
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-    return v;
-}
 
 // ------------------------------------------------------------------ time conditioning
 struct TList { int t[16]; };
@@ -106,7 +95,7 @@ __global__ void gemv_kernel(GemvSet set, const float* __restrict__ in, int rows,
 #pragma unroll
         for (int b = 0; b < MAXB; ++b) {
             if (b < batch) {
-                float v = wave_sum(acc[r][b]);
+                float v = sum_of_64(acc[r][b]);
                 if (lane == 0) {
                     v += bias[row0 + r];
                     if (act == 1) v = silu_f(v);
@@ -587,7 +576,7 @@ __global__ void ln_modulate_kernel(const float* __restrict__ X, T* __restrict__ 
             s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
         }
     }
-    float mean = wave_sum(s) / (float)D;
+    float mean = sum_of_64(s) / (float)D;
     float q = 0.f;
 #pragma unroll
     for (int i = 0; i < MAXV; ++i) {
@@ -597,7 +586,7 @@ __global__ void ln_modulate_kernel(const float* __restrict__ X, T* __restrict__ 
             q += (a * a + b * b) + (cc * cc + d * d);
         }
     }
-    float rstd = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
+    float rstd = 1.0f / sqrtf(sum_of_64(q) / (float)D + eps);
     int b = row / g.tokens, n = row % g.tokens;
     int off = n < g.text_tokens ? 6 : 0;
     const float4* sh = reinterpret_cast<const float4*>(mod_layer + b * mod_bs + (long)(shift_chunk + off) * D);
@@ -626,7 +615,7 @@ __global__ void ln_modulate_kernel(const float* __restrict__ X, T* __restrict__ 
 
 // Sum over the 256 threads of a workgroup, the same value in every thread.  `sm`: 4 floats, one set per call.
 __device__ __forceinline__ float block_sum(float v, float* sm) {
-    v = wave_sum(v);
+    v = sum_of_64(v);
     if (threadIdx.x % WAVE == 0) sm[threadIdx.x / WAVE] = v;
     __syncthreads();
     return (sm[0] + sm[1]) + (sm[2] + sm[3]);
@@ -753,7 +742,7 @@ __global__ void final_proj_kernel(const float* __restrict__ X, const float* __re
     int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
     float s = 0.f;
     for (int c = threadIdx.x; c < D; c += blockDim.x) { float v = xr[c]; y[c] = v; s += v; }
-    s = wave_sum(s);
+    s = sum_of_64(s);
     if (lane == 0) red[wave] = s;
     __syncthreads();
     float tot = 0.f;
@@ -762,7 +751,7 @@ __global__ void final_proj_kernel(const float* __restrict__ X, const float* __re
     __syncthreads();
     float q = 0.f;
     for (int c = threadIdx.x; c < D; c += blockDim.x) { float dlt = y[c] - mean; q += dlt * dlt; }
-    q = wave_sum(q);
+    q = sum_of_64(q);
     if (lane == 0) red[wave] = q;
     __syncthreads();
     float qt = 0.f;
@@ -779,7 +768,7 @@ __global__ void final_proj_kernel(const float* __restrict__ X, const float* __re
         const T* w = W_out + (long)o * D;
         float acc = 0.f;
         for (int c = lane; c < D; c += WAVE) acc += to_f32(w[c]) * y[c];
-        acc = wave_sum(acc);
+        acc = sum_of_64(acc);
         if (lane == 0) {
             int dx = o % patch, dy = (o / patch) % patch, c = o / (patch * patch);
             eps_out[((((long)b * C + c) * F + f) * H + (i * patch + dy)) * Wd + (j * patch + dx)] = acc + b_out[o];
@@ -846,7 +835,7 @@ __device__ __forceinline__ void block_store_partials(double (&acc)[NS], double* 
     int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
-        double v = wave_sum_d(acc[k]);
+        double v = sum_of_64(acc[k]);
         if (lane == 0) sm[k][wave] = v;
     }
     __syncthreads();
@@ -900,7 +889,7 @@ __device__ __forceinline__ void reduce_partials(const double* __restrict__ part,
     int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
-        double v = wave_sum_d(acc[k]);
+        double v = sum_of_64(acc[k]);
         if (lane == 0) sm2[k][wave] = v;
     }
     __syncthreads();

@@ -12,6 +12,7 @@
 // us per forward of 2 layers of hidden 64 with the launches of the conditioning, a launch per operation and this: 32 tokens
 // 99 and 48, 134 tokens 109 and 56, 416 tokens 125 and 71.
 #include "few_epilogue.h"
+#include "lane_sums.h"
 #include "slim.h"
 
 namespace ps {
@@ -62,13 +63,6 @@ struct Project {
     }
 };
 
-// sum over the 16 lanes that share a row
-__device__ __forceinline__ float row_sum(float v) {
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 // out = LN(in) * (1 + scale) + shift for rows 4 * wave + lane / 16; shift, scale: of that row
 template <int D>
 __device__ __forceinline__ void slim_norm(const float* in, float* out, const float* shift, const float* scale, float eps) {
@@ -79,10 +73,10 @@ __device__ __forceinline__ void slim_norm(const float* in, float* out, const flo
     for (int i = 0; i < V; ++i) { h[i] = shift[l16 + 16 * i]; k[i] = scale[l16 + 16 * i]; }
 #pragma unroll
     for (int i = 0; i < V; ++i) { v[i] = in[l16 + 16 * i]; s += v[i]; }
-    const float mean = row_sum(s) / (float)D;
+    const float mean = sum_of_16(s) / (float)D;
 #pragma unroll
     for (int i = 0; i < V; ++i) q += (v[i] - mean) * (v[i] - mean);
-    const float rstd = 1.0f / sqrtf(row_sum(q) / (float)D + eps);
+    const float rstd = 1.0f / sqrtf(sum_of_16(q) / (float)D + eps);
 #pragma unroll
     for (int i = 0; i < V; ++i) out[l16 + 16 * i] = (v[i] - mean) * rstd * (1.f + k[i]) + h[i];
 }
@@ -213,8 +207,7 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
                     tmax = fmaxf(tmax, sc[t][i]);
                 }
             }
-            tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-            tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+            tmax = max_xor32(max_xor16(tmax));
             const float mn = fmaxf(m, tmax), alpha = expf(m - mn);   // exp(-inf) = 0 on the first keys
             m = mn;
             l *= alpha;
@@ -234,8 +227,7 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
                     for (int d = 0; d < NB; ++d) acc[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][e][d], sc[t][e], acc[d], 0, 0, 0);
             }
         }
-        l += __shfl_xor(l, 16, 64);
-        l += __shfl_xor(l, 32, 64);
+        l = sum_xor32(sum_xor16(l));
         const float inv = 1.0f / l;
 #pragma unroll
         for (int d = 0; d < NB; ++d) *reinterpret_cast<f32x4_t*>(ht + l16 * LD + h * HD + d * 16 + kgrp * 4) = acc[d] * inv;
