@@ -41,7 +41,7 @@ struct Project {
 #pragma unroll
         for (int j = 0; j < G; ++j) load(j, pre[j]);
     }
-    // in: LDS, this lane's row (lane % 16); epi(first of the lane's 4 columns, sums)
+    // in: LDS, this lane's row (lane % 16); epi(j, first of the lane's 4 columns, sums) for its j-th block
     template <class Epi>
     __device__ __forceinline__ void run(const float* in, Epi epi) const {
         const int kgrp = (threadIdx.x & 63) >> 4;
@@ -58,44 +58,77 @@ struct Project {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     s[i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(j < G ? pre[j < G ? j : 0][i][e] : later[i][e], a[i][e], s[i & 1], 0, 0, 0);
-            epi((wave + 4 * j) * 16 + kgrp * 4, s[0] + s[1]);
+            epi(j, (wave + 4 * j) * 16 + kgrp * 4, s[0] + s[1]);
         }
+    }
+};
+
+// What the phases read besides activations and weights -- biases, gates, modulation, rotary table -- is requested with the
+// first loads of a launch, or behind its attention: asked for when its turn came, each of the six was a trip to L2 in the middle
+// of the chain (8 steps of 2 layers of 64 on 128 tokens: 386 -> 352 us).
+// BlockVec: 4 columns of each of a wave's blocks of 16.
+template <int NF>
+struct BlockVec {
+    f32x4_t v[NF];
+    __device__ __forceinline__ void request(const float* p, int wave, int blocks) {
+        const int kgrp = (threadIdx.x & 63) >> 4;
+#pragma unroll
+        for (int j = 0; j < NF; ++j) v[j] = quad(p + min(wave + 4 * j, blocks - 1) * 16 + kgrp * 4);
     }
 };
 
 // out = LN(in) * (1 + scale) + shift for rows 4 * wave + lane / 16; shift, scale: of that row
 template <int D>
-__device__ __forceinline__ void slim_norm(const float* in, float* out, const float* shift, const float* scale, float eps) {
-    constexpr int V = D / 16;
-    const int l16 = threadIdx.x & 15;
-    float v[V], h[V], k[V], s = 0.f, q = 0.f;
+struct SlimNorm {
+    static constexpr int V = D / 16;
+    float h[V], k[V];
+    __device__ __forceinline__ void request(const float* shift, const float* scale) {
+        const int l16 = threadIdx.x & 15;
 #pragma unroll
-    for (int i = 0; i < V; ++i) { h[i] = shift[l16 + 16 * i]; k[i] = scale[l16 + 16 * i]; }
+        for (int i = 0; i < V; ++i) { h[i] = shift[l16 + 16 * i]; k[i] = scale[l16 + 16 * i]; }
+    }
+    __device__ __forceinline__ void run(const float* in, float* out, float eps) const {
+        const int l16 = threadIdx.x & 15;
+        float v[V], s = 0.f, q = 0.f;
 #pragma unroll
-    for (int i = 0; i < V; ++i) { v[i] = in[l16 + 16 * i]; s += v[i]; }
-    const float mean = sum_of_16(s) / (float)D;
+        for (int i = 0; i < V; ++i) { v[i] = in[l16 + 16 * i]; s += v[i]; }
+        const float mean = sum_of_16(s) / (float)D;
 #pragma unroll
-    for (int i = 0; i < V; ++i) q += (v[i] - mean) * (v[i] - mean);
-    const float rstd = 1.0f / sqrtf(sum_of_16(q) / (float)D + eps);
+        for (int i = 0; i < V; ++i) q += (v[i] - mean) * (v[i] - mean);
+        const float rstd = 1.0f / sqrtf(sum_of_16(q) / (float)D + eps);
 #pragma unroll
-    for (int i = 0; i < V; ++i) out[l16 + 16 * i] = (v[i] - mean) * rstd * (1.f + k[i]) + h[i];
-}
+        for (int i = 0; i < V; ++i) out[l16 + 16 * i] = (v[i] - mean) * rstd * (1.f + k[i]) + h[i];
+    }
+};
 
 // q, k, v of a row block: bias, rotation, store
 template <int D>
-__device__ __forceinline__ void slim_qkv(const SlimArgs& g, const SlimLayer& w, const Project<D / 16, (3 * D / 16 + 3) / 4>& pj,
-                                         const float* in, int b, int n) {
-    Epilogue ep{};
-    ep.kind = EPI_QKV_ROPE; ep.bias = w.b_qkv; ep.D = D; ep.geom = TokenGeom{g.tokens, g.text_tokens};
-    ep.rope_cs = g.rope; ep.rope_F = g.pg.F; ep.rope_Hp = g.pg.H / g.pg.patch; ep.rope_Wp = g.pg.W / g.pg.patch;
-    ep.head_dim = g.head_dim; ep.q_scale = 1.0f;
-    const int row = b * g.tokens + min(n, g.tokens - 1);
-    const EpiRow r = epilogue_row<EPI_QKV_ROPE>(ep, row);
-    pj.run(in, [&](int col, f32x4_t x) {
-        const EpiOperands o = epilogue_operands<EPI_QKV_ROPE>(ep, 3 * D, r, row, col);
-        if (n < g.tokens) epilogue_quad<EPI_QKV_ROPE, float>(ep, g.qkv_out, 3 * D, r, row, col, x, quad(w.b_qkv + col), o);
-    });
-}
+struct SlimQkv {
+    static constexpr int NF = (3 * D / 16 + 3) / 4, BLOCKS = 3 * D / 16;
+    Epilogue ep;
+    EpiRow r;
+    int row;
+    BlockVec<NF> bias;
+    EpiOperands o[NF];
+    __device__ __forceinline__ void request(const SlimArgs& g, const SlimLayer& w, int wave, int b, int n) {
+        ep = Epilogue{};
+        ep.kind = EPI_QKV_ROPE; ep.bias = w.b_qkv; ep.D = D; ep.geom = TokenGeom{g.tokens, g.text_tokens};
+        ep.rope_cs = g.rope; ep.rope_F = g.pg.F; ep.rope_Hp = g.pg.H / g.pg.patch; ep.rope_Wp = g.pg.W / g.pg.patch;
+        ep.head_dim = g.head_dim; ep.q_scale = 1.0f;
+        row = b * g.tokens + min(n, g.tokens - 1);
+        r = epilogue_row<EPI_QKV_ROPE>(ep, row);
+        bias.request(w.b_qkv, wave, BLOCKS);
+        const int kgrp = (threadIdx.x & 63) >> 4;
+#pragma unroll
+        for (int j = 0; j < NF; ++j)
+            o[j] = epilogue_operands<EPI_QKV_ROPE>(ep, 3 * D, r, row, min(wave + 4 * j, BLOCKS - 1) * 16 + kgrp * 4);
+    }
+    __device__ __forceinline__ void run(const SlimArgs& g, const Project<D / 16, NF>& pj, const float* in, int n) const {
+        pj.run(in, [&](int j, int col, f32x4_t x) {
+            if (n < g.tokens) epilogue_quad<EPI_QKV_ROPE, float>(ep, g.qkv_out, 3 * D, r, row, col, x, bias.v[j], o[j]);
+        });
+    }
+};
 
 // Embedding, first LayerNorm and q, k, v.  P = 16 * PB values per patch.
 template <int D, int PB>
@@ -109,6 +142,16 @@ __global__ void __launch_bounds__(256, 1) slim_begin_kernel(SlimArgs g, SlimLaye
     embed.request(g.W_pe, wave, D / 16);
     Project<D / 16, (3 * D / 16 + 3) / 4> qkv;
     qkv.request(w.W_qkv, wave, 3 * D / 16);
+    BlockVec<(D / 16 + 3) / 4> b_pe;
+    b_pe.request(g.b_pe, wave, D / 16);
+    const int nr = wave * 4 + (lane >> 4);               // this lane's row in the LayerNorm
+    SlimNorm<D> norm;
+    {
+        const float* m = g.mod + b * g.mod_bs + (n0 + nr < L ? 6 * D : 0);
+        norm.request(m, m + D);
+    }
+    SlimQkv<D> out;
+    out.request(g, w, wave, b, n);
     const PatchGeom& pg = g.pg;
     const int Hp = pg.H / pg.patch, Wp = pg.W / pg.patch, ps2 = pg.patch * pg.patch;
     for (int e = threadIdx.x; e < ROWS * P; e += 256) {
@@ -121,20 +164,16 @@ __global__ void __launch_bounds__(256, 1) slim_begin_kernel(SlimArgs g, SlimLaye
         pt[r * LP + p] = v;
     }
     __syncthreads();
-    embed.run(pt + l16 * LP, [&](int col, f32x4_t x) {
-        x += quad(g.b_pe + col);
+    embed.run(pt + l16 * LP, [&](int j, int col, f32x4_t x) {
+        x += b_pe.v[j];
         if (n < L) x = quad(g.ctx + b * g.ctx_bs + (long)n * D + col);
         *reinterpret_cast<f32x4_t*>(xt + l16 * LD + col) = x;
         if (n < N) *reinterpret_cast<f32x4_t*>(g.X + ((long)b * N + n) * D + col) = x;
     });
     __syncthreads();
-    {
-        const int r = wave * 4 + (lane >> 4);
-        const float* m = g.mod + b * g.mod_bs + (n0 + r < L ? 6 * D : 0);
-        slim_norm<D>(xt + r * LD, ht + r * LD, m, m + D, g.eps);
-    }
+    norm.run(xt + nr * LD, ht + nr * LD, g.eps);
     __syncthreads();
-    slim_qkv<D>(g, w, qkv, ht + l16 * LD, b, n);
+    out.run(g, qkv, ht + l16 * LD, n);
 }
 
 // One layer from its attention on; `next`: the following layer's q, k, v, or after the last layer the final projection.
@@ -152,6 +191,16 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
     for (int e = threadIdx.x; e < ROWS * (D / 4); e += 256) {
         const int r = e / (D / 4), c = e % (D / 4) * 4;
         *reinterpret_cast<f32x4_t*>(xt + r * LD + c) = quad(g.X + ((long)b * N + min(n0 + r, N - 1)) * D + c);
+    }
+    constexpr int NO = (D / 16 + 3) / 4;
+    const int nr = wave * 4 + kgrp;                      // this lane's row in the LayerNorms
+    BlockVec<NO> b_o, gate_a;
+    b_o.request(w.b_o, wave, D / 16);
+    gate_a.request(gates + 2 * D, wave, D / 16);
+    SlimNorm<D> mid;
+    {
+        const float* m = mod + (n0 + nr < L ? 6 * D : 0);
+        mid.request(m + 3 * D, m + 4 * D);
     }
     // attention: a wave per head, its 16 queries in lane % 16.  S^T = K Q^T leaves keys 4 * (lane / 16) + i of every 16-key
     // block, the layout the second operand of O^T = V^T P^T wants: the probabilities stay in their registers, in fp32.
@@ -232,56 +281,64 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
 #pragma unroll
         for (int d = 0; d < NB; ++d) *reinterpret_cast<f32x4_t*>(ht + l16 * LD + h * HD + d * 16 + kgrp * 4) = acc[d] * inv;
     }
-    __syncthreads();
     Project<D / 16, D / 16> p1;
     p1.request(w.W_1, wave, F / 16);
-    auto residual = [&](const float* bias, const float* gate) {
-        return [=](int col, f32x4_t x) {
+    BlockVec<D / 16> b_1;
+    b_1.request(w.b_1, wave, F / 16);
+    BlockVec<NO> b_2, gate_m;
+    b_2.request(w.b_2, wave, D / 16);
+    gate_m.request(gates + 5 * D, wave, D / 16);
+    SlimNorm<D> end;
+    {
+        const float* m = LAST ? g.modf + b * 2 * D : mod + 12 * D + (n0 + nr < L ? 6 * D : 0);
+        end.request(m, m + D);
+    }
+    const int P = g.pg.C * g.pg.patch * g.pg.patch;
+    BlockVec<1> b_out;
+    SlimQkv<D> out;
+    if constexpr (LAST) b_out.request(g.b_out, wave, P / 16); else out.request(g, next, wave, b, n);
+    __syncthreads();
+    auto residual = [&](const BlockVec<NO>& bias, const BlockVec<NO>& gate) {
+        return [=](int j, int col, f32x4_t x) {
             float* at = xt + l16 * LD + col;
-            *reinterpret_cast<f32x4_t*>(at) = quad(at) + quad(gate + col) * (x + quad(bias + col));
+            *reinterpret_cast<f32x4_t*>(at) = quad(at) + gate.v[j] * (x + bias.v[j]);
         };
     };
-    po.run(ht + l16 * LD, residual(w.b_o, gates + 2 * D));
+    po.run(ht + l16 * LD, residual(b_o, gate_a));
     __syncthreads();
-    const int nr = wave * 4 + kgrp;                      // this lane's row in the LayerNorms
-    {
-        const float* m = mod + (n0 + nr < L ? 6 * D : 0);
-        slim_norm<D>(xt + nr * LD, ht + nr * LD, m + 3 * D, m + 4 * D, g.eps);
-    }
+    mid.run(xt + nr * LD, ht + nr * LD, g.eps);
     __syncthreads();
-    Project<F / 16, (D / 16 + 3) / 4> p2;
+    Project<F / 16, NO> p2;
     p2.request(w.W_2, wave, D / 16);
-    p1.run(ht + l16 * LD, [&](int col, f32x4_t x) {
-        x += quad(w.b_1 + col);
+    p1.run(ht + l16 * LD, [&](int j, int col, f32x4_t x) {
+        x += b_1.v[j];
 #pragma unroll
         for (int c = 0; c < 4; ++c) x[c] = gelu_tanh_f(x[c]);
         *reinterpret_cast<f32x4_t*>(ut + l16 * LF + col) = x;
     });
     __syncthreads();
-    p2.run(ut + l16 * LF, residual(w.b_2, gates + 5 * D));
+    p2.run(ut + l16 * LF, residual(b_2, gate_m));
     Project<D / 16, LAST ? 1 : (3 * D / 16 + 3) / 4> pn;
-    pn.request(LAST ? g.W_out : next.W_qkv, wave, LAST ? g.pg.C * g.pg.patch * g.pg.patch / 16 : 3 * D / 16);
+    pn.request(LAST ? g.W_out : next.W_qkv, wave, LAST ? P / 16 : 3 * D / 16);
     __syncthreads();
     if constexpr (LAST) {
-        const float* m = g.modf + b * 2 * D;
-        slim_norm<D>(xt + nr * LD, ht + nr * LD, m, m + D, g.eps);
+        end.run(xt + nr * LD, ht + nr * LD, g.eps);
         __syncthreads();
         Epilogue ep{};
         ep.kind = EPI_UNPATCHIFY; ep.bias = g.b_out; ep.resid = g.eps_out; ep.geom = TokenGeom{N, L}; ep.pg = g.pg;
-        const int P = g.pg.C * g.pg.patch * g.pg.patch, row = b * N + min(n, N - 1);
+        const int row = b * N + min(n, N - 1);
         const EpiRow r = epilogue_row<EPI_UNPATCHIFY>(ep, row);
-        pn.run(ht + l16 * LD, [&](int col, f32x4_t x) {
-            if (n < N) epilogue_quad<EPI_UNPATCHIFY, float>(ep, nullptr, P, r, row, col, x, quad(g.b_out + col), epilogue_operands<EPI_UNPATCHIFY>(ep, P, r, row, col));
+        pn.run(ht + l16 * LD, [&](int j, int col, f32x4_t x) {
+            if (n < N) epilogue_quad<EPI_UNPATCHIFY, float>(ep, nullptr, P, r, row, col, x, b_out.v[j], epilogue_operands<EPI_UNPATCHIFY>(ep, P, r, row, col));
         });
     } else {
         for (int e = threadIdx.x; e < ROWS * (D / 4); e += 256) {
             const int r = e / (D / 4), c = e % (D / 4) * 4;
             if (n0 + r < N) *reinterpret_cast<f32x4_t*>(g.X + ((long)b * N + n0 + r) * D + c) = quad(xt + r * LD + c);
         }
-        const float* m = mod + 12 * D + (n0 + nr < L ? 6 * D : 0);
-        slim_norm<D>(xt + nr * LD, ht + nr * LD, m, m + D, g.eps);
+        end.run(xt + nr * LD, ht + nr * LD, g.eps);
         __syncthreads();
-        slim_qkv<D>(g, next, pn, ht + l16 * LD, b, n);
+        out.run(g, pn, ht + l16 * LD, n);
     }
 }
 
