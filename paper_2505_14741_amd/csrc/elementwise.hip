@@ -154,85 +154,88 @@ hipError_t launch_gemv(int dtype, const void* W, const float* bias, const float*
 
 // The modulation matrices as one matrix product in fp32, out[b][row] = W[row] . in[b] + bias[row], on
 // v_mfma_f32_16x16x4_f32: 16 rows x up to 16 vectors per instruction, weights widened to fp32, so that one pass over the
-// weights (708 MB for 30 layers of 1920) serves every timestep of a run's next steps.  Reading them is the bound.  A wave
-// takes 16 or 32 rows at a time; lane l reads 16 adjacent weights of row l % 16, whole 128-byte lines (bf16) per row and 64 columns.  Four
-// sums per output.  The same kernel serves one vector, so a vector's result does not depend on the batch.
-// (The kernel above pays six shuffles per row and vector: 148 us for one vector and 30 layers, 295 for four; this takes 163
-// for one and 181 for nine.)
+// weights (708 MB for 30 layers of 1920) serves every timestep of a run's next steps.  Reading them is the bound, the matrix
+// instructions (72 us of those 708 MB) come second.  A wave takes 16 rows at a time; lane l reads 16 adjacent weights of row
+// l % 16, whole 128-byte lines (bf16) per row and 64 columns.  512 columns in bf16, 256 in fp32 are in flight per wave, the
+// first of them requested before the vectors are staged, each step's registers refilled for what comes next behind its products.
+// Four sums per output.  The same kernel serves one vector, so a vector's result does not depend on the batch.
+// us, weights from memory, all loads of a pass and then its products / this: 30 layers bf16 162 / 147 (4.85 TB/s, a plain copy
+// 5.1), nine vectors 176 / 160, one layer 12.9 / 12.0; fp32, two layers 31.3 / 25.0, one 19.4 / 14.9.
+// (The kernel above pays six shuffles per row and vector: 148 us for one vector and 30 layers, 295 for four.)
 static constexpr int MOD_MAX_COLS = 1000;                // 16 vectors of cols + 4 floats within 64 KB of LDS
-template <typename T, int R>                             // R: groups of 16 rows per wave and pass
-__global__ void __launch_bounds__(256)
+template <typename T>
+__global__ void __launch_bounds__(256, 4)
 modulation_kernel(ModSet set, const float* __restrict__ in, int cols, int batch, long in_bs, int wg_rows) {
     typedef __attribute__((ext_vector_type(4))) float f4;
     extern __shared__ __attribute__((aligned(16))) float xs[];   // [batch][cols + 4]: 4 banks from vector to vector
     const int rows = set.rows[blockIdx.y], ld = cols + 4;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kgrp = lane >> 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kgrp = lane >> 4;
     if ((int)blockIdx.x * wg_rows >= rows) return;       // (whole workgroup)
+    const int row_end = min(rows, (int)(blockIdx.x + 1) * wg_rows);
+    const T* W = static_cast<const T*>(set.g.W[blockIdx.y]);
+    constexpr int NQ = sizeof(T);                        // 16-byte loads per 16 weights: 2 (bf16) or 4
+    constexpr int CH = 16 / NQ;                          // steps of 64 columns in flight
+    uint4 raw[CH][NQ];
+    auto row_of = [&](int row0) { return W + (long)min(row0 + l16, rows - 1) * cols + kgrp * 16; };
+    auto request = [&](const T* w, int c0, int h) {      // (columns past the end: read again, not multiplied)
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) raw[h][i] = *reinterpret_cast<const uint4*>(w + min(c0 + 64 * h, cols - 64) + i * (16 / NQ));
+    };
+    int row0 = blockIdx.x * wg_rows + wave * 16;
+    {
+        const T* w = row_of(row0);
+#pragma unroll
+        for (int h = 0; h < CH; ++h) request(w, 0, h);
+    }
     for (int e = threadIdx.x * 4; e < batch * cols; e += 1024) {
         const int b = e / cols, c = e - b * cols;
         *reinterpret_cast<f4*>(xs + b * ld + c) = *reinterpret_cast<const f4*>(in + b * in_bs + c);
     }
     __syncthreads();
-    const T* W = static_cast<const T*>(set.g.W[blockIdx.y]);
-    const float* x = xs + (l16 < batch ? l16 : 0) * ld + kgrp * 16;   // columns past the batch repeat vector 0, unused
-    for (int row0 = blockIdx.x * wg_rows + wave * 16 * R; row0 < min(rows, (int)(blockIdx.x + 1) * wg_rows); row0 += 64 * R) {
-        const T* w[R];
+    const int xoff = (l16 < batch ? l16 : 0) * ld + kgrp * 16;   // columns past the batch repeat vector 0, unused
+    f4 acc[4];
+    // 64 * CH columns of the 16 rows at row0; NEXT: refill from `w`, column `nc0`, behind the products
+    auto columns = [&](int c0, auto next_c, const T* w, int nc0) {
+        constexpr bool NEXT = decltype(next_c)::value;
+        int xo = xoff + c0;
+        asm volatile("" : "+v"(xo));                     // (else the vectors are kept in registers over the passes, which spill)
 #pragma unroll
-        for (int r = 0; r < R; ++r) w[r] = W + (long)min(row0 + r * 16 + l16, rows - 1) * cols + kgrp * 16;
-        f4 acc[R][4];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int a = 0; a < 4; ++a) acc[r][a] = f4{0.f, 0.f, 0.f, 0.f};
-        // 16 loads of 16 bytes per lane requested together, then multiplied (512 columns in bf16 with R = 1)
-        constexpr int NQ = sizeof(T);                    // 16-byte loads per 16 weights: 2 (bf16) or 4
-        constexpr int CH = 16 / (NQ * R);                      // steps of 64 columns in flight
-        for (int c0 = 0; c0 < cols; c0 += 64 * CH) {
-            uint4 raw[CH][R][NQ];
-#pragma unroll
-            for (int h = 0; h < CH; ++h)
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-#pragma unroll
-                    for (int i = 0; i < NQ; ++i) {
-                        const int c = min(c0 + 64 * h, cols - 64);   // (past the end: read again, not multiplied)
-                        raw[h][r][i] = *reinterpret_cast<const uint4*>(w[r] + c + i * (16 / NQ));
-                    }
-#pragma unroll
-            for (int h = 0; h < CH; ++h) {
-                if (c0 + 64 * h >= cols) break;
+        for (int h = 0; h < CH; ++h) {
+            if (c0 + 64 * h < cols) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const f4 xv = *reinterpret_cast<const f4*>(x + c0 + 64 * h + i * 4);
+                    const f4 xv = *reinterpret_cast<const f4*>(xs + xo + 64 * h + i * 4);
+                    f4 wv;
+                    if constexpr (sizeof(T) == 2) {
+                        const unsigned* u = reinterpret_cast<const unsigned*>(&raw[h][i / 2]) + (i & 1) * 2;
 #pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        f4 wv;
-                        if constexpr (sizeof(T) == 2) {
-                            const unsigned* u = reinterpret_cast<const unsigned*>(&raw[h][r][i / 2]) + (i & 1) * 2;
-#pragma unroll
-                            for (int e = 0; e < 2; ++e) {            // bf16 -> fp32: the upper half of the word
-                                wv[2 * e] = __uint_as_float(u[e] << 16);
-                                wv[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
-                            }
-                        } else {
-                            wv = __builtin_bit_cast(f4, raw[h][r][i]);
+                        for (int e = 0; e < 2; ++e) {    // bf16 -> fp32: the upper half of the word
+                            wv[2 * e] = __uint_as_float(u[e] << 16);
+                            wv[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
                         }
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            acc[r][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], xv[e], acc[r][e], 0, 0, 0);
+                    } else {
+                        wv = __builtin_bit_cast(f4, raw[h][i]);
                     }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], xv[e], acc[e], 0, 0, 0);
                 }
             }
+            if constexpr (NEXT) request(w, nc0, h);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if (l16 >= batch) continue;
+    };
+    for (; row0 < row_end; row0 += 64) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int row = row0 + r * 16 + kgrp * 4;    // rows % 4 == 0: inside or outside together
-            if (row >= rows) continue;
-            const f4 s = (acc[r][0] + acc[r][1]) + (acc[r][2] + acc[r][3]);
-            *reinterpret_cast<f4*>(set.g.out[blockIdx.y] + l16 * set.out_bs[blockIdx.y] + row) =
-                s + *reinterpret_cast<const f4*>(set.g.bias[blockIdx.y] + row);
-        }
+        for (int a = 0; a < 4; ++a) acc[a] = f4{0.f, 0.f, 0.f, 0.f};
+        const int out_row = row0 + kgrp * 4;             // rows % 4 == 0: inside or outside together
+        const f4 bias = *reinterpret_cast<const f4*>(set.g.bias[blockIdx.y] + min(out_row, rows - 4));
+        int c0 = 0;
+        for (; c0 + 64 * CH < cols; c0 += 64 * CH) columns(c0, std::true_type{}, row_of(row0), c0 + 64 * CH);
+        if (row0 + 64 < row_end) columns(c0, std::true_type{}, row_of(row0 + 64), 0);
+        else columns(c0, std::false_type{}, nullptr, 0);
+        if (l16 < batch && out_row < rows)
+            *reinterpret_cast<f4*>(set.g.out[blockIdx.y] + l16 * set.out_bs[blockIdx.y] + out_row) =
+                ((acc[0] + acc[1]) + (acc[2] + acc[3])) + bias;
     }
 }
 
@@ -256,16 +259,14 @@ hipError_t launch_modulation(int dtype, const ModSet& set, int count, const floa
         }
         return hipSuccess;
     }
-    // Few matrices have to fill the chip: 64 rows per workgroup, 16 per wave.  Many: 256, 32 at a time, so that the vectors
-    // are read from LDS half as often and staged less.  (The values are the same.)  23040 x 512 bf16, one layer and the
-    // final matrix: 13.7 us against 26; 30 layers: 188 us against 163.
+    // Few matrices have to fill the chip: 64 rows per workgroup.  Many: 256, so that the vectors are staged less.  (The values
+    // are the same.)  23040 x 512 bf16, 30 layers: 128 rows 146 us, nine vectors 165, 256 rows 147 and 160, 512 rows 155 and 166.
     const bool few = (long)most * count <= 200000;
     const int wg_rows = few ? 64 : 256;
     dim3 grid((most + wg_rows - 1) / wg_rows, count);
     const size_t sh = (size_t)batch * (cols + 4) * sizeof(float);
-    auto go = [&](auto kernel) { kernel<<<grid, 256, sh, st>>>(set, in, cols, batch, in_bs, wg_rows); };
-    if (dtype == PS_BF16) { if (few) go(modulation_kernel<bf16_t, 1>); else go(modulation_kernel<bf16_t, 2>); }
-    else { if (few) go(modulation_kernel<float, 1>); else go(modulation_kernel<float, 2>); }
+    if (dtype == PS_BF16) modulation_kernel<bf16_t><<<grid, 256, sh, st>>>(set, in, cols, batch, in_bs, wg_rows);
+    else modulation_kernel<float><<<grid, 256, sh, st>>>(set, in, cols, batch, in_bs, wg_rows);
     return hipGetLastError();
 }
 
