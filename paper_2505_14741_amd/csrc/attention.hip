@@ -149,7 +149,10 @@ attn_f32_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __res
     attn_f4_t acc[NB];                                   // O^T: lane's query, d = 16 * block + 4 * kgrp + i
 #pragma unroll
     for (int d = 0; d < NB; ++d) acc[d] = attn_f4_t{0.f, 0.f, 0.f, 0.f};
-    float m = -INFINITY, l = 0.f;                        // l: over this lane's keys only
+    // Exponentials are the hardware's, of log2(e) times the score less log2(e) times the maximum, one fused operation with one
+    // rounding like the difference it replaces (an exponential of the math library is 13 instructions).
+    constexpr float LOG2E = 1.4426950408889634f;
+    float m = -INFINITY, l = 0.f;                        // m: in powers of two; l: over this lane's keys only
     fetch(0);
     for (int k0 = 0; k0 < seq; k0 += KT) {
         __syncthreads();                                 // nobody reads the last tile any more
@@ -182,7 +185,7 @@ attn_f32_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __res
             }
         }
         tmax = max_xor32(max_xor16(tmax));
-        const float mn = fmaxf(m, tmax), alpha = expf(m - mn);   // exp(-inf) = 0 on the first tile
+        const float mn = fmaxf(m, tmax * LOG2E), alpha = __builtin_amdgcn_exp2f(m - mn);   // 0 on the first tile
         m = mn;
         l *= alpha;
 #pragma unroll
@@ -192,7 +195,7 @@ attn_f32_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __res
             if (g >= blocks) continue;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                sc[g][i] = expf(sc[g][i] - mn);          // masked keys: exp(-inf) = 0
+                sc[g][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[g][i], LOG2E, -mn));   // masked keys: 0
                 l += sc[g][i];
             }
 #pragma unroll
@@ -205,10 +208,9 @@ attn_f32_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __res
     }
     l = sum_xor32(sum_xor16(l));
     if (qi >= seq) return;
-    const float inv = 1.0f / l;
     T* op = o + b * s.o_batch + (long)qi * s.o_tok + h * s.o_head + kgrp * 4;
 #pragma unroll
-    for (int d = 0; d < NB; ++d) store_quad(op + d * 16, acc[d] * inv);
+    for (int d = 0; d < NB; ++d) store_quad(op + d * 16, acc[d] / l);   // (a division: one rounding less than a reciprocal and a product)
 }
 
 template <typename T>

@@ -420,3 +420,21 @@ def test_profile_of_a_narrow_network_and_of_one_that_is_not(mode):
         if mode == 1:
             assert prof["ln_modulate"][1] == 0 if one_launch else prof["ln_modulate"][1] >= 6
             assert prof["other"][1] == 4 + 1 + 3 if one_launch else prof["other"][1] > 0
+
+
+@pytest.mark.parametrize("rows", [5, 64])
+def test_fp32_gelu_over_its_range(rows):
+    """The fp32 GELU epilogue alone (zero product, the value in the bias): both tails, the cut where its quotient is no longer
+    refined, zeros, infinity and NaN, against float64.  A result of a few operations of one rounding each: 8 units in the last
+    place of the larger of result and 1/8 of the argument (the exponent's rounding, up to |t| * 2^-24 of a factor below 1)."""
+    v = np.concatenate([np.linspace(-14, 14, 449), [-1e4, -3e18, 0.0, -0.0, 1e-30, -1e-30, 1e4, 3e18, np.inf, np.nan], np.linspace(-7, -4, 53)])
+    bias = torch.tensor(v, dtype=torch.float32, device=DEV)
+    a, w = torch.zeros(rows, 64, device=DEV), torch.zeros(len(v), 64, device=DEV)
+    out = B.dit_linear(a, w, bias, act=1).cpu().double()
+    x = bias.cpu().double()
+    ref = torch.nn.functional.gelu(x, approximate="tanh")
+    assert torch.equal(torch.isnan(out), torch.isnan(ref).expand(rows, -1))
+    assert (out[:, v == np.inf] == np.inf).all()
+    m = torch.isfinite(ref)
+    bound = 8 * 2.0 ** -24 * torch.maximum(ref.abs(), x.abs().clamp(max=14) / 8)[m] + 1e-36
+    assert ((out[:, m] - ref[m]).abs() <= bound).all()
