@@ -27,6 +27,7 @@ __device__ __forceinline__ f32x4_t quad(const float* p) { return *reinterpret_ca
 template <int KB, int NF>
 struct Project {
     static constexpr int G = KB >= 16 ? 1 : NF * KB <= 16 ? NF : 16 / KB;
+    static constexpr int LOADS = G * KB, STEPS = NF * KB;
     f32x4_t pre[G][KB];
     const float* W;
     int wave, blocks;
@@ -36,31 +37,51 @@ struct Project {
 #pragma unroll
         for (int i = 0; i < KB; ++i) w[i] = quad(p + i * 16);
     }
+    __device__ __forceinline__ void prepare(const float* weights, int w, int n) { W = weights; wave = w; blocks = n; }
     __device__ __forceinline__ void request(const float* weights, int w, int n) {
-        W = weights; wave = w; blocks = n;
+        prepare(weights, w, n);
 #pragma unroll
         for (int j = 0; j < G; ++j) load(j, pre[j]);
     }
-    // in: LDS, this lane's row (lane % 16); epi(j, first of the lane's 4 columns, sums) for its j-th block
-    template <class Epi>
-    __device__ __forceinline__ void run(const float* in, Epi epi) const {
+    // its share of step s of `steps`
+    __device__ __forceinline__ void request_step(int s, int steps) {
+        const int lane = threadIdx.x & 63, per = (LOADS + steps - 1) / steps;
+#pragma unroll
+        for (int u = s * per; u < (s + 1) * per && u < LOADS; ++u) {
+            const int col = min(wave + 4 * (u / KB), blocks - 1) * 16 + (lane & 15);
+            pre[u / KB][u % KB] = quad(W + col * (16 * KB) + (lane >> 4) * 4 + u % KB * 16);
+        }
+    }
+    // in: LDS, this lane's row (lane % 16); epi(j, first of the lane's 4 columns, sums) for its j-th block.  between(s): what
+    // goes behind the s-th four products, the loads of another projection: issued in one go they held the products up for as
+    // long as a compute unit takes to accept them, about 160 cycles for one of each wave.
+    template <class Epi, class Between>
+    __device__ __forceinline__ void run(const float* in, Epi epi, Between between) const {
         const int kgrp = (threadIdx.x & 63) >> 4;
         f32x4_t a[KB];
 #pragma unroll
         for (int i = 0; i < KB; ++i) a[i] = quad(in + i * 16 + kgrp * 4);
 #pragma unroll
         for (int j = 0; j < NF; ++j) {
-            if (wave + 4 * j >= blocks) break;
+            if (wave + 4 * j >= blocks) {                // (whole wave)
+#pragma unroll
+                for (int i = 0; i < KB; ++i) between(j * KB + i);
+                continue;
+            }
             f32x4_t later[KB], s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
             if (j >= G) load(j, later);
 #pragma unroll
-            for (int i = 0; i < KB; ++i)
+            for (int i = 0; i < KB; ++i) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     s[i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(j < G ? pre[j < G ? j : 0][i][e] : later[i][e], a[i][e], s[i & 1], 0, 0, 0);
+                between(j * KB + i);
+            }
             epi(j, (wave + 4 * j) * 16 + kgrp * 4, s[0] + s[1]);
         }
     }
+    template <class Epi>
+    __device__ __forceinline__ void run(const float* in, Epi epi) const { run(in, epi, [](int) {}); }
 };
 
 // What the phases read besides activations and weights -- biases, gates, modulation, rotary table -- is requested with the
@@ -80,24 +101,23 @@ struct BlockVec {
 // out = LN(in) * (1 + scale) + shift for rows 4 * wave + lane / 16; shift, scale: of that row
 template <int D>
 struct SlimNorm {
-    static constexpr int V = D / 16;
-    float h[V], k[V];
-    __device__ __forceinline__ void request(const float* shift, const float* scale) {
-        const int l16 = threadIdx.x & 15;
-#pragma unroll
-        for (int i = 0; i < V; ++i) { h[i] = shift[l16 + 16 * i]; k[i] = scale[l16 + 16 * i]; }
-    }
+    static constexpr int V = D / 16;                     // adjacent values of a lane
+    typedef __attribute__((ext_vector_type(V))) float vec;
+    vec h, k;
+    static __device__ __forceinline__ vec at(const float* p) { return *reinterpret_cast<const vec*>(p + (threadIdx.x & 15) * V); }
+    __device__ __forceinline__ void request(const float* shift, const float* scale) { h = at(shift); k = at(scale); }
     __device__ __forceinline__ void run(const float* in, float* out, float eps) const {
-        const int l16 = threadIdx.x & 15;
-        float v[V], s = 0.f, q = 0.f;
+        vec v = at(in), o;
+        float s = 0.f, q = 0.f;
 #pragma unroll
-        for (int i = 0; i < V; ++i) { v[i] = in[l16 + 16 * i]; s += v[i]; }
+        for (int i = 0; i < V; ++i) s += v[i];
         const float mean = sum_of_16(s) / (float)D;
 #pragma unroll
         for (int i = 0; i < V; ++i) q += (v[i] - mean) * (v[i] - mean);
         const float rstd = 1.0f / sqrtf(sum_of_16(q) / (float)D + eps);
 #pragma unroll
-        for (int i = 0; i < V; ++i) out[l16 + 16 * i] = (v[i] - mean) * rstd * (1.f + k[i]) + h[i];
+        for (int i = 0; i < V; ++i) o[i] = (v[i] - mean) * rstd * (1.f + k[i]) + h[i];
+        *reinterpret_cast<vec*>(out + (threadIdx.x & 15) * V) = o;
     }
 };
 
@@ -177,20 +197,55 @@ __global__ void __launch_bounds__(256, 1) slim_begin_kernel(SlimArgs g, SlimLaye
 }
 
 // One layer from its attention on; `next`: the following layer's q, k, v, or after the last layer the final projection.
+// A wave's code runs once, on one wave per SIMD: every instruction counts, and so does every line of it that comes from L2.
+// So the first keys and values are requested first of all and everything else in their shadow, divisions of positions
+// included, and exponentials and GELU are the hardware's with their arguments in powers of two (an exponential of the math
+// library is 13 instructions, its tanh 35).  What a compute unit accepts of loads, 112 to 196 KB of weights per layer, is the other
+// bound: they are issued between products, not ahead of them.  Cycles of a layer of 64 on 128 tokens, one after the other / the
+// requests in attention's shadow / and between products: 34700 / 29800 / 26000, the last layer 42500 / 25300 / 23400; 8 steps
+// of 2 such layers 352 / 301 / 285 us, with W_1 behind the attention and LayerNorm's vectors in one load each 272.  (Slower: values
+// stored [column][token] for 16-byte loads, 287; W_1 between W_o's products, 278.)
 template <int D, int HD, bool LAST>
 __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLayer w, SlimLayer next) {
     constexpr int LD = D + 4, F = 4 * D, LF = F + 4, NB = HD / 16, HEADS = D / HD;
+    static_assert(HEADS <= 4, "a wave per head");
     __shared__ __attribute__((aligned(16))) float xt[ROWS * LD], ht[ROWS * LD], ut[ROWS * LF];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kgrp = lane >> 4;
     const int n0 = blockIdx.x * ROWS, b = blockIdx.y, N = g.tokens, L = g.text_tokens;
-    const int n = n0 + l16;
+    const int n = n0 + l16, row = b * N + min(n, N - 1);
+    // attention: a wave per head, its 16 queries in lane % 16.  S^T = K Q^T leaves keys 4 * (lane / 16) + i of every 16-key
+    // block, the layout the second operand of O^T = V^T P^T wants: the probabilities stay in their registers, in fp32.
+    const int head = min(wave, HEADS - 1);
+    const float* base = g.qkv + (long)b * N * 3 * D + head * HD;
+    f32x4_t qf[NB];
+#pragma unroll
+    for (int d = 0; d < NB; ++d) qf[d] = quad(base + (row - b * N) * 3 * D + d * 16 + kgrp * 4);
+    f32x4_t kn[4][NB];                                   // the next 64 keys (past the end: the last one again, masked)
+    float vn[4][4][NB];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int d = 0; d < NB; ++d) {
+                kn[t][d] = quad(base + min(k0 + t * 16 + l16, N - 1) * 3 * D + D + d * 16 + kgrp * 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    vn[t][e][d] = base[min(k0 + t * 16 + kgrp * 4 + e, N - 1) * 3 * D + 2 * D + d * 16 + l16];
+            }
+    };
+    fetch(0);
+    __builtin_amdgcn_sched_barrier(0);
+
     const float* mod = g.mod + b * g.mod_bs + (long)g.layer * 12 * D;
     const float* gates = mod + (n < L ? 6 * D : 0);      // of this lane's row
     Project<D / 16, (D / 16 + 3) / 4> po;
     po.request(w.W_o, wave, D / 16);
-    for (int e = threadIdx.x; e < ROWS * (D / 4); e += 256) {
-        const int r = e / (D / 4), c = e % (D / 4) * 4;
-        *reinterpret_cast<f32x4_t*>(xt + r * LD + c) = quad(g.X + ((long)b * N + min(n0 + r, N - 1)) * D + c);
+    constexpr int XV = ROWS * (D / 4) / 256 > 0 ? ROWS * (D / 4) / 256 : 1;
+    f32x4_t x_in[XV];
+#pragma unroll
+    for (int i = 0; i < XV; ++i) {
+        const int e = min((int)threadIdx.x + 256 * i, ROWS * (D / 4) - 1);
+        x_in[i] = quad(g.X + ((long)b * N + min(n0 + e / (D / 4), N - 1)) * D + e % (D / 4) * 4);
     }
     constexpr int NO = (D / 16 + 3) / 4;
     const int nr = wave * 4 + kgrp;                      // this lane's row in the LayerNorms
@@ -202,87 +257,6 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
         const float* m = mod + (n0 + nr < L ? 6 * D : 0);
         mid.request(m + 3 * D, m + 4 * D);
     }
-    // attention: a wave per head, its 16 queries in lane % 16.  S^T = K Q^T leaves keys 4 * (lane / 16) + i of every 16-key
-    // block, the layout the second operand of O^T = V^T P^T wants: the probabilities stay in their registers, in fp32.
-    const float* base = g.qkv + (long)b * N * 3 * D;
-    for (int h = wave; h < HEADS; h += 4) {
-        f32x4_t qf[NB], acc[NB];
-#pragma unroll
-        for (int d = 0; d < NB; ++d) {
-            qf[d] = quad(base + (long)min(n, N - 1) * 3 * D + h * HD + d * 16 + kgrp * 4) * g.scale;
-            acc[d] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        }
-        f32x4_t kn[4][NB];                               // the next 64 keys; values past the end are zero
-        float vn[4][4][NB];
-        auto fetch = [&](int k0) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int d = 0; d < NB; ++d) {
-                    kn[t][d] = quad(base + (long)min(k0 + t * 16 + l16, N - 1) * 3 * D + D + h * HD + d * 16 + kgrp * 4);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int key = k0 + t * 16 + kgrp * 4 + e;
-                        const float u = base[(long)min(key, N - 1) * 3 * D + 2 * D + h * HD + d * 16 + l16];
-                        vn[t][e][d] = key < N ? u : 0.f;
-                    }
-                }
-        };
-        float m = -INFINITY, l = 0.f;                    // l: over this lane's keys only
-        fetch(0);
-        for (int k0 = 0; k0 < N; k0 += 64) {
-            f32x4_t kf[4][NB], sc[4];
-            float vf[4][4][NB];
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int d = 0; d < NB; ++d) {
-                    kf[t][d] = kn[t][d];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) vf[t][e][d] = vn[t][e][d];
-                }
-            if (k0 + 64 < N) fetch(k0 + 64);
-            float tmax = -INFINITY;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                sc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int d = 0; d < NB; ++d)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) sc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][d][e], qf[d][e], sc[t], 0, 0, 0);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (k0 + t * 16 + kgrp * 4 + i >= N) sc[t][i] = -INFINITY;
-                    tmax = fmaxf(tmax, sc[t][i]);
-                }
-            }
-            tmax = max_xor32(max_xor16(tmax));
-            const float mn = fmaxf(m, tmax), alpha = expf(m - mn);   // exp(-inf) = 0 on the first keys
-            m = mn;
-            l *= alpha;
-#pragma unroll
-            for (int d = 0; d < NB; ++d) acc[d] *= alpha;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                if (k0 + t * 16 >= N) continue;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    sc[t][i] = expf(sc[t][i] - mn);      // masked keys: exp(-inf) = 0
-                    l += sc[t][i];
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int d = 0; d < NB; ++d) acc[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][e][d], sc[t][e], acc[d], 0, 0, 0);
-            }
-        }
-        l = sum_xor32(sum_xor16(l));
-        const float inv = 1.0f / l;
-#pragma unroll
-        for (int d = 0; d < NB; ++d) *reinterpret_cast<f32x4_t*>(ht + l16 * LD + h * HD + d * 16 + kgrp * 4) = acc[d] * inv;
-    }
-    Project<D / 16, D / 16> p1;
-    p1.request(w.W_1, wave, F / 16);
     BlockVec<D / 16> b_1;
     b_1.request(w.b_1, wave, F / 16);
     BlockVec<NO> b_2, gate_m;
@@ -296,7 +270,92 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
     const int P = g.pg.C * g.pg.patch * g.pg.patch;
     BlockVec<1> b_out;
     SlimQkv<D> out;
-    if constexpr (LAST) b_out.request(g.b_out, wave, P / 16); else out.request(g, next, wave, b, n);
+    int at[4];                                           // where this lane's four values of a patch lie in the latent
+    if constexpr (LAST) {
+        b_out.request(g.b_out, wave, P / 16);
+        const PatchGeom& pg = g.pg;
+        const int Hp = pg.H / pg.patch, Wp = pg.W / pg.patch, ps2 = pg.patch * pg.patch, nv = max(min(n, N - 1) - L, 0);
+        const int q1 = nv / Wp, pj = nv - q1 * Wp, f = q1 / Hp, pi = q1 - f * Hp;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int q = wave * 16 + kgrp * 4 + c, ch = q / ps2, in = q - ch * ps2, dy = in / pg.patch, dx = in - dy * pg.patch;
+            at[c] = (((b * pg.C + ch) * pg.F + f) * pg.H + pi * pg.patch + dy) * pg.W + pj * pg.patch + dx;
+        }
+    } else {
+        out.request(g, next, wave, b, n);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    if (wave < HEADS) {
+        f32x4_t acc[NB];
+        constexpr float LOG2E = 1.4426950408889634f;
+#pragma unroll
+        for (int d = 0; d < NB; ++d) { qf[d] *= g.scale; acc[d] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+        float m = -INFINITY, l = 0.f;                    // m: in powers of two; l: over this lane's keys only
+        for (int k0 = 0; k0 < N; k0 += 64) {
+            f32x4_t kf[4][NB], sc[4];
+            float vf[4][4][NB];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int d = 0; d < NB; ++d) {
+                    kf[t][d] = kn[t][d];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) vf[t][e][d] = vn[t][e][d];
+                }
+            if (k0 + 64 < N) fetch(k0 + 64);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) sc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int d = 0; d < NB; ++d)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][d][e], qf[d][e], sc[t], 0, 0, 0);
+            if (k0 + 64 > N) {                           // keys past the end: no weight, and values that can't reach the sums
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (k0 + t * 16 + kgrp * 4 + i >= N) {
+                            sc[t][i] = -INFINITY;
+#pragma unroll
+                            for (int d = 0; d < NB; ++d) vf[t][i][d] = 0.f;
+                        }
+            }
+            float tmax = -INFINITY;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) tmax = fmaxf(tmax, fmaxf(fmaxf(sc[t][0], sc[t][1]), fmaxf(sc[t][2], sc[t][3])));
+            tmax = max_xor32(max_xor16(tmax));
+            const float mn = fmaxf(m, tmax * LOG2E), alpha = __builtin_amdgcn_exp2f(m - mn);   // 0 on the first keys
+            m = mn;
+            l *= alpha;
+#pragma unroll
+            for (int d = 0; d < NB; ++d) acc[d] *= alpha;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    sc[t][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[t][i], LOG2E, -mn));   // masked keys: 0
+                    l += sc[t][i];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int d = 0; d < NB; ++d) acc[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][e][d], sc[t][e], acc[d], 0, 0, 0);
+            }
+        }
+        l = sum_xor32(sum_xor16(l));
+#pragma unroll
+        for (int d = 0; d < NB; ++d) *reinterpret_cast<f32x4_t*>(ht + l16 * LD + head * HD + d * 16 + kgrp * 4) = acc[d] / l;
+    }
+    Project<D / 16, D / 16> p1;
+    p1.request(w.W_1, wave, F / 16);
+#pragma unroll
+    for (int i = 0; i < XV; ++i) {
+        const int e = threadIdx.x + 256 * i;
+        if (e < ROWS * (D / 4)) *reinterpret_cast<f32x4_t*>(xt + e / (D / 4) * LD + e % (D / 4) * 4) = x_in[i];
+    }
     __syncthreads();
     auto residual = [&](const BlockVec<NO>& bias, const BlockVec<NO>& gate) {
         return [=](int j, int col, f32x4_t x) {
@@ -309,27 +368,32 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
     mid.run(xt + nr * LD, ht + nr * LD, g.eps);
     __syncthreads();
     Project<F / 16, NO> p2;
-    p2.request(w.W_2, wave, D / 16);
+    p2.prepare(w.W_2, wave, D / 16);
+    Project<D / 16, LAST ? 1 : (3 * D / 16 + 3) / 4> pn;
+    pn.prepare(LAST ? g.W_out : next.W_qkv, wave, LAST ? P / 16 : 3 * D / 16);
     p1.run(ht + l16 * LD, [&](int j, int col, f32x4_t x) {
         x += b_1.v[j];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) x[c] = gelu_tanh_f(x[c]);
+        for (int c = 0; c < 4; ++c) x[c] = gelu_of(x[c], 0.f);
         *reinterpret_cast<f32x4_t*>(ut + l16 * LF + col) = x;
+    }, [&](int s) {
+        p2.request_step(s, p1.STEPS);
+        __builtin_amdgcn_sched_barrier(0);
     });
     __syncthreads();
-    p2.run(ut + l16 * LF, residual(b_2, gate_m));
-    Project<D / 16, LAST ? 1 : (3 * D / 16 + 3) / 4> pn;
-    pn.request(LAST ? g.W_out : next.W_qkv, wave, LAST ? P / 16 : 3 * D / 16);
+    p2.run(ut + l16 * LF, residual(b_2, gate_m), [&](int s) {
+        pn.request_step(s, p2.STEPS);
+        __builtin_amdgcn_sched_barrier(0);
+    });
     __syncthreads();
     if constexpr (LAST) {
         end.run(xt + nr * LD, ht + nr * LD, g.eps);
         __syncthreads();
-        Epilogue ep{};
-        ep.kind = EPI_UNPATCHIFY; ep.bias = g.b_out; ep.resid = g.eps_out; ep.geom = TokenGeom{N, L}; ep.pg = g.pg;
-        const int row = b * N + min(n, N - 1);
-        const EpiRow r = epilogue_row<EPI_UNPATCHIFY>(ep, row);
         pn.run(ht + l16 * LD, [&](int j, int col, f32x4_t x) {
-            if (n < N) epilogue_quad<EPI_UNPATCHIFY, float>(ep, nullptr, P, r, row, col, x, b_out.v[j], epilogue_operands<EPI_UNPATCHIFY>(ep, P, r, row, col));
+            x += b_out.v[j];
+            if (n < N && n >= L)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) g.eps_out[at[c]] = x[c];
         });
     } else {
         for (int e = threadIdx.x; e < ROWS * (D / 4); e += 256) {
