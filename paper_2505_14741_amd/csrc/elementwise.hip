@@ -417,7 +417,8 @@ patch_embed_kernel(const float* __restrict__ x, const T* __restrict__ ctx, const
 // patches of 64 tokens in registers and walks its columns, 32 at a time (whole lines of X), whose weights come straight from
 // global memory in operand layout; writing X is the bound.
 // (One workgroup per 64 x 64 outputs gathered the pixels once per 64 columns, in fp32 products: 13.4 us at 112 tokens x 1920,
-// 31 at 4516, 100 at 17776; this takes 7.4, 20 and 58.)
+// 31 at 4516, 100 at 17776; this took 7.4, 20 and 58.  Pixels requested without branches, the first weights and the biases with
+// them and not when they have arrived: 8.8 -> 8.0, 20.0 -> 18.4, 58 -> 52.)
 __global__ void __launch_bounds__(256)
 patch_embed64_kernel(const float* __restrict__ x, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ W_pe,
                      const float* __restrict__ b_pe, float* __restrict__ X, int C, int F, int H, int Wd, int patch,
@@ -439,28 +440,11 @@ patch_embed64_kernel(const float* __restrict__ x, const bf16_t* __restrict__ ctx
         }
         if (n0 + TILE <= text_tokens) return;            // (whole workgroup)
     }
-    {
-        const int n = n0 + lane, nv = n - text_tokens;   // lane = token while staging: neighbours read adjacent pixels
-        const bool video = n < N && nv >= 0;
-        const int j = nv % Wp, i = (nv / Wp) % Hp, f = nv / (Wp * Hp);
-        const float* xp = x + (((long)b * C * F + f) * H + (long)i * patch) * Wd + (long)j * patch;
-        // where patch value `lane` lies, one division per lane; read from that lane below
-        const int lc = lane / (patch * patch), lr = lane - lc * patch * patch, ly = lr / patch;
-        const int in_plane = ly * Wd + (lr - ly * patch);
-        float pv[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {                   // patch value wave + 4u of every token (uniform per wave)
-            const int c = __builtin_amdgcn_readlane(lc, wave + 4 * u);
-            const int at = __builtin_amdgcn_readlane(in_plane, wave + 4 * u);
-            pv[u] = video && wave + 4 * u < P ? xp[(long)c * F * H * Wd + at] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 16; ++u) pt[lane * LD + wave + 4 * u] = pv[u];
-    }
     // lane l of step s: k = 16 * (l / 16) + 8s .. + 7, of a token in one operand and of a column in the other
-    auto weights = [&](int col0, b8 (&w)[2][2]) {
+    auto weights = [&](int col0, b8 (&w)[2][2], f4 (&bias)[2]) {
 #pragma unroll
         for (int y = 0; y < 2; ++y) {
+            bias[y] = *reinterpret_cast<const f4*>(b_pe + min(col0 + y * 16 + kgrp * 4, D - 4));
             const bf16_t* wp = W_pe + (long)min(col0 + y * 16 + l16, D - 1) * P + kgrp * 16;
             if (P == 64) {
 #pragma unroll
@@ -472,8 +456,28 @@ patch_embed64_kernel(const float* __restrict__ x, const bf16_t* __restrict__ ctx
         }
     };
     b8 w[2][2], wn[2][2];
+    f4 bias[2], bias_n[2];
     int c0 = d0 + wave * 32;
-    if (c0 < d1) weights(c0, w);
+    {
+        const int n = n0 + lane, nv = n - text_tokens;   // lane = token while staging: neighbours read adjacent pixels
+        const bool video = n < N && nv >= 0;
+        const int at_video = max(min(nv, N - 1 - text_tokens), 0);   // (of the other lanes: read, not used)
+        const int j = at_video % Wp, i = (at_video / Wp) % Hp, f = at_video / (Wp * Hp);
+        const float* xp = x + (((long)b * C * F + f) * H + (long)i * patch) * Wd + (long)j * patch;
+        // where patch value `lane` lies, one division per lane; read from that lane below
+        const int lv = min(lane, P - 1), lc = lv / (patch * patch), lr = lv - lc * patch * patch, ly = lr / patch;
+        const int in_plane = ly * Wd + (lr - ly * patch);
+        float pv[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {                   // patch value wave + 4u of every token (uniform per wave)
+            const int c = __builtin_amdgcn_readlane(lc, wave + 4 * u);
+            const int at = __builtin_amdgcn_readlane(in_plane, wave + 4 * u);
+            pv[u] = xp[(long)c * F * H * Wd + at];
+        }
+        weights(min(c0, D - 1), w, bias);                // behind the pixels, not behind their arrival
+#pragma unroll
+        for (int u = 0; u < 16; ++u) pt[lane * LD + wave + 4 * u] = video && wave + 4 * u < P ? pv[u] : 0.f;
+    }
     __syncthreads();
     b8 p[4][2][3];                                       // [16 tokens][step][part]
 #pragma unroll
@@ -489,7 +493,7 @@ patch_embed64_kernel(const float* __restrict__ x, const bf16_t* __restrict__ ctx
                 p[t][s][0][e] = (__bf16)hi; p[t][s][1][e] = (__bf16)mid; p[t][s][2][e] = (__bf16)(rest - mid);
             }
     for (; c0 < d1; c0 += 128) {
-        if (c0 + 128 < d1) weights(c0 + 128, wn);
+        if (c0 + 128 < d1) weights(c0 + 128, wn, bias_n);
         f4 acc[4][2];
 #pragma unroll
         for (int t = 0; t < 4; ++t)
@@ -511,13 +515,15 @@ patch_embed64_kernel(const float* __restrict__ x, const bf16_t* __restrict__ ctx
 #pragma unroll
             for (int y = 0; y < 2; ++y) {
                 const int col = c0 + y * 16 + kgrp * 4;  // D % 4 == 0: inside or outside together
-                if (col < d1) *reinterpret_cast<f4*>(X + ((long)b * N + n) * D + col) = acc[t][y] + *reinterpret_cast<const f4*>(b_pe + col);
+                if (col < d1) *reinterpret_cast<f4*>(X + ((long)b * N + n) * D + col) = acc[t][y] + bias[y];
             }
         }
 #pragma unroll
-        for (int y = 0; y < 2; ++y)
+        for (int y = 0; y < 2; ++y) {
+            bias[y] = bias_n[y];
 #pragma unroll
             for (int s = 0; s < 2; ++s) w[y][s] = wn[y][s];
+        }
     }
 }
 
