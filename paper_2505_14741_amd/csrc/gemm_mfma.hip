@@ -365,11 +365,12 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
         for (int y = 0; y < FB; ++y) fb[0][y] = *reinterpret_cast<const bf16x8_t*>(lds + boff[y] + slot);
     }
     int slot_d = 0;                                      // deep ring's slot of stage kt
-    // One stage.  LEFT: stages after it, DEEP or more: any number, which is the steady state and has no branch inside (with the
+    // One stage.  LEFT: stages after it, STEADY or more: any number, which is the steady state and has no branch inside (with the
     // waits and loads behind run-time conditions and a 64-bit vector address per load, us at 17776 rows: 5760 x 1920 329 ->
     // 316, 7680 x 1920 449 -> 436, 1920 x 7680 467 -> 441, 1920 x 1920 126 -> 117; at 4516 rows 92.5 -> 90.4, 127.7 -> 123.6,
     // 117.9 -> 110.7, 37.9 -> 34.4).  No stage follows the last one: no hand-over there, and no loads for stages past the end
     // (the fragment reads of the last step then fetch stale, unused data from the other slot).
+    constexpr int STEADY = steady_form(DEEP, PRE);
     auto stage = [&](int kt, auto left_c) {
         constexpr int LEFT = decltype(left_c)::value;
         const int s2 = kt & 1, sd = JOINT ? s2 : slot_d, nd = JOINT ? s2 ^ 1 : sd + 1 == DEEP ? 0 : sd + 1;
@@ -397,10 +398,10 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
                         for (int i = 0; i < GPW; ++i) { const int g = i < GB ? GA + i : i - GB; issue_one(kt + NSA, sa, g); }
                     }
                 }
-                if constexpr (PRE && (LEFT == 1 || LEFT == 2)) {
+                if constexpr (constexpr int STRIP = strip_of_form(LEFT); PRE && STRIP >= 0) {
                     if (have_pre) {
 #pragma unroll
-                        for (int k = 0; k < 8; ++k) pre[LEFT == 2 ? 0 : 1][k] = resid_fetch(ep, M, Nn, m0 + wm * WM, n0 + wn * WN, lane, LEFT == 2 ? 0 : 1, k);
+                        for (int k = 0; k < 8; ++k) pre[STRIP][k] = resid_fetch(ep, M, Nn, m0 + wm * WM, n0 + wn * WN, lane, STRIP, k);
                     }
                 }
                 from_a = na * STEP_A; from_w = nw * STEP_W;
@@ -451,8 +452,8 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
         }
     };
     int kt = 0;
-    for (; kt + DEEP < nkt; ++kt) stage(kt, std::integral_constant<int, DEEP>{});
-    if (DEEP > 2 && kt + 2 < nkt) stage(kt++, std::integral_constant<int, 2>{});
+    for (; kt + STEADY < nkt; ++kt) stage(kt, std::integral_constant<int, STEADY>{});
+    if (STEADY > 2 && kt + 2 < nkt) stage(kt++, std::integral_constant<int, 2>{});
     if (kt + 1 < nkt) stage(kt++, std::integral_constant<int, 1>{});
     stage(kt, std::integral_constant<int, 0>{});
     wait_vmcnt<0>();                                     // the look-ahead loads past the end have landed

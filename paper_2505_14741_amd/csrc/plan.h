@@ -184,6 +184,14 @@ constexpr GemmPlan gemm_plan(int tokens, int Nn, int K, bool allow_split, int fo
     return p;
 }
 
+// The stages of a tile of gemm_mfma.hip are compiled in forms, one per number of stages that are left behind them; the largest
+// form is the steady state and serves every larger number.  strips: the tile requests its residual ahead, strip 0 with two
+// stages left and strip 1 with one, so the form of two must be the third-last stage alone.  (With rings of two stages and the
+// form of two as the steady state, strip 0 was read again in every stage, as many bytes as both operands.  1920 x 1920 gated on
+// 128 x 128 tiles inside the network, us, so / now: 3400 tokens 53.3 / 36.4, 8400 102 / 72.6, 17000 211 / 147, 33976 424 / 297.)
+constexpr int steady_form(int deep, bool strips) { return strips && deep < 3 ? 3 : deep; }
+constexpr int strip_of_form(int form) { return form == 2 ? 0 : form == 1 ? 1 : -1; }
+
 // Longest operand row the tile kernels take: a load's offset inside a tile's rows (256 at most) is 32 bits.
 constexpr long TILE_MAX_ROW_BYTES = 1L << 23;
 

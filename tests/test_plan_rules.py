@@ -29,6 +29,8 @@ extern "C" void wide(int tokens, int n, int k, int* out) {
 }
 extern "C" int narrow(long bh, int seq) { return ps::attn_narrow_items(bh, seq, 256); }
 extern "C" int route(int batch, int seq, int heads, int path) { return ps::attention_route(batch, seq, heads, path, 256); }
+extern "C" int steady(int deep, int strips) { return ps::steady_form(deep, strips != 0); }
+extern "C" int strip(int form) { return ps::strip_of_form(form); }
 extern "C" int kinds(int* few) { *few = ps::FEW_TILE_KINDS; return ps::TILE_KINDS; }
 extern "C" long scratch(int bf16, int tokens, int n, int k, int batch) {
     return (long)ps::few_workspace_bytes(bf16 != 0, ps::few_plan(bf16 != 0, tokens, n, k, 0), batch, tokens, n, k);
@@ -206,3 +208,14 @@ def test_sizes_of_the_attention_tests_take_the_kernels_they_name(rules):
         for keys in (1, 64, 300, 512, 513, 2000, 17776):
             small = heads * -(-keys // 256) < 512
             assert all((rules.route(b, keys, heads, 0) < FLAGS) == small for b in (1, 2, 16, 1024))
+
+
+@pytest.mark.parametrize("deep", [2, 3])
+def test_a_tile_requests_each_strip_of_its_residual_once(rules, deep):
+    """Stage by stage as the tile's loop takes its forms: the steady one while more stages are left than its number, then the
+    written-out ones.  Strip 0 in the third-last stage, strip 1 in the second-last, nothing in any other."""
+    assert rules.steady(deep, 0) == deep
+    steady = rules.steady(deep, 1)
+    for stages in (3, 4, 5, 30, 120):
+        strips = [rules.strip(min(left, steady)) for left in reversed(range(stages))]
+        assert strips == [-1] * (stages - 3) + [0, 1, -1]
