@@ -4,14 +4,15 @@
 
 namespace ps {
 
-// GELU where the result stays fp32: x over 1 + 2^t, the quotient refined once (fourteen instructions; with the math library's
-// tanh, whose two branches a wave both takes, 35).  t: such that the sum stays finite (beyond, the result is 0 in fp32) and
-// that the quotient of an infinite x is not refined.
+// GELU where the result stays fp32: x over 1 + 2^t, the quotient refined once (sixteen instructions; with the math library's
+// tanh, whose two branches a wave both takes, 35).  Where the sum would not be finite (from x = -10 down) the result is a zero,
+// NaN for -infinity, as with the tanh; where it is 1 in fp32 the quotient of an infinite x must not be refined.
 __device__ __forceinline__ float gelu_of(float x, float) {
     constexpr float c0 = -2.0f * 0.7978845608028654f * 1.4426950408889634f, c1 = c0 * 0.044715f;
-    const float t = fminf(x * __builtin_fmaf(c1 * x, x, c0), 126.0f);
+    const float t = x * __builtin_fmaf(c1 * x, x, c0);
     const float d = 1.0f + __builtin_amdgcn_exp2f(t), r = __builtin_amdgcn_rcpf(d), y = x * r;
-    return t < -64.0f ? x : __builtin_fmaf(__builtin_fmaf(-d, y, x), r, y);
+    const float g = __builtin_fmaf(__builtin_fmaf(-d, y, x), r, y);
+    return t < -64.0f ? x : t > 126.0f ? x * 0.0f : g;
 }
 __device__ __forceinline__ float gelu_of(float x, bf16_t) { return gelu_fast(x); }
 

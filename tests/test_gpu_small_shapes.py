@@ -438,3 +438,28 @@ def test_fp32_gelu_over_its_range(rows):
     m = torch.isfinite(ref)
     bound = 8 * 2.0 ** -24 * torch.maximum(ref.abs(), x.abs().clamp(max=14) / 8)[m] + 1e-36
     assert ((out[:, m] - ref[m]).abs() <= bound).all()
+
+
+def gelu64(x):
+    """tanh-form GELU in float64 as x / (1 + exp(-2u)), which does not cancel in the negative tail."""
+    return x / (1 + np.exp(np.minimum(-2 * math.sqrt(2 / math.pi) * (x + 0.044715 * x ** 3), 700)))
+
+
+def gelu_alone(values, rows=1):
+    """The fp32 GELU epilogue on `values`: zero product, the value in the bias."""
+    bias = torch.tensor(values, dtype=torch.float32, device=DEV)
+    return B.dit_linear(torch.zeros(rows, 64, device=DEV), torch.zeros(len(values), 64, device=DEV), bias, act=1).cpu().double().numpy()
+
+
+@pytest.mark.parametrize("rows", [1, 64])
+def test_fp32_gelu_of_large_negative_arguments(rows):
+    """Zero, not a fraction of the argument; and down to where it vanishes as good as its exponent: t = -2u log2(e) is rounded
+    two or three times, 2^-24 * |t| of the result each at most, everything else a few roundings more."""
+    far = [-11.0, -1e2, -1e4, -3e18, -1e19, -1e31, -1e38, -np.finfo(np.float32).max]
+    out = gelu_alone(np.concatenate([far, [0.0] * 4]), rows)
+    assert (out == 0).all(), out[0]
+    x = np.linspace(-10, -0.5, 764).astype(np.float32).astype(np.float64)
+    t = 2 * math.sqrt(2 / math.pi) * np.abs(x + 0.044715 * x ** 3) / math.log(2)
+    out, ref = gelu_alone(x, rows), gelu64(x)
+    assert (np.abs(out - ref) <= 2.0 ** -24 * (4 + 3 * t) * np.abs(ref) + 1e-37).all()
+    assert np.isnan(gelu_alone([-np.inf, np.nan, 0, 0])[0, :2]).all()
