@@ -4,14 +4,17 @@
 
 namespace ps {
 
-// GELU where the result stays fp32: x over 1 + 2^t, the quotient refined once (sixteen instructions; with the math library's
-// tanh, whose two branches a wave both takes, 35).  Where the sum would not be finite (from x = -10 down) the result is a zero,
+// GELU where the result stays fp32: x over 1 + 2^t, the quotient refined once, for the sum as it is before its rounding (19
+// instructions; with the math library's tanh, whose two branches a wave both takes, 35).  The rounding of the sum counts in full
+// where 2^t is small, i.e. for x > 0: left in, the error against 64 bits over N(0, 1) is 4.21e-8 of the result's norm, carried
+// 2.72e-8, with the tanh form 3.75e-8.  Where the sum would not be finite (from x = -10 down) the result is a zero,
 // NaN for -infinity, as with the tanh; where it is 1 in fp32 the quotient of an infinite x must not be refined.
 __device__ __forceinline__ float gelu_of(float x, float) {
     constexpr float c0 = -2.0f * 0.7978845608028654f * 1.4426950408889634f, c1 = c0 * 0.044715f;
     const float t = x * __builtin_fmaf(c1 * x, x, c0);
-    const float d = 1.0f + __builtin_amdgcn_exp2f(t), r = __builtin_amdgcn_rcpf(d), y = x * r;
-    const float g = __builtin_fmaf(__builtin_fmaf(-d, y, x), r, y);
+    const float e = __builtin_amdgcn_exp2f(t), d = 1.0f + e, lost = e - (d - 1.0f);
+    const float r = __builtin_amdgcn_rcpf(d), y = x * r;
+    const float g = __builtin_fmaf(__builtin_fmaf(-lost, y, __builtin_fmaf(-d, y, x)), r, y);
     return t < -64.0f ? x : t > 126.0f ? x * 0.0f : g;
 }
 __device__ __forceinline__ float gelu_of(float x, bf16_t) { return gelu_fast(x); }

@@ -463,3 +463,14 @@ def test_fp32_gelu_of_large_negative_arguments(rows):
     out, ref = gelu_alone(x, rows), gelu64(x)
     assert (np.abs(out - ref) <= 2.0 ** -24 * (4 + 3 * t) * np.abs(ref) + 1e-37).all()
     assert np.isnan(gelu_alone([-np.inf, np.nan, 0, 0])[0, :2]).all()
+
+
+def test_fp32_gelu_is_as_good_as_the_tanh_form():
+    """Error against float64 over N(0, 1) and wider.  0.5 x (1 + tanh(u)) in fp32 with a correctly rounded tanh has 3.80e-8 of the
+    result's norm at one standard deviation, 4.05e-8 at a quarter and 2.80e-8 at three."""
+    rng = np.random.default_rng(5)
+    for scale, bound in ((1.0, 3.80e-8), (0.25, 4.05e-8), (3.0, 2.80e-8)):
+        x = (scale * rng.standard_normal(200000)).astype(np.float32).astype(np.float64)
+        err = rel(gelu64(x), gelu_alone(x)[0])
+        print(scale, err, flush=True)
+        assert err <= bound, (scale, err)
