@@ -103,9 +103,11 @@ static hipError_t launch_generic_attn(const T* q, const T* k, const T* v, T* o, 
 // A workgroup takes 64 queries of a head (16 per wave) and walks the keys 64 at a time, K and V widened to fp32 in LDS,
 // the next tile's global loads in flight meanwhile.  S^T = K Q^T leaves a query in lane % 16 with keys 4 * (lane / 16) + i
 // of every 16-key block, which is the layout the second operand of O^T = V^T P^T wants: the probabilities stay in their
-// registers, in fp32.  Full fp32 products, sums and expf throughout.  The matrix instructions bind (128 of them, 32
-// cycles each, per wave and tile; LDS reads take a quarter of that).  One thread per query took 130 us at 112 tokens x 30
-// heads, 1104 at 1024 tokens and 9.7 us at 32 tokens x 4 heads of 16; this takes 10.2, 107 (75 TFLOP/s) and 3.5.
+// registers, in fp32.  Full fp32 products and sums throughout, exponentials as exact as expf.  The matrix instructions bind (128 of
+// them, 32 cycles each, per wave and tile; LDS reads take a quarter of that).  One thread per query took 130 us at 112 tokens x
+// 30 heads, 1104 at 1024 tokens and 9.7 us at 32 tokens x 4 heads of 16; this takes 9.3, 90 (90 TFLOP/s) and 3.5.
+// 30 heads of 64, 1024 / 3000 keys, with expf throughout 102 / 785 us; with exp_near, its accumulators in other registers than
+// the rest's and two waves per SIMD 95 / 788; with room for three 90 / 680 (64 keys masked or not without a branch 90 / 689).
 typedef __attribute__((ext_vector_type(4))) float attn_f4_t;
 __device__ __forceinline__ attn_f4_t load_quad(const float* p) { return *reinterpret_cast<const attn_f4_t*>(p); }
 __device__ __forceinline__ attn_f4_t load_quad(const bf16_t* p) {
@@ -119,7 +121,7 @@ __device__ __forceinline__ void store_quad(bf16_t* p, attn_f4_t v) {
 }
 
 template <typename T, int HD>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, HD == 64 ? 3 : HD == 32 ? 4 : 6)
 attn_f32_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, T* __restrict__ o, int seq,
                 float scale, AttnStrides s) {
     constexpr int KT = 64, LD = HD + 4, NB = HD / 16;    // LD: rows 16-byte aligned, four rows 16 banks apart
@@ -149,10 +151,7 @@ attn_f32_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __res
     attn_f4_t acc[NB];                                   // O^T: lane's query, d = 16 * block + 4 * kgrp + i
 #pragma unroll
     for (int d = 0; d < NB; ++d) acc[d] = attn_f4_t{0.f, 0.f, 0.f, 0.f};
-    // Exponentials are the hardware's, of log2(e) times the score less log2(e) times the maximum, one fused operation with one
-    // rounding like the difference it replaces (an exponential of the math library is 13 instructions).
-    constexpr float LOG2E = 1.4426950408889634f;
-    float m = -INFINITY, l = 0.f;                        // m: in powers of two; l: over this lane's keys only
+    float m = -INFINITY, l = 0.f;                        // l: over this lane's keys only
     fetch(0);
     for (int k0 = 0; k0 < seq; k0 += KT) {
         __syncthreads();                                 // nobody reads the last tile any more
@@ -166,7 +165,7 @@ attn_f32_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __res
         if (k0 + KT < seq) fetch(k0 + KT);
         const int blocks = min(4, (seq - k0 + 15) / 16); // 16-key blocks with a key in them
         attn_f4_t sc[4];
-        float tmax = -INFINITY;
+        float tmax = -INFINITY, tmin = INFINITY;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             sc[g] = attn_f4_t{0.f, 0.f, 0.f, 0.f};
@@ -178,26 +177,36 @@ attn_f32_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __res
                     for (int e = 0; e < 4; ++e) sc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qf[d][e], sc[g], 0, 0, 0);
                 }
             }
+            if (k0 + (g + 1) * 16 > seq) {               // keys past the end
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (k0 + g * 16 + kgrp * 4 + i >= seq) sc[g][i] = -INFINITY;
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if (k0 + g * 16 + kgrp * 4 + i >= seq) sc[g][i] = -INFINITY;
                 tmax = fmaxf(tmax, sc[g][i]);
+                tmin = fminf(tmin, sc[g][i]);
             }
         }
         tmax = max_xor32(max_xor16(tmax));
-        const float mn = fmaxf(m, tmax * LOG2E), alpha = __builtin_amdgcn_exp2f(m - mn);   // 0 on the first tile
+        const float mn = fmaxf(m, tmax), alpha = expf(m - mn);   // exp(-inf) = 0 on the first tile
         m = mn;
         l *= alpha;
 #pragma unroll
         for (int d = 0; d < NB; ++d) acc[d] *= alpha;
+        const bool near = __ballot(tmin - mn < EXP_NEAR) == 0;       // (of the whole wave; not with masked keys)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             if (g >= blocks) continue;
+            if (near) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                sc[g][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[g][i], LOG2E, -mn));   // masked keys: 0
-                l += sc[g][i];
+                for (int i = 0; i < 4; ++i) sc[g][i] = exp_near(sc[g][i] - mn);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sc[g][i] = expf(sc[g][i] - mn);      // masked keys: exp(-inf) = 0
             }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) l += sc[g][i];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll

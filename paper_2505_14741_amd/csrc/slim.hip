@@ -199,12 +199,13 @@ __global__ void __launch_bounds__(256, 1) slim_begin_kernel(SlimArgs g, SlimLaye
 // One layer from its attention on; `next`: the following layer's q, k, v, or after the last layer the final projection.
 // A wave's code runs once, on one wave per SIMD: every instruction counts, and so does every line of it that comes from L2.
 // So the first keys and values are requested first of all and everything else in their shadow, divisions of positions
-// included, and exponentials and GELU are the hardware's with their arguments in powers of two (an exponential of the math
-// library is 13 instructions, its tanh 35).  What a compute unit accepts of loads, 112 to 196 KB of weights per layer, is the other
-// bound: they are issued between products, not ahead of them.  Cycles of a layer of 64 on 128 tokens, one after the other / the
-// requests in attention's shadow / and between products: 34700 / 29800 / 26000, the last layer 42500 / 25300 / 23400; 8 steps
-// of 2 such layers 352 / 301 / 285 us, with W_1 behind the attention and LayerNorm's vectors in one load each 272.  (Slower: values
-// stored [column][token] for 16-byte loads, 287; W_1 between W_o's products, 278.)
+// included, and exponentials and GELU take six and 19 instructions (in the math library an exponential is 13, a tanh 35).  What a
+// compute unit accepts of loads, 112 to 196 KB of weights per layer, is the other bound: they are issued between products, not
+// ahead of them.  Cycles of a layer of 64 on 128 tokens, one after the other / the requests in attention's shadow / and between
+// products: 34700 / 29800 / 26000, the last layer 42500 / 25300 / 23400; 8 steps of 2 such layers 352 / 301 / 285 us, with W_1
+// behind the attention and LayerNorm's vectors in one load each 272.  Of this, exponentials and GELU had lost digits; as exact
+// as the math library's 282, with its expf 287.  (Slower: values stored [column][token] for 16-byte loads, 285 -> 287; W_1
+// between W_o's products, 270 -> 278.)
 template <int D, int HD, bool LAST>
 __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLayer w, SlimLayer next) {
     constexpr int LD = D + 4, F = 4 * D, LF = F + 4, NB = HD / 16, HEADS = D / HD;
@@ -288,10 +289,9 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
 
     if (wave < HEADS) {
         f32x4_t acc[NB];
-        constexpr float LOG2E = 1.4426950408889634f;
 #pragma unroll
         for (int d = 0; d < NB; ++d) { qf[d] *= g.scale; acc[d] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
-        float m = -INFINITY, l = 0.f;                    // m: in powers of two; l: over this lane's keys only
+        float m = -INFINITY, l = 0.f;                    // l: over this lane's keys only
         for (int k0 = 0; k0 < N; k0 += 64) {
             f32x4_t kf[4][NB], sc[4];
             float vf[4][4][NB];
@@ -323,22 +323,38 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
                             for (int d = 0; d < NB; ++d) vf[t][i][d] = 0.f;
                         }
             }
-            float tmax = -INFINITY;
+            float tmax = -INFINITY, tmin = INFINITY;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) tmax = fmaxf(tmax, fmaxf(fmaxf(sc[t][0], sc[t][1]), fmaxf(sc[t][2], sc[t][3])));
+            for (int t = 0; t < 4; ++t) {
+                tmax = fmaxf(tmax, fmaxf(fmaxf(sc[t][0], sc[t][1]), fmaxf(sc[t][2], sc[t][3])));
+                tmin = fminf(tmin, fminf(fminf(sc[t][0], sc[t][1]), fminf(sc[t][2], sc[t][3])));
+            }
             tmax = max_xor32(max_xor16(tmax));
-            const float mn = fmaxf(m, tmax * LOG2E), alpha = __builtin_amdgcn_exp2f(m - mn);   // 0 on the first keys
+            const float mn = fmaxf(m, tmax), alpha = expf(m - mn);   // exp(-inf) = 0 on the first keys
             m = mn;
             l *= alpha;
 #pragma unroll
             for (int d = 0; d < NB; ++d) acc[d] *= alpha;
+            const bool near = __ballot(tmin - mn < EXP_NEAR) == 0;       // (of the whole wave; not with masked keys)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sc[t][i] -= mn;
+            if (near) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sc[t][i] = exp_near(sc[t][i]);
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sc[t][i] = expf(sc[t][i]);   // masked keys: exp(-inf) = 0
+            }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    sc[t][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[t][i], LOG2E, -mn));   // masked keys: 0
-                    l += sc[t][i];
-                }
+                for (int i = 0; i < 4; ++i) l += sc[t][i];
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
 #pragma unroll

@@ -474,3 +474,81 @@ def test_fp32_gelu_is_as_good_as_the_tanh_form():
         err = rel(gelu64(x), gelu_alone(x)[0])
         print(scale, err, flush=True)
         assert err <= bound, (scale, err)
+
+
+def as_scores(scores, head_dim):
+    """q, k [1, N, 1, d] whose scores at scale 1 are scores[j] for every query: one product that is not zero, of 2^40 and a
+    multiple of 2^-40."""
+    n = len(scores)
+    q, k = torch.zeros(1, n, 1, head_dim, device=DEV), torch.zeros(1, n, 1, head_dim, device=DEV)
+    q[..., 5] = 2.0 ** 40
+    k[0, :, 0, 5] = torch.tensor(np.asarray(scores, np.float32) * np.float32(2.0 ** -40), device=DEV)
+    return q, k
+
+
+@pytest.mark.parametrize("d", [16, 32, 64])
+@pytest.mark.parametrize("n", [9, 64, 130])
+def test_attention_fp32_of_scores_near_the_end_of_the_range(d, n):
+    """Finite scores beyond the largest number over log2(e) (2.36e38), of either sign: differences are huge or zero, so the
+    result is the value of the largest score's key, or the mean of two."""
+    rng = np.random.default_rng(n)
+    v = torch.randn(1, n, 1, d, device=DEV, generator=torch.Generator(device=DEV).manual_seed(n))
+    for top, rest in ((3e38, 2.5e38), (3e38, -3e38), (-2.9e38, -3.2e38), (2.4e38, 0.0), (-2.4e38, -3.3e38)):
+        at = rng.permutation(n)[:2]
+        for winners in (at[:1], at):
+            s = np.full(n, rest)
+            s[winners] = top
+            q, k = as_scores(s, d)
+            out = B.attn3d(q, k, v, 1.0)[0, :, 0]
+            want = v[0, winners, 0].double().mean(0).float().expand(n, d)
+            assert torch.equal(out, want), (top, rest, winners)
+
+
+@pytest.mark.parametrize("seed", [0, 1])
+def test_attention_fp32_probabilities_one_by_one(seed):
+    """Values that are the unit vectors: the result is the probabilities.  Scores whose differences are exact, down to 87 below
+    the largest, where exp(-87) is the smallest normal number.  An exponential of one unit in the last place (2^-23 of it at
+    most), 18 roundings of the key sum, one each of the products with 1 and of the division: 12 * 2^-23."""
+    rng = np.random.default_rng(seed)
+    s = -np.round(rng.uniform(0, 87, 64) * 1024) / 1024
+    s[rng.integers(64)] = 0.0
+    q, k = as_scores(s, 64)
+    out = B.attn3d(q, k, torch.eye(64, device=DEV)[None, :, None], 1.0)[0, :, 0].double().cpu().numpy()
+    e = np.exp(s)
+    ref = np.broadcast_to(e / e.sum(), out.shape)
+    assert (np.abs(out - ref) <= 12 * 2.0 ** -23 * ref).all(), np.max(np.abs(out - ref) / ref)
+
+
+@pytest.mark.parametrize("n", [64, 128, 200])
+def test_attention_fp32_keeps_probabilities_below_the_normal_range(n):
+    """Weights of 2^-127 to 2^-149 on values of 1e30, in a tile with nothing else that is far and behind others: two units of
+    2^-149, and a few roundings."""
+    for far in ([-88.0], [-88.0, -92.0, -100.0]):
+        s = np.zeros(n)
+        s[7:7 + len(far)] = far
+        q, k = as_scores(s, 64)
+        v = torch.zeros(1, n, 1, 64, device=DEV)
+        for i in range(len(far)):
+            v[0, 7 + i, 0, i] = 1e30
+        out = B.attn3d(q, k, v, 1.0)[0, :, 0, :len(far)].double().cpu().numpy() * (n - len(far))
+        ref = np.exp(np.asarray(far)) * 1e30
+        assert (np.abs(out - ref) <= 2 * 2.0 ** -149 * 1e30 + 1e-6 * ref).all(), (far, out[0], ref)
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_narrow_network_of_scores_near_the_end_of_the_range(sign):
+    """Queries and keys of the first head from their biases alone, turned by their frame: scores of 3.2e38 times the cosine of
+    the distance in frames, equal within a frame.  Against the oracle and the kernels of an operation each."""
+    cfg = I.CONFIGS["tiny_text"].with_(layers=2, frames=2, height=8, width=8, text_tokens=0)
+    W = [(name, np.array(w)) for name, w in I.make_weights(cfg, 1001, "unit")]
+    hd = cfg.head_dim
+    for name, w in W:
+        if name.startswith("b_qkv."):
+            w[0], w[cfg.hidden] = np.float32(1e19) * np.float32(hd ** 0.5), np.float32(sign * 3.2e19)
+    d = B.dit_create(cfg, B.weights_to_device(cfg, W, DEV))
+    x = I.make_latent(cfg, 1)
+    eps = B.dit_forward(d, torch.from_numpy(x).to(DEV), None, [500]).clone()
+    assert torch.isfinite(eps).all()
+    assert O.rel_mae(O.dit_forward(cfg, dict(W), x, None, [500]), eps.cpu().numpy())[2] <= 1e-5
+    B.dit_set_kernel_path(d, 1)
+    assert O.rel_mae(eps.cpu().numpy(), B.dit_forward(d, torch.from_numpy(x).to(DEV), None, [500]).cpu().numpy())[2] <= 1e-5
