@@ -45,7 +45,7 @@ gemm_few_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict_
     constexpr int NW = WR * WC, BM = WR * TM * 16, BN = WC * TN * 16;
     // load groups of 8 rows, the same number for every wave: the A rows are filled up (and not multiplied)
     constexpr int GPW = ((BM + BN) / 8 + NW - 1) / NW, AROWS = GPW * NW * 8 - BN, STAGE = (AROWS + BN) * ROWB;
-    static_assert(NST >= 2 && NST <= 4, "wait_stages counts to 3");
+    static_assert(NST >= 2 && NST <= 4, "the stages behind the steady state are written out for rings of up to 4");
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
     const int M = g.rows, pieces = INREG ? 1 : g.nsplit;
     int id = xcd_remap(blockIdx.x, gridDim.x), piece, m0, n0;
@@ -120,14 +120,19 @@ gemm_few_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict_
 
     // The bias, and on small tiles all that the epilogue reads besides the sums, is requested now, with the first stages, and
     // not when the sums are done (rows and columns past the edge: clamped, not stored).
-    constexpr bool EARLY = TM * TN <= 4;
+    // (On 192 x 192 tiles the sums of the pieces before the current one leave no room for it: 12 to 32 registers spilled.  Two
+    // layers, four samples of 1100 tokens 972 -> 964 us, eight of 545 942 -> 933.)
+    constexpr bool EARLY = TM * TN <= 4, TIGHT = INREG && TM * TN > 12;
     auto col_of = [&](int y) { return n0 + (wn * TN + y) * 16 + kgrp * 4; };
     auto row_of = [&](int x) { return m0 + (wm * TM + x) * 16 + l16; };
     f32x4_t bias[TN];
     EpiOperands eo[EARLY ? TM : 1][EARLY ? TN : 1];
-    if (pieces == 1) {
+    auto request_bias = [&]() {
 #pragma unroll
         for (int y = 0; y < TN; ++y) bias[y] = *reinterpret_cast<const f32x4_t*>(ep.bias + min(col_of(y), Nn - 4));
+    };
+    if (pieces == 1) {
+        if constexpr (!TIGHT) request_bias();
         if constexpr (EARLY) {
 #pragma unroll
             for (int x = 0; x < TM; ++x) {
@@ -243,6 +248,7 @@ gemm_few_kernel(const T* __restrict__ A, const T* __restrict__ W, T* __restrict_
     // Larger tiles: what the epilogue reads is requested for several rows at once (one 16 x 16 block after the other, each
     // waiting for its own: 2 us on 8 blocks per wave, 4 on 16).
     constexpr int CHUNK = EARLY ? TM : TM * TN <= 12 ? TM : 2;
+    if constexpr (TIGHT) request_bias();
 #pragma unroll
     for (int x0 = 0; x0 < TM; x0 += CHUNK) {
         EpiRow rows[CHUNK];

@@ -369,7 +369,8 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, const bf
     // waits and loads behind run-time conditions and a 64-bit vector address per load, us at 17776 rows: 5760 x 1920 329 ->
     // 316, 7680 x 1920 449 -> 436, 1920 x 7680 467 -> 441, 1920 x 1920 126 -> 117; at 4516 rows 92.5 -> 90.4, 127.7 -> 123.6,
     // 117.9 -> 110.7, 37.9 -> 34.4).  No stage follows the last one: no hand-over there, and no loads for stages past the end
-    // (the fragment reads of the last step then fetch stale, unused data from the other slot).
+    // (the fragment reads of the last step then fetch stale, unused data from the other slot).  Written out, the stages cost three
+    // of the 256 x 256 kernels one to four registers, stored in front of the loop and read back behind it.
     constexpr int STEADY = steady_form(DEEP, PRE);
     auto stage = [&](int kt, auto left_c) {
         constexpr int LEFT = decltype(left_c)::value;

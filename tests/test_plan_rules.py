@@ -219,3 +219,27 @@ def test_a_tile_requests_each_strip_of_its_residual_once(rules, deep):
     for stages in (3, 4, 5, 30, 120):
         strips = [rules.strip(min(left, steady)) for left in reversed(range(stages))]
         assert strips == [-1] * (stages - 3) + [0, 1, -1]
+
+
+def spilled_registers():
+    """Vector registers each kernel of the built library spills, from its metadata."""
+    import re
+    with open(build.LIB, "rb") as f:
+        d = f.read()
+    out = {}
+    for m in re.finditer(rb"\.vgpr_spill_count([\x00-\x7f]|\xcc.|\xcd..)", d, re.S):
+        at = d.rfind(b".symbol", 0, m.start())
+        name = re.match(rb"\.symbol(?:[\xa0-\xbf]|\xd9.|\xda..)(\w+)\.kd", d[at:at + 600], re.S).group(1).decode()
+        out[name] = m.group(1)[0] if len(m.group(1)) == 1 else int.from_bytes(m.group(1)[1:], "big")
+    return out
+
+
+def test_matrix_kernels_keep_their_registers():
+    """Few-token tiles spill nothing, the wide ones a handful at most (256 x 256, outside the loop)."""
+    if not os.path.exists(build.LIB):
+        build.build_library()
+    spilled = spilled_registers()
+    few, wide = ({n: v for n, v in spilled.items() if k in n} for k in ("gemm_few_kernel", "gemm_mfma_kernel"))
+    assert len(few) >= 60 and len(wide) >= 20
+    assert not any(few.values()), {n: v for n, v in few.items() if v}
+    assert max(wide.values()) <= 4
