@@ -99,9 +99,11 @@ static bool uses_tiles(int dtype, int tokens, int Nn, int K, int path) {
     return dtype == PS_BF16 && (path & 0xff) != 1 && gemm_mfma_supported(tokens, Nn, K);
 }
 
-// A forced tile variant takes a bf16 shape of few tokens to the tile kernel, with the K pieces of the shape: it decides
-// which workgroup computes an output, not its value.
-static bool forced_tiles(int dtype, int path) { return dtype == PS_BF16 && (path >> 8) != 0; }
+// A forced tile variant takes a bf16 shape of few tokens to the tile kernel, where that takes it, with the K pieces of the
+// shape: it decides which workgroup computes an output, not its value.
+static bool forced_tiles(int dtype, int tokens, int Nn, int K, int path) {
+    return (path >> 8) != 0 && uses_tiles(dtype, tokens, Nn, K, path);
+}
 
 bool gemm_uses_mfma(int dtype, int tokens, int Nn, int K, int path) {
     return few_plan(dtype == PS_BF16, tokens, Nn, K, path).use || uses_tiles(dtype, tokens, Nn, K, path);
@@ -109,7 +111,8 @@ bool gemm_uses_mfma(int dtype, int tokens, int Nn, int K, int path) {
 
 size_t gemm_split_workspace_bytes(int dtype, int batch, int tokens, int Nn, int K, int path) {
     const FewPlan few = few_plan(dtype == PS_BF16, tokens, Nn, K, path);
-    if (few.use && !forced_tiles(dtype, path)) return few_workspace_bytes(dtype == PS_BF16, few, batch, tokens, Nn, K);
+    if (few.use && !forced_tiles(dtype, tokens, Nn, K, path))
+        return few_workspace_bytes(dtype == PS_BF16, few, batch, tokens, Nn, K);
     return uses_tiles(dtype, tokens, Nn, K, path)
                ? gemm_tiles_workspace_bytes(batch, tokens, Nn, K, path, few.use ? few.nsplit : 0) : 0;
 }
@@ -120,13 +123,14 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, void* C, int bat
     if (batch <= 0 || tokens <= 0 || Nn <= 0 || K <= 0 || (Nn & 1)) return hipErrorInvalidValue;
     const bool bf16 = dtype == PS_BF16;
     FewPlan few = few_plan(bf16, tokens, Nn, K, path);
-    if (few.use && !forced_tiles(dtype, path)) {
+    if (few.use && !forced_tiles(dtype, tokens, Nn, K, path)) {
         if (epi.split_ws == nullptr || epi.split_ws_bytes < few_workspace_bytes(bf16, few, batch, tokens, Nn, K)) few.nsplit = 1;
         const FewHow how = few_how(bf16, few, batch, tokens, Nn, K);
         if (how == FEW_TILES && few.nsplit == 1)         // (whole sums: the fastest tile of either kernel)
             return launch_gemm_mfma((const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C, batch, tokens, Nn, K, epi, path, 1, st);
         const bool apart = how == FEW_PIECES;
-        const int tile = bf16 ? best_tile(FEW_64x64, FEW_TILE_KINDS - 1, (long)batch * tokens, Nn, K, apart ? few.nsplit : 1,
+        const int tile = bf16 && K * 2L <= ANY_TILE_ROW_BYTES
+                              ? best_tile(FEW_64x64, FEW_TILE_KINDS - 1, (long)batch * tokens, Nn, K, apart ? few.nsplit : 1,
                                           epi.kind == EPI_GATE_RESIDUAL && !apart, compute_units())
                               : FEW_64x64;
         return launch_gemm_few(dtype, A, W, C, batch, tokens, Nn, K, tile, few.nsplit, !apart, epi, deferred, st);

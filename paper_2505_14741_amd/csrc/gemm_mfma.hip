@@ -585,7 +585,7 @@ gemm_tail_kernel(bf16_t* __restrict__ C, int Nn, GemmGrid g, Epilogue ep) {
 
 // `tokens` rows per sample; offsets inside a sample are 32-bit element indices, inside a tile's rows 32-bit byte offsets
 bool gemm_mfma_supported(int tokens, int Nn, int K) {
-    return K % 64 == 0 && Nn % 4 == 0 && tokens >= 1 && Nn >= 64 && K >= 64 && K <= TILE_MAX_ROW_BYTES / 2 &&
+    return K % 64 == 0 && Nn % 4 == 0 && tokens >= 1 && Nn >= 64 && K >= 64 && K <= ANY_TILE_ROW_BYTES / 2 &&
            (long)tokens * Nn < (1L << 31);
 }
 

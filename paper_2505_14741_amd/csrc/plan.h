@@ -192,8 +192,10 @@ constexpr GemmPlan gemm_plan(int tokens, int Nn, int K, bool allow_split, int fo
 constexpr int steady_form(int deep, bool strips) { return strips && deep < 3 ? 3 : deep; }
 constexpr int strip_of_form(int form) { return form == 2 ? 0 : form == 1 ? 1 : -1; }
 
-// Longest operand row the tile kernels take: a load's offset inside a tile's rows (256 at most) is 32 bits.
-constexpr long TILE_MAX_ROW_BYTES = 1L << 23;
+// Longest operand rows of the matrix kernels.  A load's offset inside a tile's rows is 32 bits: 256 rows at most, and 64 on the
+// 64 x 64 tile of gemm_few.hip, which takes the rows that are longer than the others do.  (Bases of eight rows, which any
+// tile could use, cost 0.4 to 1 % of every forward.  64 rows x 64 columns, K = 2^22 + 64 in bf16 2.4 ms, 480 on the FMA kernel.)
+constexpr long ANY_TILE_ROW_BYTES = 1L << 23, TILE_64_ROW_BYTES = 1L << 26;
 
 // ---- projections of few tokens and of fp32 operands (gemm_few.hip)
 constexpr int FEW_ROW_BYTES = 128;                       // bytes of an operand row per stage: 64 bf16 or 32 fp32
@@ -228,7 +230,7 @@ constexpr int few_long_pieces(int tokens, int Nn, int nk) {
 // A sample's plan: a function of the sample's shape alone, so that its result does not depend on the batch.  tiles_m x
 // tiles_n tiles of 64 x 64.
 //   bf16: up to 640 of them, 512 with K >= 4096, where a sample is cut into K pieces that wider tiles would also need, and
-//     beyond as long as it is cut.
+//     beyond as long as it is cut, or its operand rows are longer than wider tiles take.
 //   fp32: every size (the matrix instructions bind, 32 cycles per 2048 operations, not the LDS reads).
 // K pieces, short K: as many as bring the workgroups to 256 (one per compute unit), 8 at most (fp32 16) and each at least 5
 // stages.  1920 x 1920 bf16 at 112 tokens (60 tiles), without / with the launch that adds them: 1 piece 10.3 us, 4 pieces
@@ -240,7 +242,7 @@ struct FewPlan { bool use; int tiles_m, tiles_n, nsplit; };
 constexpr FewPlan few_plan(bool bf16, int tokens, int Nn, int K, int path) {
     FewPlan p{false, 0, 0, 1};
     const long row_bytes = (long)K * (bf16 ? 2 : 4);
-    if ((path & 0xff) == 1 || row_bytes % FEW_ROW_BYTES != 0 || row_bytes > TILE_MAX_ROW_BYTES || Nn % 4 != 0 || tokens < 1) return p;
+    if ((path & 0xff) == 1 || row_bytes % FEW_ROW_BYTES != 0 || row_bytes > TILE_64_ROW_BYTES || Nn % 4 != 0 || tokens < 1) return p;
     p.tiles_m = (tokens + 63) / 64;
     p.tiles_n = (Nn + 63) / 64;
     const long tiles = (long)p.tiles_m * p.tiles_n, nk = row_bytes / FEW_ROW_BYTES;
@@ -249,7 +251,7 @@ constexpr FewPlan few_plan(bool bf16, int tokens, int Nn, int K, int path) {
     long ns = (nk >= 60 ? 512 : 256) / tiles;
     if (bf16 && nk >= 60 && tokens > 128) ns = few_long_pieces(tokens, Nn, (int)nk);
     if ((path & 0xff) == 4) ns = 1;
-    if (bf16 && ns <= 1 && tiles > (K >= 4096 ? 512 : 640)) return p;
+    if (bf16 && ns <= 1 && tiles > (K >= 4096 ? 512 : 640) && row_bytes <= ANY_TILE_ROW_BYTES) return p;
     p.use = true;
     ns = ns < most ? ns : most;
     ns = ns < nk / 5 ? ns : nk / 5;
@@ -275,7 +277,7 @@ constexpr FewHow few_how(bool bf16, const FewPlan& p, int batch, int tokens, int
     const long tiles = (long)batch * p.tiles_m * p.tiles_n;
     if (p.nsplit > 1 && (bf16 && K >= 60 * 64 ? few_one_round((long)batch * tokens, Nn, p.nsplit) : tiles < (bf16 ? 256 : 640)))
         return FEW_PIECES;
-    return bf16 && tiles > 768 && p.tiles_m > 1 ? FEW_TILES : FEW_INREG;
+    return bf16 && tiles > 768 && p.tiles_m > 1 && K * 2L <= ANY_TILE_ROW_BYTES ? FEW_TILES : FEW_INREG;
 }
 
 // scratch for the K pieces, [piece][row][column] in fp32, of the largest batch up to `batch` whose pieces pass through memory

@@ -113,6 +113,24 @@ def test_fewer_stages_than_the_ring_and_a_few_more(M, Nn, K):
             assert torch.equal(out, B.dit_linear(a, w, bias, 0, kernel_path=variant << 8)), variant
 
 
+@pytest.mark.parametrize("M", [3, 70, 700])
+def test_linear_of_operand_rows_longer_than_8_mb(M):
+    """The rows of one 64 x 64 tile are half a GB apart from first to last; edges inside a tile and past it.  fp32 sums as above."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M)
+    for td, K in ((torch.float32, (1 << 21) + 32), (torch.bfloat16, (1 << 22) + 64)):
+        print(f"dit_linear M={M} N=68 K={K}", flush=True)
+        a = torch.randn(M, K, generator=g, device=DEV, dtype=td)
+        w = torch.randn(68, K, generator=g, device=DEV, dtype=td).mul_(K ** -0.5)
+        bias = torch.randn(68, generator=g, device=DEV)
+        ref = bias.double().expand(M, 68).clone()
+        for k in range(0, K, 1 << 18):
+            ref += a[:, k:k + (1 << 18)].double() @ w[:, k:k + (1 << 18)].double().t()
+        bound = 5e-6 * (K / 7680) ** 0.5 + (2.0 ** -9 if td == torch.bfloat16 else 0)
+        for kw in ({}, {"use_workspace": False}, {"kernel_path": 0x200}):
+            assert rel(ref.cpu().numpy(), B.dit_linear(a, w, bias, 0, **kw).double().cpu().numpy()) <= bound, (td, kw)
+
+
 @pytest.mark.parametrize("N", [1, 15, 16, 17, 63, 64, 65, 200])
 @pytest.mark.parametrize("d", [16, 32, 64])
 def test_attention_fp32_math_ragged(N, d):

@@ -221,6 +221,20 @@ def test_a_tile_requests_each_strip_of_its_residual_once(rules, deep):
         assert strips == [-1] * (stages - 3) + [0, 1, -1]
 
 
+@pytest.mark.parametrize("bf16", [0, 1])
+def test_operand_rows_of_any_length_stay_on_matrix_kernels(rules, bf16):
+    """256 rows of more than 8 MB are beyond a load's 32-bit offset: the 64 x 64 tile takes them at every token count and batch, up
+    to 64 MB each."""
+    size = 2 if bf16 else 4
+    for row in ((1 << 23) + 128, 1 << 25, 1 << 26):
+        for tokens in (1, 64, 129, 1281, 5000, 33976):
+            for n in (64, 68, 1920):
+                assert rules.few(bf16, tokens, n, row // size, 0) > 0, (row, tokens, n)
+                assert all(rules.how(bf16, tokens, n, row // size, b) != TILES for b in (1, 16))
+    assert rules.few(bf16, 5000, 1920, (1 << 23) // size, 0) == (0 if bf16 else 1)
+    assert rules.few(bf16, 64, 64, ((1 << 26) + 128) // size, 0) == 0
+
+
 def spilled_registers():
     """Vector registers each kernel of the built library spills, from its metadata."""
     import re
