@@ -10,7 +10,7 @@
 // fp32 products and sums on v_mfma_f32_16x16x4_f32 throughout; instruction e of a 16-deep step multiplies k = 4 * (lane / 16)
 // + e, even and odd steps have sums of their own.
 // us per forward of 2 layers of hidden 64 with the launches of the conditioning, a launch per operation and this: 32 tokens
-// 99 and 48, 134 tokens 109 and 56, 416 tokens 125 and 71.
+// 94 and 42, 128 tokens 98 and 42, 416 tokens 112 and 55.
 #include "few_epilogue.h"
 #include "lane_sums.h"
 #include "slim.h"
@@ -206,8 +206,10 @@ __global__ void __launch_bounds__(256, 1) slim_begin_kernel(SlimArgs g, SlimLaye
 // behind the attention and LayerNorm's vectors in one load each 272.  Of this, exponentials and GELU had lost digits; as exact
 // as the math library's 282, with its expf 287.  (Slower: values stored [column][token] for 16-byte loads, 285 -> 287; W_1
 // between W_o's products, 270 -> 278.)
+// Workgroups per compute unit, four waves each: 16 samples of 800 tokens of hidden 32 take 158 us in heads of 16 with two and 219
+// in heads of 32 with one, 137 and 166 with three and two (three at the price of 12 to 20 spilled registers).
 template <int D, int HD, bool LAST>
-__global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLayer w, SlimLayer next) {
+__global__ void __launch_bounds__(256, (D == 32) + (HD == 16) + 1) slim_layer_kernel(SlimArgs g, SlimLayer w, SlimLayer next) {
     constexpr int LD = D + 4, F = 4 * D, LF = F + 4, NB = HD / 16, HEADS = D / HD;
     static_assert(HEADS <= 4, "a wave per head");
     __shared__ __attribute__((aligned(16))) float xt[ROWS * LD], ht[ROWS * LD], ut[ROWS * LF];
@@ -312,17 +314,6 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
                 for (int e = 0; e < 4; ++e)
 #pragma unroll
                     for (int t = 0; t < 4; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][d][e], qf[d][e], sc[t], 0, 0, 0);
-            if (k0 + 64 > N) {                           // keys past the end: no weight, and values that can't reach the sums
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (k0 + t * 16 + kgrp * 4 + i >= N) {
-                            sc[t][i] = -INFINITY;
-#pragma unroll
-                            for (int d = 0; d < NB; ++d) vf[t][i][d] = 0.f;
-                        }
-            }
             float tmax = -INFINITY, tmin = INFINITY;
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
@@ -335,7 +326,7 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
             l *= alpha;
 #pragma unroll
             for (int d = 0; d < NB; ++d) acc[d] *= alpha;
-            const bool near = __ballot(tmin - mn < EXP_NEAR) == 0;       // (of the whole wave; not with masked keys)
+            const bool near = __ballot(tmin - mn < EXP_NEAR) == 0;       // (of the whole wave)
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -349,7 +340,18 @@ __global__ void __launch_bounds__(256, 1) slim_layer_kernel(SlimArgs g, SlimLaye
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) sc[t][i] = expf(sc[t][i]);   // masked keys: exp(-inf) = 0
+                    for (int i = 0; i < 4; ++i) sc[t][i] = expf(sc[t][i]);
+            }
+            if (k0 + 64 > N) {                           // keys past the end (the last one again): no weight, and no value
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (k0 + t * 16 + kgrp * 4 + i >= N) {
+                            sc[t][i] = 0.f;
+#pragma unroll
+                            for (int d = 0; d < NB; ++d) vf[t][i][d] = 0.f;
+                        }
             }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
