@@ -27,8 +27,9 @@ __device__ __forceinline__ void sinusoid_entry(const TList& tl, float* __restric
 // One wave per GEMV_ROWS consecutive output rows; weights stream once from HBM (16 bytes per lane and load when the row
 // length allows, the loads of the wave's rows in flight together), inputs stay in cache and are read once for the wave's
 // rows.  Each row's sum is formed as if the wave had that row alone (same lanes, same order).  Few rows in all (a time MLP
-// layer: 512) take a wave each, which spreads the loads and the six shuffles per row and vector over the chip: 512 rows of
-// 1920 bf16 weights, one vector 9.0 -> 5.3 us (8 rows per wave), 64 rows of 64 fp32, nine vectors 20 -> 5.
+// layer: 512) take a wave each, which spreads the loads and the sums over lanes, one per row and vector, over the chip: 512 rows
+// of 1920 bf16 weights, one vector 9.0 -> 5.3 us (8 rows per wave), 64 rows of 64 fp32, nine vectors 20 -> 5 (as measured with
+// sums of six shuffles).
 // blockIdx.y picks one of up to GEMV_SET matrices of the same shape applied to the same input.
 template <typename T, int MAXB, int GEMV_ROWS>
 __global__ void gemv_kernel(GemvSet set, const float* __restrict__ in, int rows,
@@ -159,9 +160,11 @@ hipError_t launch_gemv(int dtype, const void* W, const float* bias, const float*
 // l % 16, whole 128-byte lines (bf16) per row and 64 columns.  512 columns in bf16, 256 in fp32 are in flight per wave, the
 // first of them requested before the vectors are staged, each step's registers refilled for what comes next behind its products.
 // Four sums per output.  The same kernel serves one vector, so a vector's result does not depend on the batch.
-// us, weights from memory, all loads of a pass and then its products / this: 30 layers bf16 162 / 147 (4.85 TB/s, a plain copy
-// 5.1), nine vectors 176 / 160, one layer 12.9 / 12.0; fp32, two layers 31.3 / 25.0, one 19.4 / 14.9.
-// (The kernel above pays six shuffles per row and vector: 148 us for one vector and 30 layers, 295 for four.)
+// us, weights from memory, all loads of a pass and then its products / this: 30 layers bf16 162 / 147 (4.85 TB/s; rel_mae_kernel,
+// which like this one only reads, reaches 6.8), nine vectors 176 / 160, one layer 12.9 / 12.0; fp32, two layers 31.3 / 25.0, one
+// 19.4 / 14.9.
+// (The kernel above has a sum over lanes per row and vector and reads the vectors again for every eight or four rows: 30 layers,
+// one / four / nine vectors 143 / 259 / 569 us, this 145 / 157 / 161.)
 static constexpr int MOD_MAX_COLS = 1000;                // 16 vectors of cols + 4 floats within 64 KB of LDS
 template <typename T>
 __global__ void __launch_bounds__(256, 4)
@@ -634,8 +637,10 @@ __device__ __forceinline__ float block_sum(float v, float* sm) {
 // (PendingResidual): the pieces are added in order, X is updated in place and its new row is normalised from registers,
 // which saves the launch and the pass over X that a reduction of its own would take.
 // CAP: pieces at most (0: none are apart).  All that a row reads is requested at once, without branches: one operand after the
-// other, and the pieces four at a time, were up to six trips to memory in a row.  112 rows x 1920, 4 or 8 pieces 5.1 -> 4.5 us,
-// 448 rows 8.0 -> 7.6 and 8.3; the 30-layer step at 112 tokens 2047 -> 2013, fp32 5.2 -> 4.9.
+// other, and the pieces four at a time, were up to six trips to memory in a row.  Rows x pieces of 1920, us: bf16 48 x 6 5.8 ->
+// 4.4, 48 x 8 4.9 -> 4.2, 112 x 4 4.7 -> 4.4, 112 x 8 5.3 -> 4.2, 448 x 4 7.5 -> 7.1, 448 x 8 8.2 -> 8.0, 560 x 8 9.8 -> 9.6,
+// 900 x 3 8.8 -> 8.6, 1100 x 3 10.6 both, 1250 x 3 10.25 -> 10.3 (the piece read for a fourth comes from the same lines); fp32
+// 112 x 8 6.0 -> 5.4, 161 x 5 6.2 -> 5.9.
 template <typename T, int CAP>
 __global__ void __launch_bounds__(256)
 ln_modulate_row_kernel(float* __restrict__ X, T* __restrict__ out, int M, int D, float eps,

@@ -82,10 +82,11 @@ constexpr AttnRoute attention_route(int batch, int seq, int heads, int path, int
 // Output tiles of the matrix kernels: gemm_few.hip (any K pieces; fp32 and bf16) and gemm_mfma.hip (bf16).
 enum TileId { FEW_64x64, FEW_128x64, FEW_128x128, FEW_192x128, FEW_256x128, FEW_192x192, FEW_TILE_KINDS,
               WIDE_256x256 = FEW_TILE_KINDS, WIDE_128x128, WIDE_192x256, WIDE_192x128, TILE_KINDS };
-// Measured us of a round of workgroups, one tile each: fixed + stages of 64 k * stage.  per_cu = 2: two workgroups share a
-// CU; `half`: a round that leaves at most one to each.  (bf16, operands that change from call to call, 32 to 9000 rows x
-// 1920 to 7680 columns x K = 1920 and 7680.)  gated: what an epilogue that reads and writes an fp32 residual adds to a round
-// (17776 rows x 1920, K = 1920: 184, 170, 164 and 168 us on the tiles of gemm_mfma.hip in their order below).
+// Us of a round of workgroups, one tile each: fixed + stages of 64 k * stage.  per_cu = 2: two workgroups share a CU; `half`: a
+// round that leaves at most one to each.  (Fitted to bf16, operands that change from call to call, 32 to 9000 rows x 1920 to 7680
+// columns x K = 1920 and 7680, with loops that had branches in a stage: all tiles are 2 to 13 % faster now, in the same order.)
+// gated: what an epilogue that reads and writes an fp32 residual adds to a round (17776 rows x 1920, K = 1920, then 184, 170,
+// 164 and 168 us on the tiles of gemm_mfma.hip in their order below, now 184, 162, 160 and 170).
 struct Tile { int bm, bn, per_cu; float half_fixed, half_stage, fixed, stage, gated; };
 constexpr Tile kTiles[TILE_KINDS] = {
     {64, 64, 2, 3.0f, 0.235f, 4.5f, 0.40f, 1.9f},        // 8 waves of 16 x 32
@@ -121,9 +122,9 @@ constexpr float tile_time(int id, long wgs, float stages, bool gated, int cus) {
     return (float)(wgs / slots) * full + last;
 }
 // The bf16 tile with the least estimated time: `pieces` workgroups per tile along K; [first, last]: the kinds to choose from.
-// Inside the network, 26 token counts from 64 to 33976 x the four projections of a layer, the one picked is 0.6 % slower than
-// the fastest on average, and 7 % at most but for QKV and fc1 at 1024 tokens (128 x 128 of gemm_mfma.hip 43.0 and 41.4 us, 256 x
-// 128 here 37.3 and 35.3).
+// Inside the network, 28 token counts from 64 to 33976 x the four projections of a layer, those that are not cut into pieces, the
+// one picked is 0.8 % slower than the fastest on average, and 6 % at most but for QKV and fc1 at 1024 tokens (128 x 128 of
+// gemm_mfma.hip 41.0 and 39.6 us, 256 x 128 here 35.9 and 32.3).
 constexpr int best_tile(int first, int last, long rows, int Nn, int K, int pieces, bool gated, int cus) {
     int best = first;
     float least = 0.f;

@@ -15,10 +15,10 @@ struct SlimArgs {
 };
 
 // What slim.hip takes: fp32, hidden 32 or 64 in heads of 16 or 32, mlp_ratio 4, whole 16-value blocks of up to 64 values
-// per patch, up to 1024 tokens.  us per forward of 2 layers, a launch per operation / this: hidden 64, 4 heads: 32 tokens 99 /
-// 48, 416 tokens 125 / 71, 976 tokens 159 / 103 (16 samples 428 / 300).  A head of 64 keeps one wave per workgroup busy for
+// per patch, up to 1024 tokens.  us per forward of 2 layers, a launch per operation / this: hidden 64, 4 heads: 32 tokens 94 /
+// 42, 416 tokens 112 / 55, 976 tokens 141 / 77 (16 samples 326 / 230).  A head of 64 keeps one wave per workgroup busy for
 // long (416 tokens 156 / 183), and a hidden size of 128 has too much to do per token for one workgroup (416 tokens, 8 heads
-// 135 / 143).
+// 135 / 143; both of when hidden 64 took 125 / 71).
 constexpr int SLIM_TOKENS = 1024;
 constexpr bool slim_network(int dtype, int hidden, int head_dim, int mlp_ratio, int patch_values, int tokens) {
     return dtype == PS_F32 && (hidden == 32 || hidden == 64) && head_dim <= 32 && mlp_ratio == 4 && patch_values % 16 == 0 &&
